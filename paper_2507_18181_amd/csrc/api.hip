@@ -16,6 +16,7 @@
 #include "../../include/specasr_profile.h"
 #include "kernels.h"
 #include "kernels_mfma.h"
+#include "kernels_slice.h"
 
 using namespace specasr;
 
@@ -41,8 +42,8 @@ struct WsLayout {
 
 }  // namespace
 
-// Packed (MFMA-tiled) weights of one decoder layer: q|k|v and gate|up are concatenated
-// band-aligned so that each pair is one GEMM.
+// Packed (MFMA-tiled) weights of one decoder layer: q|k|v are concatenated band-aligned and gate|up
+// interleaved by 8 rows, so that each is one GEMM.
 struct PackedLayer {
   PackedMatrix qkv, o, gu, down;
 };
@@ -71,7 +72,8 @@ struct specasr_ctx {
   std::vector<PackedLayer> packed;
   PackedMatrix lm_head;
   std::vector<void *> owned;  // device allocations made by create
-  int col_k = 0, col_v = 0, col_up = 0;  // column offsets inside the concatenated outputs
+  int col_k = 0, col_v = 0;  // column offsets inside the concatenated q|k|v output
+  bool paired = false;       // query and key heads packed in rotary pairs (launch_repack_rope)
   size_t part_floats = 0;
   size_t wide_part_floats = 0;  // partial-sum buffer of a wide prefill pass, in floats (0: no wide path)
   // stage profiling (benchmark aid)
@@ -150,6 +152,63 @@ GemmPlan plan_gemm(int n_bands, int ksteps, int nb, int n_cu) {
   return best;
 }
 
+// Half-bands per workgroup of an unsplit GEMM that finishes its own output (kernels_slice.hip), or
+// hb = 0 where the split kernel keeps the projection.  One workgroup per compute unit and round;
+// more than one round is taken only where the last one is nearly full (a half empty round costs
+// more than the finishing kernel that is saved).
+SlicePlan plan_slice(int epi, int n_half, int ksteps, int rows, int n_cu) {
+  SlicePlan pl;
+  pl.nc = (rows + 15) / 16;
+  if (ksteps % 2) return pl;  // the kernel takes k-steps in pairs
+  if (epi == kSliceResid) {
+    // o: one half-band per workgroup, so each workgroup reads all activations for 16 output columns.
+    // Two row groups at most: 1.1B (128 k-steps) 5.5 / 7.2 / 10.7 us at 1 / 2 / 3 groups and 7B 8.9 / 12.6
+    // at 1 / 2, against 8.8 / 8.9 / 9.3 and 13 / 13.8 of the split kernel plus residual kernel; 13B
+    // (320 half-bands, two per workgroup) 22 against 17.
+    if (pl.nc <= 2 && n_half <= n_cu) pl.hb = 1;
+    return pl;
+  }
+  for (int rounds = 1; rounds <= 8; ++rounds) {
+    int hb = (n_half + n_cu * rounds - 1) / (n_cu * rounds);
+    while (hb <= 8 && !slice_shape_built(epi, hb, pl.nc)) ++hb;
+    if (hb > 8) continue;
+    const int tiles = (n_half + hb - 1) / hb;
+    if (rounds == 1 || tiles * 100 >= n_cu * rounds * 85) pl.hb = hb;
+    break;
+  }
+  return pl;
+}
+
+// The down projection has few output features and a long k, so it stays split; with one row group
+// (<= 16 rows) or more than two the half-band kernel streams it faster than the split kernel: 1.1B 8.3 ->
+// 7.4 (16 rows), 11.5 -> 9.2 us (37 rows), 11.5 -> 9.8 (64 rows); 7B 26.8 -> 22.4 (40 rows), but 18.6 against
+// 20.3 at 32 rows, where the split kernel holds its activations in registers and has spare wavefronts
+// for the sums, and no gain at 64 rows (1 MB of activations per workgroup).  Cost model in us: bytes of one workgroup at 60 bytes/ns or the weight stream at 5.9
+// bytes/ps, whichever is longer, plus 0.3 us per MB of partial sums.
+SlicePlan plan_slice_down(int n_half, int ksteps, int rows, int n_cu) {
+  SlicePlan pl;
+  pl.nc = (rows + 15) / 16;
+  if (ksteps % 2 || pl.nc == 2) return pl;
+  double best = 1e300;
+  for (int hb = 2; hb <= 8; hb *= 2) {
+    if (!slice_shape_built(kSlicePartial, hb, pl.nc)) continue;
+    const int tiles = (n_half + hb - 1) / hb;
+    int S = n_cu / tiles;
+    if (S > 16) S = 16;
+    while (S > 1 && ksteps / 2 / S < 8) --S;  // at least one pair of k-steps per wavefront
+    if (S < 1) continue;
+    const double wg_kb = (double)(hb + 2 * pl.nc) * ksteps / 2 / S, w_mb = (double)n_half * ksteps * 0.512e-3;
+    if (pl.nc > 3 && wg_kb > 512) continue;
+    const double cost = std::max(wg_kb / 60.0, w_mb / 5.9) + S * (double)rows * n_half * 64e-6 * 0.3;
+    if (cost < best) {
+      best = cost;
+      pl.hb = hb;
+      pl.S = S;
+    }
+  }
+  return pl;
+}
+
 WsLayout ws_layout(const specasr_ctx *ctx, int batch);
 
 WsLayout ws_layout(const specasr_config &c, int batch) {
@@ -192,7 +251,7 @@ WsLayout ws_layout(const specasr_ctx *ctx, int batch) {
   L.attb = take(2 * 64 * dq * 2);
   L.tb = take(2 * 64 * (size_t)c.d_ffn * 2);
   L.part = take(64 * ctx->part_floats * 4);  // [split][band][rows padded to 32 or 64][32]
-  L.ssq = take(64 * (size_t)residual_slabs(c.d_model) * 4);
+  L.ssq = take(64 * (size_t)((c.d_model + 15) / 16) * 4);  // one per row and slab of 32, or of 16, columns
   const size_t nblk = (size_t)logits_argmax_blocks(c.vocab);
   L.blk_val = take(R * nblk * 4);
   L.blk_idx = take(R * nblk * 4);
@@ -227,7 +286,7 @@ WsLayout ws_layout_wide(const specasr_ctx *ctx, int batch) {
   L.attb = take(2 * Rp * dq * 2);
   L.tb = take(2 * Rp * (size_t)c.d_ffn * 2);
   L.part = take(ctx->wide_part_floats * 4);
-  L.ssq = take(R * (size_t)residual_slabs(c.d_model) * 4);
+  L.ssq = take(R * (size_t)((c.d_model + 15) / 16) * 4);
   L.qb = take(2 * R * dq * 2);
   // a pass has >= 2 pieces, so the key chunks of the attention number at most 128 / n_kv_heads + 1
   const size_t mc = (size_t)128 / c.n_kv_heads + 2;
@@ -535,6 +594,21 @@ void gemm_stage(specasr_ctx *ctx, int stage, bool profiled_layer, const PackedMa
     launch_gemm_skinny(W, Xp, rows, part, plan, stage, st, ev0, ev1);
 }
 
+// The same for an unsplit GEMM with a finishing epilogue.
+void slice_stage(specasr_ctx *ctx, int stage, bool profiled_layer, int epi, const SliceArgs &a, const SlicePlan &pl,
+                 hipStream_t st) {
+  const bool prof = ctx->prof_stage == stage && profiled_layer && !ctx->prof_ev.empty() && ctx->prof_mode != 2;
+  hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  if (prof) {
+    if (ctx->prof_used + 2 > ctx->prof_ev.size()) (void)prof_drain(ctx);
+    ev0 = ctx->prof_ev[ctx->prof_used];
+    ev1 = ctx->prof_ev[ctx->prof_used + 1];
+    ctx->prof_used += 2;
+    ctx->prof_rows += a.rows;
+  }
+  launch_gemm_slice(epi, a, pl, st, ev0, ev1);
+}
+
 // Ordering between two forwards that run on different streams and meet in the KV cache (chunk c+1
 // of a prefill reads, layer by layer, the rows chunk c writes): `record[l]` is recorded once the
 // K/V rows of layer l are in the cache, `wait[l]` is waited for before layer l's attention.
@@ -598,7 +672,20 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       pls[i]->lw = nb == 1 ? (len <= 4 ? 4 : len <= 8 ? 8 : len <= 12 ? 12 : 16) : (len <= 4 ? 4 : 8);
     }
   }
+  // projections that finish their own output (a forced split count keeps the split kernel)
+  SlicePlan sl_qkv, sl_o, sl_gu, sl_dn;
+  if (!wide) {
+    const int *forced = ctx->tune.gemm_splits;
+    if (ctx->paired && !forced[0]) sl_qkv = plan_slice(kSliceQkv, 2 * p0.qkv.n_bands, p0.qkv.ksteps, R, ctx->n_cu);
+    if (!forced[1]) sl_o = plan_slice(kSliceResid, d / 16, p0.o.ksteps, R, ctx->n_cu);
+    if (!forced[2]) sl_gu = plan_slice(kSliceSwiglu, F / 8, p0.gu.ksteps, R, ctx->n_cu);
+    if (!forced[3]) sl_dn = plan_slice_down(d / 16, p0.down.ksteps, R, ctx->n_cu);
+    if ((size_t)sl_dn.S * p0.down.ldo > ctx->part_floats) sl_dn.hb = 0;
+    if (sl_dn.hb) pl_dn.n_splits = sl_dn.S;
+  }
+  const RowNorm nrm16{ssq, d / 16, d, md.rms_eps};  // statistics as the o projection's epilogue leaves them
   if (ctx->tune.debug) {
+    if (!wide) fprintf(stderr, "[specasr] half-bands per workgroup: qkv %d, o %d, gate_up %d, down %d (S %d)\n", sl_qkv.hb, sl_o.hb, sl_gu.hb, sl_dn.hb, sl_dn.S);
     const GemmPlan *pls[5] = {&pl_qkv, &pl_o, &pl_gu, &pl_dn, &pl_lm};
     const char *nm[5] = {"qkv", "o", "gate_up", "down", "lm_head"};
     const PackedMatrix *pm[5] = {&p0.qkv, &p0.o, &p0.gu, &p0.down, &ctx->lm_head};
@@ -615,25 +702,55 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
     const specasr_layer_weights &lw = ctx->layers[l];
     const PackedLayer &pk = ctx->packed[l];
     launch_residual_gain(x, part, pending, R, pending_ld, lw.attn_norm, d, hb, hb_lo, nb, ssq, st);
-    gemm_stage(ctx, SPECASR_STAGE_QKV, pl, pk.qkv, hb, R, part, pl_qkv, st);
+    SliceArgs sa{};
+    sa.rows = R;
+    sa.S = 1;
+    if (sl_qkv.hb) {
+      sa.W = pk.qkv.data; sa.X = hb; sa.n_half = 2 * pk.qkv.n_bands; sa.ksteps = pk.qkv.ksteps; sa.nrm = nrm;
+      sa.m = m; sa.g = g; sa.layer = l; sa.H = md.n_heads; sa.Hkv = md.n_kv_heads; sa.hd = md.head_dim; sa.hd_shift = md.head_dim == 64 ? 6 : 7;
+      sa.col_k = ctx->col_k; sa.col_v = ctx->col_v; sa.cs = cs; sa.qb = qb; sa.qb_lo = qb_lo;
+      sa.kc = (uint16_t *)kv->k; sa.vc = (uint16_t *)kv->v; sa.qscale = 1.0f / sqrtf((float)md.head_dim);
+      slice_stage(ctx, SPECASR_STAGE_QKV, pl, kSliceQkv, sa, sl_qkv, st);
+    } else {
+      gemm_stage(ctx, SPECASR_STAGE_QKV, pl, pk.qkv, hb, R, part, pl_qkv, st);
+    }
     if (mfma_attn) {
-      launch_qkv_finish(m, md, g, l, part, pl_qkv.n_splits, pk.qkv.ldo, nrm, ctx->col_k, ctx->col_v, cs, nullptr, qb, qb_lo, kv->k, kv->v, st);
+      if (!sl_qkv.hb)
+        launch_qkv_finish(m, md, g, l, part, pl_qkv.n_splits, pk.qkv.ldo, nrm, ctx->col_k, ctx->col_v, cs, nullptr, qb, qb_lo, kv->k, kv->v, ctx->paired, st);
       if (sync.record) HIP_TRY(ctx, hipEventRecord(sync.record[l], st));
       if (sync.wait) HIP_TRY(ctx, hipStreamWaitEvent(st, sync.wait[l], 0));
       launch_tree_attention(m, md, g, l, hs.max_total_keys, hs.max_seq_nodes, qb, qb_lo, kv->k, kv->v,
                             (float *)(ws + L.attn_o), (float *)(ws + L.attn_ml), attb, attb_lo, nb, ctx->tune.attn_chunk, st);
     } else {
-      launch_qkv_finish(m, md, g, l, part, pl_qkv.n_splits, pk.qkv.ldo, nrm, ctx->col_k, ctx->col_v, cs, q, nullptr, nullptr, kv->k, kv->v, st);
+      launch_qkv_finish(m, md, g, l, part, pl_qkv.n_splits, pk.qkv.ldo, nrm, ctx->col_k, ctx->col_v, cs, q, nullptr, nullptr, kv->k, kv->v, ctx->paired, st);
       if (sync.record) HIP_TRY(ctx, hipEventRecord(sync.record[l], st));
       if (sync.wait) HIP_TRY(ctx, hipStreamWaitEvent(st, sync.wait[l], 0));
       launch_attention_generic(m, md, g, l, q, kv->k, kv->v, att, st);
       launch_to_bf16(att, R, dq, attb, attb_lo, st);
     }
-    gemm_stage(ctx, SPECASR_STAGE_O, pl, pk.o, attb, R, part, pl_o, st);
-    launch_residual_gain(x, part, pl_o.n_splits, R, pk.o.ldo, lw.ffn_norm, d, hb, hb_lo, nb, ssq, st);
-    gemm_stage(ctx, SPECASR_STAGE_GATE_UP, pl, pk.gu, hb, R, part, pl_gu, st);
-    launch_swiglu_finish(part, pl_gu.n_splits, R, pk.gu.ldo, nrm, ctx->col_up, F, tb, tb_lo, nb, st);
-    gemm_stage(ctx, SPECASR_STAGE_DOWN, pl, pk.down, tb, R, part, pl_dn, st);
+    if (sl_o.hb) {
+      sa.W = pk.o.data; sa.X = attb; sa.n_half = d / 16; sa.ksteps = pk.o.ksteps;
+      sa.x = x; sa.gain = (const uint16_t *)lw.ffn_norm; sa.d = d; sa.t = hb; sa.t_lo = hb_lo;
+      sa.ssq_out = ssq; sa.n_slab_out = nrm16.n_slab;
+      slice_stage(ctx, SPECASR_STAGE_O, pl, kSliceResid, sa, sl_o, st);
+    } else {
+      gemm_stage(ctx, SPECASR_STAGE_O, pl, pk.o, attb, R, part, pl_o, st);
+      launch_residual_gain(x, part, pl_o.n_splits, R, pk.o.ldo, lw.ffn_norm, d, hb, hb_lo, nb, ssq, st);
+    }
+    const RowNorm &nrm_ffn = sl_o.hb ? nrm16 : nrm;
+    if (sl_gu.hb) {
+      sa.W = pk.gu.data; sa.X = hb; sa.n_half = F / 8; sa.ksteps = pk.gu.ksteps; sa.nrm = nrm_ffn; sa.t = tb; sa.t_lo = tb_lo;
+      slice_stage(ctx, SPECASR_STAGE_GATE_UP, pl, kSliceSwiglu, sa, sl_gu, st);
+    } else {
+      gemm_stage(ctx, SPECASR_STAGE_GATE_UP, pl, pk.gu, hb, R, part, pl_gu, st);
+      launch_swiglu_finish(part, pl_gu.n_splits, R, pk.gu.ldo, nrm_ffn, F, tb, tb_lo, nb, st);
+    }
+    if (sl_dn.hb) {
+      sa.W = pk.down.data; sa.X = tb; sa.n_half = d / 16; sa.ksteps = pk.down.ksteps; sa.S = sl_dn.S; sa.part = part;
+      slice_stage(ctx, SPECASR_STAGE_DOWN, pl, kSlicePartial, sa, sl_dn, st);
+    } else {
+      gemm_stage(ctx, SPECASR_STAGE_DOWN, pl, pk.down, tb, R, part, pl_dn, st);
+    }
     pending = pl_dn.n_splits;
     pending_ld = pk.down.ldo;
   }
@@ -732,11 +849,13 @@ std::vector<SeqGroup> split_call(const specasr_ctx *ctx, const specasr_kv *kv, c
 }
 
 // One-time repack of the bf16 weights into MFMA-tile order (values unchanged).  Allocates the
-// packed copies; q|k|v and gate|up are concatenated, each part starting on a 32-row band.
+// packed copies; q|k|v are concatenated, each part starting on a 32-row band (query and key heads in
+// rotary pairs where the MFMA attention covers the head size), gate and up rows are interleaved.
 specasr_status build_packed(specasr_ctx *ctx) {
   const specasr_config &c = ctx->cfg;
   const int d = c.d_model, F = c.d_ffn, dq = c.n_heads * c.head_dim, dkv = c.n_kv_heads * c.head_dim;
   HIP_TRY(ctx, gemm_skinny_set_lds_limit());
+  HIP_TRY(ctx, gemm_slice_set_lds_limit());
   HIP_TRY(ctx, tree_attention_set_lds_limit());
   {
     int dev = 0, cus = 0;
@@ -754,21 +873,25 @@ specasr_status build_packed(specasr_ctx *ctx) {
   };
   ctx->col_k = pad32(dq);
   ctx->col_v = ctx->col_k + pad32(dkv);
-  ctx->col_up = pad32(F);
+  ctx->paired = tree_attention_supported(c.head_dim);
   ctx->packed.resize(c.n_layers);
   hipStream_t st = nullptr;
   for (int l = 0; l < c.n_layers; ++l) {
     const specasr_layer_weights &lw = ctx->layers[l];
     PackedLayer &pk = ctx->packed[l];
     HIP_TRY(ctx, alloc(pk.qkv, ctx->col_v + pad32(dkv), d));
-    launch_repack(lw.wq, dq, d, pk.qkv.data, 0, st);
-    launch_repack(lw.wk, dkv, d, pk.qkv.data, ctx->col_k / 32, st);
+    if (ctx->paired) {
+      launch_repack_rope(lw.wq, c.n_heads, c.head_dim, d, pk.qkv.data, 0, st);
+      launch_repack_rope(lw.wk, c.n_kv_heads, c.head_dim, d, pk.qkv.data, ctx->col_k / 32, st);
+    } else {
+      launch_repack(lw.wq, dq, d, pk.qkv.data, 0, st);
+      launch_repack(lw.wk, dkv, d, pk.qkv.data, ctx->col_k / 32, st);
+    }
     launch_repack(lw.wv, dkv, d, pk.qkv.data, ctx->col_v / 32, st);
     HIP_TRY(ctx, alloc(pk.o, pad32(d), dq));
     launch_repack(lw.wo, d, dq, pk.o.data, 0, st);
-    HIP_TRY(ctx, alloc(pk.gu, 2 * pad32(F), d));
-    launch_repack(lw.w_gate, F, d, pk.gu.data, 0, st);
-    launch_repack(lw.w_up, F, d, pk.gu.data, ctx->col_up / 32, st);
+    HIP_TRY(ctx, alloc(pk.gu, 2 * F, d));  // F is a multiple of 16
+    launch_repack_gate_up(lw.w_gate, lw.w_up, F, d, pk.gu.data, st);
     HIP_TRY(ctx, alloc(pk.down, pad32(d), F));
     launch_repack(lw.w_down, d, F, pk.down.data, 0, st);
     HIP_TRY(ctx, hipGetLastError());

@@ -22,6 +22,8 @@ struct GemmPlan {
 
 void launch_read_probe(const void *buf, size_t bytes, int grid, uint32_t *sink, hipStream_t st);
 void launch_repack(const void *src, int n_out, int K, void *dst, int band0, hipStream_t st);
+void launch_repack_gate_up(const void *gate, const void *up, int F, int K, void *dst, hipStream_t st);
+void launch_repack_rope(const void *src, int heads, int hd, int K, void *dst, int band0, hipStream_t st);
 hipError_t gemm_skinny_set_lds_limit();
 void launch_gemm_skinny(const PackedMatrix &W, const uint16_t *Xp, int rows, float *part,
                         const GemmPlan &plan, int stage, hipStream_t st,
@@ -38,9 +40,9 @@ void launch_residual_gain(float *x, const float *part, int n_splits, int rows, i
 void launch_qkv_finish(const StepMeta &m, const ModelDims &md, const KvGeom &g, int layer,
                        const float *part, int n_splits, int ldp, const RowNorm &nrm, int col_k,
                        int col_v, const float2 *cs, float *q, uint16_t *qb, uint16_t *qb_lo, void *kc,
-                       void *vc, hipStream_t st);
+                       void *vc, bool paired, hipStream_t st);
 void launch_swiglu_finish(const float *part, int n_splits, int rows, int ldp, const RowNorm &nrm,
-                          int col_up, int F, uint16_t *t, uint16_t *t_lo, int nb, hipStream_t st);
+                          int F, uint16_t *t, uint16_t *t_lo, int nb, hipStream_t st);
 void launch_to_bf16(const float *src, int rows, int K, uint16_t *dst, uint16_t *dst_lo, hipStream_t st);
 int logits_argmax_blocks(int V);
 void launch_logits_argmax(const StepMeta &m, const float *part, int n_splits, int ldp,

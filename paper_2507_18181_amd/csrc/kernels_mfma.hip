@@ -50,6 +50,35 @@ __global__ void repack_kernel(const uint16_t *src, int n_out, int K, uint16_t *d
   reinterpret_cast<u32x4 *>(dst)[((int64_t)(band0 + band) * ksteps + kt) * 64 + l] = v;
 }
 
+// The same with permuted rows, so that every group of 16 packed rows (a half-band) holds what an
+// epilogue combines: packed rows 16i .. 16i+7 are rows 8i .. 8i+7 of `a` and rows 16i+8 .. +15 rows
+// 8i .. 8i+7 of `b` (both [n][K]).  gate|up: a = w_gate, b = w_up.  Rotary heads: per head of hd
+// rows, a = its first half and b = its second half (n = hd/2, one call per head's row range:
+// group = hd/16 half-bands, a and b advance by hd rows from head to head).
+__global__ void repack_pairs_kernel(const uint16_t *a, const uint16_t *b, int group, int64_t head_rows, int K, uint16_t *dst, int band0, int n_rows) {
+  const int ksteps = K / 16;
+  const int64_t tile = blockIdx.x;
+  const int band = (int)(tile / ksteps), kt = (int)(tile - (int64_t)band * ksteps);
+  const int l = threadIdx.x, prow = band * 32 + (l & 31);
+  u32x4 v = (u32x4){0u, 0u, 0u, 0u};
+  if (prow < n_rows) {
+    const int hb = prow >> 4, in = prow & 15, head = hb / group, j = (hb - head * group) * 8 + (in & 7);
+    const uint16_t *src = (in < 8 ? a : b) + (head * head_rows + j) * K;
+    v = *reinterpret_cast<const u32x4 *>(src + kt * 16 + 8 * (l >> 5));
+  }
+  reinterpret_cast<u32x4 *>(dst)[((int64_t)(band0 + band) * ksteps + kt) * 64 + l] = v;
+}
+
+void launch_repack_gate_up(const void *gate, const void *up, int F, int K, void *dst, hipStream_t st) {
+  const int64_t tiles = (int64_t)((2 * F + 31) / 32) * (K / 16);
+  repack_pairs_kernel<<<(unsigned)tiles, 64, 0, st>>>((const uint16_t *)gate, (const uint16_t *)up, F / 8, 0, K, (uint16_t *)dst, 0, 2 * F);
+}
+
+void launch_repack_rope(const void *src, int heads, int hd, int K, void *dst, int band0, hipStream_t st) {
+  const int64_t tiles = (int64_t)((heads * hd + 31) / 32) * (K / 16);
+  repack_pairs_kernel<<<(unsigned)tiles, 64, 0, st>>>((const uint16_t *)src, (const uint16_t *)src + (int64_t)(hd / 2) * K, hd / 16, hd, K, (uint16_t *)dst, band0, heads * hd);
+}
+
 void launch_repack(const void *src, int n_out, int K, void *dst, int band0, hipStream_t st) {
   const int bands = (n_out + 31) / 32;
   const int64_t tiles = (int64_t)bands * (K / 16);
@@ -555,13 +584,16 @@ void launch_residual_gain(float *x, const float *part, int n_splits, int rows, i
 // q, k, v = sum of partials; rotary embedding at the node's depth position (Sec. II-B: each
 // branch is verified as its own sequence, so position = kv_len + depth).  Outputs: q either as
 // fp32 [rows][H*hd] (generic attention) or as bf16 pre-multiplied by 1/sqrt(hd) (MFMA
-// attention); k, v -> bf16 cache slot kv_len + node.  Packed columns: [q | pad | k | pad | v].
+// attention); k, v -> bf16 cache slot kv_len + node.  Packed columns: [q | pad | k | pad | v]; with
+// `paired` the rows of a query or key head are stored as launch_repack_rope leaves them.
+__device__ __forceinline__ int rope_col(int j, int paired) { return paired ? ((j >> 3) << 4) + (j & 7) : j; }
+__device__ __forceinline__ int rope_step(int half, int paired) { return paired ? 8 : half; }
 __global__ __launch_bounds__(256) void qkv_finish_kernel(StepMeta m, KvGeom g, int layer, int H, int Hkv,
                                                          int hd, const float *part, int n_splits,
                                                          int ldp, RowNorm nrm, int col_k, int col_v,
                                                          const float2 *cs, float *q, uint16_t *qb,
                                                          uint16_t *qb_lo, float qscale, uint16_t *kc,
-                                                         uint16_t *vc) {
+                                                         uint16_t *vc, int paired) {
   const int r = blockIdx.y, half = hd / 2, rows = m.rows;
   const int idx0 = blockIdx.x * 256 + threadIdx.x, n_items = (H + Hkv) * half;
   const bool live = idx0 < n_items;
@@ -584,10 +616,11 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(StepMeta m, KvGeom g, i
     }
   };
   float t[4];
+  const int jc = rope_col(j, paired), j2 = jc + rope_step(half, paired);
   if (a < H)
-    val4(a * hd + j, a * hd + j + half, a * hd + j, a * hd + j + half, t);
+    val4(a * hd + jc, a * hd + j2, a * hd + jc, a * hd + j2, t);
   else
-    val4(col_k + (a - H) * hd + j, col_k + (a - H) * hd + j + half, col_v + (a - H) * hd + j, col_v + (a - H) * hd + j + half, t);
+    val4(col_k + (a - H) * hd + jc, col_k + (a - H) * hd + j2, col_v + (a - H) * hd + j, col_v + (a - H) * hd + j + half, t);
   const float rs = row_rms_finish(nrm, lane_ssq);
   if (!live) return;
   t[0] *= rs; t[1] *= rs; t[2] *= rs; t[3] *= rs;
@@ -622,7 +655,7 @@ __global__ __launch_bounds__(256) void qkv_finish_wide_kernel(StepMeta m, KvGeom
                                                               int ldp, RowNorm nrm, int col_k, int col_v,
                                                               const float2 *cs, uint16_t *qb,
                                                               uint16_t *qb_lo, float qscale, uint16_t *kc,
-                                                              uint16_t *vc) {
+                                                              uint16_t *vc, int paired) {
   const int rows = m.rows, half = hd / 2;
   const int a = blockIdx.x, r = blockIdx.y * 32 + (threadIdx.x >> 3), sub = threadIdx.x & 7;
   const int rr = r < rows ? r : rows - 1;
@@ -661,7 +694,8 @@ __global__ __launch_bounds__(256) void qkv_finish_wide_kernel(StepMeta m, KvGeom
   const int b = a - H;
   const int c0 = is_q ? a * hd : col_k + b * hd;
   for (int j = sub * 4; j < half; j += 32) {
-    const float4 x0 = sum4(c0 + j), x1 = sum4(c0 + j + half);
+    const int jc = rope_col(j, paired);
+    const float4 x0 = sum4(c0 + jc), x1 = sum4(c0 + jc + rope_step(half, paired));
     const float4 cs01 = *reinterpret_cast<const float4 *>(cs + (int64_t)r * half + j);       // (cos, sin) of j, j+1
     const float4 cs23 = *reinterpret_cast<const float4 *>(cs + (int64_t)r * half + j + 2);   // ... of j+2, j+3
     const float co[4] = {cs01.x, cs01.z, cs23.x, cs23.z}, si[4] = {cs01.y, cs01.w, cs23.y, cs23.w};
@@ -700,24 +734,26 @@ __global__ __launch_bounds__(256) void qkv_finish_wide_kernel(StepMeta m, KvGeom
 void launch_qkv_finish(const StepMeta &m, const ModelDims &md, const KvGeom &g, int layer,
                        const float *part, int n_splits, int ldp, const RowNorm &nrm, int col_k,
                        int col_v, const float2 *cs, float *q, uint16_t *qb, uint16_t *qb_lo, void *kc,
-                       void *vc, hipStream_t st) {
+                       void *vc, bool paired, hipStream_t st) {
   if (m.rows > 64 && qb != nullptr && md.head_dim % 64 == 0) {
     dim3 wgrid(md.n_heads + md.n_kv_heads, (m.rows + 31) / 32);
-    qkv_finish_wide_kernel<<<wgrid, 256, 0, st>>>(m, g, layer, md.n_heads, md.n_kv_heads, md.head_dim, part, n_splits, ldp, nrm, col_k, col_v, cs, qb, qb_lo, 1.0f / sqrtf((float)md.head_dim), (uint16_t *)kc, (uint16_t *)vc);
+    qkv_finish_wide_kernel<<<wgrid, 256, 0, st>>>(m, g, layer, md.n_heads, md.n_kv_heads, md.head_dim, part, n_splits, ldp, nrm, col_k, col_v, cs, qb, qb_lo, 1.0f / sqrtf((float)md.head_dim), (uint16_t *)kc, (uint16_t *)vc, paired ? 1 : 0);
     return;
   }
   const int items = (md.n_heads + md.n_kv_heads) * (md.head_dim / 2);
   dim3 grid((items + 255) / 256, m.rows);
-  qkv_finish_kernel<<<grid, 256, 0, st>>>(m, g, layer, md.n_heads, md.n_kv_heads, md.head_dim, part, n_splits, ldp, nrm, col_k, col_v, cs, q, qb, qb_lo, 1.0f / sqrtf((float)md.head_dim), (uint16_t *)kc, (uint16_t *)vc);
+  qkv_finish_kernel<<<grid, 256, 0, st>>>(m, g, layer, md.n_heads, md.n_kv_heads, md.head_dim, part, n_splits, ldp, nrm, col_k, col_v, cs, q, qb, qb_lo, 1.0f / sqrtf((float)md.head_dim), (uint16_t *)kc, (uint16_t *)vc, paired ? 1 : 0);
 }
 
-// t[r][f] = bf16 planes of silu(sum_s gate) * (sum_s up); gate at column f, up at column col_up + f.
+// t[r][f] = bf16 planes of silu(sum_s gate) * (sum_s up); gate at column 16*(f/8) + f%8, up 8 columns
+// further (launch_repack_gate_up).
+__device__ __forceinline__ int gate_col(int f) { return ((f >> 3) << 4) + (f & 7); }
 // One workgroup per (band of 32 features, group of 32 rows): in the partial-sum layout that is one
 // contiguous 4 KB block of gate and one of up per split, read with 16 bytes per thread (thread t:
 // row t/8, features 4*(t%8)..+3), and one contiguous 1 KB block per k-step and plane on the way
 // out.  The 8 threads of a row also share the sum over its norm slabs.
 __global__ __launch_bounds__(256) void swiglu_finish_kernel(const float *part, int n_splits, int rows,
-                                                            int ldp, RowNorm nrm, int col_up, int F,
+                                                            int ldp, RowNorm nrm, int F,
                                                             uint16_t *t, uint16_t *t_lo, int nb) {
   const int r = blockIdx.y * 32 + (threadIdx.x >> 3), sub = threadIdx.x & 7;
   const int f = blockIdx.x * 32 + sub * 4;
@@ -744,8 +780,8 @@ __global__ __launch_bounds__(256) void swiglu_finish_kernel(const float *part, i
   const int rows_pad = part_rows_pad(rows), n_bands = ldp >> 5;
 #pragma unroll 4
   for (int s = 0; s < n_splits; ++s) {
-    const float4 a = *reinterpret_cast<const float4 *>(part + part_offset(s, r, f, n_bands, rows_pad));
-    const float4 b = *reinterpret_cast<const float4 *>(part + part_offset(s, r, col_up + f, n_bands, rows_pad));
+    const float4 a = *reinterpret_cast<const float4 *>(part + part_offset(s, r, gate_col(f), n_bands, rows_pad));
+    const float4 b = *reinterpret_cast<const float4 *>(part + part_offset(s, r, gate_col(f) + 8, n_bands, rows_pad));
     gt.x += a.x; gt.y += a.y; gt.z += a.z; gt.w += a.w;
     up.x += b.x; up.y += b.y; up.z += b.z; up.w += b.w;
   }
@@ -766,7 +802,7 @@ __global__ __launch_bounds__(256) void swiglu_finish_kernel(const float *part, i
 // too often (7B, 32 rows: 5.5 against 6.8 us; from 33 rows on the band-block mapping wins: 7B, 64
 // rows 5.17 -> 5.11 ms per step).
 __global__ __launch_bounds__(256) void swiglu_finish_rows_kernel(const float *part, int n_splits, int rows,
-                                                            int ldp, RowNorm nrm, int col_up, int F,
+                                                            int ldp, RowNorm nrm, int F,
                                                             uint16_t *t, uint16_t *t_lo, int nb) {
   const int r = blockIdx.y;
   const int f = (blockIdx.x * 256 + threadIdx.x) * 4;
@@ -776,8 +812,8 @@ __global__ __launch_bounds__(256) void swiglu_finish_rows_kernel(const float *pa
   if (f < F) {
 #pragma unroll 4
     for (int s = 0; s < n_splits; ++s) {
-      const float4 a = *reinterpret_cast<const float4 *>(part + part_offset(s, r, f, n_bands, rows_pad));
-      const float4 b = *reinterpret_cast<const float4 *>(part + part_offset(s, r, col_up + f, n_bands, rows_pad));
+      const float4 a = *reinterpret_cast<const float4 *>(part + part_offset(s, r, gate_col(f), n_bands, rows_pad));
+      const float4 b = *reinterpret_cast<const float4 *>(part + part_offset(s, r, gate_col(f) + 8, n_bands, rows_pad));
       gt.x += a.x; gt.y += a.y; gt.z += a.z; gt.w += a.w;
       up.x += b.x; up.y += b.y; up.z += b.z; up.w += b.w;
     }
@@ -797,14 +833,14 @@ __global__ __launch_bounds__(256) void swiglu_finish_rows_kernel(const float *pa
 }
 
 void launch_swiglu_finish(const float *part, int n_splits, int rows, int ldp, const RowNorm &nrm,
-                          int col_up, int F, uint16_t *t, uint16_t *t_lo, int nb, hipStream_t st) {
+                          int F, uint16_t *t, uint16_t *t_lo, int nb, hipStream_t st) {
   if (rows <= 32) {
     dim3 grid((F / 4 + 255) / 256, rows);
-    swiglu_finish_rows_kernel<<<grid, 256, 0, st>>>(part, n_splits, rows, ldp, nrm, col_up, F, t, t_lo, nb);
+    swiglu_finish_rows_kernel<<<grid, 256, 0, st>>>(part, n_splits, rows, ldp, nrm, F, t, t_lo, nb);
     return;
   }
   dim3 grid((F + 31) / 32, (rows + 31) / 32);
-  swiglu_finish_kernel<<<grid, 256, 0, st>>>(part, n_splits, rows, ldp, nrm, col_up, F, t, t_lo, nb);
+  swiglu_finish_kernel<<<grid, 256, 0, st>>>(part, n_splits, rows, ldp, nrm, F, t, t_lo, nb);
 }
 
 // fp32 -> bf16 row conversion (attention output feeding the output projection)

@@ -1,0 +1,48 @@
+"""The unsplit projections that finish their own output (SwiGLU, rotary embedding + cache rows, residual
+update) and the half-band down projection, at the sizes where they can go wrong."""
+import numpy as np
+import pytest
+
+import oracle
+import workload as wl
+from parity_util import TOL_BF16, check_forward, check_tree_kv
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("shape", [
+    # 864 gate|up half-bands (4 per workgroup), 480 q|k|v ones (2); 3 k-step pairs: fewer than wavefronts
+    dict(d_model=96, d_ffn=6912, n_heads=20, n_kv_heads=20, head_dim=128),
+    # 1728 (7 per workgroup with two row groups, split kernel with three) and 960 (4); o: more columns than k
+    dict(d_model=160, d_ffn=13824, n_heads=40, n_kv_heads=40, head_dim=128),
+    # grouped heads of 64: key and value parts that end inside a band of 32; half-band count odd
+    dict(d_model=592, d_ffn=1072, n_heads=6, n_kv_heads=3, head_dim=64),
+    # 2 half-bands per workgroup in the last, half filled tile; 1288 features
+    dict(d_model=320, d_ffn=5152, n_heads=2, n_kv_heads=1, head_dim=64),
+])
+def test_half_band_projections_match_oracle(shape):
+    """1 .. 64 rows around the edges of the 16-row groups, against the fp64 oracle.  The bound is the
+    regression guard of check_forward: activations enter with 16 mantissa bits, so what is left are
+    K and V elements that round the other way (one bf16 step each)."""
+    cfg = dict(wl.MODELS["tiny"], n_layers=2, vocab=97, **shape)
+    w = wl.make_weights(cfg, 311, "bf16")
+    rng = np.random.default_rng(312)
+    L, cap = 40, 112
+    K, V = wl.seeded_cache(cfg, 313, L, cap, "bf16")
+    om = oracle.OracleModel(cfg, w)
+    from paper_2507_18181_amd.runtime import Verifier
+    ver = Verifier(cfg, w, "bf16", max_nodes=64, capacity=cap)
+    for n in (1, 15, 16, 17, 32, 33, 48, 49, 64):
+        parents = wl.random_tree(rng, n, max_children=3)
+        tokens = rng.integers(0, cfg["vocab"], n).astype(np.int32)
+        ver.set_cache(K, V, [L])
+        ref = om.tree_forward(np.ascontiguousarray(K[0]), np.ascontiguousarray(V[0]), L, tokens, parents)
+        fw = ver.tree_forward([tokens], [parents])
+        assert fw["status"] == 0
+        check_forward(ref, fw["logits"][0].cpu().numpy(), fw["argmax"][0].cpu().numpy(), TOL_BF16)
+        k1, v1 = ver.get_cache()
+        check_tree_kv(k1[0], v1[0], L, ref, TOL_BF16)
+        assert np.array_equal(k1[0][:, :, :L], K[0][:, :, :L]) and np.array_equal(v1[0][:, :, :L], V[0][:, :, :L])
+    ver.close()
