@@ -696,6 +696,8 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
   launch_rope_table(m, md.head_dim, md.rope_theta, cs, st);
   launch_embed(m, 1, ctx->w.tok_embed, tree->input_embeds, ctx->cfg.max_nodes, d, x, st);
   int pending = 0, pending_ld = 0;  // partial sums of the previous down projection, not yet added to x
+  // kv_len, row_start, n_nodes of the sequences as build_step laid them out
+  const int32_t *seq_words = hs.words.data() + 10 * (size_t)hs.batch * ctx->cfg.max_nodes;
   const int prof_layer = (int)(ctx->prof_calls++ % md.n_layers);
   for (int l = 0; l < md.n_layers; ++l) {
     const bool pl = l == prof_layer;
@@ -709,7 +711,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       sa.W = pk.qkv.data; sa.X = hb; sa.n_half = 2 * pk.qkv.n_bands; sa.ksteps = pk.qkv.ksteps; sa.nrm = nrm;
       sa.m = m; sa.g = g; sa.layer = l; sa.H = md.n_heads; sa.Hkv = md.n_kv_heads; sa.hd = md.head_dim; sa.hd_shift = md.head_dim == 64 ? 6 : 7;
       sa.col_k = ctx->col_k; sa.col_v = ctx->col_v; sa.cs = cs; sa.qb = qb; sa.qb_lo = qb_lo;
-      sa.kc = (uint16_t *)kv->k; sa.vc = (uint16_t *)kv->v; sa.qscale = 1.0f / sqrtf((float)md.head_dim);
+      sa.kc = (uint16_t *)kv->k; sa.vc = (uint16_t *)kv->v; sa.qscale = tree_attention_qscale(md.head_dim);
       slice_stage(ctx, SPECASR_STAGE_QKV, pl, kSliceQkv, sa, sl_qkv, st);
     } else {
       gemm_stage(ctx, SPECASR_STAGE_QKV, pl, pk.qkv, hb, R, part, pl_qkv, st);
@@ -720,7 +722,8 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       if (sync.record) HIP_TRY(ctx, hipEventRecord(sync.record[l], st));
       if (sync.wait) HIP_TRY(ctx, hipStreamWaitEvent(st, sync.wait[l], 0));
       launch_tree_attention(m, md, g, l, hs.max_total_keys, hs.max_seq_nodes, qb, qb_lo, kv->k, kv->v,
-                            (float *)(ws + L.attn_o), (float *)(ws + L.attn_ml), attb, attb_lo, nb, ctx->tune.attn_chunk, st);
+                            (float *)(ws + L.attn_o), (float *)(ws + L.attn_ml), attb, attb_lo, nb, ctx->tune.attn_chunk,
+                            seq_words, seq_words + m.batch, seq_words + 2 * m.batch, st);
     } else {
       launch_qkv_finish(m, md, g, l, part, pl_qkv.n_splits, pk.qkv.ldo, nrm, ctx->col_k, ctx->col_v, cs, q, nullptr, nullptr, kv->k, kv->v, ctx->paired, st);
       if (sync.record) HIP_TRY(ctx, hipEventRecord(sync.record[l], st));
@@ -856,7 +859,6 @@ specasr_status build_packed(specasr_ctx *ctx) {
   const int d = c.d_model, F = c.d_ffn, dq = c.n_heads * c.head_dim, dkv = c.n_kv_heads * c.head_dim;
   HIP_TRY(ctx, gemm_skinny_set_lds_limit());
   HIP_TRY(ctx, gemm_slice_set_lds_limit());
-  HIP_TRY(ctx, tree_attention_set_lds_limit());
   {
     int dev = 0, cus = 0;
     HIP_TRY(ctx, hipGetDevice(&dev));

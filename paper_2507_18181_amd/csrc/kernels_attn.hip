@@ -2,20 +2,28 @@
 // token tree; Sec. IV-C: used to verify the two-pass sparse tree).
 //
 // Every tree node attends to the cached prefix [0, kv_len) and to the cache slots of the nodes
-// on its own root path.  The KV cache is streamed exactly once per KV head: one wavefront takes
-// (sequence, KV head, chunk of keys) and serves ALL query rows that share the head (the
-// grouped-query heads times the tree nodes), 32 queries per MFMA column block.
+// on its own root path.  A workgroup takes (sequence, KV head, 32 query rows, chunk of keys); the
+// query rows that share the head are the grouped-query heads times the tree nodes.  Its wavefronts
+// take the chunk's 32-key tiles round-robin, each with its own online softmax, and are merged
+// through LDS at the end.
 //
-//   S^T[key][query] = K[key][:] . Q[query][:]      A = K tile (rows = keys, read straight from
-//                                                   the cache, 16 B per lane), B = Q^T
-//   online softmax per query column (fp32; max and sum via one cross-half shuffle)
+//   S^T[key][query] = K[key][:] . Q[query][:]      A = K tile, B = Q^T
+//   online softmax per query column (fp32, base 2: log2(e) is part of the query scale)
 //   Q and P enter the matrix cores as hi + lo bf16 planes (two MFMAs), so only the bf16 storage
 //   of the cache itself limits the precision.
-//   O^T[c][query]  += V^T[c][key] * P^T[key][query] A = V^T gathered from an LDS copy of the V
-//                                                   tile with key pairs interleaved, B = P^T,
-//                                                   which is exactly how the lanes already hold P
+//   O^T[c][query]  += V^T[c][key] * P^T[key][query] A = V^T, B = P^T, which is exactly how the lanes
+//                                                   already hold P
 //
-// Partial (unnormalised) outputs per key chunk are merged by a second small kernel.
+// K and V tiles go into LDS row by row with direct-to-LDS loads (whole 128-byte lines per request, no
+// staging registers), 16-byte chunks of a row XOR-permuted by its row number so that both kinds of
+// read are free of bank conflicts beyond the minimum: K as 16-byte rows of the A operand, V^T through the
+// transposing LDS read (ds_read_b64_tr_b16: 16 lanes give 4 rows x 16 columns and get 4 keys of one
+// column each).  Each wavefront has one buffer for K and one for V and requests the next tile of
+// either as soon as the current one has been consumed: K flies during softmax and PV, V during the
+// next QK^T and softmax.
+//
+// What bounds it: per 32 x 32 tile 32 MFMAs (head_dim 128; 1024 cycles) and about 170 vector
+// instructions; two wavefronts per SIMD overlap the two.
 #include "kernels.h"
 #include "kernels_mfma.h"
 
@@ -24,10 +32,6 @@ namespace specasr {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-  return (uint32_t)f32_to_bf16_bits(lo) | ((uint32_t)f32_to_bf16_bits(hi) << 16);
-}
 
 // Two finite floats -> their hi planes packed (a in the low half) and their lo planes packed, with
 // the hardware's round-to-nearest-even conversion (one v_cvt_pk_bf16_f32 per pair and plane; the
@@ -42,330 +46,364 @@ __device__ __forceinline__ void split_bf16_pair(float a, float b, uint32_t &hi, 
   lo = __builtin_bit_cast(uint32_t, l);
 }
 
-// grid (8 * n_rgb * ceil(n_chunks * Hkv / 8), 1, batch), block 256.  Workgroups go to the 8 XCDs
-// round-robin by their linear index, so the n_rgb workgroups that stream the SAME keys for
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+
+// The K operands of a tile (16-byte LDS reads) with their wait, and transposing LDS reads with theirs.  As assembly, because for ordinary LDS reads the compiler waits for every direct-to-LDS load in
+// flight, those of the other buffer among them.  Transposing read: 16 lanes give the addresses of 4 rows x 16 columns (8 bytes
+// each) and get 4 rows of one column each.
+template <int N>
+__device__ __forceinline__ void read_k(u32x4 (&k)[N], const uint32_t (&a)[N]) {
+  if constexpr (N == 8)
+    asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+                 "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(k[0]), "=&v"(k[1]), "=&v"(k[2]), "=&v"(k[3]), "=&v"(k[4]), "=&v"(k[5]), "=&v"(k[6]), "=&v"(k[7])
+                 : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]) : "memory");
+  else
+    asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(k[0]), "=&v"(k[1]), "=&v"(k[2]), "=&v"(k[3]) : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]) : "memory");
+}
+// V^T quads of (cb, part) = 0 .. N-1 for the keys OFF / row size .. +15 of the tile
+template <int N, int OFF>
+__device__ __forceinline__ void read_v(u32x2 (&v)[N], const uint32_t (&a)[N]) {
+  if constexpr (N == 8)
+    asm volatile("ds_read_b64_tr_b16 %0, %8 offset:%16\n\tds_read_b64_tr_b16 %1, %9 offset:%16\n\tds_read_b64_tr_b16 %2, %10 offset:%16\n\tds_read_b64_tr_b16 %3, %11 offset:%16\n\t"
+                 "ds_read_b64_tr_b16 %4, %12 offset:%16\n\tds_read_b64_tr_b16 %5, %13 offset:%16\n\tds_read_b64_tr_b16 %6, %14 offset:%16\n\tds_read_b64_tr_b16 %7, %15 offset:%16\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+                 : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "i"(OFF) : "memory");
+  else
+    asm volatile("ds_read_b64_tr_b16 %0, %4 offset:%8\n\tds_read_b64_tr_b16 %1, %5 offset:%8\n\tds_read_b64_tr_b16 %2, %6 offset:%8\n\tds_read_b64_tr_b16 %3, %7 offset:%8\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "i"(OFF) : "memory");
+}
+
+__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+// maximum / sum of a value over lanes l and l ^ 32
+__device__ __forceinline__ float max_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void load_16_to_lds(const char *src_lane, u32x4 *dst_64) {
+  __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src_lane, (void __attribute__((address_space(3))) *)dst_64, 16, 0, 0);
+}
+
+constexpr int kAttnWaves = 4;  // 8 were measured: 5 .. 30 % slower everywhere (more outputs to merge per workgroup)
+
+// Chunk (16 bytes) c of row r of a tile sits at chunk c ^ swizzle(r) of that row.
+template <int HD>
+__device__ __forceinline__ int swizzle(int r) {
+  return HD == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+}
+
+// grid (8 * n_rg * ceil(n_chunks * Hkv / 8), 1, batch), block 256.  Workgroups go to the 8 XCDs
+// round-robin by their linear index, so the n_rg workgroups that stream the SAME keys for
 // different query row groups are placed 8 apart: they run on one XCD and share its L2.
-// Block 256: the four wavefronts of a workgroup take the
-// 32-key tiles of the chunk round-robin, each with its own online softmax, and merge their
-// (max, sum, output) through LDS into ONE partial result per chunk.  RGW = query row groups (of
-// 32) per workgroup.
-template <int HD, int RGW>
-__global__ __launch_bounds__(256) void tree_attention_kernel(StepMeta m, KvGeom g, int layer, int H,
-                                                            int Hkv, int n_rgb,
-                                                            const uint16_t *__restrict__ qb,
-                                                            const uint16_t *__restrict__ qb_lo,
-                                                            const uint16_t *__restrict__ kc,
-                                                            const uint16_t *__restrict__ vc,
-                                                            int chunk_keys, int n_chunks,
-                                                            float *__restrict__ o_part,
-                                                            float *__restrict__ ml_part,
-                                                            uint16_t *__restrict__ out,
-                                                            uint16_t *__restrict__ out_lo, int nb) {
-  constexpr int KK = HD / 16;  // MFMA k-steps across the head dimension
-  constexpr int CB = HD / 32;  // 32-wide output column blocks
-  // LDS: per wavefront two V tiles [key pair][column] (low half = even key); reused afterwards
-  // for the cross-wavefront merge: o[wave][rg][cb][j][lane] floats, then (m, l)[wave][rg][32]
-  extern __shared__ uint32_t lds_attn[];
+// Sequences of a batched call in the kernel arguments (up to 16), in dispatch order, longest first: all
+// of a workgroup's metadata is one scalar load (the arrays in memory are a cold load each), and the
+// workgroups that start last are short (16 utterances on the 1.1B model 23.2 -> 21.0 us).
+struct AttnSeqs {
+  int4 e[16];     // kv_len, n_nodes, first row, sequence
+  int32_t count;  // 0: one sequence (StepMeta has it) or more than 16 (metadata arrays)
+};
+
+template <int HD>
+__global__ __launch_bounds__(64 * kAttnWaves, HD == 64 ? 3 : 2) void tree_attention_kernel(StepMeta m, AttnSeqs sq, KvGeom g, int layer, int H,
+                                                                    int Hkv, int n_rg,
+                                                                    const uint16_t *__restrict__ qb,
+                                                                    const uint16_t *__restrict__ qb_lo,
+                                                                    const uint16_t *__restrict__ kc,
+                                                                    const uint16_t *__restrict__ vc,
+                                                                    int chunk_keys, int n_chunks,
+                                                                    float *__restrict__ o_part,
+                                                                    float *__restrict__ ml_part,
+                                                                    uint16_t *__restrict__ out,
+                                                                    uint16_t *__restrict__ out_lo, int nb) {
+  constexpr int KK = HD / 16;         // MFMA k-steps across the head dimension
+  constexpr int CB = HD / 32;         // 32-wide output column blocks
+  constexpr int CR = HD / 8;          // 16-byte chunks of a row
+  constexpr int TU = 32 * CR;         // 16-byte units of a tile
+  constexpr int NI = TU / 64;         // direct-to-LDS loads of a tile
+  constexpr int RI = 64 / CR;         // rows per such load
+  constexpr int NW = kAttnWaves;
+  __shared__ u32x4 kbuf[NW * TU], vbuf[NW * TU];  // afterwards: the wavefronts' outputs, for the merge
+  __shared__ float2 ml[NW * 32];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint32_t *vp = lds_attn + wave * (2 * 16 * HD);
   const int lane = threadIdx.x & 63, h = lane >> 5, ql = lane & 31;
-  const int rgb = (blockIdx.x >> 3) % n_rgb, base = ((blockIdx.x >> 3) / n_rgb) * 8 + (blockIdx.x & 7);
-  if (base >= n_chunks * Hkv) return;
-  // Sequences are dispatched last to first: the pieces of a prefill pass come in order of growing
-  // key count, and the workgroups with the longest key loops should start first.
-  const int chunk = base % n_chunks, kvh = base / n_chunks, seq = gridDim.z - 1 - blockIdx.z;
-  const int G = H / Hkv;
-  const int L = m.seq_kv_len(seq), n = m.seq_n_nodes(seq), r0 = m.seq_row_start(seq), rows = m.rows;
+  const uint32_t bx = blockIdx.x >> 3, rg = bx % (uint32_t)n_rg, base = bx / (uint32_t)n_rg * 8 + (blockIdx.x & 7);
+  if (base >= (uint32_t)(n_chunks * Hkv)) return;
+  const int chunk = base % (uint32_t)n_chunks, kvh = base / (uint32_t)n_chunks;
+  int seq = gridDim.z - 1 - blockIdx.z, L, n, r0;
+  if (sq.count) {
+    const int4 e = sq.e[blockIdx.z];
+    L = e.x; n = e.y; r0 = e.z; seq = e.w;
+  } else {
+    L = m.seq_kv_len(seq); n = m.seq_n_nodes(seq); r0 = m.seq_row_start(seq);
+  }
+  const int G = (uint32_t)H / (uint32_t)Hkv, rows = m.rows;
   const int T = L + n, QR = G * n;
   const int t_begin = chunk * chunk_keys;
-  if (t_begin >= T || rgb * RGW * 32 >= QR) return;
+  if (t_begin >= T || (int)rg * 32 >= QR) return;
   const int t_end = min(T, t_begin + chunk_keys);
 
-  // queries of this wavefront
-  bool valid[RGW];
-  int out_row[RGW], out_head[RGW];
-  uint64_t anc[RGW];
-  u32x4 qreg[RGW][KK], qlo[RGW][KK];  // queries as hi + lo bf16 planes
+  const char *kbase = reinterpret_cast<const char *>(kc + g.row(seq, layer, kvh, 0));
+  const char *vbase = reinterpret_cast<const char *>(vc + g.row(seq, layer, kvh, 0));
+  u32x4 *kb = kbuf + wave * TU, *vb = vbuf + wave * TU;
+  // load i of a tile: lane l brings chunk c of row r = RI*i + l/CR to position l of the 1 KB block i
+  const int lr = lane / CR;
+  auto issue = [&](const char *src, u32x4 *dst, int t0) {
 #pragma unroll
-  for (int w = 0; w < RGW; ++w) {
-    const int qrow = (rgb * RGW + w) * 32 + ql;
-    valid[w] = qrow < QR;
-    const int gi = valid[w] ? qrow / n : 0, node = valid[w] ? qrow - gi * n : 0;
-    out_row[w] = r0 + node;
-    out_head[w] = kvh * G + gi;
-    anc[w] = valid[w] ? m.anc[out_row[w]] : 0ull;
-    const int64_t qoff = ((int64_t)out_row[w] * H + out_head[w]) * HD + 8 * h;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      qreg[w][kk] = valid[w] ? *reinterpret_cast<const u32x4 *>(qb + qoff + 16 * kk) : (u32x4){0u, 0u, 0u, 0u};
-      qlo[w][kk] = valid[w] ? *reinterpret_cast<const u32x4 *>(qb_lo + qoff + 16 * kk) : (u32x4){0u, 0u, 0u, 0u};
+    for (int i = 0; i < NI; ++i) {
+      const int r = RI * i + lr, c = (lane & (CR - 1)) ^ swizzle<HD>(r);
+      load_16_to_lds(src + (uint32_t)(min(t0 + r, T - 1) * (HD * 2) + c * 16), dst + i * 64);
     }
+  };
+  const int t_first = t_begin + 32 * wave;  // this wavefront's tiles: t_first, + 32 NW, ...
+  if (t_first < t_end) {
+    issue(kbase, kb, t_first);
+    issue(vbase, vb, t_first);
   }
-  float m_run[RGW], l_run[RGW];
-  f32x16 o[RGW][CB];
-#pragma unroll
-  for (int w = 0; w < RGW; ++w) {
-    m_run[w] = -INFINITY;
-    l_run[w] = 0.f;
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-      for (int j = 0; j < 16; ++j) o[w][cb][j] = 0.f;
-  }
-  const uint16_t *kbase = kc + g.row(seq, layer, kvh, 0);
-  const uint16_t *vbase = vc + g.row(seq, layer, kvh, 0);
 
-  // One register set for the tile in flight: K as A-operand registers, V as raw row pairs that are
-  // interleaved into LDS when consumed.  Each half is requested again for the wavefront's NEXT
-  // tile as soon as the current tile has consumed it (V after its copy to LDS, K after the last
-  // QK^T product), so the loads have the rest of the tile's work to arrive -- and the kernel keeps
-  // one tile's worth of staging registers instead of two.
-  constexpr int VI = HD / 32;  // (key pair, 8-column group) items per lane
-  u32x4 kreg[KK], va[VI], vb[VI];
-  auto issue_k = [&](int t0) {
-    const uint16_t *kp = kbase + (int64_t)min(t0 + ql, T - 1) * HD + 8 * h;
+  // queries of this wavefront (the same 32 for all of them)
+  const int qrow = rg * 32 + ql;
+  const bool valid = qrow < QR;
+  const int gi = valid ? (uint32_t)qrow / (uint32_t)n : 0, node = valid ? qrow - gi * n : 0;
+  const int out_row = r0 + node, out_head = kvh * G + gi;
+  const uint64_t anc = valid ? m.anc[out_row] : 0ull;
+  u32x4 qh[KK], qlo[KK];  // queries as hi + lo bf16 planes; surplus columns repeat node 0, without stores
+  {
+    const int64_t qoff = ((int64_t)out_row * H + out_head) * HD + 8 * h;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) kreg[kk] = *reinterpret_cast<const u32x4 *>(kp + 16 * kk);
-  };
-  auto issue_v = [&](int t0) {
+    for (int kk = 0; kk < KK; ++kk) qh[kk] = *reinterpret_cast<const u32x4 *>(qb + qoff + 16 * kk);
 #pragma unroll
-    for (int x = 0; x < VI; ++x) {
-      const int it = lane + 64 * x;
-      const int pair = it / (HD / 8), cg = it - pair * (HD / 8);
-      const int k0 = min(t0 + 2 * pair, T - 1), k1 = min(t0 + 2 * pair + 1, T - 1);
-      va[x] = *reinterpret_cast<const u32x4 *>(vbase + (int64_t)k0 * HD + 8 * cg);
-      vb[x] = *reinterpret_cast<const u32x4 *>(vbase + (int64_t)k1 * HD + 8 * cg);
-    }
-  };
-  auto compute = [&](int t0, uint32_t *vpb, bool more) {
-    // V tile into LDS, two keys interleaved per 32-bit word (low half = even key)
+    for (int kk = 0; kk < KK; ++kk) qlo[kk] = *reinterpret_cast<const u32x4 *>(qb_lo + qoff + 16 * kk);
+  }
+  float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's keys only, the halves are added at the end
+  f32x16 o[CB];
 #pragma unroll
-    for (int x = 0; x < VI; ++x) {
-      const int it = lane + 64 * x;
-      const int pair = it / (HD / 8), cg = it - pair * (HD / 8);
-      const u32x4 a = va[x], b = vb[x];
-      u32x4 lo, hi;  // columns 8cg..8cg+3 and 8cg+4..8cg+7
-      lo[0] = (a[0] & 0xffffu) | (b[0] << 16);
-      lo[1] = (a[0] >> 16) | (b[0] & 0xffff0000u);
-      lo[2] = (a[1] & 0xffffu) | (b[1] << 16);
-      lo[3] = (a[1] >> 16) | (b[1] & 0xffff0000u);
-      hi[0] = (a[2] & 0xffffu) | (b[2] << 16);
-      hi[1] = (a[2] >> 16) | (b[2] & 0xffff0000u);
-      hi[2] = (a[3] & 0xffffu) | (b[3] << 16);
-      hi[3] = (a[3] >> 16) | (b[3] & 0xffff0000u);
-      u32x4 *dst = reinterpret_cast<u32x4 *>(vpb + pair * HD + 8 * cg);
-      dst[0] = lo;
-      dst[1] = hi;
-    }
-    // only this wavefront reads the tile back: its own LDS operations stay in program order
-    __builtin_amdgcn_wave_barrier();
-    if (more) issue_v(t0 + 128);
+  for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-    for (int w = 0; w < RGW; ++w) {
-      f32x16 sT, sT2;  // hi and lo query planes on separate accumulators (independent chains)
+    for (int j = 0; j < 16; ++j) o[cb][j] = 0.f;
+
+  // LDS addresses of the operands.  K: row ql, chunk 2 kk + h.  V^T of (mm, part, cb): lane i of a group of
+  // 16 addresses row 16 mm + 8 part + 4 h + i/4, columns 32 cb + 16 (group & 1) + 4 (i%4).
+  uint32_t ka[KK];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) { sT[j] = 0.f; sT2[j] = 0.f; }
+  for (int kk = 0; kk < KK; ++kk) ka[kk] = (uint32_t)(uintptr_t)(lds_u32x4 *)(kb + ql * CR + (h ^ swizzle<HD>(ql) ^ (2 * kk)));
+  const int vi = lane & 15, vrow = 4 * h + (vi >> 2);
+  const int vx = (2 * ((lane >> 4) & 1) + ((vi & 3) >> 1)) ^ swizzle<HD>(vrow);
+  uint32_t va[2 * CB];  // LDS byte address of (cb, part); mm adds 16 rows
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int part = 0; part < 2; ++part)
+      va[2 * cb + part] = (uint32_t)(uintptr_t)(lds_u32x4 *)(vb + (vrow + 8 * part) * CR + (vx ^ (4 * cb) ^ (2 * part))) + (vi & 1) * 8;
+
+  // s_waitcnt immediates: vmcnt in bits 3:0 and 15:14; lgkmcnt and expcnt not waited for
+  constexpr int kVm = 0x0F70 | NI, kVm0 = 0x0F70;
+  for (int t0 = t_first; t0 < t_end; t0 += 32 * NW) {
+    const bool more = t0 + 32 * NW < t_end;
+    // K of this tile has landed; the NI loads of its V may still be in flight
+    __builtin_amdgcn_s_waitcnt(kVm);
+    asm volatile("" ::: "memory");
+    f32x16 sT;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) sT[j] = 0.f;
+    {  // (the reads have returned where their assembly ends: the buffer is free then)
+      u32x4 kreg[KK];
+      read_k(kreg, ka);
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) {
-        sT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kreg[kk]),
-                                                     __builtin_bit_cast(bf16x8, qreg[w][kk]), sT, 0, 0, 0);
-        sT2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kreg[kk]),
-                                                      __builtin_bit_cast(bf16x8, qlo[w][kk]), sT2, 0, 0, 0);
+        sT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kreg[kk]), __builtin_bit_cast(bf16x8, qlo[kk]), sT, 0, 0, 0);
+        sT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kreg[kk]), __builtin_bit_cast(bf16x8, qh[kk]), sT, 0, 0, 0);
       }
-      if (w == RGW - 1 && more) issue_k(t0 + 128);
-      // lane holds, for query ql, the keys t0 + 8*(j/4) + 4*h + j%4
-      float mx = -INFINITY;
-      if (t0 + 32 <= L) {  // tile inside the prefix: every key visible to every valid query
+    }
+    if (more) issue(kbase, kb, t0 + 32 * NW);
+    // lane holds, for query ql, the keys t0 + 8*(j/4) + 4*h + j%4
+    if (t0 + 32 > L) {  // a tile with tree slots: bit i of w = key t0 + i is visible
+      const int d = t0 - L;
+      uint32_t w = d >= 0 ? (uint32_t)(anc >> d) : ((uint32_t)(anc << -d) | ((1u << -d) - 1u));
+      w >>= 4 * h;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          sT[j] = valid[w] ? sT[j] + sT2[j] : -INFINITY;
-          mx = fmaxf(mx, sT[j]);
-        }
-      } else {
+      for (int j = 0; j < 16; ++j) sT[j] = (w >> (8 * (j >> 2) + (j & 3))) & 1u ? sT[j] : -INFINITY;
+    }
+    float mx = sT[0];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int key = t0 + 8 * (j >> 2) + 4 * h + (j & 3);
-          const bool vis = valid[w] && key < T && (key < L || ((anc[w] >> ((key - L) & 63)) & 1ull));
-          sT[j] = vis ? sT[j] + sT2[j] : -INFINITY;
-          mx = fmaxf(mx, sT[j]);
-        }
+    for (int j = 1; j < 16; ++j) mx = fmaxf(mx, sT[j]);
+    mx = max_halves(mx);
+    // The reference maximum moves only when the scores outgrow it by 2^8: probabilities stay below 2^8,
+    // exact enough in fp32 sums and in two bf16 planes, and the output is rarely rescaled.
+    const bool grow = mx > m_run + 8.f;  // also the first visible key (m_run = -inf)
+    if (__ballot(grow) != 0ull) {
+      const float m_new = grow ? mx : m_run;
+      const float alpha = grow ? exp2_fast(m_run - m_new) : 1.f;
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) o[cb][j] *= alpha;
+    }
+    // a query that has seen no key yet subtracts 0: its scores stay -inf and give probability 0
+    const float m_sub = m_run == -INFINITY ? 0.f : m_run;
+    float p[16], ps[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      p[j] = exp2_fast(sT[j] - m_sub);
+      ps[j & 3] += p[j];
+    }
+    l_run += (ps[0] + ps[1]) + (ps[2] + ps[3]);
+    // P^T as B operand: MFMA mm covers keys 16*mm .. 16*mm+15 of the tile; this lane's k-slots
+    // i = 0..7 are keys 16*mm + 8*(i/4) + 4*h + i%4, i.e. its own p[8*mm + i]
+    u32x4 pb[2], pl[2];
+#pragma unroll
+    for (int mm = 0; mm < 2; ++mm)
+#pragma unroll
+      for (int i2 = 0; i2 < 4; ++i2) {
+        uint32_t hi2, lo2;
+        split_bf16_pair(p[8 * mm + 2 * i2], p[8 * mm + 2 * i2 + 1], hi2, lo2);
+        pb[mm][i2] = hi2;
+        pl[mm][i2] = lo2;
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m_run[w], mx);
-      const bool any = m_new != -INFINITY;
-      const float alpha = (m_run[w] == -INFINITY) ? 0.f : __expf(m_run[w] - m_new);
-      // exp(-inf) = 0 covers the masked keys; a query that has seen no key yet (m_new = -inf)
-      // subtracts 0 instead, so that all of its scores stay -inf and give 0 as well
-      const float m_sub = any ? m_new : 0.f;
-      float p[16], psum = 0.f;
+    // V of this tile has landed; the NI loads of the next K may still be in flight
+    if (more) __builtin_amdgcn_s_waitcnt(kVm);
+    else __builtin_amdgcn_s_waitcnt(kVm0);
+    asm volatile("" ::: "memory");
+    auto pv = [&](const u32x2 (&v)[2 * CB], int mm) {
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        p[j] = __expf(sT[j] - m_sub);
-        psum += p[j];
-      }
-      psum += __shfl_xor(psum, 32, 64);
-      const bool rescale = alpha != 1.0f && l_run[w] != 0.f;  // something accumulated and the max moved
-      l_run[w] = l_run[w] * alpha + psum;
-      m_run[w] = m_new;
-      if (__ballot(rescale) != 0ull) {
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-          for (int j = 0; j < 16; ++j) o[w][cb][j] *= alpha;
-      }
-      // P^T as B operand: MFMA mm covers keys 16*mm .. 16*mm+15 of the tile; this lane's k-slots
-      // i = 0..7 are keys 16*mm + 8*(i/4) + 4*h + i%4, i.e. its own p[8*mm + i]
-#pragma unroll
-      for (int mm = 0; mm < 2; ++mm) {
-        u32x4 pb, pl;  // probabilities as hi + lo bf16 planes
-#pragma unroll
-        for (int i2 = 0; i2 < 4; ++i2) {
-          uint32_t hi2, lo2;
-          split_bf16_pair(p[8 * mm + 2 * i2], p[8 * mm + 2 * i2 + 1], hi2, lo2);
-          pb[i2] = hi2;
-          pl[i2] = lo2;
-        }
-        // matching V^T k-slots: key pairs 8*mm + 2*h, +1, 8*mm + 4 + 2*h, +1
-        const uint32_t *vrow = vpb + (8 * mm + 2 * h) * HD + ql;
+      for (int pass = 0; pass < 2; ++pass)  // lo products, then hi: CB independent accumulators in between
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
-          u32x4 vreg;
-          vreg[0] = vrow[32 * cb];
-          vreg[1] = vrow[32 * cb + HD];
-          vreg[2] = vrow[32 * cb + 4 * HD];
-          vreg[3] = vrow[32 * cb + 5 * HD];
-          o[w][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vreg),
-                                                             __builtin_bit_cast(bf16x8, pb), o[w][cb], 0, 0, 0);
-          o[w][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vreg),
-                                                             __builtin_bit_cast(bf16x8, pl), o[w][cb], 0, 0, 0);
+          const u32x4 vv = (u32x4){v[2 * cb][0], v[2 * cb][1], v[2 * cb + 1][0], v[2 * cb + 1][1]};
+          o[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv), __builtin_bit_cast(bf16x8, pass ? pb[mm] : pl[mm]), o[cb], 0, 0, 0);
         }
-      }
+    };
+    {
+      u32x2 v0[2 * CB], v1[2 * CB];
+      read_v<2 * CB, 0>(v0, va);
+      pv(v0, 0);
+      read_v<2 * CB, 16 * HD * 2>(v1, va);
+      pv(v1, 1);
     }
-  };
-
-  const int t_first = t_begin + 32 * wave;  // this wavefront's tiles: t_first, +128, +256, ...
-  if (t_first < t_end) {
-    issue_k(t_first);
-    issue_v(t_first);
+    if (more) issue(vbase, vb, t0 + 32 * NW);
   }
-  int vbuf = 0;  // the two LDS tiles of the wavefront alternate
-  for (int t0 = t_first; t0 < t_end; t0 += 128, vbuf ^= 1) compute(t0, vp + vbuf * (16 * HD), t0 + 128 < t_end);
 
-  // merge the four wavefronts: everything to LDS in register layout, then wavefront cb reduces
-  // column block cb and writes the workgroup's partial result
+  // Merge: every wavefront leaves its output in its own two tile buffers (column blocks of the lower half of
+  // the head in kbuf, of the upper half in vbuf), C layout [cb][q][lane] x 4 columns, then all threads
+  // reduce: item = (cb, q, lane) = query lane%32, columns 32 cb + 8 q + 4 (lane/32) .. +3
+  constexpr int HB = CB / 2;
+  l_run = sum_halves(l_run);
+  float4 *ko = reinterpret_cast<float4 *>(kbuf), *vo = reinterpret_cast<float4 *>(vbuf);
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) {
+    float4 *dst = (cb < HB ? ko : vo) + wave * TU + (cb % HB) * 256 + lane;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) dst[q * 64] = make_float4(o[cb][4 * q], o[cb][4 * q + 1], o[cb][4 * q + 2], o[cb][4 * q + 3]);
+  }
+  if (h == 0) ml[wave * 32 + ql] = make_float2(m_run, l_run);
   __syncthreads();
-  float *lo_ = reinterpret_cast<float *>(lds_attn);
-  float *lml = lo_ + 4 * RGW * CB * 1024;
+  if (!valid) return;
+  float wgt[NW], M = -INFINITY, Lsum = 0.f;
 #pragma unroll
-  for (int w = 0; w < RGW; ++w) {
+  for (int v = 0; v < NW; ++v) {
+    wgt[v] = ml[v * 32 + ql].x;
+    M = fmaxf(M, wgt[v]);
+  }
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
+  for (int v = 0; v < NW; ++v) {
+    wgt[v] = wgt[v] == -INFINITY ? 0.f : exp2_fast(wgt[v] - M);
+    Lsum += wgt[v] * ml[v * 32 + ql].y;
+  }
+  const int64_t pbase = ((int64_t)chunk * rows + out_row) * H + out_head;
+  if (out == nullptr && wave == 0 && h == 0) *reinterpret_cast<float2 *>(ml_part + pbase * 2) = make_float2(M, Lsum);
+  const float inv = 1.f / Lsum;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) lo_[(((wave * RGW + w) * CB + cb) * 16 + j) * 64 + lane] = o[w][cb][j];
-    if (h == 0) {
-      lml[((wave * RGW + w) * 32 + ql) * 2] = m_run[w];
-      lml[((wave * RGW + w) * 32 + ql) * 2 + 1] = l_run[w];
+  for (int u = wave; u < CB * 4; u += NW) {
+    const int cb = u >> 2, q = u & 3;
+    const float4 *src = (cb < HB ? ko : vo) + (cb % HB) * 256 + q * 64 + lane;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < NW; ++v) {
+      const float4 z = src[v * TU];
+      acc[0] += wgt[v] * z.x; acc[1] += wgt[v] * z.y; acc[2] += wgt[v] * z.z; acc[3] += wgt[v] * z.w;
     }
-  }
-  __syncthreads();
-  if (wave < CB) {
-    const int cb = wave;
+    const int col = 32 * cb + 8 * q + 4 * h;
+    if (out != nullptr) {
+      // every sequence is a single chunk: this IS the result -- normalise and write the packed hi/lo
+      // planes the output projection reads (what the merge kernel would do with one chunk)
+      uint32_t hi2[2], lo2[2];
 #pragma unroll
-    for (int w = 0; w < RGW; ++w) {
-      float mw[4], M = -INFINITY;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        mw[v] = lml[((v * RGW + w) * 32 + ql) * 2];
-        M = fmaxf(M, mw[v]);
-      }
-      float Lsum = 0.f, acc[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) acc[j] = 0.f;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const float wgt = (mw[v] == -INFINITY) ? 0.f : __expf(mw[v] - M);
-        Lsum += wgt * lml[((v * RGW + w) * 32 + ql) * 2 + 1];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) acc[j] += wgt * lo_[(((v * RGW + w) * CB + cb) * 16 + j) * 64 + lane];
-      }
-      if (!valid[w]) continue;
-      // O^T lane layout = query column ql, output columns 32*cb + 8*(j/4) + 4*h + j%4
-      if (out != nullptr) {
-        // every sequence is a single chunk: this IS the result -- normalise and write the packed
-        // hi/lo planes the output projection reads (what the merge kernel would do with one chunk)
-        const int col0 = out_head[w] * HD + 32 * cb + 4 * h;
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          uint16_t hi4[4], lo4[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) split_bf16(acc[4 * q4 + i] / Lsum, hi4[i], lo4[i]);
-          const int64_t po = packed_act_offset(out_row[w], col0 + 8 * q4, nb);
-          *reinterpret_cast<uint2 *>(out + po) =
-              make_uint2((uint32_t)hi4[0] | ((uint32_t)hi4[1] << 16), (uint32_t)hi4[2] | ((uint32_t)hi4[3] << 16));
-          *reinterpret_cast<uint2 *>(out_lo + po) =
-              make_uint2((uint32_t)lo4[0] | ((uint32_t)lo4[1] << 16), (uint32_t)lo4[2] | ((uint32_t)lo4[3] << 16));
-        }
-        continue;
-      }
-      const int64_t base = ((int64_t)chunk * rows + out_row[w]) * H + out_head[w];
-      float *op = o_part + base * HD + 32 * cb + 4 * h;
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4)
-        *reinterpret_cast<float4 *>(op + 8 * q4) = make_float4(acc[4 * q4], acc[4 * q4 + 1], acc[4 * q4 + 2], acc[4 * q4 + 3]);
-      if (cb == 0 && h == 0) {
-        ml_part[base * 2] = M;
-        ml_part[base * 2 + 1] = Lsum;
-      }
+      for (int i = 0; i < 2; ++i) split_bf16_pair(acc[2 * i] * inv, acc[2 * i + 1] * inv, hi2[i], lo2[i]);
+      const int64_t po = packed_act_offset(out_row, out_head * HD + col, nb);
+      *reinterpret_cast<uint2 *>(out + po) = make_uint2(hi2[0], hi2[1]);
+      *reinterpret_cast<uint2 *>(out_lo + po) = make_uint2(lo2[0], lo2[1]);
+    } else {
+      *reinterpret_cast<float4 *>(o_part + pbase * HD + col) = make_float4(acc[0], acc[1], acc[2], acc[3]);
     }
   }
 }
 
-// Merge the key chunks: out = sum_c e^(m_c - M) o_c / sum_c e^(m_c - M) l_c, rounded to bf16.
-// grid (H, rows), block HD.
-__global__ void tree_attention_merge_kernel(StepMeta m, int H, int HD, int chunk_keys,
-                                            const float *__restrict__ o_part,
-                                            const float *__restrict__ ml_part,
-                                            uint16_t *__restrict__ out, uint16_t *__restrict__ out_lo,
-                                            int nb) {
-  const int a = blockIdx.x, r = blockIdx.y, c = threadIdx.x, rows = m.rows;
+// Merge the key chunks: out = sum_c 2^(m_c - M) o_c / sum_c 2^(m_c - M) l_c, as hi/lo planes.  One thread
+// per 4 columns of a (row, head): 16-byte loads, 8 chunks of them in flight (7B, 32 rows, 7 chunks: 4.9 us with
+// one column per thread).  grid ceil(rows * H * HD / 1024), block 256.
+template <int HD>
+__global__ __launch_bounds__(256) void tree_attention_merge_kernel(StepMeta m, int H, int chunk_keys,
+                                                                   const float *__restrict__ o_part,
+                                                                   const float *__restrict__ ml_part,
+                                                                   uint16_t *__restrict__ out, uint16_t *__restrict__ out_lo,
+                                                                   int nb) {
+  constexpr int TPR = HD / 4;  // threads per (row, head)
+  const int rows = m.rows;
+  const uint32_t rh = (blockIdx.x * 256 + threadIdx.x) / TPR;  // row * H + head
+  if (rh >= (uint32_t)(rows * H)) return;
+  const int c = (threadIdx.x & (TPR - 1)) * 4, r = rh / (uint32_t)H, a = rh - r * H;
   const int seq = m.seq_of_row(r);
   const int T = m.seq_kv_len(seq) + m.seq_n_nodes(seq);
-  const int n_chunks = (T + chunk_keys - 1) / chunk_keys;
+  const int n_chunks = (uint32_t)(T + chunk_keys - 1) / (uint32_t)chunk_keys;
   // batches of 8 chunks with all loads issued together; running (max, numerator, denominator)
-  float M = -INFINITY, num = 0.f, den = 0.f;
+  float M = -INFINITY, den = 0.f, num[4] = {0.f, 0.f, 0.f, 0.f};
   const int64_t cstride = (int64_t)rows * H;
-  const int64_t base0 = (int64_t)r * H + a;
   for (int c0 = 0; c0 < n_chunks; c0 += 8) {
-    float mc[8], lc[8], oc[8];
+    float2 ml[8];
+    float4 oc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int ch = min(c0 + i, n_chunks - 1);
-      const int64_t base = base0 + ch * cstride;
-      mc[i] = (c0 + i < n_chunks) ? ml_part[base * 2] : -INFINITY;
-      lc[i] = ml_part[base * 2 + 1];
-      oc[i] = o_part[base * HD + c];
+      const int64_t base = rh + min(c0 + i, n_chunks - 1) * cstride;
+      ml[i] = *reinterpret_cast<const float2 *>(ml_part + base * 2);
+      oc[i] = *reinterpret_cast<const float4 *>(o_part + base * HD + c);
     }
     float Mb = M;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) Mb = fmaxf(Mb, mc[i]);
+    for (int i = 0; i < 8; ++i) {
+      if (c0 + i >= n_chunks) ml[i].x = -INFINITY;
+      Mb = fmaxf(Mb, ml[i].x);
+    }
     if (Mb == -INFINITY) continue;
-    const float scale = (M == -INFINITY) ? 0.f : __expf(M - Mb);
-    num *= scale;
+    const float scale = (M == -INFINITY) ? 0.f : exp2_fast(M - Mb);
     den *= scale;
 #pragma unroll
+    for (int k = 0; k < 4; ++k) num[k] *= scale;
+#pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float wgt = (mc[i] == -INFINITY) ? 0.f : __expf(mc[i] - Mb);
-      num += wgt * oc[i];
-      den += wgt * lc[i];
+      const float wgt = (ml[i].x == -INFINITY) ? 0.f : exp2_fast(ml[i].x - Mb);
+      num[0] += wgt * oc[i].x; num[1] += wgt * oc[i].y; num[2] += wgt * oc[i].z; num[3] += wgt * oc[i].w;
+      den += wgt * ml[i].y;
     }
     M = Mb;
   }
-  const int64_t oi = packed_act_offset(r, a * HD + c, nb);  // B-operand order of the output projection
-  split_bf16(num / den, out[oi], out_lo[oi]);
+  const float inv = 1.f / den;
+  uint32_t hi2[2], lo2[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) split_bf16_pair(num[2 * i] * inv, num[2 * i + 1] * inv, hi2[i], lo2[i]);
+  const int64_t po = packed_act_offset(r, a * HD + c, nb);  // B-operand order of the output projection
+  *reinterpret_cast<uint2 *>(out + po) = make_uint2(hi2[0], hi2[1]);
+  *reinterpret_cast<uint2 *>(out_lo + po) = make_uint2(lo2[0], lo2[1]);
 }
 
 template <int HD>
-static void launch_attn_hd(const StepMeta &m, const ModelDims &md, const KvGeom &g, int layer,
+static void launch_attn_hd(const StepMeta &m, const AttnSeqs &sq, const ModelDims &md, const KvGeom &g, int layer,
                            int max_seq_nodes, int chunk_keys, int n_chunks,
                            const uint16_t *qb, const uint16_t *qb_lo, const void *kc, const void *vc,
                            float *o_part, float *ml_part, uint16_t *out, uint16_t *out_lo, int nb,
@@ -373,49 +411,41 @@ static void launch_attn_hd(const StepMeta &m, const ModelDims &md, const KvGeom 
   const int G = md.n_heads / md.n_kv_heads;
   const int row_groups = (G * max_seq_nodes + 31) / 32;
   const bool direct = n_chunks == 1;  // nothing to merge: the attention kernel writes the final planes
-  // LDS: 4 wavefronts x 2 V tiles, reused for the merge (4 x RGW x HD/32 x 4 KB + (m, l))
-  auto lds_bytes = [](int rgw) {
-    const size_t vt = (size_t)4 * 2 * 16 * HD * 4;
-    const size_t mg = (size_t)4 * rgw * (HD / 32) * 4096 + (size_t)4 * rgw * 32 * 2 * 4;
-    return vt > mg ? vt : mg;
-  };
   dim3 grid((n_chunks * md.n_kv_heads + 7) / 8 * 8 * row_groups, 1, m.batch);
-  tree_attention_kernel<HD, 1><<<grid, 256, lds_bytes(1), st>>>(m, g, layer, md.n_heads, md.n_kv_heads, row_groups, qb, qb_lo, (const uint16_t *)kc, (const uint16_t *)vc, chunk_keys, n_chunks, o_part, ml_part, direct ? out : nullptr, direct ? out_lo : nullptr, nb);
+  tree_attention_kernel<HD><<<grid, 64 * kAttnWaves, 0, st>>>(m, sq, g, layer, md.n_heads, md.n_kv_heads, row_groups, qb, qb_lo, (const uint16_t *)kc, (const uint16_t *)vc, chunk_keys, n_chunks, o_part, ml_part, direct ? out : nullptr, direct ? out_lo : nullptr, nb);
   if (direct) return;
-  dim3 mgrid(md.n_heads, m.rows);
-  tree_attention_merge_kernel<<<mgrid, HD, 0, st>>>(m, md.n_heads, HD, chunk_keys, o_part, ml_part, out, out_lo, nb);
+  const unsigned mgrid = (unsigned)(((int64_t)m.rows * md.n_heads * HD + 1023) / 1024);
+  tree_attention_merge_kernel<HD><<<mgrid, 256, 0, st>>>(m, md.n_heads, chunk_keys, o_part, ml_part, out, out_lo, nb);
 }
+
+float tree_attention_qscale(int head_dim) { return 1.44269504088896340736f / sqrtf((float)head_dim); }
 
 bool tree_attention_supported(int head_dim) { return head_dim == 64 || head_dim == 128; }
 
 int tree_attention_max_chunks(int n_kv_heads) { return 256 / n_kv_heads + 2; }
 
-hipError_t tree_attention_set_lds_limit() {
-  const int big = 4 * 4 * 4096 + 4 * 32 * 2 * 4;  // merge area at head_dim 128: the larger of the two uses
-  hipError_t e = hipFuncSetAttribute((const void *)tree_attention_kernel<128, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, big);
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute((const void *)tree_attention_kernel<64, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, big);
-}
-
 // Key-chunk size (a multiple of 32).  One sequence: ~256 workgroups (one per compute unit) over
 // its keys.  Several sequences (a batch, or the pieces of a wide prefill pass): if (KV heads x
-// sequences x row-group blocks) already gives a workgroup per compute unit, every sequence is one
-// chunk (measured on the 7B prefill: 23.7 us against 28.8 with two chunks); otherwise the sequences
-// differ in length and there are few heads to spread them, so the chunks are made smaller -- ~1024
-// workgroups if all were as long as the longest, at least 128 keys (one tile per wavefront) -- and
-// the short ones simply need fewer of them (1.1B, 16 utterances: 67 us against 80); the number of
+// sequences x row-group blocks) already gives half a workgroup per compute unit, every sequence is one
+// chunk and no merge runs (4 utterances of 200 .. 1500 keys on the 7B model, 128 workgroups: 23.2 us against
+// 19.0 + 6.0 in chunks of 320 keys); otherwise the sequences differ in length and there are few heads to
+// spread them, so the chunks are made smaller -- ~1024 workgroups if all were as long as the longest, at
+// least 128 keys (one tile per wavefront) -- and the short ones simply need fewer of them; the number of
 // chunks stays within what the wide workspace holds (128 / n_kv_heads + 1).
 int tree_attention_chunk_keys(int max_total_keys, int n_kv_heads, int batch, int row_group_blocks, int min_chunk_keys) {
   const long target = batch > 1 ? 1024 : 256;
   long want = ((long)max_total_keys * n_kv_heads * batch * row_group_blocks + target - 1) / target;
   long ck = (want + 31) / 32 * 32;
-  if (ck < 32) ck = 32;
+  // at least one tile per wavefront; more chunks only make the merge longer (1.1B, one row, 1600 keys: attention +
+  // merge 8.5 us with chunks of 256 keys, 9.0 with 128)
+  if (ck < 128) ck = batch == 1 && max_total_keys > 1280 ? 256 : 128;
   // a short single sequence: one chunk, the attention kernel writes the result itself and no merge
-  // kernel runs (1.1B, ~360 keys: 1.536 against 1.555 ms per forward; at 842 keys it loses)
-  if (batch == 1 && max_total_keys <= 512) ck = 512;
+  // kernel runs.  1.1B: 0.7 us per further round of 4 tiles against 3.1 for the merge (one chunk: 5.9 us at 331 keys,
+  // about 8 at 700; 128-key chunks + merge 7.9 at 800); 7B, 32 nodes: 1.1 us against 4.5 (842 keys: 14.7
+  // against 13.5)
+  if (batch == 1 && max_total_keys <= 704) ck = 704;
   if (batch > 1) {
-    if (ck < 128) ck = 128;
-    if ((long)n_kv_heads * batch * row_group_blocks >= 256) ck = ((long)max_total_keys + 31) / 32 * 32;
+    if ((long)n_kv_heads * batch * row_group_blocks >= 128) ck = ((long)max_total_keys + 31) / 32 * 32;
     const long max_chunks = 128 / n_kv_heads + 1;
     const long ck_min = ((max_total_keys + max_chunks - 1) / max_chunks + 31) / 32 * 32;
     if (ck < ck_min) ck = ck_min;
@@ -428,7 +458,17 @@ void launch_tree_attention(const StepMeta &m, const ModelDims &md, const KvGeom 
                            int max_total_keys, int max_seq_nodes, const uint16_t *qb,
                            const uint16_t *qb_lo, const void *kc, const void *vc, float *o_part,
                            float *ml_part, uint16_t *out, uint16_t *out_lo, int nb, int min_chunk_keys,
-                           hipStream_t st) {
+                           const int32_t *seq_kv_len, const int32_t *seq_row_start, const int32_t *seq_n_nodes, hipStream_t st) {
+  AttnSeqs sq{};
+  if (m.batch > 1 && m.batch <= 16) {
+    sq.count = m.batch;
+    for (int b = 0; b < m.batch; ++b) {
+      const int4 e = make_int4(seq_kv_len[b], seq_n_nodes[b], seq_row_start[b], b);
+      int at = b;  // insertion by falling key count
+      for (; at > 0 && sq.e[at - 1].x + sq.e[at - 1].y < e.x + e.y; --at) sq.e[at] = sq.e[at - 1];
+      sq.e[at] = e;
+    }
+  }
   const int G = md.n_heads / md.n_kv_heads;
   // One query row group (32 rows) per workgroup.  Two per workgroup would halve the key traffic
   // (head_dim 64: the accumulators would fit), but the keys of a head are L2 hits after their
@@ -438,9 +478,9 @@ void launch_tree_attention(const StepMeta &m, const ModelDims &md, const KvGeom 
   const int ck = tree_attention_chunk_keys(max_total_keys, md.n_kv_heads, m.batch, row_groups, min_chunk_keys);
   const int n_chunks = (max_total_keys + ck - 1) / ck;
   if (md.head_dim == 64)
-    launch_attn_hd<64>(m, md, g, layer, max_seq_nodes, ck, n_chunks, qb, qb_lo, kc, vc, o_part, ml_part, out, out_lo, nb, st);
+    launch_attn_hd<64>(m, sq, md, g, layer, max_seq_nodes, ck, n_chunks, qb, qb_lo, kc, vc, o_part, ml_part, out, out_lo, nb, st);
   else
-    launch_attn_hd<128>(m, md, g, layer, max_seq_nodes, ck, n_chunks, qb, qb_lo, kc, vc, o_part, ml_part, out, out_lo, nb, st);
+    launch_attn_hd<128>(m, sq, md, g, layer, max_seq_nodes, ck, n_chunks, qb, qb_lo, kc, vc, o_part, ml_part, out, out_lo, nb, st);
 }
 
 }  // namespace specasr

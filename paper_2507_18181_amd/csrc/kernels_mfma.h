@@ -51,12 +51,13 @@ void launch_logits_argmax(const StepMeta &m, const float *part, int n_splits, in
 
 // tree-masked MFMA attention (kernels_attn.hip)
 bool tree_attention_supported(int head_dim);
+float tree_attention_qscale(int head_dim);  // factor of the queries it is given: log2(e) / sqrt(head_dim)
 int tree_attention_max_chunks(int n_kv_heads);
-hipError_t tree_attention_set_lds_limit();
 void launch_tree_attention(const StepMeta &m, const ModelDims &md, const KvGeom &g, int layer,
                            int max_total_keys, int max_seq_nodes, const uint16_t *qb,
                            const uint16_t *qb_lo, const void *kc, const void *vc, float *o_part,
                            float *ml_part, uint16_t *out, uint16_t *out_lo, int nb, int min_chunk_keys,
+                           const int32_t *seq_kv_len, const int32_t *seq_row_start, const int32_t *seq_n_nodes,  // host, [batch]
                            hipStream_t st);
 
 }  // namespace specasr

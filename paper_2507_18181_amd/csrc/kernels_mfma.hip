@@ -583,7 +583,7 @@ void launch_residual_gain(float *x, const float *part, int n_splits, int rows, i
 
 // q, k, v = sum of partials; rotary embedding at the node's depth position (Sec. II-B: each
 // branch is verified as its own sequence, so position = kv_len + depth).  Outputs: q either as
-// fp32 [rows][H*hd] (generic attention) or as bf16 pre-multiplied by 1/sqrt(hd) (MFMA
+// fp32 [rows][H*hd] (generic attention) or as bf16 pre-multiplied by log2(e)/sqrt(hd) (MFMA
 // attention); k, v -> bf16 cache slot kv_len + node.  Packed columns: [q | pad | k | pad | v]; with
 // `paired` the rows of a query or key head are stored as launch_repack_rope leaves them.
 __device__ __forceinline__ int rope_col(int j, int paired) { return paired ? ((j >> 3) << 4) + (j & 7) : j; }
@@ -737,12 +737,12 @@ void launch_qkv_finish(const StepMeta &m, const ModelDims &md, const KvGeom &g, 
                        void *vc, bool paired, hipStream_t st) {
   if (m.rows > 64 && qb != nullptr && md.head_dim % 64 == 0) {
     dim3 wgrid(md.n_heads + md.n_kv_heads, (m.rows + 31) / 32);
-    qkv_finish_wide_kernel<<<wgrid, 256, 0, st>>>(m, g, layer, md.n_heads, md.n_kv_heads, md.head_dim, part, n_splits, ldp, nrm, col_k, col_v, cs, qb, qb_lo, 1.0f / sqrtf((float)md.head_dim), (uint16_t *)kc, (uint16_t *)vc, paired ? 1 : 0);
+    qkv_finish_wide_kernel<<<wgrid, 256, 0, st>>>(m, g, layer, md.n_heads, md.n_kv_heads, md.head_dim, part, n_splits, ldp, nrm, col_k, col_v, cs, qb, qb_lo, tree_attention_qscale(md.head_dim), (uint16_t *)kc, (uint16_t *)vc, paired ? 1 : 0);
     return;
   }
   const int items = (md.n_heads + md.n_kv_heads) * (md.head_dim / 2);
   dim3 grid((items + 255) / 256, m.rows);
-  qkv_finish_kernel<<<grid, 256, 0, st>>>(m, g, layer, md.n_heads, md.n_kv_heads, md.head_dim, part, n_splits, ldp, nrm, col_k, col_v, cs, q, qb, qb_lo, 1.0f / sqrtf((float)md.head_dim), (uint16_t *)kc, (uint16_t *)vc, paired ? 1 : 0);
+  qkv_finish_kernel<<<grid, 256, 0, st>>>(m, g, layer, md.n_heads, md.n_kv_heads, md.head_dim, part, n_splits, ldp, nrm, col_k, col_v, cs, q, qb, qb_lo, tree_attention_qscale(md.head_dim), (uint16_t *)kc, (uint16_t *)vc, paired ? 1 : 0);
 }
 
 // t[r][f] = bf16 planes of silu(sum_s gate) * (sum_s up); gate at column 16*(f/8) + f%8, up 8 columns
