@@ -1395,8 +1395,9 @@ specasr_status specasr_accept_from_logits(specasr_ctx *ctx, const specasr_tree *
   s = upload_meta(ctx, hs, ws, L, st);
   if (s != SPECASR_OK) return s;
   StepMeta m = device_meta(ctx, ws, L, batch, hs);
-  launch_argmax(m, logits_dev, true, ctx->cfg.max_nodes, ctx->cfg.vocab, argmax_dev, st);
-  launch_accept(m, ctx->cfg.max_nodes, argmax_dev, path_dev, accept_len_dev, next_token_dev, st);
+  // piece records in the read-out scratch: 2 floats per 4096 ids of a row, where 3 per 1024 are held
+  launch_argmax_accept(m, logits_dev, ctx->cfg.max_nodes, ctx->cfg.vocab, (float *)(ws + L.top2_v), argmax_dev, path_dev,
+                       accept_len_dev, next_token_dev, st);
   HIP_TRY(ctx, hipGetLastError());
   return SPECASR_OK;
 }

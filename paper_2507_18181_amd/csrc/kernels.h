@@ -55,6 +55,11 @@ void launch_top2(const StepMeta &m, const float *src, bool from_partials, int n_
 // greedy acceptance, one wavefront per sequence; argmax in [batch][max_nodes] layout
 void launch_accept(const StepMeta &m, int max_nodes, const int32_t *argmax, int32_t *path,
                    int32_t *accept_len, int32_t *next_token, hipStream_t st);
+// argmax of the caller's padded logits ([batch][max_nodes][V]), then the acceptance above.  rec: rows *
+// argmax_pieces(V) pairs of floats.
+int argmax_pieces(int V);
+void launch_argmax_accept(const StepMeta &m, const float *logits, int max_nodes, int V, float *rec, int32_t *argmax,
+                          int32_t *path, int32_t *accept_len, int32_t *next_token, hipStream_t st);
 // in-place compaction of the accepted path's cache rows (path/accept_len on the device)
 void launch_compact(int dtype, const KvGeom &g, int batch, int max_nodes, const int32_t *kv_len,
                     const int32_t *path, const int32_t *accept_len, void *kcache, void *vcache,

@@ -294,6 +294,52 @@ void launch_argmax(const StepMeta &m, const float *logits, bool padded_in, int m
   argmax_kernel<<<m.rows, 256, 0, st>>>(m, logits, padded_in ? 1 : 0, max_nodes, V, argmax);
 }
 
+// The same for the caller's padded logits, the vocabulary of a row cut into pieces of kArgmaxPiece ids so
+// that a 64-node tree fills the chip (64 rows x 32000: one workgroup per row 23.4 us, 8 per row 4.5):
+// record (value, lowest id) per (row, piece); accept_kernel merges them.
+constexpr int kArgmaxPiece = 4096;
+int argmax_pieces(int V) { return (V + kArgmaxPiece - 1) / kArgmaxPiece; }
+
+__global__ __launch_bounds__(256) void argmax_pieces_kernel(StepMeta m, const float *logits, int max_nodes, int V, float2 *rec) {
+  __shared__ float bv[4];
+  __shared__ int bi[4];
+  const int r = blockIdx.y, t0 = blockIdx.x * kArgmaxPiece;
+  const float *row = logits + (int64_t)(m.seq[r] * max_nodes + m.node[r]) * V;
+  float best = -INFINITY;
+  int besti = 0x7fffffff;
+  auto take = [&](float v, int t) {
+    if (v > best || (v == best && t < besti)) { best = v; besti = t; }
+  };
+  const int t1 = min(t0 + kArgmaxPiece, V);
+  if ((V & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0) {  // every row starts on 16 bytes
+    float4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = t0 + (i * 256 + (int)threadIdx.x) * 4;
+      v[i] = t < t1 ? *reinterpret_cast<const float4 *>(row + t) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = t0 + (i * 256 + (int)threadIdx.x) * 4;
+      if (t < t1) { take(v[i].x, t); take(v[i].y, t + 1); take(v[i].z, t + 2); take(v[i].w, t + 3); }
+    }
+  } else {
+    for (int t = t0 + threadIdx.x; t < t1; t += 256) take(row[t], t);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const float ov = __shfl_xor(best, o, 64);
+    const int oi = __shfl_xor(besti, o, 64);
+    take(ov, oi);
+  }
+  if ((threadIdx.x & 63) == 0) { bv[threadIdx.x >> 6] = best; bi[threadIdx.x >> 6] = besti; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w) take(bv[w], bi[w]);
+    rec[(int64_t)r * gridDim.x + blockIdx.x] = make_float2(best, __int_as_float(besti));
+  }
+}
+
 __global__ void scatter_logits_kernel(StepMeta m, const float *compact, int max_nodes, int V,
                                       float *padded) {
   const int r = blockIdx.x;
@@ -457,21 +503,39 @@ void launch_top2(const StepMeta &m, const float *src, bool from_partials, int n_
 // target's greedy token at its parent; ballot gathers the match flags into one mask; a node is
 // acceptable when its ancestor mask has no unmatched bit; the deepest acceptable node wins
 // (lowest index among equals).
+// pieces > 0: the argmax of a node is first merged from its piece records and written (argmax_pieces_kernel).
 __global__ __launch_bounds__(64) void accept_kernel(StepMeta m, int max_nodes,
-                                                    const int32_t *argmax, int32_t *path,
+                                                    int32_t *argmax, const float2 *rec, int pieces, int32_t *path,
                                                     int32_t *accept_len, int32_t *next_token) {
   const int s = blockIdx.x, lane = threadIdx.x;
   const int n = m.n_nodes[s], r0 = m.row_start[s];
-  const int32_t *am = argmax + (int64_t)s * max_nodes;
+  int32_t *am = argmax + (int64_t)s * max_nodes;
   bool matched = false;
   uint64_t anc = 0;
-  int depth = 0;
+  int depth = 0, par = 0, tok = 0, mine = 0;
   if (lane < n) {
-    const int par = max(m.parent[r0 + lane], 0);
-    matched = (lane == 0) || (m.token[r0 + lane] == am[par]);
+    par = max(m.parent[r0 + lane], 0);
+    tok = m.token[r0 + lane];
     anc = m.anc[r0 + lane];
     depth = m.depth[r0 + lane];
+    if (pieces > 0) {
+      float best = -INFINITY;
+      int besti = 0x7fffffff;
+      const float2 *p = rec + (int64_t)(r0 + lane) * pieces;
+#pragma unroll 8
+      for (int i = 0; i < pieces; ++i) {
+        const float2 q = p[i];
+        const int qi = __float_as_int(q.y);
+        if (q.x > best || (q.x == best && qi < besti)) { best = q.x; besti = qi; }
+      }
+      mine = besti == 0x7fffffff ? 0 : besti;
+      am[lane] = mine;
+    } else {
+      mine = am[lane];
+    }
   }
+  const int want = __shfl(mine, par, 64);  // the target's token after the parent
+  if (lane < n) matched = lane == 0 || tok == want;
   const uint64_t mm = __ballot(matched);
   const bool ok = lane < n && (anc & ~mm) == 0ull;
   int key = ok ? (depth * 64 + (63 - lane)) : -1;
@@ -483,15 +547,23 @@ __global__ __launch_bounds__(64) void accept_kernel(StepMeta m, int max_nodes,
   int32_t *p = path + (int64_t)s * max_nodes;
   if (lane < max_nodes && lane > wdepth) p[lane] = -1;
   if (lane < n && ((wanc >> lane) & 1ull)) p[depth] = lane;
+  const int next = __shfl(mine, win, 64);
   if (lane == 0) {
     accept_len[s] = wdepth + 1;
-    next_token[s] = am[win];
+    next_token[s] = next;
   }
 }
 
 void launch_accept(const StepMeta &m, int max_nodes, const int32_t *argmax, int32_t *path,
                    int32_t *accept_len, int32_t *next_token, hipStream_t st) {
-  accept_kernel<<<m.batch, 64, 0, st>>>(m, max_nodes, argmax, path, accept_len, next_token);
+  accept_kernel<<<m.batch, 64, 0, st>>>(m, max_nodes, const_cast<int32_t *>(argmax), nullptr, 0, path, accept_len, next_token);  // only read
+}
+
+void launch_argmax_accept(const StepMeta &m, const float *logits, int max_nodes, int V, float *rec, int32_t *argmax,
+                          int32_t *path, int32_t *accept_len, int32_t *next_token, hipStream_t st) {
+  const int pieces = argmax_pieces(V);
+  argmax_pieces_kernel<<<dim3(pieces, m.rows), 256, 0, st>>>(m, logits, max_nodes, V, (float2 *)rec);
+  accept_kernel<<<m.batch, 64, 0, st>>>(m, max_nodes, argmax, (const float2 *)rec, pieces, path, accept_len, next_token);
 }
 
 // --------------------------------------------------------------------------- KV compaction

@@ -172,19 +172,24 @@ class Verifier:
     def accept(self, tokens, parents, argmax_dev=None, logits_dev=None, stream=None):
         nb = len(tokens)
         tree, keep = self._tree(tokens, parents)
-        path = torch.full((nb, self.max_nodes), -7, dtype=torch.int32, device=self.device)
-        alen = torch.zeros(nb, dtype=torch.int32, device=self.device)
-        nxt = torch.zeros(nb, dtype=torch.int32, device=self.device)
+        # path | accept_len | next_token | argmax in one buffer: one fill and one copy to the host
+        n = nb * self.max_nodes
+        buf = torch.full((2 * n + 2 * nb,), -1, dtype=torch.int32, device=self.device)
+        path, alen, nxt = buf[:n], buf[n:n + nb], buf[n + nb:n + 2 * nb]
         if logits_dev is not None:
-            argmax_dev = torch.full((nb, self.max_nodes), -1, dtype=torch.int32, device=self.device)
+            argmax_dev = buf[n + 2 * nb:].view(nb, self.max_nodes)
             rc = B.specasr_accept_from_logits(self.ctx, tree, nb, logits_dev, argmax_dev, path,
                                               alen, nxt, self.ws_ptr, self.ws_bytes, stream)
         else:
             rc = B.specasr_accept(self.ctx, tree, nb, argmax_dev, path, alen, nxt, self.ws_ptr,
                                   self.ws_bytes, stream)
         torch.cuda.synchronize()
-        return dict(status=rc, argmax=argmax_dev, path=path.cpu().numpy(),
-                    accept_len=alen.cpu().numpy(), next_token=nxt.cpu().numpy())
+        if rc != B.SPECASR_OK:
+            path.fill_(-7)
+            buf[n:n + 2 * nb] = 0
+        host = buf[:n + 2 * nb].cpu().numpy()
+        return dict(status=rc, argmax=argmax_dev, path=host[:n].reshape(nb, self.max_nodes),
+                    accept_len=host[n:n + nb], next_token=host[n + nb:])
 
     def commit(self, n_nodes, paths, stream=None):
         nb = self.batch

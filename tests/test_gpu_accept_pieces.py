@@ -1,0 +1,48 @@
+"""Acceptance from logits with the vocabulary cut into pieces: ties, infinities and NaN at the piece
+borders, vocabularies that are no multiple of 4 or of a piece, against numpy's argmax rule."""
+import numpy as np
+import pytest
+
+import oracle
+import workload as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("vocab", [1, 97, 4095, 4096, 4097, 8190, 32000])
+def test_argmax_pieces_and_acceptance(vocab):
+    from paper_2507_18181_amd.runtime import Verifier
+    cfg = dict(wl.MODELS["tiny"], n_layers=1, d_model=64, n_heads=1, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=vocab)
+    ver = Verifier(cfg, wl.make_weights(cfg, 511, "f32"), "f32", max_nodes=64, capacity=64, max_batch=3)
+    rng = np.random.default_rng([512, vocab])
+    sizes = (64, 1, 23)
+    trees = [wl.random_tree(rng, n, max_children=3) for n in sizes]
+    toks = [rng.integers(0, vocab, n).astype(np.int32) for n in sizes]
+    lg = rng.integers(-3, 4, (3, 64, vocab)).astype(np.float32)        # many ties: the lowest id wins
+    lg[0, 1] = -np.inf                                                 # no finite logit: id 0
+    lg[0, 2] = np.nan                                                  # none comparable: id 0
+    lg[0, 3, :] = -np.inf
+    lg[0, 3, vocab - 1] = -1e30                                        # the very last id
+    lg[0, 4, vocab // 2] = np.nan                                      # NaN never wins
+    lg[0, 5, ::4096] = np.inf                                          # ties between pieces
+    want = np.zeros((3, 64), np.int32)
+    for b in range(3):
+        for i in range(sizes[b]):
+            row = np.where(np.isnan(lg[b, i]), -np.inf, lg[b, i])
+            want[b, i] = int(np.argmax(row)) if not np.isnan(lg[b, i]).all() else 0
+    # follow the target along the first tree: some drafts are accepted
+    for i in range(1, 64):
+        if i % 4:
+            toks[0][i] = want[0, trees[0][i]]
+    out = ver.accept(toks, trees, logits_dev=torch.from_numpy(lg).to(ver.device))
+    assert out["status"] == 0
+    am = out["argmax"].cpu().numpy()
+    for b, n in enumerate(sizes):
+        assert np.array_equal(am[b, :n], want[b, :n])
+        assert (am[b, n:] == -1).all()
+        path, alen, nxt = oracle.accept(toks[b], trees[b], want[b, :n])
+        assert (out["accept_len"][b], out["next_token"][b]) == (alen, nxt)
+        assert out["path"][b, :alen].tolist() == path.tolist() and (out["path"][b, alen:] == -1).all()
+    ver.close()
