@@ -578,7 +578,8 @@ specasr_status prof_drain(specasr_ctx *ctx) {
 
 // Launches one projection GEMM; brackets it with events when it is the profiled one.
 void gemm_stage(specasr_ctx *ctx, int stage, bool profiled_layer, const PackedMatrix &W,
-                const uint16_t *Xp, int rows, float *part, const GemmPlan &plan, hipStream_t st) {
+                const uint16_t *Xp, int rows, float *part, const GemmPlan &plan, hipStream_t st,
+                const RowNorm *swiglu_nrm = nullptr, uint16_t *t = nullptr, uint16_t *t_lo = nullptr) {
   const bool prof = ctx->prof_stage == stage && profiled_layer && !ctx->prof_ev.empty() && (ctx->prof_mode != 2 || plan.wide);
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   if (prof) {
@@ -588,7 +589,9 @@ void gemm_stage(specasr_ctx *ctx, int stage, bool profiled_layer, const PackedMa
     ctx->prof_used += 2;
     ctx->prof_rows += rows;
   }
-  if (plan.wide)
+  if (swiglu_nrm)
+    launch_gemm_wide_swiglu(W, Xp, rows, *swiglu_nrm, t, t_lo, st, ev0, ev1);
+  else if (plan.wide)
     launch_gemm_wide(W, Xp, rows, part, plan.n_splits, stage, st, ev0, ev1);
   else
     launch_gemm_skinny(W, Xp, rows, part, plan, stage, st, ev0, ev1);
@@ -744,6 +747,8 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
     if (sl_gu.hb) {
       sa.W = pk.gu.data; sa.X = hb; sa.n_half = F / 8; sa.ksteps = pk.gu.ksteps; sa.nrm = nrm_ffn; sa.t = tb; sa.t_lo = tb_lo;
       slice_stage(ctx, SPECASR_STAGE_GATE_UP, pl, kSliceSwiglu, sa, sl_gu, st);
+    } else if (wide && pl_gu.n_splits == 1) {
+      gemm_stage(ctx, SPECASR_STAGE_GATE_UP, pl, pk.gu, hb, R, part, pl_gu, st, &nrm_ffn, tb, tb_lo);
     } else {
       gemm_stage(ctx, SPECASR_STAGE_GATE_UP, pl, pk.gu, hb, R, part, pl_gu, st);
       launch_swiglu_finish(part, pl_gu.n_splits, R, pk.gu.ldo, nrm_ffn, F, tb, tb_lo, nb, st);

@@ -30,6 +30,37 @@ __device__ __forceinline__ void split_bf16(float v, uint16_t &hi, uint16_t &lo) 
   lo = f32_to_bf16_bits(v - __uint_as_float(((uint32_t)hi) << 16));
 }
 
+// Two floats -> their hi planes packed (a in the low half) and their lo planes packed, with the
+// hardware's round-to-nearest-even conversion (one v_cvt_pk_bf16_f32 per pair and plane; the same
+// values as split_bf16).
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+__device__ __forceinline__ void split_bf16_pair(float a, float b, uint32_t &hi, uint32_t &lo) {
+  const bf16x2_t h = __builtin_convertvector((f32x2_t){a, b}, bf16x2_t);
+  hi = __builtin_bit_cast(uint32_t, h);
+  const float ra = a - __uint_as_float(hi << 16), rb = b - __uint_as_float(hi & 0xffff0000u);
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){ra, rb}, bf16x2_t));
+}
+// 4 consecutive values of both planes (8 bytes each) at element offset o.
+__device__ __forceinline__ void store_planes4(const float (&y)[4], uint16_t *hi_p, uint16_t *lo_p, int64_t o) {
+  uint2 hi, lo;
+  split_bf16_pair(y[0], y[1], hi.x, lo.x);
+  split_bf16_pair(y[2], y[3], hi.y, lo.y);
+  *reinterpret_cast<uint2 *>(hi_p + o) = hi;
+  *reinterpret_cast<uint2 *>(lo_p + o) = lo;
+}
+__device__ __forceinline__ void store_bf16x4(const float (&y)[4], uint16_t *p) {
+  *reinterpret_cast<uint2 *>(p) = make_uint2(__builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){y[0], y[1]}, bf16x2_t)),
+                                            __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){y[2], y[3]}, bf16x2_t)));
+}
+
+// SwiGLU of one feature with the row's 1/rms: silu(g * rs) * (u * rs).  The reciprocal is the hardware's
+// (1 ulp); the result goes into two bf16 planes, 2^-17.
+__device__ __forceinline__ float swiglu_act(float g, float u, float rs) {
+  g *= rs;
+  return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * (u * rs);
+}
+
 template <class T> __device__ __forceinline__ T from_f32(float f);
 template <> __device__ __forceinline__ float from_f32<float>(float f) { return f; }
 template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float f) {

@@ -33,19 +33,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-// Two finite floats -> their hi planes packed (a in the low half) and their lo planes packed, with
-// the hardware's round-to-nearest-even conversion (one v_cvt_pk_bf16_f32 per pair and plane; the
-// same values as split_bf16 for the probabilities this is used on).
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-__device__ __forceinline__ void split_bf16_pair(float a, float b, uint32_t &hi, uint32_t &lo) {
-  const bf16x2 h = __builtin_convertvector((f32x2){a, b}, bf16x2);
-  hi = __builtin_bit_cast(uint32_t, h);
-  const float ra = a - __uint_as_float(hi << 16), rb = b - __uint_as_float(hi & 0xffff0000u);
-  const bf16x2 l = __builtin_convertvector((f32x2){ra, rb}, bf16x2);
-  lo = __builtin_bit_cast(uint32_t, l);
-}
-
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 

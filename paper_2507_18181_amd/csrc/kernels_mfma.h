@@ -33,6 +33,8 @@ int wide_row_groups(int rows);
 int wide_gemm_splits(int n_bands, int ksteps, int rows, int n_cu);
 void launch_gemm_wide(const PackedMatrix &W, const uint16_t *Xp, int rows, float *part, int n_splits,
                       int stage, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+void launch_gemm_wide_swiglu(const PackedMatrix &W, const uint16_t *Xp, int rows, const RowNorm &nrm, uint16_t *t,
+                             uint16_t *t_lo, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 int residual_slabs(int d);
 void launch_residual_gain(float *x, const float *part, int n_splits, int rows, int ldp,
                           const void *gain, int d, uint16_t *hb, uint16_t *hb_lo, int nb, float *ssq,

@@ -356,12 +356,21 @@ __device__ __forceinline__ void copy_tile_to_lds(const u32x4 *src_lane, u32x4 *d
                                    (void __attribute__((address_space(3))) *)dst_tile, 16, 0, 0);
 }
 
-template <int STAGE>
+// SWIGLU (gate|up, unsplit): the epilogue is the finishing step instead.  gate and up rows are interleaved
+// by 8, so a lane's accumulator quads 0 and 1 (2 and 3) are gate and up of the same 4 features: SwiGLU
+// happens in registers and the planes of the down projection leave as 512-byte runs.  Saves the
+// finishing kernel and the fp32 output (1.1B, 384 rows: 17 MB written and read again for 8.6 MB of planes).
+struct WideSwiglu {
+  RowNorm nrm;
+  uint16_t *t, *t_lo;
+};
+
+template <int STAGE, bool SWIGLU = false>
 __global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const u32x4 *__restrict__ Wp,
                                                            const u32x4 *__restrict__ Xp,
                                                            float *__restrict__ part, int rows,
                                                            int rows_pad, int n_bands, int ksteps,
-                                                           int nb, int S) {
+                                                           int nb, int S, WideSwiglu sw) {
   // four separate arrays: the compiler can tell a copy into one from the reads of another
   __shared__ u32x4 s0[kWideStageTiles * 64], s1[kWideStageTiles * 64], s2[kWideStageTiles * 64], s3[kWideStageTiles * 64];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -434,6 +443,15 @@ __global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const u32x4 *__restri
   issue(s0, k0);
   issue(s1, k0 + 1);
   issue(s2, k0 + 2);
+  __shared__ float rms[SWIGLU ? 32 * kWideTileGroups : 1];
+  if (SWIGLU) {  // 1 / rms of the tile's rows, two threads per row, while the first stages arrive
+    const int rl = threadIdx.x >> 1;
+    const float *sq = sw.nrm.ssq + (int64_t)min(mt * 32 * kWideTileGroups + rl, rows - 1) * sw.nrm.n_slab;
+    float ss = 0.f;
+    for (int i = threadIdx.x & 1; i < sw.nrm.n_slab; i += 2) ss += sq[i];
+    ss += __shfl_xor(ss, 1, 64);
+    if ((threadIdx.x & 1) == 0) rms[rl] = 1.0f / sqrtf(ss / (float)sw.nrm.d + sw.nrm.eps);
+  }
   for (int kt = k0; kt < k1; kt += 4) {
     step(s0, s3, kt);
     step(s1, s0, kt + 1);
@@ -450,6 +468,17 @@ __global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const u32x4 *__restri
     for (int g = 0; g < 2; ++g) {
       const int row = (mt * kWideTileGroups + 2 * wm + g) * 32 + (lane & 31);
       if (row >= rows) continue;
+      if (SWIGLU) {
+        const float rs = rms[(2 * wm + g) * 32 + (lane & 31)];
+#pragma unroll
+        for (int q = 0; q < 4; q += 2) {
+          float y[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = swiglu_act(acc[i][g][4 * q + e], acc[i][g][4 * q + 4 + e], rs);
+          store_planes4(y, sw.t, sw.t_lo, packed_act_offset(row, band * 16 + 4 * q + 4 * (lane >> 5), nb));
+        }
+        continue;
+      }
       float *dst = part + part_offset(s, row, band * 32 + 4 * (lane >> 5), n_bands, rows_pad);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
@@ -484,17 +513,24 @@ int wide_gemm_splits(int n_bands, int ksteps, int rows, int n_cu) {
   return best;
 }
 
-template <int STAGE>
+template <int STAGE, bool SWIGLU = false>
 static void launch_gemm_wide_s(const PackedMatrix &W, const uint16_t *Xp, int rows, float *part,
-                               int n_splits, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+                               int n_splits, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1,
+                               const WideSwiglu &sw = WideSwiglu{}) {
   const int nb = wide_row_groups(rows);
   const int n_nt = (W.n_bands + kWideTileBands - 1) / kWideTileBands;
   const unsigned grid = 8u * (nb / kWideTileGroups) * ((n_nt + 7) / 8) * n_splits;
   if (ev0 != nullptr)
-    hipExtLaunchKernelGGL((gemm_wide_kernel<STAGE>), dim3(grid), dim3(256), 0u, st, ev0, ev1, 0u, (const u32x4 *)W.data,
-                          (const u32x4 *)Xp, part, rows, part_rows_pad(rows), W.n_bands, W.ksteps, nb, n_splits);
+    hipExtLaunchKernelGGL((gemm_wide_kernel<STAGE, SWIGLU>), dim3(grid), dim3(256), 0u, st, ev0, ev1, 0u, (const u32x4 *)W.data,
+                          (const u32x4 *)Xp, part, rows, part_rows_pad(rows), W.n_bands, W.ksteps, nb, n_splits, sw);
   else
-    gemm_wide_kernel<STAGE><<<grid, 256, 0, st>>>((const u32x4 *)W.data, (const u32x4 *)Xp, part, rows, part_rows_pad(rows), W.n_bands, W.ksteps, nb, n_splits);
+    gemm_wide_kernel<STAGE, SWIGLU><<<grid, 256, 0, st>>>((const u32x4 *)W.data, (const u32x4 *)Xp, part, rows, part_rows_pad(rows), W.n_bands, W.ksteps, nb, n_splits, sw);
+}
+
+// gate|up with the SwiGLU epilogue (unsplit): planes t / t_lo of silu(gate) * up
+void launch_gemm_wide_swiglu(const PackedMatrix &W, const uint16_t *Xp, int rows, const RowNorm &nrm, uint16_t *t,
+                             uint16_t *t_lo, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  launch_gemm_wide_s<2, true>(W, Xp, rows, nullptr, 1, st, ev0, ev1, WideSwiglu{nrm, t, t_lo});
 }
 
 void launch_gemm_wide(const PackedMatrix &W, const uint16_t *Xp, int rows, float *part, int n_splits,
@@ -556,14 +592,7 @@ __global__ __launch_bounds__(512) void residual_gain_kernel(float *x, const floa
     const uint2 g = *reinterpret_cast<const uint2 *>(gain + c);
     const float y[4] = {v.x * bf16_bits_to_f32(g.x & 0xffffu), v.y * bf16_bits_to_f32(g.x >> 16),
                         v.z * bf16_bits_to_f32(g.y & 0xffffu), v.w * bf16_bits_to_f32(g.y >> 16)};
-    uint16_t hi[4], lo[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) split_bf16(y[i], hi[i], lo[i]);
-    const int64_t po = packed_act_offset(r, c, nb);
-    *reinterpret_cast<uint2 *>(hb + po) =
-        make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-    *reinterpret_cast<uint2 *>(hb_lo + po) =
-        make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
+    store_planes4(y, hb, hb_lo, packed_act_offset(r, c, nb));
   }
 }
 
@@ -686,10 +715,6 @@ __global__ __launch_bounds__(256) void qkv_finish_wide_kernel(StepMeta m, KvGeom
     v.x *= rs; v.y *= rs; v.z *= rs; v.w *= rs;
     return v;
   };
-  auto pack4 = [](const float (&y)[4]) {
-    return make_uint2((uint32_t)f32_to_bf16_bits(y[0]) | ((uint32_t)f32_to_bf16_bits(y[1]) << 16),
-                      (uint32_t)f32_to_bf16_bits(y[2]) | ((uint32_t)f32_to_bf16_bits(y[3]) << 16));
-  };
   const bool is_q = a < H;
   const int b = a - H;
   const int c0 = is_q ? a * hd : col_k + b * hd;
@@ -708,25 +733,18 @@ __global__ __launch_bounds__(256) void qkv_finish_wide_kernel(StepMeta m, KvGeom
     }
     if (is_q) {
       const int64_t o = ((int64_t)r * H + a) * hd + j;
-      uint16_t h0[4], l0[4], h1[4], l1[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        split_bf16(y0[i] * qscale, h0[i], l0[i]);
-        split_bf16(y1[i] * qscale, h1[i], l1[i]);
-      }
-      auto pk = [](const uint16_t (&v)[4]) { return make_uint2((uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16)); };
-      *reinterpret_cast<uint2 *>(qb + o) = pk(h0);
-      *reinterpret_cast<uint2 *>(qb_lo + o) = pk(l0);
-      *reinterpret_cast<uint2 *>(qb + o + half) = pk(h1);
-      *reinterpret_cast<uint2 *>(qb_lo + o + half) = pk(l1);
+      for (int i = 0; i < 4; ++i) { y0[i] *= qscale; y1[i] *= qscale; }
+      store_planes4(y0, qb, qb_lo, o);
+      store_planes4(y1, qb, qb_lo, o + half);
     } else {
       const float4 v0 = sum4(col_v + b * hd + j), v1 = sum4(col_v + b * hd + j + half);
       const int64_t base = g.row(m.seq[r], layer, b, m.slot[r]);
-      *reinterpret_cast<uint2 *>(kc + base + j) = pack4(y0);
-      *reinterpret_cast<uint2 *>(kc + base + j + half) = pack4(y1);
+      store_bf16x4(y0, kc + base + j);
+      store_bf16x4(y1, kc + base + j + half);
       const float w0[4] = {v0.x, v0.y, v0.z, v0.w}, w1[4] = {v1.x, v1.y, v1.z, v1.w};
-      *reinterpret_cast<uint2 *>(vc + base + j) = pack4(w0);
-      *reinterpret_cast<uint2 *>(vc + base + j + half) = pack4(w1);
+      store_bf16x4(w0, vc + base + j);
+      store_bf16x4(w1, vc + base + j + half);
     }
   }
 }
@@ -785,16 +803,8 @@ __global__ __launch_bounds__(256) void swiglu_finish_kernel(const float *part, i
     gt.x += a.x; gt.y += a.y; gt.z += a.z; gt.w += a.w;
     up.x += b.x; up.y += b.y; up.z += b.z; up.w += b.w;
   }
-  auto act = [rs](float gv, float uv) { gv *= rs; return gv / (1.0f + __expf(-gv)) * (uv * rs); };
-  const float y[4] = {act(gt.x, up.x), act(gt.y, up.y), act(gt.z, up.z), act(gt.w, up.w)};
-  uint16_t hi[4], lo[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) split_bf16(y[i], hi[i], lo[i]);
-  const int64_t po = packed_act_offset(r, f, nb);
-  *reinterpret_cast<uint2 *>(t + po) =
-      make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-  *reinterpret_cast<uint2 *>(t_lo + po) =
-      make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
+  const float y[4] = {swiglu_act(gt.x, up.x, rs), swiglu_act(gt.y, up.y, rs), swiglu_act(gt.z, up.z, rs), swiglu_act(gt.w, up.w, rs)};
+  store_planes4(y, t, t_lo, packed_act_offset(r, f, nb));
 }
 
 // The same for one row group (<= 32 rows): one workgroup per (1024 features, row), one sum over the
@@ -820,16 +830,8 @@ __global__ __launch_bounds__(256) void swiglu_finish_rows_kernel(const float *pa
   }
   const float rs = row_rms_finish(nrm, lane_ssq);
   if (f >= F) return;
-  auto act = [rs](float gv, float uv) { gv *= rs; return gv / (1.0f + __expf(-gv)) * (uv * rs); };
-  const float y[4] = {act(gt.x, up.x), act(gt.y, up.y), act(gt.z, up.z), act(gt.w, up.w)};
-  uint16_t hi[4], lo[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) split_bf16(y[i], hi[i], lo[i]);
-  const int64_t po = packed_act_offset(r, f, nb);
-  *reinterpret_cast<uint2 *>(t + po) =
-      make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-  *reinterpret_cast<uint2 *>(t_lo + po) =
-      make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
+  const float y[4] = {swiglu_act(gt.x, up.x, rs), swiglu_act(gt.y, up.y, rs), swiglu_act(gt.z, up.z, rs), swiglu_act(gt.w, up.w, rs)};
+  store_planes4(y, t, t_lo, packed_act_offset(r, f, nb));
 }
 
 void launch_swiglu_finish(const float *part, int n_splits, int rows, int ldp, const RowNorm &nrm,

@@ -31,18 +31,6 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int kSliceWaves = 8;
 
-__device__ __forceinline__ void store_planes4(const float (&y)[4], uint16_t *hi_p, uint16_t *lo_p, int64_t o) {
-  uint16_t hi[4], lo[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) split_bf16(y[i], hi[i], lo[i]);
-  *reinterpret_cast<uint2 *>(hi_p + o) = make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-  *reinterpret_cast<uint2 *>(lo_p + o) = make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
-}
-__device__ __forceinline__ void store_bf16x4(const float (&y)[4], uint16_t *p) {
-  *reinterpret_cast<uint2 *>(p) = make_uint2((uint32_t)f32_to_bf16_bits(y[0]) | ((uint32_t)f32_to_bf16_bits(y[1]) << 16),
-                                            (uint32_t)f32_to_bf16_bits(y[2]) | ((uint32_t)f32_to_bf16_bits(y[3]) << 16));
-}
-
 // Accumulators per tile (see the kernel) and register stages of the ring: 8, 4 or 2, as many as fit
 // 250 registers next to the accumulators (a spill costs more than a stage gives: 7B gate|up 33.3 us
 // with 2 .. 3 stages, 41 with 4 and 80 bytes spilled).  Powers of two, because a wavefront's slice is 8 k-step
@@ -234,8 +222,7 @@ __global__ __launch_bounds__(kSliceWaves * 64, 2) void gemm_slice_kernel(SliceAr
         const float4 gt = sum(t, qd * 16 + (u & 15)), up = sum(t, (qd + 2) * 16 + (u & 15));
         if (row >= p.rows || hb >= p.n_half) continue;
         const float rs = rms[row];
-        auto act = [rs](float gv, float uv) { gv *= rs; return gv / (1.0f + __expf(-gv)) * (uv * rs); };
-        const float y[4] = {act(gt.x, up.x), act(gt.y, up.y), act(gt.z, up.z), act(gt.w, up.w)};
+        const float y[4] = {swiglu_act(gt.x, up.x, rs), swiglu_act(gt.y, up.y, rs), swiglu_act(gt.z, up.z, rs), swiglu_act(gt.w, up.w, rs)};
         store_planes4(y, p.t, p.t_lo, packed_act_offset(row, 8 * hb + 4 * qd, nb));
       }
     } else if (EPI == kSliceQkv) {
