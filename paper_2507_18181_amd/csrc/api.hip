@@ -589,7 +589,9 @@ void gemm_stage(specasr_ctx *ctx, int stage, bool profiled_layer, const PackedMa
     ctx->prof_used += 2;
     ctx->prof_rows += rows;
   }
-  if (swiglu_nrm)
+  if (plan.mid.a > 0)
+    launch_gemm_mid(W, Xp, rows, part, plan.mid, swiglu_nrm, t, t_lo, st, ev0, ev1);
+  else if (swiglu_nrm)
     launch_gemm_wide_swiglu(W, Xp, rows, *swiglu_nrm, t, t_lo, st, ev0, ev1);
   else if (plan.wide)
     launch_gemm_wide(W, Xp, rows, part, plan.n_splits, stage, st, ev0, ev1);
@@ -663,6 +665,20 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       if (v >= 1 && v <= pm[i]->ksteps && (size_t)v * pm[i]->ldo * part_rows_pad(R) <= ctx->wide_part_floats)
         pls[i]->n_splits = v;
     }
+    for (int i = 0; i < 5; ++i) {  // the small-tile kernel where the tiled one runs out of workgroups
+      if (ctx->tune.wide_splits[i] >= 1) continue;
+      if (i == 2) {  // gate|up: the tiled kernel unsplit finishes SwiGLU itself
+        const double out_mb = (double)pm[i]->ldo * R * 4e-6;
+        const int S = pls[i]->n_splits;
+        if (S > 1 && wide_gemm_cost(pm[i]->n_bands, pm[i]->ksteps, R, ctx->n_cu, 1) - out_mb * 0.2 <
+                         wide_gemm_cost(pm[i]->n_bands, pm[i]->ksteps, R, ctx->n_cu, S) + S * out_mb * 0.12 + 4.0)
+          pls[i]->n_splits = 1;
+      }
+      const MidPlan mp = plan_mid(pm[i]->n_bands, pm[i]->ksteps, R, pls[i]->n_splits, i == 2, ctx->n_cu);
+      if (mp.a == 0 || (size_t)mp.S * pm[i]->ldo * part_rows_pad(R) > ctx->wide_part_floats) continue;
+      pls[i]->mid = mp;
+      pls[i]->n_splits = mp.S;
+    }
   } else {
     GemmPlan *pls[5] = {&pl_qkv, &pl_o, &pl_gu, &pl_dn, &pl_lm};
     const PackedMatrix *pm[5] = {&p0.qkv, &p0.o, &p0.gu, &p0.down, &ctx->lm_head};
@@ -694,7 +710,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
     const PackedMatrix *pm[5] = {&p0.qkv, &p0.o, &p0.gu, &p0.down, &ctx->lm_head};
     for (int i = 0; i < 5; ++i)
       fprintf(stderr, "[specasr] %-8s bands=%d ksteps=%d rows=%d: %s splits=%d ring=%d grid=%d\n", nm[i],
-              pm[i]->n_bands, pm[i]->ksteps, R, wide ? "wide" : "skinny", pls[i]->n_splits, pls[i]->lw, pls[i]->grid);
+              pm[i]->n_bands, pm[i]->ksteps, R, pls[i]->mid.a ? "mid" : wide ? "wide" : "skinny", pls[i]->n_splits, pls[i]->lw, pls[i]->grid);
   }
   launch_rope_table(m, md.head_dim, md.rope_theta, cs, st);
   launch_embed(m, 1, ctx->w.tok_embed, tree->input_embeds, ctx->cfg.max_nodes, d, x, st);
@@ -864,6 +880,7 @@ specasr_status build_packed(specasr_ctx *ctx) {
   const int d = c.d_model, F = c.d_ffn, dq = c.n_heads * c.head_dim, dkv = c.n_kv_heads * c.head_dim;
   HIP_TRY(ctx, gemm_skinny_set_lds_limit());
   HIP_TRY(ctx, gemm_slice_set_lds_limit());
+  HIP_TRY(ctx, gemm_mid_set_lds_limit());
   {
     int dev = 0, cus = 0;
     HIP_TRY(ctx, hipGetDevice(&dev));

@@ -13,11 +13,16 @@ struct PackedMatrix {
   int ldo = 0;      // n_bands * 32: row stride of the partial-sum output
 };
 
+struct MidPlan {
+  int a = 0, b = 0, S = 1;  // bands x row groups per workgroup, k-splits; a = 0: not this kernel
+};
+
 struct GemmPlan {
   int n_splits = 1;  // k-chunks across workgroups (partial sums per output)
   int lw = 16;       // ring slots per wavefront: >= its k-slice, one of the instantiated sizes
   int grid = 256;    // workgroups, a multiple of n_splits (one per compute unit)
-  bool wide = false; // many rows: the tiled kernel (only n_splits applies)
+  bool wide = false; // many rows: the tiled kernel (only n_splits applies) ...
+  MidPlan mid;       // ... or, where mid.a > 0, the small-tile kernel (n_splits = mid.S)
 };
 
 void launch_read_probe(const void *buf, size_t bytes, int grid, uint32_t *sink, hipStream_t st);
@@ -30,11 +35,18 @@ void launch_gemm_skinny(const PackedMatrix &W, const uint16_t *Xp, int rows, flo
                         hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // large row counts (prefill): rows padded to workgroup tiles of 128, in groups of 32
 int wide_row_groups(int rows);
+double wide_gemm_cost(int n_bands, int ksteps, int rows, int n_cu, int S);
 int wide_gemm_splits(int n_bands, int ksteps, int rows, int n_cu);
 void launch_gemm_wide(const PackedMatrix &W, const uint16_t *Xp, int rows, float *part, int n_splits,
                       int stage, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 void launch_gemm_wide_swiglu(const PackedMatrix &W, const uint16_t *Xp, int rows, const RowNorm &nrm, uint16_t *t,
                              uint16_t *t_lo, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// a few hundred rows (kernels_mid.hip)
+hipError_t gemm_mid_set_lds_limit();
+MidPlan plan_mid(int n_bands, int ksteps, int rows, int wide_splits, bool swiglu, int n_cu);
+// nrm == nullptr: partial sums; otherwise (gate|up) the planes of silu(gate) * up
+void launch_gemm_mid(const PackedMatrix &W, const uint16_t *Xp, int rows, float *part, const MidPlan &pl, const RowNorm *nrm,
+                     uint16_t *t, uint16_t *t_lo, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 int residual_slabs(int d);
 void launch_residual_gain(float *x, const float *part, int n_splits, int rows, int ldp,
                           const void *gain, int d, uint16_t *hb, uint16_t *hb_lo, int nb, float *ssq,

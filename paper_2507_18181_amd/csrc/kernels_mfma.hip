@@ -499,15 +499,19 @@ int wide_row_groups(int rows) { return (rows + 32 * kWideTileGroups - 1) / (32 *
 // partial sums that the consumer reads again (0.3 us per MB + 0.5 us per split).  What this mostly decides is how
 // many rounds of workgroups a launch takes: gate|up at 512 rows of the 7B model has 344 tiles on
 // 256 compute units: S = 1 187 us, S = 2 162 us, S = 4 183 us.
-int wide_gemm_splits(int n_bands, int ksteps, int rows, int n_cu) {
+double wide_gemm_cost(int n_bands, int ksteps, int rows, int n_cu, int S) {
   const int64_t tiles = (int64_t)((n_bands + kWideTileBands - 1) / kWideTileBands) * (wide_row_groups(rows) / kWideTileGroups);
   const double out_mb = (double)n_bands * 32 * part_rows_pad(rows) * 4 / 1e6;
+  const int64_t wgs = tiles * S, per_cu = (wgs + n_cu - 1) / n_cu;
+  const double len = (double)ksteps / S, tk = wgs >= n_cu ? 0.33 : 0.28;
+  return 18.0 + per_cu * len * tk + (per_cu - 1) * 6.0 + S * (out_mb * 0.3 + 0.5);
+}
+
+int wide_gemm_splits(int n_bands, int ksteps, int rows, int n_cu) {
   int best = 1;
   double best_cost = 1e300;
   for (int S = 1; S <= 16 && ksteps / S >= 8; ++S) {
-    const int64_t wgs = tiles * S, per_cu = (wgs + n_cu - 1) / n_cu;
-    const double len = (double)ksteps / S, tk = wgs >= n_cu ? 0.33 : 0.28;
-    const double cost = 18.0 + per_cu * len * tk + (per_cu - 1) * 6.0 + S * (out_mb * 0.3 + 0.5);
+    const double cost = wide_gemm_cost(n_bands, ksteps, rows, n_cu, S);
     if (cost < best_cost) { best_cost = cost; best = S; }
   }
   return best;

@@ -1,0 +1,276 @@
+// GEMMs for a few hundred activation rows at most (a small batch of trees, a short prefill), gfx950.
+//
+// Between the skinny kernels (<= 64 rows, bound by the weight stream) and the tiled kernel of
+// kernels_mfma.hip (256 features x 128 rows per workgroup, bound by the matrix cores) the tiled kernel
+// runs out of workgroups: it has to cut k into 5 .. 13 splits to fill the chip, each an output-sized
+// fp32 buffer that the consumer reads again.  Here the output tile is small (2 .. 3 bands of 32
+// features x 2 .. 3 groups of 32 rows) and k is cut INSIDE the workgroup: every wavefront takes a slice
+// of k for the whole tile and streams its operands straight into registers (a ring of D stages; both
+// operands are stored in MFMA operand order), without LDS or barriers in the loop; the slices are
+// summed through LDS at the end.  One wavefront multiplies A x B tiles from A + 2B loads.
+// What bounds it: the bytes a compute unit can pull out of its L2, about 58 per ns.
+// Measured (us, tiled kernel -> this): 96 rows of the 7B model gate|up 53.7 -> 46.8 and SwiGLU included,
+// q|k|v 37.9 (5 splits) -> 28.7 (2), o 17.4 (8) -> 15.4 (4), down 31.5 (13) -> 31.0 (4); 384 rows of the
+// 1.1B model q|k|v 19.8 (5) -> 15.0 (1), o 17.1 (5) -> 14.2 (1).
+#include <hip/hip_ext.h>
+
+#include <algorithm>
+
+#include "kernels.h"
+#include "kernels_mfma.h"
+
+namespace specasr {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+constexpr int kMidTile = 8 * 33;  // float4 of one 32 x 32 tile in LDS: [feature quad][row], one pad per quad row
+
+// Tiles of a workgroup summed through LDS at a time (at most 152 KB).
+template <int A, int B, int NW>
+constexpr int mid_chunk() {
+  constexpr int fit = 152 * 1024 / (NW * kMidTile * 16);
+  return fit < A * B ? fit : A * B;
+}
+
+struct MidArgs {
+  const void *W;
+  const uint16_t *X;
+  float *part;
+  int rows, rows_pad, n_bands, ksteps, nb, S;  // nb: row groups in the planes
+  int n_mt, total, per_xcd;                    // row tiles, workgroups, workgroups per XCD
+  RowNorm nrm;                                 // SwiGLU epilogue
+  uint16_t *t, *t_lo;
+};
+
+// ONCE: one row tile, every weight is used once and need not stay in the L2.
+// grid 8 * per_xcd, block 64 * NW.  An XCD (workgroup index mod 8) owns a contiguous run of tiles, row tiles of
+// one feature tile next to each other.
+template <int A, int B, int D, int NW, bool SWIGLU, bool ONCE = false>
+__global__ __launch_bounds__(NW * 64, NW / 4) void gemm_mid_kernel(MidArgs p) {
+  extern __shared__ float4 lds_mid[];
+  __shared__ float rms[SWIGLU ? 32 * B : 1];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const uint32_t slot = blockIdx.x >> 3, id = (blockIdx.x & 7) * p.per_xcd + slot;
+  if (slot >= (uint32_t)p.per_xcd || id >= (uint32_t)p.total) return;
+  const uint32_t mt = id % (uint32_t)p.n_mt, rest = id / (uint32_t)p.n_mt, s = rest % (uint32_t)p.S, nt = rest / (uint32_t)p.S;
+  const uint32_t ks = p.ksteps, c0 = ks * s / p.S, c1 = ks * (s + 1) / p.S;
+  const int w0 = c0 + (c1 - c0) * wave / NW, len = (int)(c0 + (c1 - c0) * (wave + 1) / NW) - w0;
+  const int n_groups = (p.rows + 31) >> 5;
+  const u32x4 *wp[A], *xp[2][B];
+#pragma unroll
+  for (int a = 0; a < A; ++a) wp[a] = (const u32x4 *)p.W + ((int64_t)min((int)nt * A + a, p.n_bands - 1) * p.ksteps + w0) * 64 + lane;
+  const int64_t plane = (int64_t)p.ksteps * p.nb * 64;
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int b = 0; b < B; ++b) xp[h][b] = (const u32x4 *)p.X + h * plane + ((int64_t)w0 * p.nb + min((int)mt * B + b, n_groups - 1)) * 64 + lane;
+  const uint32_t xs = p.nb * 64;
+  f32x16 acc[A][B];
+#pragma unroll
+  for (int a = 0; a < A; ++a)
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[a][b][j] = 0.f;
+  u32x4 wa[D][A], xb[D][2][B];
+  auto load = [&](int j, uint32_t k) {
+#pragma unroll
+    for (int a = 0; a < A; ++a) wa[j][a] = ONCE ? __builtin_nontemporal_load(wp[a] + k * 64) : wp[a][k * 64];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int b = 0; b < B; ++b) xb[j][h][b] = xp[h][b][k * xs];
+  };
+  auto mul = [&](int j) {  // hi products first, then lo: A * B independent accumulators in between
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int a = 0; a < A; ++a)
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wa[j][a]), __builtin_bit_cast(bf16x8, xb[j][h][b]), acc[a][b], 0, 0, 0);
+  };
+  if (len > 0) {
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+      load(j, min(j, len - 1));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if (SWIGLU) {  // 1 / rms of the tile's rows, 8 threads per row, while the ring fills
+#pragma unroll
+    for (int r0 = 0; r0 < 32 * B; r0 += NW * 8) {
+      const int rl = r0 + (threadIdx.x >> 3);
+      const float *sq = p.nrm.ssq + (int64_t)min((int)mt * B * 32 + rl, p.rows - 1) * p.nrm.n_slab;
+      float ss = 0.f;
+#pragma unroll 4
+      for (int i = threadIdx.x & 7; i < p.nrm.n_slab; i += 8) ss += sq[i];
+      ss += __shfl_xor(ss, 1, 64);
+      ss += __shfl_xor(ss, 2, 64);
+      ss += __shfl_xor(ss, 4, 64);
+      if ((threadIdx.x & 7) == 0 && rl < 32 * B) rms[rl] = 1.0f / sqrtf(ss / (float)p.nrm.d + p.nrm.eps);
+    }
+  }
+  if (len > 0) {
+    int base = 0;
+    for (; base + 2 * D <= len; base += D) {
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        mul(j);
+        __builtin_amdgcn_sched_barrier(0);
+        load(j, base + D + j);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (base + D < len) {  // the last refills, fewer than D
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        mul(j);
+        __builtin_amdgcn_sched_barrier(0);
+        if (base + D + j < len) load(j, base + D + j);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      base += D;
+    }
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+      if (base + j < len) mul(j);
+  }
+  // sum of the NW slices through LDS, CH tiles at a time.  C layout: register 4q + e of lane l = row l%32,
+  // feature 8q + 4(l/32) + e, i.e. feature quad 2q + l/32
+  constexpr int NT = A * B, CH = mid_chunk<A, B, NW>();
+#pragma unroll
+  for (int t0 = 0; t0 < NT; t0 += CH) {
+    if (t0) __syncthreads();
+#pragma unroll
+    for (int t = t0; t < NT && t < t0 + CH; ++t) {
+      const f32x16 &z = acc[t / B][t % B];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        lds_mid[((t - t0) * NW + wave) * kMidTile + (2 * q + (lane >> 5)) * 33 + (lane & 31)] = make_float4(z[4 * q], z[4 * q + 1], z[4 * q + 2], z[4 * q + 3]);
+    }
+    __syncthreads();
+    const int n_here = CH < NT - t0 ? CH : NT - t0;
+    auto sum = [&](int t, int quad, int rl) {
+      const float4 *src = lds_mid + (t - t0) * NW * kMidTile + quad * 33 + rl;
+      auto add = [](const float4 &a, const float4 &b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); };
+      float4 v = add(add(src[0], src[kMidTile]), add(src[2 * kMidTile], src[3 * kMidTile]));
+      if constexpr (NW == 8) v = add(v, add(add(src[4 * kMidTile], src[5 * kMidTile]), add(src[6 * kMidTile], src[7 * kMidTile])));
+      return v;
+    };
+    if (SWIGLU) {
+      // quads 0, 1 (4, 5) are gate, 2, 3 (6, 7) up of the same 8 features; item = (tile, quad pair, row)
+      for (int u = threadIdx.x; u < n_here * 128; u += NW * 64) {
+        const int t = t0 + (u >> 7), gq = (u >> 5) & 3, rl = u & 31, quad = (gq & 1) + 4 * (gq >> 1);
+        const int row = ((int)mt * B + t % B) * 32 + rl, band = (int)nt * A + t / B;
+        const float4 g = sum(t, quad, rl), up = sum(t, quad + 2, rl);
+        if (row >= p.rows || band >= p.n_bands) continue;
+        const float rs = rms[(t % B) * 32 + rl];
+        const float y[4] = {swiglu_act(g.x, up.x, rs), swiglu_act(g.y, up.y, rs), swiglu_act(g.z, up.z, rs), swiglu_act(g.w, up.w, rs)};
+        store_planes4(y, p.t, p.t_lo, packed_act_offset(row, band * 16 + 8 * (gq >> 1) + 4 * (gq & 1), p.nb));
+      }
+    } else {
+      for (int u = threadIdx.x; u < n_here * 256; u += NW * 64) {  // item = (tile, row, quad): 128 bytes per row
+        const int t = t0 + (u >> 8), rl = (u >> 3) & 31, quad = u & 7;
+        const int row = ((int)mt * B + t % B) * 32 + rl, band = (int)nt * A + t / B;
+        const float4 v = sum(t, quad, rl);
+        if (row < p.rows && band < p.n_bands)
+          *reinterpret_cast<float4 *>(p.part + part_offset(s, row, band * 32 + quad * 4, p.n_bands, p.rows_pad)) = v;
+      }
+    }
+  }
+}
+
+namespace {
+
+template <int A, int B, int D, int NW, bool SWIGLU, bool ONCE = false>
+void launch_mid_t(MidArgs a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  a.n_mt = ((a.rows + 31) / 32 + B - 1) / B;
+  a.total = a.n_mt * ((a.n_bands + A - 1) / A) * a.S;
+  a.per_xcd = (a.total + 7) / 8;
+  constexpr unsigned lds = mid_chunk<A, B, NW>() * NW * kMidTile * 16;
+  if (ev0 != nullptr)
+    hipExtLaunchKernelGGL((gemm_mid_kernel<A, B, D, NW, SWIGLU, ONCE>), dim3(8u * a.per_xcd), dim3(NW * 64), lds, st, ev0, ev1, 0u, a);
+  else
+    gemm_mid_kernel<A, B, D, NW, SWIGLU, ONCE><<<8u * a.per_xcd, NW * 64, lds, st>>>(a);
+}
+
+template <int A, int B, int D, int NW, bool SWIGLU, bool ONCE = false>
+hipError_t set_lds_mid() {
+  return hipFuncSetAttribute((const void *)gemm_mid_kernel<A, B, D, NW, SWIGLU, ONCE>, hipFuncAttributeMaxDynamicSharedMemorySize, mid_chunk<A, B, NW>() * NW * kMidTile * 16);
+}
+
+}  // namespace
+
+// The built tiles; ring and wavefronts as many as their registers allow.
+hipError_t gemm_mid_set_lds_limit() {
+  hipError_t e = set_lds_mid<2, 2, 4, 8, false>();
+  if (e == hipSuccess) e = set_lds_mid<2, 3, 3, 8, false>();
+  if (e == hipSuccess) e = set_lds_mid<3, 3, 4, 4, false>();
+  if (e == hipSuccess) e = set_lds_mid<2, 3, 3, 8, true>();
+  if (e == hipSuccess) e = set_lds_mid<3, 3, 4, 4, true>();
+  if (e == hipSuccess) e = set_lds_mid<3, 3, 4, 4, false, true>();
+  if (e == hipSuccess) e = set_lds_mid<3, 3, 4, 4, true, true>();
+  return e;
+}
+
+// Tile and split of a GEMM over `rows` (> 64) rows, or a = 0 where the tiled kernel with `wide_splits` splits is
+// estimated faster.  Costs in us, each fitted to the measurements above and to the tiled kernel's at 96 .. 810
+// rows: here launch, ring fill and sums 3.5, per round of workgroups the bytes of one at 58 per ns or its
+// MFMAs, at least the weight stream; there 10 plus its k-loop; in both 0.1 per MB of partial sums written and
+// 0.12 per MB read again (none with the SwiGLU epilogue, which also saves a kernel of about 4).
+MidPlan plan_mid(int n_bands, int ksteps, int rows, int wide_splits, bool swiglu, int n_cu) {
+  MidPlan best;
+  const int nb = (rows + 31) / 32;
+  const double out_mb = (double)n_bands * 32 * rows * 4e-6, w_mb = (double)n_bands * ksteps * 1.024e-3;
+  double best_cost;
+  {
+    const int64_t wgs = (int64_t)((n_bands + 7) / 8) * (wide_row_groups(rows) / 4) * wide_splits, per_cu = (wgs + n_cu - 1) / n_cu;
+    const double tk = wgs >= n_cu ? 0.33 : 0.28;
+    best_cost = 10.0 + per_cu * ((double)ksteps / wide_splits) * tk + (per_cu - 1) * 6.0;
+    best_cost += swiglu && wide_splits == 1 ? out_mb * 0.1 : wide_splits * out_mb * 0.22 + (swiglu ? 4.0 : 0.0);
+  }
+  const int tiles[3][2] = {{2, 2}, {2, 3}, {3, 3}};
+  for (const auto &t : tiles) {
+    const int a = t[0], b = t[1];
+    if (swiglu && b == 2) continue;
+    const int64_t n = (int64_t)((n_bands + a - 1) / a) * ((nb + b - 1) / b);
+    for (int S = 1; S <= (swiglu ? 1 : 8) && ksteps / S >= 32; ++S) {
+      const double len = (double)ksteps / S, rounds = (double)((n * S + n_cu - 1) / n_cu);
+      const double wg = std::max((a + 2 * b) * len * 1.024 / 58.0, a * b * 2 * len * 8.0 / 2100.0);
+      const double cost = 3.5 + std::max(rounds * wg, w_mb / 5.9) + (swiglu ? out_mb * 0.1 : S * out_mb * 0.22);
+      if (cost < best_cost) {
+        best_cost = cost;
+        best.a = a;
+        best.b = b;
+        best.S = S;
+      }
+    }
+  }
+  return best;
+}
+
+void launch_gemm_mid(const PackedMatrix &W, const uint16_t *Xp, int rows, float *part, const MidPlan &pl, const RowNorm *nrm,
+                     uint16_t *t, uint16_t *t_lo, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  MidArgs a{};
+  a.W = W.data; a.X = Xp; a.part = part;
+  a.rows = rows; a.rows_pad = part_rows_pad(rows); a.n_bands = W.n_bands; a.ksteps = W.ksteps; a.nb = wide_row_groups(rows); a.S = pl.S;
+  if (nrm != nullptr) {  // SwiGLU epilogue
+    a.nrm = *nrm; a.t = t; a.t_lo = t_lo;
+    if (pl.a == 2) launch_mid_t<2, 3, 3, 8, true>(a, st, ev0, ev1);
+    else if (rows <= 96) launch_mid_t<3, 3, 4, 4, true, true>(a, st, ev0, ev1);
+    else launch_mid_t<3, 3, 4, 4, true>(a, st, ev0, ev1);
+  } else if (pl.a == 3 && rows <= 96) {
+    launch_mid_t<3, 3, 4, 4, false, true>(a, st, ev0, ev1);
+  } else if (pl.a == 3) {
+    launch_mid_t<3, 3, 4, 4, false>(a, st, ev0, ev1);
+  } else if (pl.b == 3) {
+    launch_mid_t<2, 3, 3, 8, false>(a, st, ev0, ev1);
+  } else {
+    launch_mid_t<2, 2, 4, 8, false>(a, st, ev0, ev1);
+  }
+}
+
+}  // namespace specasr
