@@ -34,7 +34,7 @@ struct Staging {
 
 // offsets (in bytes) of the regions of a workspace sized for `rows_max` rows / `batch` sequences
 struct WsLayout {
-  size_t meta, outs, rope, x, h, q, k, v, att, gu, t, logits, top2_v, top2_i, total;
+  size_t meta, outs, rope, x, h, q, k, v, att, t, logits, top2_v, top2_i, total;
   size_t hb, attb, tb, part, ssq, blk_val, blk_idx;  // bf16 activations and split-k partial sums (MFMA path)
   size_t qb, attn_o, attn_ml;                   // MFMA attention: bf16 queries, per-chunk partial outputs
   size_t meta_words;
@@ -227,7 +227,6 @@ WsLayout ws_layout(const specasr_config &c, int batch) {
   L.k = take(R * dkv * 4);
   L.v = take(R * dkv * 4);
   L.att = take(R * dq * 4);
-  L.gu = take(R * 2 * c.d_ffn * 4);
   L.t = take(R * c.d_ffn * 4);
   L.logits = take(R * c.vocab * 4);
   L.top2_v = take(R * (size_t)top2_blocks(c.vocab) * 3 * 4);
@@ -530,7 +529,7 @@ void forward_generic(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g, speca
   const int dq = md.n_heads * md.head_dim, dkv = md.n_kv_heads * md.head_dim, R = m.rows;
   float *x = (float *)(ws + L.x), *h = (float *)(ws + L.h), *q = (float *)(ws + L.q);
   float *k = (float *)(ws + L.k), *v = (float *)(ws + L.v), *att = (float *)(ws + L.att);
-  float *gu = (float *)(ws + L.gu), *t = (float *)(ws + L.t), *lg = (float *)(ws + L.logits);
+  float *t = (float *)(ws + L.t), *lg = (float *)(ws + L.logits);
   float2 *cs = (float2 *)(ws + L.rope);
 
   launch_rope_table(m, md.head_dim, md.rope_theta, cs, st);
@@ -538,16 +537,13 @@ void forward_generic(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g, speca
   for (int l = 0; l < md.n_layers; ++l) {
     const specasr_layer_weights &lw = ctx->layers[l];
     launch_rmsnorm(dt, x, lw.attn_norm, R, d, md.rms_eps, h, st);
-    launch_linear(dt, lw.wq, dq, d, h, d, q, dq, R, false, st);
-    launch_linear(dt, lw.wk, dkv, d, h, d, k, dkv, R, false, st);
-    launch_linear(dt, lw.wv, dkv, d, h, d, v, dkv, R, false, st);
+    const LinearJob qkv[3] = {{lw.wq, dq, q, dq}, {lw.wk, dkv, k, dkv}, {lw.wv, dkv, v, dkv}};
+    launch_linears(dt, qkv, 3, d, h, d, R, false, st);
     launch_rope_kv(m, md, g, l, cs, q, k, v, kv->k, kv->v, st);
     launch_attention_generic(m, md, g, l, q, kv->k, kv->v, att, st);
     launch_linear(dt, lw.wo, d, dq, att, dq, x, d, R, true, st);
     launch_rmsnorm(dt, x, lw.ffn_norm, R, d, md.rms_eps, h, st);
-    launch_linear(dt, lw.w_gate, F, d, h, d, gu, 2 * F, R, false, st);
-    launch_linear(dt, lw.w_up, F, d, h, d, gu + F, 2 * F, R, false, st);
-    launch_swiglu(gu, R, F, t, st);
+    launch_linear_swiglu(dt, lw.w_gate, lw.w_up, F, d, h, d, t, R, st);
     launch_linear(dt, lw.w_down, d, F, t, F, x, d, R, true, st);
   }
   if (ro.none()) return;

@@ -23,6 +23,17 @@ void launch_rmsnorm(int dtype, const float *x, const void *gain, int rows, int d
 // y[row][o] (+)= sum_k W[o][k] * a[row][k]
 void launch_linear(int dtype, const void *W, int n_out, int n_in, const float *a, int lda,
                    float *y, int ldy, int rows, bool accumulate, hipStream_t st);
+// the same for up to 3 matrices with one input in one launch
+struct LinearJob {
+  const void *W;
+  int n_out;
+  float *y;
+  int ldy;
+};
+void launch_linears(int dtype, const LinearJob *jobs, int n, int n_in, const float *a, int lda, int rows, bool accumulate, hipStream_t st);
+// t[row][f] = silu(gate[f] . a[row]) * (up[f] . a[row])
+void launch_linear_swiglu(int dtype, const void *gate, const void *up, int F, int n_in, const float *a, int lda, float *t, int rows,
+                          hipStream_t st);
 // rotate q in place, rotate k, write k and v to their cache slots
 void launch_rope_kv(const StepMeta &m, const ModelDims &md, const KvGeom &g, int layer,
                     const float2 *cs, float *q, const float *k, const float *v, void *kcache,
@@ -31,8 +42,6 @@ void launch_rope_kv(const StepMeta &m, const ModelDims &md, const KvGeom &g, int
 void launch_attention_generic(const StepMeta &m, const ModelDims &md, const KvGeom &g, int layer,
                               const float *q, const void *kcache, const void *vcache, float *out,
                               hipStream_t st);
-// t = silu(gate) * up, gate/up interleaved as gu[row][0:F] and gu[row][F:2F]
-void launch_swiglu(const float *gu, int rows, int F, float *t, hipStream_t st);
 // argmax[seq][node] = lowest index of the maximum of the row's logits.  The logits are
 // either compact ([rows][V], padded_in = false) or padded ([batch][max_nodes][V]).
 void launch_argmax(const StepMeta &m, const float *logits, bool padded_in, int max_nodes, int V,
