@@ -147,6 +147,7 @@ GemmPlan plan_gemm(int n_bands, int ksteps, int nb, int n_cu) {
       best.n_splits = S;
       best.lw = nb == 1 ? (len <= 4 ? 4 : len <= 8 ? 8 : len <= 12 ? 12 : 16) : (len <= 4 ? 4 : 8);
       best.grid = n_cu;
+      best.cost_us = cost;
     }
   }
   return best;
@@ -183,7 +184,8 @@ SlicePlan plan_slice(int epi, int n_half, int ksteps, int rows, int n_cu) {
 // (<= 16 rows) or more than two the half-band kernel streams it faster than the split kernel: 1.1B 8.3 ->
 // 7.4 (16 rows), 11.5 -> 9.2 us (37 rows), 11.5 -> 9.8 (64 rows); 7B 26.8 -> 22.4 (40 rows), but 18.6 against
 // 20.3 at 32 rows, where the split kernel holds its activations in registers and has spare wavefronts
-// for the sums, and no gain at 64 rows (1 MB of activations per workgroup).  Cost model in us: bytes of one workgroup at 60 bytes/ns or the weight stream at 5.9
+// for the sums, and no gain where a workgroup streams more than 1 MB (13B, 40 rows: 35.5 against 32.5; 512 KB
+// with four row groups).  Cost model in us: bytes of one workgroup at 60 bytes/ns or the weight stream at 5.9
 // bytes/ps, whichever is longer, plus 0.3 us per MB of partial sums.
 SlicePlan plan_slice_down(int n_half, int ksteps, int rows, int n_cu) {
   SlicePlan pl;
@@ -198,7 +200,7 @@ SlicePlan plan_slice_down(int n_half, int ksteps, int rows, int n_cu) {
     while (S > 1 && ksteps / 2 / S < 8) --S;  // at least one pair of k-steps per wavefront
     if (S < 1) continue;
     const double wg_kb = (double)(hb + 2 * pl.nc) * ksteps / 2 / S, w_mb = (double)n_half * ksteps * 0.512e-3;
-    if (pl.nc > 3 && wg_kb > 512) continue;
+    if (wg_kb > (pl.nc > 3 ? 512 : 1024) && pl.nc > 2) continue;
     const double cost = std::max(wg_kb / 60.0, w_mb / 5.9) + S * (double)rows * n_half * 64e-6 * 0.3;
     if (cost < best) {
       best = cost;
@@ -670,7 +672,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
                          wide_gemm_cost(pm[i]->n_bands, pm[i]->ksteps, R, ctx->n_cu, S) + S * out_mb * 0.12 + 4.0)
           pls[i]->n_splits = 1;
       }
-      const MidPlan mp = plan_mid(pm[i]->n_bands, pm[i]->ksteps, R, pls[i]->n_splits, i == 2, ctx->n_cu);
+      const MidPlan mp = plan_mid(pm[i]->n_bands, pm[i]->ksteps, R, wide_gemm_estimate(pm[i]->n_bands, pm[i]->ksteps, R, pls[i]->n_splits, i == 2, ctx->n_cu), i == 2, ctx->n_cu);
       if (mp.a == 0 || (size_t)mp.S * pm[i]->ldo * part_rows_pad(R) > ctx->wide_part_floats) continue;
       pls[i]->mid = mp;
       pls[i]->n_splits = mp.S;
@@ -697,6 +699,22 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
     if (!forced[3]) sl_dn = plan_slice_down(d / 16, p0.down.ksteps, R, ctx->n_cu);
     if ((size_t)sl_dn.S * p0.down.ldo > ctx->part_floats) sl_dn.hb = 0;
     if (sl_dn.hb) pl_dn.n_splits = sl_dn.S;
+    if (R > 32) {  // two row groups: the small-tile kernel where it beats the split kernel
+      GemmPlan *pls[4] = {&pl_qkv, &pl_o, &pl_gu, &pl_dn};
+      const PackedMatrix *pm[4] = {&p0.qkv, &p0.o, &p0.gu, &p0.down};
+      SlicePlan *sl[4] = {&sl_qkv, &sl_o, &sl_gu, &sl_dn};
+      for (int i = 0; i < 4; ++i) {
+        if (forced[i] || sl[i]->hb) continue;
+        const double out_mb = (double)pm[i]->ldo * R * 4e-6;
+        // the split kernel: its planner's estimate against measurements (1.1B 5.1 .. 11.8 -> 8.5 .. 14.9, 7B 8.5 .. 38.4 ->
+        // 13.2 .. 39.3, 13B 14.3 .. 72.4 -> 16.5 .. 67.8), plus the reading of its partial sums
+        const double other = 0.92 * pls[i]->cost_us + 3.2 + pls[i]->n_splits * out_mb * 0.12 + (i == 2 ? 4.0 : 0.0);
+        const MidPlan mp = plan_mid(pm[i]->n_bands, pm[i]->ksteps, R, other, i == 2, ctx->n_cu);
+        if (mp.a == 0 || (size_t)mp.S * pm[i]->ldo > ctx->part_floats) continue;
+        pls[i]->mid = mp;
+        pls[i]->n_splits = mp.S;
+      }
+    }
   }
   const RowNorm nrm16{ssq, d / 16, d, md.rms_eps};  // statistics as the o projection's epilogue leaves them
   if (ctx->tune.debug) {
@@ -759,7 +777,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
     if (sl_gu.hb) {
       sa.W = pk.gu.data; sa.X = hb; sa.n_half = F / 8; sa.ksteps = pk.gu.ksteps; sa.nrm = nrm_ffn; sa.t = tb; sa.t_lo = tb_lo;
       slice_stage(ctx, SPECASR_STAGE_GATE_UP, pl, kSliceSwiglu, sa, sl_gu, st);
-    } else if (wide && pl_gu.n_splits == 1) {
+    } else if (pl_gu.mid.a > 0 || (wide && pl_gu.n_splits == 1)) {
       gemm_stage(ctx, SPECASR_STAGE_GATE_UP, pl, pk.gu, hb, R, part, pl_gu, st, &nrm_ffn, tb, tb_lo);
     } else {
       gemm_stage(ctx, SPECASR_STAGE_GATE_UP, pl, pk.gu, hb, R, part, pl_gu, st);

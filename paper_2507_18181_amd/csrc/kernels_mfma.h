@@ -21,6 +21,7 @@ struct GemmPlan {
   int n_splits = 1;  // k-chunks across workgroups (partial sums per output)
   int lw = 16;       // ring slots per wavefront: >= its k-slice, one of the instantiated sizes
   int grid = 256;    // workgroups, a multiple of n_splits (one per compute unit)
+  double cost_us = 0; // of the split kernel, as its planner estimates it (without launch)
   bool wide = false; // many rows: the tiled kernel (only n_splits applies) ...
   MidPlan mid;       // ... or, where mid.a > 0, the small-tile kernel (n_splits = mid.S)
 };
@@ -43,7 +44,8 @@ void launch_gemm_wide_swiglu(const PackedMatrix &W, const uint16_t *Xp, int rows
                              uint16_t *t_lo, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // a few hundred rows (kernels_mid.hip)
 hipError_t gemm_mid_set_lds_limit();
-MidPlan plan_mid(int n_bands, int ksteps, int rows, int wide_splits, bool swiglu, int n_cu);
+MidPlan plan_mid(int n_bands, int ksteps, int rows, double other_us, bool swiglu, int n_cu);
+double wide_gemm_estimate(int n_bands, int ksteps, int rows, int splits, bool swiglu, int n_cu);
 // nrm == nullptr: partial sums; otherwise (gate|up) the planes of silu(gate) * up
 void launch_gemm_mid(const PackedMatrix &W, const uint16_t *Xp, int rows, float *part, const MidPlan &pl, const RowNorm *nrm,
                      uint16_t *t, uint16_t *t_lo, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);

@@ -11,7 +11,9 @@
 // What bounds it: the bytes a compute unit can pull out of its L2, about 58 per ns.
 // Measured (us, tiled kernel -> this): 96 rows of the 7B model gate|up 53.7 -> 46.8 and SwiGLU included,
 // q|k|v 37.9 (5 splits) -> 28.7 (2), o 17.4 (8) -> 15.4 (4), down 31.5 (13) -> 31.0 (4); 384 rows of the
-// 1.1B model q|k|v 19.8 (5) -> 15.0 (1), o 17.1 (5) -> 14.2 (1).
+// 1.1B model q|k|v 19.8 (5) -> 15.0 (1), o 17.1 (5) -> 14.2 (1).  At 33 .. 64 rows it also replaces the split skinny
+// kernel where one round of workgroups covers the output: 7B, 64 rows gate|up 39.3 + 6.4 -> 41.9, q|k|v 25.3,
+// down 26.8 and o 13.2 -> 22.2 in the mean, with 2 .. 5 splits instead of 4 .. 16.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -213,33 +215,33 @@ hipError_t gemm_mid_set_lds_limit() {
   if (e == hipSuccess) e = set_lds_mid<3, 3, 4, 4, true>();
   if (e == hipSuccess) e = set_lds_mid<3, 3, 4, 4, false, true>();
   if (e == hipSuccess) e = set_lds_mid<3, 3, 4, 4, true, true>();
+  if (e == hipSuccess) e = set_lds_mid<2, 2, 4, 8, false, true>();
+  if (e == hipSuccess) e = set_lds_mid<2, 2, 4, 8, true, true>();
+  if (e == hipSuccess) e = set_lds_mid<3, 2, 3, 8, false, true>();
+  if (e == hipSuccess) e = set_lds_mid<3, 2, 3, 8, true, true>();
   return e;
 }
 
-// Tile and split of a GEMM over `rows` (> 64) rows, or a = 0 where the tiled kernel with `wide_splits` splits is
-// estimated faster.  Costs in us, each fitted to the measurements above and to the tiled kernel's at 96 .. 810
-// rows: here launch, ring fill and sums 3.5, per round of workgroups the bytes of one at 58 per ns or its
-// MFMAs, at least the weight stream; there 10 plus its k-loop; in both 0.1 per MB of partial sums written and
-// 0.12 per MB read again (none with the SwiGLU epilogue, which also saves a kernel of about 4).
-MidPlan plan_mid(int n_bands, int ksteps, int rows, int wide_splits, bool swiglu, int n_cu) {
+// Tile and split of a GEMM over `rows` (> 32) rows, or a = 0 where the other kernel, estimated at `other_us`, is
+// faster.  Costs in us, fitted to the measurements above: launch, ring fill and sums 3.5, per round of
+// workgroups the bytes of one at 58 per ns (47 up to 64 rows) or its MFMAs, at least the weight stream, 0.1 per MB of partial
+// sums written and 0.12 per MB read again (none with the SwiGLU epilogue).
+MidPlan plan_mid(int n_bands, int ksteps, int rows, double other_us, bool swiglu, int n_cu) {
   MidPlan best;
+  double best_cost = other_us;
   const int nb = (rows + 31) / 32;
   const double out_mb = (double)n_bands * 32 * rows * 4e-6, w_mb = (double)n_bands * ksteps * 1.024e-3;
-  double best_cost;
-  {
-    const int64_t wgs = (int64_t)((n_bands + 7) / 8) * (wide_row_groups(rows) / 4) * wide_splits, per_cu = (wgs + n_cu - 1) / n_cu;
-    const double tk = wgs >= n_cu ? 0.33 : 0.28;
-    best_cost = 10.0 + per_cu * ((double)ksteps / wide_splits) * tk + (per_cu - 1) * 6.0;
-    best_cost += swiglu && wide_splits == 1 ? out_mb * 0.1 : wide_splits * out_mb * 0.22 + (swiglu ? 4.0 : 0.0);
-  }
-  const int tiles[3][2] = {{2, 2}, {2, 3}, {3, 3}};
+  const int tiles[4][2] = {{2, 2}, {2, 3}, {3, 3}, {3, 2}};
   for (const auto &t : tiles) {
     const int a = t[0], b = t[1];
-    if (swiglu && b == 2) continue;
+    if (rows <= 64 ? b == 3 : (a == 3 && b == 2) || (swiglu && b == 2)) continue;  // not built or never better
     const int64_t n = (int64_t)((n_bands + a - 1) / a) * ((nb + b - 1) / b);
     for (int S = 1; S <= (swiglu ? 1 : 8) && ksteps / S >= 32; ++S) {
       const double len = (double)ksteps / S, rounds = (double)((n * S + n_cu - 1) / n_cu);
-      const double wg = std::max((a + 2 * b) * len * 1.024 / 58.0, a * b * 2 * len * 8.0 / 2100.0);
+      // a second, part-filled round loses to the split kernel, which spreads bands evenly (13B gate|up, 40 rows: 78.6
+      // against 67.8 + 9.0)
+      if (rows <= 64 && rounds > 1) break;
+      const double wg = std::max((a + 2 * b) * len * 1.024 / (rows <= 64 ? 47.0 : 58.0), a * b * 2 * len * 8.0 / 2100.0);
       const double cost = 3.5 + std::max(rounds * wg, w_mb / 5.9) + (swiglu ? out_mb * 0.1 : S * out_mb * 0.22);
       if (cost < best_cost) {
         best_cost = cost;
@@ -252,16 +254,31 @@ MidPlan plan_mid(int n_bands, int ksteps, int rows, int wide_splits, bool swiglu
   return best;
 }
 
+// What the tiled kernel takes by the same measure: 10 plus its k-loop (its own planner's constants), and the finishing
+// kernel of a split gate|up about 4.
+double wide_gemm_estimate(int n_bands, int ksteps, int rows, int splits, bool swiglu, int n_cu) {
+  const double out_mb = (double)n_bands * 32 * rows * 4e-6;
+  const int64_t wgs = (int64_t)((n_bands + 7) / 8) * (wide_row_groups(rows) / 4) * splits, per_cu = (wgs + n_cu - 1) / n_cu;
+  const double t = 10.0 + per_cu * ((double)ksteps / splits) * (wgs >= n_cu ? 0.33 : 0.28) + (per_cu - 1) * 6.0;
+  return t + (swiglu && splits == 1 ? out_mb * 0.1 : splits * out_mb * 0.22 + (swiglu ? 4.0 : 0.0));
+}
+
 void launch_gemm_mid(const PackedMatrix &W, const uint16_t *Xp, int rows, float *part, const MidPlan &pl, const RowNorm *nrm,
                      uint16_t *t, uint16_t *t_lo, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   MidArgs a{};
   a.W = W.data; a.X = Xp; a.part = part;
-  a.rows = rows; a.rows_pad = part_rows_pad(rows); a.n_bands = W.n_bands; a.ksteps = W.ksteps; a.nb = wide_row_groups(rows); a.S = pl.S;
+  a.rows = rows; a.rows_pad = part_rows_pad(rows); a.n_bands = W.n_bands; a.ksteps = W.ksteps; a.nb = rows <= 64 ? 2 : wide_row_groups(rows); a.S = pl.S;
   if (nrm != nullptr) {  // SwiGLU epilogue
     a.nrm = *nrm; a.t = t; a.t_lo = t_lo;
-    if (pl.a == 2) launch_mid_t<2, 3, 3, 8, true>(a, st, ev0, ev1);
+    if (rows <= 64 && pl.a == 2) launch_mid_t<2, 2, 4, 8, true, true>(a, st, ev0, ev1);
+    else if (rows <= 64) launch_mid_t<3, 2, 3, 8, true, true>(a, st, ev0, ev1);
+    else if (pl.a == 2) launch_mid_t<2, 3, 3, 8, true>(a, st, ev0, ev1);
     else if (rows <= 96) launch_mid_t<3, 3, 4, 4, true, true>(a, st, ev0, ev1);
     else launch_mid_t<3, 3, 4, 4, true>(a, st, ev0, ev1);
+  } else if (rows <= 64 && pl.a == 2) {
+    launch_mid_t<2, 2, 4, 8, false, true>(a, st, ev0, ev1);
+  } else if (rows <= 64) {
+    launch_mid_t<3, 2, 3, 8, false, true>(a, st, ev0, ev1);
   } else if (pl.a == 3 && rows <= 96) {
     launch_mid_t<3, 3, 4, 4, false, true>(a, st, ev0, ev1);
   } else if (pl.a == 3) {

@@ -1,4 +1,4 @@
-"""Calls with a few hundred tree nodes: the small-tile GEMM and the unsplit tiled gate|up at the edges of
+"""Calls with 33 to a few hundred tree nodes: the small-tile GEMM and the unsplit tiled gate|up at the edges of
 their tiles (groups of 32 rows, 2 .. 3 groups and bands per workgroup, k slices shorter than the ring)."""
 import numpy as np
 import pytest
@@ -29,7 +29,7 @@ def test_row_counts_around_the_tiles(shape):
     Ls = [40, 0, 21, 33]
     K, V = wl.seeded_cache(cfg, 613, np.asarray(Ls, np.int32), cap, "bf16", batch=nb)
     ver = Verifier(cfg, w, "bf16", max_nodes=64, capacity=cap, max_batch=nb)
-    for sizes in ((60, 3, 1, 1), (64, 16, 8, 8), (64, 20, 12, 1), (64, 32, 20, 12), (33, 64, 31, 1), (64, 64, 64, 1), (64, 64, 64, 64)):
+    for sizes in ((30, 1, 1, 1), (45, 1, 1, 1), (50, 10, 2, 2), (60, 3, 1, 1), (64, 16, 8, 8), (64, 20, 12, 1), (64, 32, 20, 12), (33, 64, 31, 1), (64, 64, 64, 1), (64, 64, 64, 64)):
         trees = [wl.random_tree(rng, n, max_children=3) for n in sizes]
         toks = [rng.integers(0, cfg["vocab"], n).astype(np.int32) for n in sizes]
         ver.set_cache(K, V, Ls)
