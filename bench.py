@@ -314,14 +314,14 @@ def bench_prefill(args, spec, cfg, w_host, ver, stage_id, t_gen, log):
         rows_avg = stage_rows / stage_launches
         flops = 2.0 * rows_avg * (stage_bytes / 2.0)
         tf = flops / (kern_ms * 1e-3) / 1e12
-        roofline = {"bound": "mfma", "kernel": "gemm_wide_kernel (%s projection, %.0f rows per launch)" % (args.stage, rows_avg),
+        roofline = {"bound": "mfma", "kernel": "tiled GEMM (%s projection, %.0f rows per launch)" % (args.stage, rows_avg),
                     "achieved": round(tf, 1), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(tf / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None,
                     "launches_timed": stage_launches, "avg_launch_us": round(kern_ms * 1e3, 2),
                     "flops_per_launch": flops, "mfma_flops_issued_per_launch": 2.0 * flops}
     else:
         kern_gbs = stage_bytes / (kern_ms * 1e-3) / 1e9
-        roofline = {"bound": "hbm", "kernel": "gemm_skinny_kernel (%s projection, 64 rows)" % args.stage,
+        roofline = {"bound": "hbm", "kernel": "weight-streaming GEMM (%s projection, 64 rows)" % args.stage,
                     "achieved": round(kern_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(kern_gbs / HBM_PEAK_GBS, 4), "traffic": None,
                     "launches_timed": stage_launches, "avg_launch_us": round(kern_ms * 1e3, 2),
@@ -399,14 +399,14 @@ def bench_batch(args, spec, cfg, w_host, w_dev, t_gen, log):
     if wide:
         flops = 2.0 * (stage_rows / max(1, stage_launches)) * (stage_bytes / 2.0)
         tf = flops / (kern_ms * 1e-3) / 1e12
-        roofline = {"bound": "mfma", "kernel": "gemm_wide_kernel (%s projection, %d rows)" % (args.stage, rows),
+        roofline = {"bound": "mfma", "kernel": "tiled GEMM (%s projection, %d rows)" % (args.stage, rows),
                     "achieved": round(tf, 1), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(tf / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None,
                     "launches_timed": stage_launches, "avg_launch_us": round(kern_ms * 1e3, 2),
                     "flops_per_launch": flops, "mfma_flops_issued_per_launch": 2.0 * flops}
     else:
         gbs = stage_bytes / (kern_ms * 1e-3) / 1e9
-        roofline = {"bound": "hbm", "kernel": "gemm_skinny_kernel (%s projection)" % args.stage,
+        roofline = {"bound": "hbm", "kernel": "weight-streaming GEMM (%s projection)" % args.stage,
                     "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": None, "launches_timed": stage_launches,
                     "avg_launch_us": round(kern_ms * 1e3, 2), "bytes_per_launch": stage_bytes}
@@ -600,7 +600,7 @@ def main():
         "step_hbm_gbs": round(step_gbs, 1), "step_hbm_frac": round(step_gbs / HBM_PEAK_GBS, 4),
         "read_ceiling_gbs": ceiling,
         "step_frac_of_read_ceiling": None if not ceiling else round(step_gbs / ceiling, 4),
-        "roofline": {"bound": "hbm", "kernel": "gemm_skinny_kernel (%s projection)" % args.stage,
+        "roofline": {"bound": "hbm", "kernel": "weight-streaming GEMM (%s projection)" % args.stage,
                      "achieved": round(kern_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(kern_gbs / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_source": traffic_src, "launches_timed": stage_launches, "avg_launch_us": round(kern_ms * 1e3, 2),

@@ -12,8 +12,8 @@
 // Measured (us, tiled kernel -> this): 96 rows of the 7B model gate|up 53.7 -> 46.8 and SwiGLU included,
 // q|k|v 37.9 (5 splits) -> 28.7 (2), o 17.4 (8) -> 15.4 (4), down 31.5 (13) -> 31.0 (4); 384 rows of the
 // 1.1B model q|k|v 19.8 (5) -> 15.0 (1), o 17.1 (5) -> 14.2 (1).  At 33 .. 64 rows it also replaces the split skinny
-// kernel where one round of workgroups covers the output: 7B, 64 rows gate|up 39.3 + 6.4 -> 41.9, q|k|v 25.3,
-// down 26.8 and o 13.2 -> 22.2 in the mean, with 2 .. 5 splits instead of 4 .. 16.
+// kernel where one round of workgroups covers the output: 7B, 64 rows gate|up 39.3 + 6.4 -> 41.1, q|k|v 25.3 and
+// down 26.8 -> 26.0 in the mean with 2 .. 5 splits instead of 4 .. 16, which the next kernel reads; a pass 1.04 .. 1.09 times as fast.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -224,7 +224,7 @@ hipError_t gemm_mid_set_lds_limit() {
 
 // Tile and split of a GEMM over `rows` (> 32) rows, or a = 0 where the other kernel, estimated at `other_us`, is
 // faster.  Costs in us, fitted to the measurements above: launch, ring fill and sums 3.5, per round of
-// workgroups the bytes of one at 58 per ns (47 up to 64 rows) or its MFMAs, at least the weight stream, 0.1 per MB of partial
+// workgroups the bytes of one at 58 per ns (47 up to 64 rows: 13B q|k|v + o, 40 rows, 59.4 here against 55.3) or its MFMAs, at least the weight stream, 0.1 per MB of partial
 // sums written and 0.12 per MB read again (none with the SwiGLU epilogue).
 MidPlan plan_mid(int n_bands, int ksteps, int rows, double other_us, bool swiglu, int n_cu) {
   MidPlan best;
