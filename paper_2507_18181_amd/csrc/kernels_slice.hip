@@ -37,10 +37,13 @@ constexpr int kSliceWaves = 8;
 // pairs on a 2048-wide model and 16 on a 4096-wide one: with 6 stages the last, partial block cost
 // 2 us (1.1B gate|up 10.3 us with 4, 11.9 with 6, 9.9 with 8).
 template <int EPI, int HB, int NC>
-constexpr int slice_regs(int stages, int accs) { return stages * 4 * (HB + 2 * NC) + 4 * HB * NC * accs + 2 * HB + (EPI == kSliceQkv ? 60 : 48); }
+constexpr int slice_regs(int stages, int accs) {
+  constexpr int xo = NC ? 2 * NC : 1, tc = NC ? NC : 1;  // operands of a stage, tiles per half-band
+  return stages * 4 * (HB + xo) + 4 * HB * tc * accs + 2 * HB + (EPI == kSliceQkv ? 60 : 48);
+}
 template <int EPI, int HB, int NC>
 constexpr int slice_depth() {
-  constexpr int accs = EPI == kSliceQkv ? 3 : 1;
+  constexpr int accs = EPI != kSliceQkv ? 1 : NC ? 3 : 2;
   return slice_regs<EPI, HB, NC>(8, accs) <= 250 ? 8 : slice_regs<EPI, HB, NC>(4, accs) <= 250 ? 4 : 2;
 }
 // Accumulators per tile: what rounds is mostly the fp32 addition chain, one step per 8 products, so it is
@@ -52,19 +55,22 @@ constexpr int slice_depth() {
 template <int EPI, int HB, int NC>
 constexpr int slice_accs() {
   constexpr int D = slice_depth<EPI, HB, NC>();
+  if (NC == 0) return EPI == kSliceQkv || slice_regs<EPI, HB, NC>(D, 2) <= 250 ? 2 : 1;  // lo products have columns of their own
   return EPI == kSliceQkv || slice_regs<EPI, HB, NC>(D, 3) <= 250 ? 3 : slice_regs<EPI, HB, NC>(D, 2) <= 250 ? 2 : 1;
 }
 // Output tiles summed through LDS at a time (1 KB per tile and wavefront, at most 128 KB).
 template <int HB, int NC>
-constexpr int slice_chunk() { return HB * NC <= 16 ? HB * NC : (HB * NC + 1) / 2; }
+constexpr int slice_chunk() { constexpr int n = HB * (NC ? NC : 1); return n <= 16 ? n : (n + 1) / 2; }
 
 // grid = 8 * ceil(tiles * S / 8): an XCD (workgroup index mod 8) owns a contiguous run of tiles, so
 // its L2 sees every k-range of them.  block = 512.
-template <int EPI, int HB, int NC>
+template <int EPI, int HB, int NCP>
 __global__ __launch_bounds__(kSliceWaves * 64, 2) void gemm_slice_kernel(SliceArgs p) {
   extern __shared__ float4 lds_slice[];
   __shared__ float rms[64];
-  constexpr int NW = kSliceWaves, D = slice_depth<EPI, HB, NC>(), nb = NC <= 2 ? 1 : 2, NT = HB * NC;
+  constexpr bool BOTH = NCP == 0;  // both planes of 8 rows in one operand
+  constexpr int NC = BOTH ? 1 : NCP, NP = BOTH ? 1 : 2, RW = BOTH ? 1 : 2 * NC;  // row groups, operands per group, rows per wavefront in the norm
+  constexpr int NW = kSliceWaves, D = slice_depth<EPI, HB, NCP>(), nb = NC <= 2 ? 1 : 2, NT = HB * NC;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int slot = blockIdx.x >> 3, id = (blockIdx.x & 7) * p.per_xcd + slot;
   if (slot >= p.per_xcd || id >= p.total) return;
@@ -77,7 +83,7 @@ __global__ __launch_bounds__(kSliceWaves * 64, 2) void gemm_slice_kernel(SliceAr
   float ss[8];  // this wavefront's rows wave, wave + 8, ...: one lane's share of the slab sums of squares
   if (EPI == kSliceSwiglu || EPI == kSliceQkv) {
 #pragma unroll
-    for (int i = 0; i < 2 * NC; ++i) ss[i] = row_ssq_lane(p.nrm, min(wave + 8 * i, p.rows - 1));
+    for (int i = 0; i < RW; ++i) ss[i] = row_ssq_lane(p.nrm, min(wave + 8 * i, p.rows - 1));
   }
   // item of this thread in the residual epilogue (one per thread: HB * NC <= 8)
   const int rt = threadIdx.x >> 6;
@@ -124,9 +130,10 @@ __global__ __launch_bounds__(kSliceWaves * 64, 2) void gemm_slice_kernel(SliceAr
   }
   const int64_t plane = (int64_t)p.ksteps * nb * 64;
   const u32x4 *xp = (const u32x4 *)p.X + (int64_t)(2 * w0 + (lane >> 5)) * nb * 64 + in_tile;
+  if (BOTH && (lane & 8)) xp += plane - 8;  // operand rows 8 .. 15 are the lo plane of rows 0 .. 7
   // accumulators: 0 running products, 1 what they were after earlier blocks of D stages (D = 8: the products of the
   // block's second half instead, no additions in the loop), 2 lo products (with NA < 3 they go with the hi ones)
-  constexpr int NA = slice_accs<EPI, HB, NC>();
+  constexpr int NA = slice_accs<EPI, HB, NCP>();
   f32x4 acc[HB][NC][NA];
 #pragma unroll
   for (int a = 0; a < HB; ++a)
@@ -134,18 +141,18 @@ __global__ __launch_bounds__(kSliceWaves * 64, 2) void gemm_slice_kernel(SliceAr
     for (int c = 0; c < NC; ++c)
 #pragma unroll
       for (int i = 0; i < NA; ++i) acc[a][c][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  u32x4 wa[D][HB], xb[D][2][NC];
+  u32x4 wa[D][HB], xb[D][NP][NC];
   auto load = [&](int j, int k) {
 #pragma unroll
     for (int a = 0; a < HB; ++a) wa[j][a] = __builtin_nontemporal_load(wp[a] + (int64_t)k * 128);
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < NP; ++h)
 #pragma unroll
       for (int c = 0; c < NC; ++c) xb[j][h][c] = xp[h * plane + (int64_t)k * nb * 128 + (c >> 1) * 64 + (c & 1) * 16];
   };
   auto mul = [&](int j) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < NP; ++h)
 #pragma unroll
       for (int a = 0; a < HB; ++a)
 #pragma unroll
@@ -174,7 +181,7 @@ __global__ __launch_bounds__(kSliceWaves * 64, 2) void gemm_slice_kernel(SliceAr
   }
   if (EPI == kSliceSwiglu || EPI == kSliceQkv) {  // 1 / rms per row, while the ring fills
 #pragma unroll
-    for (int i = 0; i < 2 * NC; ++i) {
+    for (int i = 0; i < RW; ++i) {
       const float rs = row_rms_finish(p.nrm, ss[i]);
       if (lane == 0) rms[wave + 8 * i] = rs;
     }
@@ -208,7 +215,7 @@ __global__ __launch_bounds__(kSliceWaves * 64, 2) void gemm_slice_kernel(SliceAr
 
   // sum of the 8 slices through LDS, CH tiles at a time (C layout: lane l = row l%16 of the column
   // group, output features 4*(l/16) .. +3 of the half-band)
-  constexpr int CH = slice_chunk<HB, NC>();
+  constexpr int CH = slice_chunk<HB, NCP>();
 #pragma unroll
   for (int t0 = 0; t0 < NT; t0 += CH) {
     if (t0) __syncthreads();
@@ -225,7 +232,12 @@ __global__ __launch_bounds__(kSliceWaves * 64, 2) void gemm_slice_kernel(SliceAr
       const float4 *src = lds_slice + (t - t0) * NW * 64 + l;
       auto add = [](const float4 &a, const float4 &b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); };
       static_assert(NW == 8, "tree of 8 slices");
-      return add(add(add(src[0], src[64]), add(src[128], src[192])), add(add(src[256], src[320]), add(src[384], src[448])));
+      auto slices = [&](const float4 *q) { return add(add(add(q[0], q[64]), add(q[128], q[192])), add(add(q[256], q[320]), add(q[384], q[448]))); };
+      if constexpr (BOTH) {  // hi products in rows 0 .. 7, lo products in rows 8 .. 15 (surplus rows repeat them, unused)
+        const float4 *hi = src - (l & 8);
+        return add(slices(hi), slices(hi + 8));
+      }
+      return slices(src);
     };
     if (EPI == kSlicePartial) {
       for (int u = threadIdx.x; u < n_here * 64; u += NW * 64) {
@@ -337,6 +349,7 @@ bool with_hb(int hb, F f) {
 template <int EPI, class F>
 bool with_shape(int hb, int nc, F f) {
   switch (nc) {
+    case 0: return with_hb<EPI, 0>(hb, f);
     case 1: return with_hb<EPI, 1>(hb, f);
     case 2: return with_hb<EPI, 2>(hb, f);
     case 3: return with_hb<EPI, 3>(hb, f);
@@ -348,7 +361,7 @@ bool with_shape(int hb, int nc, F f) {
 template <int EPI>
 hipError_t set_lds_epi() {
   hipError_t e = hipSuccess;
-  for (int nc = 1; nc <= 4; ++nc)
+  for (int nc = 0; nc <= 4; ++nc)
     for (int hb = 1; hb <= 8; ++hb)
       with_shape<EPI>(hb, nc, [&](auto h, auto c) {
         if (e == hipSuccess) e = set_lds_one<EPI, decltype(h)::value, decltype(c)::value>();
