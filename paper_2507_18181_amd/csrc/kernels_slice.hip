@@ -333,12 +333,12 @@ template <int EPI, int NC, class F>
 bool with_hb(int hb, F f) {
   constexpr bool qkv = EPI == kSliceQkv, sw = EPI == kSliceSwiglu, part = EPI == kSlicePartial;
   // (partial sums of two row groups: the split kernel is faster)
-  if constexpr ((part && NC == 2) || (!part && NC > 3) || (EPI == kSliceResid && NC > 2)) return false;
+  if constexpr ((part && NC == 2) || (!part && NC > 3) || ((qkv || EPI == kSliceResid) && NC > 2)) return false;
   else switch (hb) {
     case 1: if constexpr (!part) { f(Int<1>{}, Int<NC>{}); return true; } break;
-    case 2: if constexpr (EPI != kSliceResid && (!qkv || NC <= 2)) { f(Int<2>{}, Int<NC>{}); return true; } break;
-    case 3: if constexpr (sw || (qkv && NC <= 2)) { f(Int<3>{}, Int<NC>{}); return true; } break;
-    case 4: if constexpr (EPI != kSliceResid && (!qkv || NC <= 2)) { f(Int<4>{}, Int<NC>{}); return true; } break;
+    case 2: if constexpr (EPI != kSliceResid) { f(Int<2>{}, Int<NC>{}); return true; } break;
+    case 3: if constexpr (sw || qkv) { f(Int<3>{}, Int<NC>{}); return true; } break;
+    case 4: if constexpr (EPI != kSliceResid) { f(Int<4>{}, Int<NC>{}); return true; } break;
     case 5: if constexpr (sw && NC <= 3) { f(Int<5>{}, Int<NC>{}); return true; } break;
     case 6: if constexpr (sw && NC <= 3) { f(Int<6>{}, Int<NC>{}); return true; } break;
     case 7: if constexpr (sw && NC <= 2) { f(Int<7>{}, Int<NC>{}); return true; } break;
