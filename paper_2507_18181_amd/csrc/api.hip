@@ -153,17 +153,13 @@ GemmPlan plan_gemm(int n_bands, int ksteps, int nb, int n_cu) {
   return best;
 }
 
-// Row groups of the half-band kernel: 0 up to 8 rows, where one operand holds both planes (half the activation loads and
-// products of one group of 16).
-int slice_row_groups(int rows) { return rows <= 8 ? 0 : (rows + 15) / 16; }
-
 // Half-bands per workgroup of an unsplit GEMM that finishes its own output (kernels_slice.hip), or
 // hb = 0 where the split kernel keeps the projection.  One workgroup per compute unit and round;
 // more than one round is taken only where the last one is nearly full (a half empty round costs
 // more than the finishing kernel that is saved).
 SlicePlan plan_slice(int epi, int n_half, int ksteps, int rows, int n_cu) {
   SlicePlan pl;
-  pl.nc = slice_row_groups(rows);
+  pl.nc = (rows + 15) / 16;
   if (ksteps % 2) return pl;  // the kernel takes k-steps in pairs
   if (epi == kSliceResid) {
     // o: one half-band per workgroup, so each workgroup reads all activations for 16 output columns.
@@ -193,7 +189,7 @@ SlicePlan plan_slice(int epi, int n_half, int ksteps, int rows, int n_cu) {
 // bytes/ps, whichever is longer, plus 0.3 us per MB of partial sums.
 SlicePlan plan_slice_down(int n_half, int ksteps, int rows, int n_cu) {
   SlicePlan pl;
-  pl.nc = slice_row_groups(rows);
+  pl.nc = (rows + 15) / 16;
   if (ksteps % 2 || pl.nc == 2) return pl;
   double best = 1e300;
   for (int hb = 2; hb <= 8; hb *= 2) {
@@ -203,7 +199,7 @@ SlicePlan plan_slice_down(int n_half, int ksteps, int rows, int n_cu) {
     if (S > 16) S = 16;
     while (S > 1 && ksteps / 2 / S < 8) --S;  // at least one pair of k-steps per wavefront
     if (S < 1) continue;
-    const double wg_kb = (double)(hb + (pl.nc ? 2 * pl.nc : 1)) * ksteps / 2 / S, w_mb = (double)n_half * ksteps * 0.512e-3;
+    const double wg_kb = (double)(hb + 2 * pl.nc) * ksteps / 2 / S, w_mb = (double)n_half * ksteps * 0.512e-3;
     if (wg_kb > (pl.nc > 3 ? 512 : 1024) && pl.nc > 2) continue;
     const double cost = std::max(wg_kb / 60.0, w_mb / 5.9) + S * (double)rows * n_half * 64e-6 * 0.3;
     if (cost < best) {
