@@ -34,7 +34,7 @@ struct Staging {
 
 // offsets (in bytes) of the regions of a workspace sized for `rows_max` rows / `batch` sequences
 struct WsLayout {
-  size_t meta, outs, rope, x, h, q, k, v, att, t, logits, top2_v, top2_i, total;
+  size_t meta, outs, rope, x, h, q, att, t, logits, top2_v, top2_i, total;
   size_t hb, attb, tb, part, ssq, blk_val, blk_idx;  // bf16 activations and split-k partial sums (MFMA path)
   size_t qb, attn_o, attn_ml;                   // MFMA attention: bf16 queries, per-chunk partial outputs
   size_t meta_words;
@@ -216,7 +216,7 @@ WsLayout ws_layout(const specasr_ctx *ctx, int batch);
 WsLayout ws_layout(const specasr_config &c, int batch) {
   WsLayout L{};
   const size_t R = (size_t)batch * c.max_nodes;
-  const size_t dq = (size_t)c.n_heads * c.head_dim, dkv = (size_t)c.n_kv_heads * c.head_dim;
+  const size_t dq = (size_t)c.n_heads * c.head_dim;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
   L.meta_words = meta_words((int)R, batch);
@@ -226,8 +226,6 @@ WsLayout ws_layout(const specasr_config &c, int batch) {
   L.x = take(R * c.d_model * 4);
   L.h = take(R * (c.d_model > (int)dq ? c.d_model : dq) * 4);
   L.q = take(R * dq * 4);
-  L.k = take(R * dkv * 4);
-  L.v = take(R * dkv * 4);
   L.att = take(R * dq * 4);
   L.t = take(R * c.d_ffn * 4);
   L.logits = take(R * c.vocab * 4);
@@ -528,35 +526,32 @@ void forward_generic(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g, speca
   float *logits_dev = ro.logits;
   const ModelDims &md = ctx->md;
   const int dt = md.dtype, d = md.d_model, F = md.d_ffn, V = md.vocab;
-  const int dq = md.n_heads * md.head_dim, dkv = md.n_kv_heads * md.head_dim, R = m.rows;
+  const int dq = md.n_heads * md.head_dim, R = m.rows;
   float *x = (float *)(ws + L.x), *h = (float *)(ws + L.h), *q = (float *)(ws + L.q);
-  float *k = (float *)(ws + L.k), *v = (float *)(ws + L.v), *att = (float *)(ws + L.att);
-  float *t = (float *)(ws + L.t), *lg = (float *)(ws + L.logits);
+  float *att = (float *)(ws + L.att), *t = (float *)(ws + L.t), *lg = (float *)(ws + L.logits);
   float2 *cs = (float2 *)(ws + L.rope);
 
-  launch_rope_table(m, md.head_dim, md.rope_theta, cs, st);
-  launch_embed(m, dt, ctx->w.tok_embed, tree->input_embeds, ctx->cfg.max_nodes, d, x, st);
+  launch_embed_rope(m, dt, ctx->w.tok_embed, tree->input_embeds, ctx->cfg.max_nodes, d, x, md.head_dim, md.rope_theta, cs, st);
   for (int l = 0; l < md.n_layers; ++l) {
     const specasr_layer_weights &lw = ctx->layers[l];
-    launch_rmsnorm(dt, x, lw.attn_norm, R, d, md.rms_eps, h, st);
-    const LinearJob qkv[3] = {{lw.wq, dq, q, dq}, {lw.wk, dkv, k, dkv}, {lw.wv, dkv, v, dkv}};
-    launch_linears(dt, qkv, 3, d, h, d, R, false, st);
-    launch_rope_kv(m, md, g, l, cs, q, k, v, kv->k, kv->v, st);
+    launch_linear_qkv(m, md, g, l, NormIn{x, lw.attn_norm, R, d, md.rms_eps, h}, lw.wq, lw.wk, lw.wv, cs, q, kv->k, kv->v, st);
     launch_attention_generic(m, md, g, l, q, kv->k, kv->v, att, st);
-    launch_linear(dt, lw.wo, d, dq, att, dq, x, d, R, true, st);
-    launch_rmsnorm(dt, x, lw.ffn_norm, R, d, md.rms_eps, h, st);
-    launch_linear_swiglu(dt, lw.w_gate, lw.w_up, F, d, h, d, t, R, st);
-    launch_linear(dt, lw.w_down, d, F, t, F, x, d, R, true, st);
+    launch_linear_add(dt, lw.wo, d, dq, att, x, R, st);
+    launch_linear_swiglu(dt, NormIn{x, lw.ffn_norm, R, d, md.rms_eps, h}, lw.w_gate, lw.w_up, F, t, st);
+    launch_linear_add(dt, lw.w_down, d, F, t, x, R, st);
   }
   if (ro.none()) return;
-  launch_rmsnorm(dt, x, ctx->w.final_norm, R, d, md.rms_eps, h, st);
-  launch_linear(dt, ctx->w.lm_head, V, d, h, d, lg, V, R, false, st);
-  if (ro.top2)
-    launch_top2(m, lg, false, 0, 0, RowNorm{nullptr, 0, 0, 0.f}, V, ctx->cfg.max_nodes, nullptr,
+  const NormIn last{x, ctx->w.final_norm, R, d, md.rms_eps, h};
+  if (ro.top2) {
+    launch_linear_logits(m, dt, last, ctx->w.lm_head, V, ctx->cfg.max_nodes, lg, false, st);
+    launch_top2(m, lg, false, 0, 0, RowNorm{nullptr, 0, 0, 0.f}, V, ctx->cfg.max_nodes, logits_dev,
                 (float *)(ws + L.top2_v), (int *)(ws + L.top2_i), ro.top2, ro.prob, argmax_dev, st);
-  else
-    launch_argmax(m, lg, false, ctx->cfg.max_nodes, V, argmax_dev, st);
-  if (logits_dev) launch_scatter_logits(m, lg, ctx->cfg.max_nodes, V, logits_dev, st);
+    return;
+  }
+  // requested logits are written where the caller wants them, and read there
+  float *dst = logits_dev ? logits_dev : lg;
+  launch_linear_logits(m, dt, last, ctx->w.lm_head, V, ctx->cfg.max_nodes, dst, logits_dev != nullptr, st);
+  launch_argmax(m, dst, logits_dev != nullptr, ctx->cfg.max_nodes, V, argmax_dev, st);
 }
 
 constexpr size_t kProfPairs = 256;
@@ -736,8 +731,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       fprintf(stderr, "[specasr] plan %s rows=%d bands=%d ksteps=%d: %s, %d splits\n", nm[i], R, pm[i]->n_bands, pm[i]->ksteps, k, S);
     }
   }
-  launch_rope_table(m, md.head_dim, md.rope_theta, cs, st);
-  launch_embed(m, 1, ctx->w.tok_embed, tree->input_embeds, ctx->cfg.max_nodes, d, x, st);
+  launch_embed_rope(m, 1, ctx->w.tok_embed, tree->input_embeds, ctx->cfg.max_nodes, d, x, md.head_dim, md.rope_theta, cs, st);
   int pending = 0, pending_ld = 0;  // partial sums of the previous down projection, not yet added to x
   // kv_len, row_start, n_nodes of the sequences as build_step laid them out
   const int32_t *seq_words = hs.words.data() + 10 * (size_t)hs.batch * ctx->cfg.max_nodes;

@@ -12,32 +12,34 @@ struct ModelDims {
 };
 
 // ---- dtype-generic stages (fp32 arithmetic on fp32 activations) ----------
-// rope table: cs[row][j] = (cos, sin)(pos[row] * theta^(-2j/hd)), computed in fp64
-void launch_rope_table(const StepMeta &m, int hd, float theta, float2 *cs, hipStream_t st);
-// x[row][:] = tok_embed[token[row]][:]  (or the caller's embedding row)
-void launch_embed(const StepMeta &m, int dtype, const void *tok_embed, const void *input_embeds,
-                  int max_nodes, int d, float *x, hipStream_t st);
-// y[row][:] = x[row][:] * rsqrt(mean(x^2)+eps) * g
-void launch_rmsnorm(int dtype, const float *x, const void *gain, int rows, int d, float eps,
-                    float *y, hipStream_t st);
-// y[row][o] (+)= sum_k W[o][k] * a[row][k]
-void launch_linear(int dtype, const void *W, int n_out, int n_in, const float *a, int lda,
-                   float *y, int ldy, int rows, bool accumulate, hipStream_t st);
-// the same for up to 3 matrices with one input in one launch
+// x[row][:] = tok_embed[token[row]][:]  (or the caller's embedding row), and the rope table
+// cs[row][j] = (cos, sin)(pos[row] * theta^(-2j/hd)), computed in fp64
+void launch_embed_rope(const StepMeta &m, int dtype, const void *tok_embed, const void *input_embeds, int max_nodes, int d, float *x,
+                       int hd, float theta, float2 *cs, hipStream_t st);
+// Input of the linears below: residual rows x [rows][d] that are normalised first, x * rsqrt(mean(x^2)+eps) * gain, either
+// by the linear itself or (wide rows) into the scratch rows h
+struct NormIn {
+  const float *x;
+  const void *gain;
+  int rows, d;
+  float eps;
+  float *h;
+};
+// y[row][o] += sum_k W[o][k] * a[row][k]
+void launch_linear_add(int dtype, const void *W, int n_out, int n_in, const float *a, float *y, int rows, hipStream_t st);
 struct LinearJob {
   const void *W;
   int n_out;
   float *y;
   int ldy;
 };
-void launch_linears(int dtype, const LinearJob *jobs, int n, int n_in, const float *a, int lda, int rows, bool accumulate, hipStream_t st);
-// t[row][f] = silu(gate[f] . a[row]) * (up[f] . a[row])
-void launch_linear_swiglu(int dtype, const void *gate, const void *up, int F, int n_in, const float *a, int lda, float *t, int rows,
-                          hipStream_t st);
-// rotate q in place, rotate k, write k and v to their cache slots
-void launch_rope_kv(const StepMeta &m, const ModelDims &md, const KvGeom &g, int layer,
-                    const float2 *cs, float *q, const float *k, const float *v, void *kcache,
-                    void *vcache, hipStream_t st);
+// t[row][f] = silu(gate[f] . h[row]) * (up[f] . h[row])
+void launch_linear_swiglu(int dtype, const NormIn &nx, const void *gate, const void *up, int F, float *t, hipStream_t st);
+// q rotated, k rotated and written with v to their cache slots
+void launch_linear_qkv(const StepMeta &m, const ModelDims &md, const KvGeom &g, int layer, const NormIn &nx, const void *wq, const void *wk,
+                       const void *wv, const float2 *cs, float *q, void *kc, void *vc, hipStream_t st);
+// logits as compact rows [rows][V], or (padded) in the caller's [batch][max_nodes][V] array
+void launch_linear_logits(const StepMeta &m, int dtype, const NormIn &nx, const void *W, int V, int max_nodes, float *logits, bool padded, hipStream_t st);
 // tree-masked attention of every (row, head) over cache slots [0, kv_len + n_nodes)
 void launch_attention_generic(const StepMeta &m, const ModelDims &md, const KvGeom &g, int layer,
                               const float *q, const void *kcache, const void *vcache, float *out,
@@ -46,15 +48,11 @@ void launch_attention_generic(const StepMeta &m, const ModelDims &md, const KvGe
 // either compact ([rows][V], padded_in = false) or padded ([batch][max_nodes][V]).
 void launch_argmax(const StepMeta &m, const float *logits, bool padded_in, int max_nodes, int V,
                    int32_t *argmax, hipStream_t st);
-// copy compact logits rows into the caller's padded [batch][max_nodes][V] array
-void launch_scatter_logits(const StepMeta &m, const float *compact, int max_nodes, int V,
-                           float *padded, hipStream_t st);
-
 // Draft-side read-out (Sec. IV-A, Sec. IV-C): top2[seq][node] = ids of the largest and second
 // largest logit (value descending, id ascending; second = -1 if V == 1), prob[seq][node] = softmax
 // probability of the first, argmax (optional) = the first id.  The logits are compact rows
-// [rows][V], or (from_partials) split-k partial sums, times 1/rms of the row if nrm.ssq is set,
-// that are also stored into logits_out ([batch][max_nodes][V], optional).  rec_v / rec_i: rows * top2_blocks(V) * 3 floats / 2 ints.
+// [rows][V], or (from_partials) split-k partial sums, times 1/rms of the row if nrm.ssq is set;
+// they are also stored into logits_out ([batch][max_nodes][V], optional).  rec_v / rec_i: rows * top2_blocks(V) * 3 floats / 2 ints.
 int top2_blocks(int V);
 void launch_top2(const StepMeta &m, const float *src, bool from_partials, int n_splits, int ldp,
                  const RowNorm &nrm, int V, int max_nodes, float *logits_out, float *rec_v, int *rec_i, int32_t *top2,

@@ -6,41 +6,38 @@
 
 namespace specasr {
 
-// --------------------------------------------------------------------------- rope table
+// --------------------------------------------------------------------------- embedding gather, rope table
+// Both start a forward and depend on nothing but the metadata, so they share a launch: blocks 0 .. rows-1 copy an
+// embedding row each, the blocks behind them fill the table.
 // Sec. II-B: a tree node is verified as if decoded after its own branch, so its rotary
 // position is kv_len + depth, shared by siblings.  Angles are formed in fp64 once per call.
-__global__ void rope_table_kernel(const int32_t *pos, int rows, int half, int hd, double theta,
-                                  float2 *cs) {
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= rows * half) return;
-  int r = idx / half, j = idx - r * half;
-  double ang = (double)pos[r] * pow(theta, -2.0 * (double)j / (double)hd);
-  cs[idx] = make_float2((float)cos(ang), (float)sin(ang));
-}
-
-void launch_rope_table(const StepMeta &m, int hd, float theta, float2 *cs, hipStream_t st) {
-  int half = hd / 2, n = m.rows * half;
-  rope_table_kernel<<<(n + 255) / 256, 256, 0, st>>>(m.pos, m.rows, half, hd, (double)theta, cs);
-}
-
-// --------------------------------------------------------------------------- embedding gather
 template <class T>
-__global__ void embed_kernel(StepMeta m, const T *E, const T *in_emb, int max_nodes, int d, float *x) {
-  int r = blockIdx.x;
+__global__ __launch_bounds__(256) void embed_rope_kernel(StepMeta m, const T *E, const T *in_emb, int max_nodes, int d, float *x, int half, int hd,
+                                                         double theta, float2 *cs) {
+  if ((int)blockIdx.x >= m.rows) {
+    const int idx = ((int)blockIdx.x - m.rows) * 256 + threadIdx.x;
+    if (idx >= m.rows * half) return;
+    const int r = idx / half, j = idx - r * half;
+    const double ang = (double)m.pos[r] * pow(theta, -2.0 * (double)j / (double)hd);
+    cs[idx] = make_float2((float)cos(ang), (float)sin(ang));
+    return;
+  }
+  const int r = blockIdx.x;
   const T *src;
   if (in_emb != nullptr && m.use_embed[r])
     src = in_emb + ((int64_t)m.seq[r] * max_nodes + m.node[r]) * d;
   else
     src = E + (int64_t)m.token[r] * d;
-  for (int c = threadIdx.x; c < d; c += blockDim.x) x[(int64_t)r * d + c] = to_f32(src[c]);
+  for (int c = threadIdx.x; c < d; c += 256) x[(int64_t)r * d + c] = to_f32(src[c]);
 }
 
-void launch_embed(const StepMeta &m, int dtype, const void *E, const void *in_emb, int max_nodes,
-                  int d, float *x, hipStream_t st) {
+void launch_embed_rope(const StepMeta &m, int dtype, const void *E, const void *in_emb, int max_nodes, int d, float *x, int hd,
+                       float theta, float2 *cs, hipStream_t st) {
+  const int half = hd / 2, blocks = m.rows + (m.rows * half + 255) / 256;
   if (dtype == 1)
-    embed_kernel<bf16_t><<<m.rows, 256, 0, st>>>(m, (const bf16_t *)E, (const bf16_t *)in_emb, max_nodes, d, x);
+    embed_rope_kernel<bf16_t><<<blocks, 256, 0, st>>>(m, (const bf16_t *)E, (const bf16_t *)in_emb, max_nodes, d, x, half, hd, (double)theta, cs);
   else
-    embed_kernel<float><<<m.rows, 256, 0, st>>>(m, (const float *)E, (const float *)in_emb, max_nodes, d, x);
+    embed_rope_kernel<float><<<blocks, 256, 0, st>>>(m, (const float *)E, (const float *)in_emb, max_nodes, d, x, half, hd, (double)theta, cs);
 }
 
 // --------------------------------------------------------------------------- RMSNorm
@@ -56,20 +53,14 @@ __global__ void rmsnorm_kernel(const float *x, const T *g, int d, float eps, flo
     y[(int64_t)blockIdx.x * d + c] = xr[c] * rs * to_f32(g[c]);
 }
 
-void launch_rmsnorm(int dtype, const float *x, const void *g, int rows, int d, float eps, float *y,
-                    hipStream_t st) {
-  if (dtype == 1)
-    rmsnorm_kernel<bf16_t><<<rows, 256, 0, st>>>(x, (const bf16_t *)g, d, eps, y);
-  else
-    rmsnorm_kernel<float><<<rows, 256, 0, st>>>(x, (const float *)g, d, eps, y);
-}
-
 // --------------------------------------------------------------------------- linear
 // One wavefront owns OW output features and RB activation rows; lanes stride over k in 4-element vectors; the
 // OW * RB dot products are finished together by a halving exchange (17 shuffles for 16 sums instead of
-// 96).  n_in % 4 == 0.  Up to three matrices with the same input share a launch (q, k and v), and gate and up
-// of one feature a wavefront, which then applies SwiGLU: on a tiny model a launch costs more than its work
-// (fp32, d_model 256, 8 rows: 15 launches of 6.8 us and 2 of SwiGLU -> 9 of 5).
+// 96).  n_in % 4 == 0.  On a tiny model a launch costs more than its work, so what stands between two products is
+// done by them: gate and up of one feature belong to one wavefront, which applies SwiGLU; q, k and v are one launch
+// whose wavefronts own the two halves of a rotary pair, rotate it and write k and v to the cache; the logits go to the
+// caller's array; and up to kNormWidth input features a workgroup normalises its 8 rows itself, in LDS.  Bound by the
+// chain of launches, about 7 us each: tiny fp32 step of 8 nodes 178 -> 148 us (15 launches for 24).
 template <class T> struct Vec4;
 template <> struct Vec4<float> {
   static __device__ __forceinline__ void load(const float *p, float w[4]) {
@@ -107,56 +98,151 @@ template <class T>
 struct LinearSet {
   const T *W[3];
   float *y[3];
-  int n_out[3], ldy[3], first[4];
+  int n_out[3], ldy[3], first[3];
+};
+
+// What the modes below need besides.
+template <class T>
+struct LinearMore {
+  const T *gain;                  // NORM
+  float eps;
+  const int32_t *seq, *slot, *node;  // QKV: seq, slot; LOGITS: seq, node
+  int max_nodes;
+  KvGeom g;                       // QKV
+  int layer, hd;
+  const float2 *cs;
+  T *kc, *vc;
 };
 
 constexpr int kLinRows = 8, kLinOut = 2;  // RB, OW
+// Widest input that a workgroup normalises itself: 8 rows of it are 32 KB of LDS and every workgroup repeats them.  An
+// 8-layer fp32 model, 16 rows, with the norm in the linear / as a kernel of its own: 532 / 617 us at d_model 512, 735 /
+// 866 at 1024 (64 rows 1311 / 1491); wider was not built, it would need more LDS or a second pass.
+constexpr int kNormWidth = 1024;
 
-// SWIGLU: W[0] = gate, W[1] = up, one feature per wavefront, y[0] = silu(gate) * up.
-template <class T, bool SWIGLU>
-__global__ __launch_bounds__(256) void linear_kernel(LinearSet<T> ls, int n_in, const float *a, int lda, int rows, int accumulate) {
-  constexpr int RB = kLinRows, OW = kLinOut;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+enum LinearMode {
+  kLinPlain = 0,   // y = W a, or y += W a
+  kLinSwiglu = 1,  // W[0] = gate, W[1] = up, one feature per wavefront, y[0] = silu(gate) * up
+  kLinQkv = 2,     // W = q, k, v; y[0] = rotated queries, rotated k and v go to their cache slots
+  kLinLogits = 3,  // row r goes to row seq * max_nodes + node of y
+};
+
+// NORM: a holds residual rows; the product takes a * gain / rms(a), as rmsnorm_kernel leaves it.
+template <class T, int MODE, bool NORM>
+__global__ __launch_bounds__(256) void linear_kernel(LinearSet<T> ls, LinearMore<T> mo, int n_in, const float *a, int lda, int rows, int accumulate) {
+  constexpr int RB = kLinRows, OW = kLinOut, NIT = kNormWidth / 256;
+  __shared__ float4 as[NORM ? RB * (kNormWidth / 4) : 1];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   // selected by value: an index into the arguments would be a second, dependent load of them
-  const bool is1 = !SWIGLU && (int)blockIdx.x >= ls.first[1], is2 = !SWIGLU && (int)blockIdx.x >= ls.first[2];
+  const bool is1 = MODE != kLinSwiglu && (int)blockIdx.x >= ls.first[1], is2 = MODE != kLinSwiglu && (int)blockIdx.x >= ls.first[2];
   const T *W = is2 ? ls.W[2] : is1 ? ls.W[1] : ls.W[0];
   float *y = is2 ? ls.y[2] : is1 ? ls.y[1] : ls.y[0];
   const int n_out = is2 ? ls.n_out[2] : is1 ? ls.n_out[1] : ls.n_out[0], ldy = is2 ? ls.ldy[2] : is1 ? ls.ldy[1] : ls.ldy[0];
-  const int b0 = (int)blockIdx.x - (is2 ? ls.first[2] : is1 ? ls.first[1] : 0);
-  const int o0 = (b0 * 4 + wave) * (SWIGLU ? 1 : OW), r0 = blockIdx.y * RB;
-  if (o0 >= n_out) return;
-  const T *w0 = W + (int64_t)o0 * n_in;
-  const T *w1 = SWIGLU ? ls.W[1] + (int64_t)o0 * n_in : W + (int64_t)min(o0 + 1, n_out - 1) * n_in;
+  const int u = ((int)blockIdx.x - (is2 ? ls.first[2] : is1 ? ls.first[1] : 0)) * 4 + wave, r0 = blockIdx.y * RB;
+  // this wavefront's outputs o0 and o1
+  int o0, o1, head = 0, j0 = 0;
+  const int half = mo.hd >> 1;
+  if (MODE == kLinQkv) {
+    head = (uint32_t)u / (uint32_t)half;
+    j0 = u - head * half;
+    o0 = head * mo.hd + j0;
+    o1 = o0 + half;
+  } else {
+    o0 = u * (MODE == kLinSwiglu ? 1 : OW);
+    o1 = o0 + 1;
+  }
+  const bool live = o0 < n_out;
+  if (!NORM && !live) return;
+  const T *w0 = W + (int64_t)min(o0, n_out - 1) * n_in;
+  const T *w1 = MODE == kLinSwiglu ? ls.W[1] + (int64_t)min(o0, n_out - 1) * n_in : W + (int64_t)min(o1, n_out - 1) * n_in;
   float acc[OW * RB];
 #pragma unroll
   for (int i = 0; i < OW * RB; ++i) acc[i] = 0.f;
+  if constexpr (NORM) {
+    // all weights of the wavefront and its 2 rows are requested at once
+    float w[NIT][OW][4];
+    float4 x[2][NIT];
+    float gn[NIT][4];
+#pragma unroll
+    for (int t = 0; t < NIT; ++t) {
+      const int k = lane * 4 + t * 256;
+      if (k < n_in) {
+        Vec4<T>::load(w0 + k, w[t][0]);
+        Vec4<T>::load(w1 + k, w[t][1]);
+        Vec4<T>::load(mo.gain + k, gn[t]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) x[i][t] = *reinterpret_cast<const float4 *>(a + (int64_t)min(r0 + 2 * wave + i, rows - 1) * lda + k);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      float ss = 0.f;
+#pragma unroll
+      for (int t = 0; t < NIT; ++t)
+        if (lane * 4 + t * 256 < n_in) ss += (x[i][t].x * x[i][t].x + x[i][t].y * x[i][t].y) + (x[i][t].z * x[i][t].z + x[i][t].w * x[i][t].w);
+      const float rs = 1.0f / sqrtf(wave_sum(ss) / (float)n_in + mo.eps);
+#pragma unroll
+      for (int t = 0; t < NIT; ++t)
+        if (lane * 4 + t * 256 < n_in)
+          as[(2 * wave + i) * (kNormWidth / 4) + lane + t * 64] =
+              make_float4(x[i][t].x * rs * gn[t][0], x[i][t].y * rs * gn[t][1], x[i][t].z * rs * gn[t][2], x[i][t].w * rs * gn[t][3]);
+    }
+    __syncthreads();
+    if (!live) return;
+#pragma unroll
+    for (int t = 0; t < NIT; ++t)
+      if (lane * 4 + t * 256 < n_in)
+#pragma unroll
+        for (int j = 0; j < RB; ++j) {
+          const float4 av = as[j * (kNormWidth / 4) + lane + t * 64];
+#pragma unroll
+          for (int i = 0; i < OW; ++i)
+            acc[i * RB + j] += w[t][i][0] * av.x + w[t][i][1] * av.y + w[t][i][2] * av.z + w[t][i][3] * av.w;
+        }
+  } else {
 #pragma unroll 2
-  for (int k = lane * 4; k < n_in; k += 256) {
-    float w[OW][4];
-    Vec4<T>::load(w0 + k, w[0]);
-    Vec4<T>::load(w1 + k, w[1]);
+    for (int k = lane * 4; k < n_in; k += 256) {
+      float w[OW][4];
+      Vec4<T>::load(w0 + k, w[0]);
+      Vec4<T>::load(w1 + k, w[1]);
 #pragma unroll
-    for (int j = 0; j < RB; ++j) {
-      const int r = min(r0 + j, rows - 1);
-      const float4 av = *reinterpret_cast<const float4 *>(a + (int64_t)r * lda + k);
+      for (int j = 0; j < RB; ++j) {
+        const float4 av = *reinterpret_cast<const float4 *>(a + (int64_t)min(r0 + j, rows - 1) * lda + k);
 #pragma unroll
-      for (int i = 0; i < OW; ++i)
-        acc[i * RB + j] += w[i][0] * av.x + w[i][1] * av.y + w[i][2] * av.z + w[i][3] * av.w;
+        for (int i = 0; i < OW; ++i)
+          acc[i * RB + j] += w[i][0] * av.x + w[i][1] * av.y + w[i][2] * av.z + w[i][3] * av.w;
+      }
     }
   }
-  const float s = wave_sum16(acc, lane);  // of output o0 + lane/32, row r0 + (lane/4)%8
-  const int j = (lane >> 2) & 7, o = o0 + (lane >> 5);
-  if (SWIGLU) {
+  const float s = wave_sum16(acc, lane);  // of output (lane < 32 ? o0 : o1), row r0 + (lane/4)%8
+  const int j = (lane >> 2) & 7, o = lane < 32 ? o0 : o1, r = r0 + j;
+  const bool mine = (lane & 3) == 0 && r < rows;
+  if (MODE == kLinSwiglu) {
     const float up = __shfl_xor(s, 32, 64);
-    if (lane < 32 && (lane & 3) == 0 && r0 + j < rows) y[(int64_t)(r0 + j) * ldy + o0] = s / (1.0f + __expf(-s)) * up;
-  } else if ((lane & 3) == 0 && o < n_out && r0 + j < rows) {
-    float *dst = y + (int64_t)(r0 + j) * ldy + o;
-    *dst = accumulate ? (*dst + s) : s;
+    if (lane < 32 && mine) y[(int64_t)r * ldy + o0] = s / (1.0f + __expf(-s)) * up;
+  } else if (MODE == kLinQkv) {
+    const float other = __shfl_xor(s, 32, 64);
+    if (!mine) return;
+    float v = s;
+    if (!is2) {  // rotary pair: x0 cos - x1 sin, x1 cos + x0 sin
+      const float2 c = mo.cs[(int64_t)r * half + j0];
+      v = lane < 32 ? s * c.x - other * c.y : s * c.x + other * c.y;
+    }
+    if (!is1 && !is2) {
+      y[(int64_t)r * ldy + o] = v;
+    } else {
+      T *cache = is2 ? mo.vc : mo.kc;
+      cache[mo.g.row(mo.seq[r], mo.layer, head, mo.slot[r]) + (o - head * mo.hd)] = from_f32<T>(v);
+    }
+  } else if (mine && o < n_out) {
+    const int64_t yr = MODE == kLinLogits ? (int64_t)mo.seq[r] * mo.max_nodes + mo.node[r] : r;
+    float *dst = y + yr * ldy + o;
+    *dst = MODE == kLinPlain && accumulate ? (*dst + s) : s;
   }
 }
 
-template <class T, bool SWIGLU>
-static void launch_linear_t(const LinearJob *jobs, int n, int n_in, const float *a, int lda, int rows, bool accumulate, hipStream_t st) {
+template <class T, int MODE, bool NORM>
+static void launch_linear_t(const LinearJob *jobs, int n, const LinearMore<T> &mo, int n_in, const float *a, int lda, int rows, bool accumulate, hipStream_t st) {
   LinearSet<T> ls{};
   int blocks = 0;
   for (int i = 0; i < 3; ++i) {
@@ -165,72 +251,66 @@ static void launch_linear_t(const LinearJob *jobs, int n, int n_in, const float 
     ls.y[i] = j.y;
     ls.n_out[i] = j.n_out;
     ls.ldy[i] = j.ldy;
-    ls.first[i] = blocks;
-    if (SWIGLU) blocks = (j.n_out + 3) / 4;
+    ls.first[i] = i < n ? blocks : 0x7fffffff;
+    if (MODE == kLinSwiglu) blocks = (j.n_out + 3) / 4;
     else if (i < n) blocks += (j.n_out + 4 * kLinOut - 1) / (4 * kLinOut);
   }
-  ls.first[3] = blocks;
   dim3 grid(blocks, (rows + kLinRows - 1) / kLinRows);
-  linear_kernel<T, SWIGLU><<<grid, 256, 0, st>>>(ls, n_in, a, lda, rows, accumulate ? 1 : 0);
+  linear_kernel<T, MODE, NORM><<<grid, 256, 0, st>>>(ls, mo, n_in, a, lda, rows, accumulate ? 1 : 0);
 }
 
-void launch_linears(int dtype, const LinearJob *jobs, int n, int n_in, const float *a, int lda, int rows, bool accumulate, hipStream_t st) {
-  if (dtype == 1) launch_linear_t<bf16_t, false>(jobs, n, n_in, a, lda, rows, accumulate, st);
-  else launch_linear_t<float, false>(jobs, n, n_in, a, lda, rows, accumulate, st);
+template <class T, int MODE>
+static void launch_linear_norm(const LinearJob *jobs, int n, LinearMore<T> mo, const NormIn &nx, hipStream_t st) {
+  if (nx.d <= kNormWidth) {
+    mo.gain = (const T *)nx.gain;
+    mo.eps = nx.eps;
+    launch_linear_t<T, MODE, true>(jobs, n, mo, nx.d, nx.x, nx.d, nx.rows, false, st);
+    return;
+  }
+  rmsnorm_kernel<T><<<nx.rows, 256, 0, st>>>(nx.x, (const T *)nx.gain, nx.d, nx.eps, nx.h);
+  launch_linear_t<T, MODE, false>(jobs, n, mo, nx.d, nx.h, nx.d, nx.rows, false, st);
 }
 
-void launch_linear(int dtype, const void *W, int n_out, int n_in, const float *a, int lda,
-                   float *y, int ldy, int rows, bool accumulate, hipStream_t st) {
-  const LinearJob j{W, n_out, y, ldy};
-  launch_linears(dtype, &j, 1, n_in, a, lda, rows, accumulate, st);
+void launch_linear_add(int dtype, const void *W, int n_out, int n_in, const float *a, float *y, int rows, hipStream_t st) {
+  const LinearJob j{W, n_out, y, n_out};
+  if (dtype == 1) launch_linear_t<bf16_t, kLinPlain, false>(&j, 1, LinearMore<bf16_t>{}, n_in, a, n_in, rows, true, st);
+  else launch_linear_t<float, kLinPlain, false>(&j, 1, LinearMore<float>{}, n_in, a, n_in, rows, true, st);
 }
 
-void launch_linear_swiglu(int dtype, const void *gate, const void *up, int F, int n_in, const float *a, int lda, float *t, int rows,
-                          hipStream_t st) {
+void launch_linear_swiglu(int dtype, const NormIn &nx, const void *gate, const void *up, int F, float *t, hipStream_t st) {
   const LinearJob j[2] = {{gate, F, t, F}, {up, F, t, F}};
-  if (dtype == 1) launch_linear_t<bf16_t, true>(j, 2, n_in, a, lda, rows, false, st);
-  else launch_linear_t<float, true>(j, 2, n_in, a, lda, rows, false, st);
+  if (dtype == 1) launch_linear_norm<bf16_t, kLinSwiglu>(j, 2, LinearMore<bf16_t>{}, nx, st);
+  else launch_linear_norm<float, kLinSwiglu>(j, 2, LinearMore<float>{}, nx, st);
 }
 
-// --------------------------------------------------------------------------- RoPE + KV append
-// q: [rows][H*hd] rotated in place.  k, v: [rows][Hkv*hd]; k is rotated and both are written
-// to cache slot kv_len + node of the row's sequence.
 template <class T>
-__global__ void rope_kv_kernel(StepMeta m, KvGeom g, int layer, int H, int Hkv, int hd,
-                               const float2 *cs, float *q, const float *k, const float *v,
-                               T *kc, T *vc) {
-  const int r = blockIdx.x, half = hd / 2;
-  const float2 *csr = cs + (int64_t)r * half;
-  float *qr = q + (int64_t)r * H * hd;
-  for (int idx = threadIdx.x; idx < H * half; idx += blockDim.x) {
-    int a = idx / half, j = idx - a * half;
-    float2 c = csr[j];
-    float x0 = qr[a * hd + j], x1 = qr[a * hd + j + half];
-    qr[a * hd + j] = x0 * c.x - x1 * c.y;
-    qr[a * hd + j + half] = x1 * c.x + x0 * c.y;
-  }
-  const int seq = m.seq[r];
-  const int64_t slot = m.slot[r];
-  const float *kr = k + (int64_t)r * Hkv * hd, *vr = v + (int64_t)r * Hkv * hd;
-  for (int idx = threadIdx.x; idx < Hkv * half; idx += blockDim.x) {
-    int b = idx / half, j = idx - b * half;
-    float2 c = csr[j];
-    float x0 = kr[b * hd + j], x1 = kr[b * hd + j + half];
-    int64_t base = g.row(seq, layer, b, slot);
-    kc[base + j] = from_f32<T>(x0 * c.x - x1 * c.y);
-    kc[base + j + half] = from_f32<T>(x1 * c.x + x0 * c.y);
-    vc[base + j] = from_f32<T>(vr[b * hd + j]);
-    vc[base + j + half] = from_f32<T>(vr[b * hd + j + half]);
-  }
+static void launch_linear_qkv_t(const NormIn &nx, const LinearJob *jobs, const StepMeta &m, const KvGeom &g, int layer, const float2 *cs,
+                                void *kc, void *vc, hipStream_t st) {
+  LinearMore<T> mo{};
+  mo.seq = m.seq; mo.slot = m.slot; mo.g = g; mo.layer = layer; mo.hd = g.head_dim; mo.cs = cs; mo.kc = (T *)kc; mo.vc = (T *)vc;
+  launch_linear_norm<T, kLinQkv>(jobs, 3, mo, nx, st);
 }
 
-void launch_rope_kv(const StepMeta &m, const ModelDims &md, const KvGeom &g, int layer,
-                    const float2 *cs, float *q, const float *k, const float *v, void *kc, void *vc,
-                    hipStream_t st) {
-  if (md.dtype == 1)
-    rope_kv_kernel<bf16_t><<<m.rows, 256, 0, st>>>(m, g, layer, md.n_heads, md.n_kv_heads, md.head_dim, cs, q, k, v, (bf16_t *)kc, (bf16_t *)vc);
-  else
-    rope_kv_kernel<float><<<m.rows, 256, 0, st>>>(m, g, layer, md.n_heads, md.n_kv_heads, md.head_dim, cs, q, k, v, (float *)kc, (float *)vc);
+void launch_linear_qkv(const StepMeta &m, const ModelDims &md, const KvGeom &g, int layer, const NormIn &nx, const void *wq, const void *wk,
+                       const void *wv, const float2 *cs, float *q, void *kc, void *vc, hipStream_t st) {
+  const int dq = md.n_heads * md.head_dim, dkv = md.n_kv_heads * md.head_dim;
+  const LinearJob jobs[3] = {{wq, dq, q, dq}, {wk, dkv, nullptr, 0}, {wv, dkv, nullptr, 0}};
+  if (md.dtype == 1) launch_linear_qkv_t<bf16_t>(nx, jobs, m, g, layer, cs, kc, vc, st);
+  else launch_linear_qkv_t<float>(nx, jobs, m, g, layer, cs, kc, vc, st);
+}
+
+template <class T>
+static void launch_linear_logits_t(const StepMeta &m, const NormIn &nx, const LinearJob &j, int max_nodes, bool padded, hipStream_t st) {
+  LinearMore<T> mo{};
+  mo.seq = m.seq; mo.node = m.node; mo.max_nodes = max_nodes;
+  if (padded) launch_linear_norm<T, kLinLogits>(&j, 1, mo, nx, st);
+  else launch_linear_norm<T, kLinPlain>(&j, 1, mo, nx, st);
+}
+
+void launch_linear_logits(const StepMeta &m, int dtype, const NormIn &nx, const void *W, int V, int max_nodes, float *logits, bool padded, hipStream_t st) {
+  const LinearJob j{W, V, logits, V};
+  if (dtype == 1) launch_linear_logits_t<bf16_t>(m, nx, j, max_nodes, padded, st);
+  else launch_linear_logits_t<float>(m, nx, j, max_nodes, padded, st);
 }
 
 // --------------------------------------------------------------------------- attention
@@ -402,20 +482,6 @@ __global__ __launch_bounds__(256) void argmax_pieces_kernel(StepMeta m, const fl
     for (int w = 1; w < 4; ++w) take(bv[w], bi[w]);
     rec[blockIdx.x] = make_float2(best, __int_as_float(besti));
   }
-}
-
-__global__ void scatter_logits_kernel(StepMeta m, const float *compact, int max_nodes, int V,
-                                      float *padded) {
-  const int r = blockIdx.x;
-  const float *src = compact + (int64_t)r * V;
-  float *dst = padded + (int64_t)(m.seq[r] * max_nodes + m.node[r]) * V;
-  for (int t = blockIdx.y * blockDim.x + threadIdx.x; t < V; t += gridDim.y * blockDim.x) dst[t] = src[t];
-}
-
-void launch_scatter_logits(const StepMeta &m, const float *compact, int max_nodes, int V,
-                           float *padded, hipStream_t st) {
-  dim3 grid(m.rows, 8);
-  scatter_logits_kernel<<<grid, 256, 0, st>>>(m, compact, max_nodes, V, padded);
 }
 
 // --------------------------------------------------------------------------- draft-side read-out
