@@ -28,6 +28,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct Staging {
   int32_t *host = nullptr;  // pinned
+  int32_t *dev = nullptr;   // the same, as the device sees it
   hipEvent_t done = nullptr;
   bool used = false;
 };
@@ -92,6 +93,7 @@ struct specasr_ctx {
   Staging stage[kStagingSlots];
   int next_stage = 0;
   int32_t *out_host = nullptr;  // pinned, results of verify_tree
+  int32_t *out_dev = nullptr;   // the same, as the device sees it
   size_t out_host_words = 0;
   int32_t last_hip = 0;
   int device = 0;
@@ -308,6 +310,7 @@ struct HostStep {
   int max_total_keys = 0;  // max over sequences of kv_len + n_nodes
   int max_seq_nodes = 0;
   std::vector<int32_t> words;  // the block copied to the device
+  Staging *staged = nullptr;   // where it waits in pinned memory
 };
 
 specasr_status validate_tree(const specasr_ctx *ctx, const specasr_tree *tree, int batch,
@@ -379,10 +382,9 @@ void build_step(const specasr_ctx *ctx, const specasr_tree *tree, int batch, con
   }
 }
 
-StepMeta device_meta(const specasr_ctx *ctx, char *ws, const WsLayout &L, int batch_cap,
-                     const HostStep &hs) {
-  const int R = batch_cap * ctx->cfg.max_nodes;
-  const int32_t *w = reinterpret_cast<const int32_t *>(ws + L.meta);
+// The metadata of one call at `w`, laid out as build_step does for hs.batch sequences.
+StepMeta meta_at(const specasr_ctx *ctx, const int32_t *w, const HostStep &hs) {
+  const size_t R = (size_t)hs.batch * ctx->cfg.max_nodes;
   StepMeta m;
   m.token = w;
   m.seq = w + R;
@@ -394,18 +396,22 @@ StepMeta device_meta(const specasr_ctx *ctx, char *ws, const WsLayout &L, int ba
   m.use_embed = w + 7 * R;
   m.anc = reinterpret_cast<const uint64_t *>(w + 8 * R);
   m.kv_len = w + 10 * R;
-  m.row_start = m.kv_len + batch_cap;
-  m.n_nodes = m.row_start + batch_cap;
+  m.row_start = m.kv_len + hs.batch;
+  m.n_nodes = m.row_start + hs.batch;
   m.rows = hs.rows;
   m.batch = hs.batch;
-  const size_t R_host = (size_t)hs.batch * ctx->cfg.max_nodes;  // layout of hs.words
-  m.kv_len0 = hs.words[10 * R_host];
-  m.n_nodes0 = hs.words[10 * R_host + 2 * (size_t)hs.batch];
+  m.kv_len0 = hs.words[10 * R];
+  m.n_nodes0 = hs.words[10 * R + 2 * (size_t)hs.batch];
   return m;
+}
+StepMeta device_meta(const specasr_ctx *ctx, char *ws, const WsLayout &L, const HostStep &hs) {
+  return meta_at(ctx, reinterpret_cast<const int32_t *>(ws + L.meta), hs);
 }
 
 // Pinned staging buffers and events are created on first use, so that a context can be
 // created -- and every host-side validation exercised -- on a machine without a GPU.
+// Coherent, as kernels read the staging slots and write the results there.
+constexpr unsigned kPinned = hipHostMallocMapped | hipHostMallocCoherent;
 specasr_status ensure_staging(specasr_ctx *ctx) {
   if (ctx->staging_ready) return SPECASR_OK;
   const specasr_config &c = ctx->cfg;
@@ -413,11 +419,13 @@ specasr_status ensure_staging(specasr_ctx *ctx) {
   const int seqs_max = c.max_batch > kWideSeqs ? c.max_batch : kWideSeqs;
   const size_t mw = meta_words(seqs_max * c.max_nodes, seqs_max);
   for (int i = 0; i < kStagingSlots; ++i) {
-    if (!ctx->stage[i].host) HIP_TRY(ctx, hipHostMalloc((void **)&ctx->stage[i].host, mw * 4, hipHostMallocDefault));
+    if (!ctx->stage[i].host) HIP_TRY(ctx, hipHostMalloc((void **)&ctx->stage[i].host, mw * 4, kPinned));
+    if (!ctx->stage[i].dev) HIP_TRY(ctx, hipHostGetDevicePointer((void **)&ctx->stage[i].dev, ctx->stage[i].host, 0));
     if (!ctx->stage[i].done) HIP_TRY(ctx, hipEventCreateWithFlags(&ctx->stage[i].done, hipEventDisableTiming));
   }
   ctx->out_host_words = (size_t)c.max_batch * c.max_nodes * 2 + (size_t)c.max_batch * 2;
-  if (!ctx->out_host) HIP_TRY(ctx, hipHostMalloc((void **)&ctx->out_host, ctx->out_host_words * 4, hipHostMallocDefault));
+  if (!ctx->out_host) HIP_TRY(ctx, hipHostMalloc((void **)&ctx->out_host, ctx->out_host_words * 4, kPinned));
+  if (!ctx->out_dev) HIP_TRY(ctx, hipHostGetDevicePointer((void **)&ctx->out_dev, ctx->out_host, 0));
   ctx->staging_ready = true;
   return SPECASR_OK;
 }
@@ -433,17 +441,17 @@ specasr_status next_slot(specasr_ctx *ctx, Staging **out) {
   return SPECASR_OK;
 }
 
-// Copy the metadata block to the device through a pinned staging slot.
-specasr_status upload_meta(specasr_ctx *ctx, const HostStep &hs, char *ws, const WsLayout &L,
-                           hipStream_t st) {
-  Staging *sp = nullptr;
-  specasr_status rc = next_slot(ctx, &sp);
+// Lay the metadata block out in a pinned staging slot, where the first kernel of the call reads it.  staged() has to
+// follow that kernel: the slot is not written again before it has ended.
+specasr_status stage_meta(specasr_ctx *ctx, HostStep &hs) {
+  specasr_status rc = next_slot(ctx, &hs.staged);
   if (rc != SPECASR_OK) return rc;
-  Staging &s = *sp;
-  memcpy(s.host, hs.words.data(), hs.words.size() * 4);
-  HIP_TRY(ctx, hipMemcpyAsync(ws + L.meta, s.host, hs.words.size() * 4, hipMemcpyHostToDevice, st));
-  HIP_TRY(ctx, hipEventRecord(s.done, st));
-  s.used = true;
+  memcpy(hs.staged->host, hs.words.data(), hs.words.size() * 4);
+  return SPECASR_OK;
+}
+specasr_status staged(specasr_ctx *ctx, const HostStep &hs, hipStream_t st) {
+  HIP_TRY(ctx, hipEventRecord(hs.staged->done, st));
+  hs.staged->used = true;
   return SPECASR_OK;
 }
 
@@ -518,10 +526,18 @@ struct ReadOut {
   bool none() const { return !argmax && !logits && !top2; }
 };
 
+// The first kernel of a forward; it reads the staged metadata in pinned memory and leaves it in the workspace.
+specasr_status begin_forward(specasr_ctx *ctx, const HostStep &hs, const specasr_tree *tree, char *ws, const WsLayout &L, int dtype, float *x,
+                             float2 *cs, const BeginPlanes *pl, hipStream_t st) {
+  launch_begin(meta_at(ctx, hs.staged->dev, hs), dtype, ctx->w.tok_embed, tree->input_embeds, ctx->cfg.max_nodes, ctx->md.d_model, x,
+               ctx->md.head_dim, ctx->md.rope_theta, cs, pl, hs.staged->dev, reinterpret_cast<int32_t *>(ws + L.meta), (int)hs.words.size(), st);
+  return staged(ctx, hs, st);
+}
+
 // Steps 1-8 with the dtype-generic kernels.
-void forward_generic(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g, specasr_kv *kv,
-                     const specasr_tree *tree, char *ws, const WsLayout &L, const ReadOut &ro,
-                     hipStream_t st) {
+specasr_status forward_generic(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g, specasr_kv *kv,
+                               const specasr_tree *tree, char *ws, const WsLayout &L, const HostStep &hs, const ReadOut &ro,
+                               hipStream_t st) {
   int32_t *argmax_dev = ro.argmax;
   float *logits_dev = ro.logits;
   const ModelDims &md = ctx->md;
@@ -531,7 +547,8 @@ void forward_generic(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g, speca
   float *att = (float *)(ws + L.att), *t = (float *)(ws + L.t), *lg = (float *)(ws + L.logits);
   float2 *cs = (float2 *)(ws + L.rope);
 
-  launch_embed_rope(m, dt, ctx->w.tok_embed, tree->input_embeds, ctx->cfg.max_nodes, d, x, md.head_dim, md.rope_theta, cs, st);
+  const specasr_status s = begin_forward(ctx, hs, tree, ws, L, dt, x, cs, nullptr, st);
+  if (s != SPECASR_OK) return s;
   for (int l = 0; l < md.n_layers; ++l) {
     const specasr_layer_weights &lw = ctx->layers[l];
     launch_linear_qkv(m, md, g, l, NormIn{x, lw.attn_norm, R, d, md.rms_eps, h}, lw.wq, lw.wk, lw.wv, cs, q, kv->k, kv->v, st);
@@ -540,18 +557,19 @@ void forward_generic(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g, speca
     launch_linear_swiglu(dt, NormIn{x, lw.ffn_norm, R, d, md.rms_eps, h}, lw.w_gate, lw.w_up, F, t, st);
     launch_linear_add(dt, lw.w_down, d, F, t, x, R, st);
   }
-  if (ro.none()) return;
+  if (ro.none()) return SPECASR_OK;
   const NormIn last{x, ctx->w.final_norm, R, d, md.rms_eps, h};
   if (ro.top2) {
     launch_linear_logits(m, dt, last, ctx->w.lm_head, V, ctx->cfg.max_nodes, lg, false, st);
     launch_top2(m, lg, false, 0, 0, RowNorm{nullptr, 0, 0, 0.f}, V, ctx->cfg.max_nodes, logits_dev,
                 (float *)(ws + L.top2_v), (int *)(ws + L.top2_i), ro.top2, ro.prob, argmax_dev, st);
-    return;
+    return SPECASR_OK;
   }
   // requested logits are written where the caller wants them, and read there
   float *dst = logits_dev ? logits_dev : lg;
   launch_linear_logits(m, dt, last, ctx->w.lm_head, V, ctx->cfg.max_nodes, dst, logits_dev != nullptr, st);
   launch_argmax(m, dst, logits_dev != nullptr, ctx->cfg.max_nodes, V, argmax_dev, st);
+  return SPECASR_OK;
 }
 
 constexpr size_t kProfPairs = 256;
@@ -731,7 +749,9 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       fprintf(stderr, "[specasr] plan %s rows=%d bands=%d ksteps=%d: %s, %d splits\n", nm[i], R, pm[i]->n_bands, pm[i]->ksteps, k, S);
     }
   }
-  launch_embed_rope(m, 1, ctx->w.tok_embed, tree->input_embeds, ctx->cfg.max_nodes, d, x, md.head_dim, md.rope_theta, cs, st);
+  const BeginPlanes first{(const uint16_t *)ctx->layers[0].attn_norm, hb, hb_lo, nb, ssq, nrm.n_slab};
+  const specasr_status begun = begin_forward(ctx, hs, tree, ws, L, 1, x, cs, &first, st);
+  if (begun != SPECASR_OK) return begun;
   int pending = 0, pending_ld = 0;  // partial sums of the previous down projection, not yet added to x
   // kv_len, row_start, n_nodes of the sequences as build_step laid them out
   const int32_t *seq_words = hs.words.data() + 10 * (size_t)hs.batch * ctx->cfg.max_nodes;
@@ -740,7 +760,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
     const bool pl = l == prof_layer;
     const specasr_layer_weights &lw = ctx->layers[l];
     const PackedLayer &pk = ctx->packed[l];
-    launch_residual_gain(x, part, pending, R, pending_ld, lw.attn_norm, d, hb, hb_lo, nb, ssq, st);
+    if (l > 0) launch_residual_gain(x, part, pending, R, pending_ld, lw.attn_norm, d, hb, hb_lo, nb, ssq, st);
     SliceArgs sa{};
     sa.rows = R;
     sa.S = 1;
@@ -835,12 +855,10 @@ specasr_status forward_common(specasr_ctx *ctx, specasr_kv *kv, const specasr_tr
                               bool wide_ws = false, bool shared_cache = false) {
   KvGeom g{kv->capacity, ctx->md.n_layers, ctx->md.n_kv_heads, ctx->md.head_dim};
   g.shared_cache = shared_cache ? 1 : 0;
-  StepMeta m = device_meta(ctx, ws, L, hs.batch, hs);
-  if (ctx->fast && (m.rows <= 64 || wide_ws)) {
-    const specasr_status s = forward_fast(ctx, m, g, kv, tree, ws, L, hs, ro, sync, st);
-    if (s != SPECASR_OK) return s;
-  } else
-    forward_generic(ctx, m, g, kv, tree, ws, L, ro, st);
+  StepMeta m = device_meta(ctx, ws, L, hs);
+  const specasr_status s = ctx->fast && (m.rows <= 64 || wide_ws) ? forward_fast(ctx, m, g, kv, tree, ws, L, hs, ro, sync, st)
+                                                                   : forward_generic(ctx, m, g, kv, tree, ws, L, hs, ro, st);
+  if (s != SPECASR_OK) return s;
   HIP_TRY(ctx, hipGetLastError());
   return SPECASR_OK;
 }
@@ -971,6 +989,16 @@ specasr_status build_packed(specasr_ctx *ctx) {
     ctx->wide_part_floats = wb;
   }
   ctx->fast = true;
+  return SPECASR_OK;
+}
+
+// Metadata of an acceptance call.  One sequence: it stays in pinned memory, where the one wavefront that needs it reads
+// it once (a copy to the device is a launch of its own).  Several: copied, all workgroups of the argmax look their row up.
+specasr_status accept_meta(specasr_ctx *ctx, HostStep &hs, char *ws, const WsLayout &L, StepMeta *m, hipStream_t st) {
+  const specasr_status s = stage_meta(ctx, hs);
+  if (s != SPECASR_OK) return s;
+  *m = hs.batch == 1 ? meta_at(ctx, hs.staged->dev, hs) : device_meta(ctx, ws, L, hs);
+  if (hs.batch > 1) HIP_TRY(ctx, hipMemcpyAsync(ws + L.meta, hs.staged->host, hs.words.size() * 4, hipMemcpyHostToDevice, st));
   return SPECASR_OK;
 }
 
@@ -1182,7 +1210,7 @@ specasr_status specasr_tree_forward(specasr_ctx *ctx, specasr_kv *kv, const spec
     char *wl = wide ? wide_ws : lanes.wsp(gi);
     HostStep hs;
     build_step(ctx, &grp.tree, grp.kv.batch, grp.kv.kv_len, &hs);
-    s = upload_meta(ctx, hs, wl, Lg, lanes.stream(gi));
+    s = stage_meta(ctx, hs);
     if (s != SPECASR_OK) return s;
     ReadOut ro;
     ro.argmax = argmax_dev + grp.s0 * MN;
@@ -1219,7 +1247,7 @@ specasr_status specasr_tree_forward_top2(specasr_ctx *ctx, specasr_kv *kv, const
     char *wl = wide ? wide_ws : lanes.wsp(gi);
     HostStep hs;
     build_step(ctx, &grp.tree, grp.kv.batch, grp.kv.kv_len, &hs);
-    s = upload_meta(ctx, hs, wl, Lg, lanes.stream(gi));
+    s = stage_meta(ctx, hs);
     if (s != SPECASR_OK) return s;
     ReadOut ro;
     ro.top2 = top2_dev + grp.s0 * MN * 2;
@@ -1330,7 +1358,7 @@ specasr_status specasr_prefill(specasr_ctx *ctx, specasr_kv *kv, const int32_t *
       specasr_tree tv{toks.data(), wide_parents.data(), wide_n.data(), emb, use_embed ? use_embed + at : nullptr};
       HostStep hs;
       build_step(ctx, &tv, pieces, wide_kv.data(), &hs);
-      s = upload_meta(ctx, hs, wide_ws, LW, st);
+      s = stage_meta(ctx, hs);
       if (s != SPECASR_OK) return s;
       ReadOut ro;
       const bool last = it.c0 + it.n == n_pos[b];
@@ -1353,7 +1381,7 @@ specasr_status specasr_prefill(specasr_ctx *ctx, specasr_kv *kv, const int32_t *
       hipStream_t sl = pipelined ? lanes.stream(ci) : st;
       HostStep hs;
       build_step(ctx, &tv, 1, kvv.kv_len, &hs);
-      s = upload_meta(ctx, hs, wl, L, sl);
+      s = stage_meta(ctx, hs);
       if (s != SPECASR_OK) return s;
       ReadOut ro;
       if (last && next_token) ro.argmax = argmax_dev + (size_t)b * c.max_nodes;
@@ -1408,12 +1436,12 @@ specasr_status specasr_accept(specasr_ctx *ctx, const specasr_tree *tree, int32_
   const WsLayout L = ws_layout(ctx, batch);
   HostStep hs;
   build_step(ctx, tree, batch, nullptr, &hs);
-  s = upload_meta(ctx, hs, ws, L, st);
+  StepMeta m;
+  s = accept_meta(ctx, hs, ws, L, &m, st);
   if (s != SPECASR_OK) return s;
-  StepMeta m = device_meta(ctx, ws, L, batch, hs);
   launch_accept(m, ctx->cfg.max_nodes, argmax_dev, path_dev, accept_len_dev, next_token_dev, st);
   HIP_TRY(ctx, hipGetLastError());
-  return SPECASR_OK;
+  return staged(ctx, hs, st);
 }
 
 specasr_status specasr_accept_from_logits(specasr_ctx *ctx, const specasr_tree *tree,
@@ -1432,14 +1460,14 @@ specasr_status specasr_accept_from_logits(specasr_ctx *ctx, const specasr_tree *
   const WsLayout L = ws_layout(ctx, batch);
   HostStep hs;
   build_step(ctx, tree, batch, nullptr, &hs);
-  s = upload_meta(ctx, hs, ws, L, st);
+  StepMeta m;
+  s = accept_meta(ctx, hs, ws, L, &m, st);
   if (s != SPECASR_OK) return s;
-  StepMeta m = device_meta(ctx, ws, L, batch, hs);
   // piece records in the read-out scratch: 2 floats per 4096 ids of a row, where 3 per 1024 are held
   launch_argmax_accept(m, logits_dev, ctx->cfg.max_nodes, ctx->cfg.vocab, (float *)(ws + L.top2_v), argmax_dev, path_dev,
                        accept_len_dev, next_token_dev, st);
   HIP_TRY(ctx, hipGetLastError());
-  return SPECASR_OK;
+  return staged(ctx, hs, st);
 }
 
 specasr_status specasr_commit(specasr_ctx *ctx, specasr_kv *kv, const int32_t *n_nodes,
@@ -1523,23 +1551,23 @@ specasr_status specasr_verify_tree(specasr_ctx *ctx, specasr_kv *kv, const speca
     hipStream_t sl = lanes.stream(gi);
     HostStep hs;
     build_step(ctx, &grp.tree, grp.kv.batch, grp.kv.kv_len, &hs);
-    s = upload_meta(ctx, hs, wl, Lg, sl);
+    s = stage_meta(ctx, hs);
     if (s != SPECASR_OK) return s;
     ReadOut ro;
     ro.argmax = argmax_dev + grp.s0 * MN;
     ro.logits = out->logits ? out->logits + grp.s0 * MN * c.vocab : nullptr;
     s = forward_common(ctx, &grp.kv, &grp.tree, ro, wl, Lg, hs, sl, LayerSync(), wide);
     if (s != SPECASR_OK) return s;
-    StepMeta m = device_meta(ctx, wl, Lg, grp.kv.batch, hs);
+    StepMeta m = device_meta(ctx, wl, Lg, hs);
     KvGeom g{kv->capacity, c.n_layers, c.n_kv_heads, c.head_dim};
-    launch_accept(m, c.max_nodes, argmax_dev + grp.s0 * MN, path_dev + grp.s0 * MN, len_dev + grp.s0, next_dev + grp.s0, sl);
+    int32_t *h = ctx->out_dev;  // laid out as the result block of the workspace
+    const AcceptMirror host{h + grp.s0 * MN, h + BN + grp.s0 * MN, h + 2 * BN + grp.s0, h + 2 * BN + B + grp.s0};
+    launch_accept(m, c.max_nodes, argmax_dev + grp.s0 * MN, path_dev + grp.s0 * MN, len_dev + grp.s0, next_dev + grp.s0, sl, host);
     launch_compact(c.dtype, g, grp.kv.batch, c.max_nodes, m.kv_len, path_dev + grp.s0 * MN, len_dev + grp.s0, grp.kv.k, grp.kv.v, sl);
     HIP_TRY(ctx, hipGetLastError());
   }
   s = lanes.end();
   if (s != SPECASR_OK) return s;
-  const size_t words = 2 * BN + 2 * (size_t)B;
-  HIP_TRY(ctx, hipMemcpyAsync(ctx->out_host, o, words * 4, hipMemcpyDeviceToHost, st));
   const auto t_enqueued = std::chrono::steady_clock::now();
   HIP_TRY(ctx, hipStreamSynchronize(st));
   if (debug_timing) {  // host time spent enqueueing the step vs waiting for the GPU to finish it

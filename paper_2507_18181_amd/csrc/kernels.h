@@ -12,10 +12,19 @@ struct ModelDims {
 };
 
 // ---- dtype-generic stages (fp32 arithmetic on fp32 activations) ----------
-// x[row][:] = tok_embed[token[row]][:]  (or the caller's embedding row), and the rope table
-// cs[row][j] = (cos, sin)(pos[row] * theta^(-2j/hd)), computed in fp64
-void launch_embed_rope(const StepMeta &m, int dtype, const void *tok_embed, const void *input_embeds, int max_nodes, int d, float *x,
-                       int hd, float theta, float2 *cs, hipStream_t st);
+// Start of a forward: x[row][:] = tok_embed[token[row]][:] (or the caller's embedding row); the rope table
+// cs[row][j] = (cos, sin)(pos[row] * theta^(-2j/hd)), computed in fp64; the metadata block words -> dst; and with pl (bf16
+// models) the planes of x * gain with the sums of squares per 32 columns.  hm: the metadata in pinned host memory, as
+// the device sees it.
+struct BeginPlanes {
+  const uint16_t *gain;
+  uint16_t *hb, *hb_lo;
+  int nb;
+  float *ssq;
+  int n_slab;
+};
+void launch_begin(const StepMeta &hm, int dtype, const void *tok_embed, const void *input_embeds, int max_nodes, int d, float *x, int hd,
+                  float theta, float2 *cs, const BeginPlanes *pl, const int32_t *words, int32_t *dst, int n_words, hipStream_t st);
 // Input of the linears below: residual rows x [rows][d] that are normalised first, x * rsqrt(mean(x^2)+eps) * gain, either
 // by the linear itself or (wide rows) into the scratch rows h
 struct NormIn {
@@ -59,9 +68,13 @@ void launch_top2(const StepMeta &m, const float *src, bool from_partials, int n_
                  float *prob, int32_t *argmax, hipStream_t st);
 
 // ---- integer stages --------------------------------------------------------
-// greedy acceptance, one wavefront per sequence; argmax in [batch][max_nodes] layout
+// greedy acceptance, one wavefront per sequence; argmax in [batch][max_nodes] layout.  The results also go to `host`
+// (pinned memory, as the device sees it), if given, so that no copy has to bring them there.
+struct AcceptMirror {
+  int32_t *argmax = nullptr, *path = nullptr, *accept_len = nullptr, *next_token = nullptr;
+};
 void launch_accept(const StepMeta &m, int max_nodes, const int32_t *argmax, int32_t *path,
-                   int32_t *accept_len, int32_t *next_token, hipStream_t st);
+                   int32_t *accept_len, int32_t *next_token, hipStream_t st, const AcceptMirror &host = AcceptMirror());
 // argmax of the caller's padded logits ([batch][max_nodes][V]), then the acceptance above.  rec: rows *
 // argmax_pieces(V) pairs of floats.
 int argmax_pieces(int V);

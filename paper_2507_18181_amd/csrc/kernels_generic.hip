@@ -6,38 +6,95 @@
 
 namespace specasr {
 
-// --------------------------------------------------------------------------- embedding gather, rope table
-// Both start a forward and depend on nothing but the metadata, so they share a launch: blocks 0 .. rows-1 copy an
-// embedding row each, the blocks behind them fill the table.
+// 4 consecutive elements
+template <class T> struct Vec4;
+template <> struct Vec4<float> {
+  static __device__ __forceinline__ void load(const float *p, float w[4]) {
+    float4 v = *reinterpret_cast<const float4 *>(p);
+    w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+  }
+};
+template <> struct Vec4<bf16_t> {
+  static __device__ __forceinline__ void load(const bf16_t *p, float w[4]) {
+    uint2 v = *reinterpret_cast<const uint2 *>(p);
+    w[0] = __uint_as_float(v.x << 16); w[1] = __uint_as_float(v.x & 0xffff0000u);
+    w[2] = __uint_as_float(v.y << 16); w[3] = __uint_as_float(v.y & 0xffff0000u);
+  }
+};
+
+// --------------------------------------------------------------------------- the start of a forward
+// One launch for what depends on nothing but the call's metadata, which it reads in pinned host memory (`m` points there):
+// blocks 0 .. rows-1 fetch an embedding row each, the next ones fill the rope table, the last ones copy the metadata block
+// to the device for all later kernels.  PLANES (MFMA path): an embedding row leaves as residual_gain_kernel would
+// leave it, x * gain in two planes and one sum of squares per 32 columns.  Bound by one read across PCIe and one of
+// the table: 7B, 32 rows copy 4.5 + embed 9.9 + rope 3.5 + residual_gain 4.9 us before.
 // Sec. II-B: a tree node is verified as if decoded after its own branch, so its rotary
 // position is kv_len + depth, shared by siblings.  Angles are formed in fp64 once per call.
-template <class T>
-__global__ __launch_bounds__(256) void embed_rope_kernel(StepMeta m, const T *E, const T *in_emb, int max_nodes, int d, float *x, int half, int hd,
-                                                         double theta, float2 *cs) {
-  if ((int)blockIdx.x >= m.rows) {
-    const int idx = ((int)blockIdx.x - m.rows) * 256 + threadIdx.x;
+template <class T, bool PLANES>
+__global__ __launch_bounds__(256) void begin_kernel(StepMeta m, const T *E, const T *in_emb, int vec, int max_nodes, int d, float *x, int half, int hd,
+                                                    double theta, float2 *cs, int rope_blocks, BeginPlanes pl, const int32_t *words, int32_t *dst, int n_words) {
+  const int r = blockIdx.x;
+  if (r >= m.rows + rope_blocks) {
+    const int i0 = (r - m.rows - rope_blocks) * 1024 + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i0 + i * 256 < n_words) dst[i0 + i * 256] = words[i0 + i * 256];
+    return;
+  }
+  if (r >= m.rows) {
+    const int idx = (r - m.rows) * 256 + threadIdx.x;
     if (idx >= m.rows * half) return;
-    const int r = idx / half, j = idx - r * half;
-    const double ang = (double)m.pos[r] * pow(theta, -2.0 * (double)j / (double)hd);
+    const int row = idx / half, j = idx - row * half;
+    const double ang = (double)m.pos[row] * pow(theta, -2.0 * (double)j / (double)hd);
     cs[idx] = make_float2((float)cos(ang), (float)sin(ang));
     return;
   }
-  const int r = blockIdx.x;
   const T *src;
   if (in_emb != nullptr && m.use_embed[r])
     src = in_emb + ((int64_t)m.seq[r] * max_nodes + m.node[r]) * d;
   else
     src = E + (int64_t)m.token[r] * d;
-  for (int c = threadIdx.x; c < d; c += 256) x[(int64_t)r * d + c] = to_f32(src[c]);
+  for (int c0 = 0; c0 < d; c0 += 1024) {
+    const int c = c0 + threadIdx.x * 4;
+    const bool ok = c < d;  // d is a multiple of 8
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (ok) {
+      if (vec) {
+        Vec4<T>::load(src + c, v);
+      } else {  // a table that is not on 4 elements (a caller's slice)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = to_f32(src[c + i]);
+      }
+      *reinterpret_cast<float4 *>(x + (int64_t)r * d + c) = make_float4(v[0], v[1], v[2], v[3]);
+    }
+    if (PLANES) {
+      float ss = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+      ss += __shfl_xor(ss, 1, 64);
+      ss += __shfl_xor(ss, 2, 64);
+      ss += __shfl_xor(ss, 4, 64);
+      if (ok) {
+        if ((threadIdx.x & 7) == 0) pl.ssq[(int64_t)r * pl.n_slab + (c >> 5)] = ss;
+        const uint2 g = *reinterpret_cast<const uint2 *>(pl.gain + c);
+        const float y[4] = {v[0] * bf16_bits_to_f32(g.x & 0xffffu), v[1] * bf16_bits_to_f32(g.x >> 16),
+                            v[2] * bf16_bits_to_f32(g.y & 0xffffu), v[3] * bf16_bits_to_f32(g.y >> 16)};
+        store_planes4(y, pl.hb, pl.hb_lo, packed_act_offset(r, c, pl.nb));
+      }
+    }
+  }
 }
 
-void launch_embed_rope(const StepMeta &m, int dtype, const void *E, const void *in_emb, int max_nodes, int d, float *x, int hd,
-                       float theta, float2 *cs, hipStream_t st) {
-  const int half = hd / 2, blocks = m.rows + (m.rows * half + 255) / 256;
-  if (dtype == 1)
-    embed_rope_kernel<bf16_t><<<blocks, 256, 0, st>>>(m, (const bf16_t *)E, (const bf16_t *)in_emb, max_nodes, d, x, half, hd, (double)theta, cs);
+void launch_begin(const StepMeta &hm, int dtype, const void *E, const void *in_emb, int max_nodes, int d, float *x, int hd, float theta,
+                  float2 *cs, const BeginPlanes *pl, const int32_t *words, int32_t *dst, int n_words, hipStream_t st) {
+  const int half = hd / 2, rope_blocks = (hm.rows * half + 255) / 256, blocks = hm.rows + rope_blocks + (n_words + 1023) / 1024;
+  const size_t esz = dtype == 1 ? 2 : 4;
+  const int vec = (((uintptr_t)E | (uintptr_t)in_emb) & (4 * esz - 1)) == 0;
+  const BeginPlanes none{};
+  if (pl != nullptr)
+    begin_kernel<bf16_t, true><<<blocks, 256, 0, st>>>(hm, (const bf16_t *)E, (const bf16_t *)in_emb, vec, max_nodes, d, x, half, hd, (double)theta, cs, rope_blocks, *pl, words, dst, n_words);
+  else if (dtype == 1)
+    begin_kernel<bf16_t, false><<<blocks, 256, 0, st>>>(hm, (const bf16_t *)E, (const bf16_t *)in_emb, vec, max_nodes, d, x, half, hd, (double)theta, cs, rope_blocks, none, words, dst, n_words);
   else
-    embed_rope_kernel<float><<<blocks, 256, 0, st>>>(m, (const float *)E, (const float *)in_emb, max_nodes, d, x, half, hd, (double)theta, cs);
+    begin_kernel<float, false><<<blocks, 256, 0, st>>>(hm, (const float *)E, (const float *)in_emb, vec, max_nodes, d, x, half, hd, (double)theta, cs, rope_blocks, none, words, dst, n_words);
 }
 
 // --------------------------------------------------------------------------- RMSNorm
@@ -61,21 +118,6 @@ __global__ void rmsnorm_kernel(const float *x, const T *g, int d, float eps, flo
 // whose wavefronts own the two halves of a rotary pair, rotate it and write k and v to the cache; the logits go to the
 // caller's array; and up to kNormWidth input features a workgroup normalises its 8 rows itself, in LDS.  Bound by the
 // chain of launches, about 7 us each: tiny fp32 step of 8 nodes 178 -> 148 us (15 launches for 24).
-template <class T> struct Vec4;
-template <> struct Vec4<float> {
-  static __device__ __forceinline__ void load(const float *p, float w[4]) {
-    float4 v = *reinterpret_cast<const float4 *>(p);
-    w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
-  }
-};
-template <> struct Vec4<bf16_t> {
-  static __device__ __forceinline__ void load(const bf16_t *p, float w[4]) {
-    uint2 v = *reinterpret_cast<const uint2 *>(p);
-    w[0] = __uint_as_float(v.x << 16); w[1] = __uint_as_float(v.x & 0xffff0000u);
-    w[2] = __uint_as_float(v.y << 16); w[3] = __uint_as_float(v.y & 0xffff0000u);
-  }
-};
-
 // Sums 16 values over the 64 lanes; every lane returns the sum of value 8*b5 + 4*b4 + 2*b3 + b2 (bits of its
 // index).
 __device__ __forceinline__ float wave_sum16(float (&v)[16], int lane) {
@@ -448,7 +490,7 @@ __global__ __launch_bounds__(256) void argmax_pieces_kernel(StepMeta m, const fl
   __shared__ float bv[4];
   __shared__ int bi[4];
   const int r = blockIdx.x / (uint32_t)pieces, t0 = (blockIdx.x - r * pieces) * kArgmaxPiece;
-  const float *row = logits + (int64_t)(m.seq[r] * max_nodes + m.node[r]) * V;
+  const float *row = logits + (int64_t)(m.batch == 1 ? r : m.seq[r] * max_nodes + m.node[r]) * V;
   float best = -INFINITY;
   int besti = 0x7fffffff;
   auto take = [&](float v, int t) {
@@ -638,9 +680,9 @@ void launch_top2(const StepMeta &m, const float *src, bool from_partials, int n_
 template <bool PIECES>
 __global__ __launch_bounds__(64) void accept_kernel(StepMeta m, int max_nodes, const int32_t *argmax,
                                                     int32_t *argmax_out, const float2 *rec, int pieces, int32_t *path,
-                                                    int32_t *accept_len, int32_t *next_token) {
+                                                    int32_t *accept_len, int32_t *next_token, AcceptMirror host) {
   const int s = blockIdx.x, lane = threadIdx.x;
-  const int n = m.n_nodes[s], r0 = m.row_start[s];
+  const int n = m.seq_n_nodes(s), r0 = m.seq_row_start(s);
   bool matched = false;
   uint64_t anc = 0;
   int depth = 0, par = 0, tok = 0, mine = 0;
@@ -675,26 +717,33 @@ __global__ __launch_bounds__(64) void accept_kernel(StepMeta m, int max_nodes, c
   const int win = 63 - (key & 63);
   const uint64_t wanc = __shfl(anc, win, 64);
   const int wdepth = key >> 6;
-  int32_t *p = path + (int64_t)s * max_nodes;
-  if (lane < max_nodes && lane > wdepth) p[lane] = -1;
-  if (lane < n && ((wanc >> lane) & 1ull)) p[depth] = lane;
   const int next = __shfl(mine, win, 64);
-  if (lane == 0) {
-    accept_len[s] = wdepth + 1;
-    next_token[s] = next;
+  auto write = [&](int32_t *path_, int32_t *len_, int32_t *next_) {
+    int32_t *p = path_ + (int64_t)s * max_nodes;
+    if (lane < max_nodes && lane > wdepth) p[lane] = -1;
+    if (lane < n && ((wanc >> lane) & 1ull)) p[depth] = lane;
+    if (lane == 0) {
+      len_[s] = wdepth + 1;
+      next_[s] = next;
+    }
+  };
+  write(path, accept_len, next_token);
+  if (host.path != nullptr) {
+    write(host.path, host.accept_len, host.next_token);
+    if (lane < n) host.argmax[(int64_t)s * max_nodes + lane] = mine;
   }
 }
 
 void launch_accept(const StepMeta &m, int max_nodes, const int32_t *argmax, int32_t *path,
-                   int32_t *accept_len, int32_t *next_token, hipStream_t st) {
-  accept_kernel<false><<<m.batch, 64, 0, st>>>(m, max_nodes, argmax, nullptr, nullptr, 0, path, accept_len, next_token);
+                   int32_t *accept_len, int32_t *next_token, hipStream_t st, const AcceptMirror &host) {
+  accept_kernel<false><<<m.batch, 64, 0, st>>>(m, max_nodes, argmax, nullptr, nullptr, 0, path, accept_len, next_token, host);
 }
 
 void launch_argmax_accept(const StepMeta &m, const float *logits, int max_nodes, int V, float *rec, int32_t *argmax,
                           int32_t *path, int32_t *accept_len, int32_t *next_token, hipStream_t st) {
   const int pieces = argmax_pieces(V);
   argmax_pieces_kernel<<<(unsigned)m.rows * pieces, 256, 0, st>>>(m, logits, max_nodes, V, pieces, (float2 *)rec);
-  accept_kernel<true><<<m.batch, 64, 0, st>>>(m, max_nodes, nullptr, argmax, (const float2 *)rec, pieces, path, accept_len, next_token);
+  accept_kernel<true><<<m.batch, 64, 0, st>>>(m, max_nodes, nullptr, argmax, (const float2 *)rec, pieces, path, accept_len, next_token, AcceptMirror{});
 }
 
 // --------------------------------------------------------------------------- KV compaction

@@ -51,7 +51,7 @@ class Verifier:
         self.v = torch.zeros(shape, dtype=self.tdtype, device=self.device)
         self.kv_len = np.zeros(max_batch, np.int32)
         self._kv = B.make_kv(self.k, self.v, capacity, self.kv_len)
-        self._accept_init = {}  # batch size -> initial values of the acceptance outputs
+        self._accept_init = {}  # batch size -> buffers of accept()
 
     def close(self):
         if self.ctx is not None:
@@ -91,8 +91,10 @@ class Verifier:
         for b in range(nb):
             n = len(tokens[b])
             nn[b] = n
-            tok[b, :min(n, self.max_nodes)] = np.asarray(tokens[b], np.int32)[:self.max_nodes]
-            par[b, :min(n, self.max_nodes)] = np.asarray(parents[b], np.int32)[:self.max_nodes]
+            if n > self.max_nodes:  # refused by the library
+                n = self.max_nodes
+            tok[b, :n] = np.asarray(tokens[b], np.int32)[:n]
+            par[b, :n] = np.asarray(parents[b], np.int32)[:n]
         ue = None
         if use_embed is not None:
             ue = np.zeros((nb, self.max_nodes), np.uint8)
@@ -173,25 +175,26 @@ class Verifier:
     def accept(self, tokens, parents, argmax_dev=None, logits_dev=None, stream=None):
         nb = len(tokens)
         tree, keep = self._tree(tokens, parents)
-        # path | accept_len | next_token | argmax in one buffer: one fill (a copy of the values that tell an
-        # untouched output) and one copy to the host
+        # path | accept_len | next_token in pinned memory that the kernel writes itself: no fill and no copy on the device
         n = nb * self.max_nodes
         if nb not in self._accept_init:
-            self._accept_init[nb] = torch.cat([torch.full((n,), -7, dtype=torch.int32), torch.zeros(2 * nb, dtype=torch.int32),
-                                               torch.full((n,), -1, dtype=torch.int32)]).to(self.device)
-        buf = self._accept_init[nb].clone()
-        path, alen, nxt = buf[:n], buf[n:n + nb], buf[n + nb:n + 2 * nb]
+            pinned = torch.empty(n + 2 * nb, dtype=torch.int32, pin_memory=self.device.type == "cuda")
+            untouched = torch.full((nb, self.max_nodes), -1, dtype=torch.int32, device=self.device)
+            self._accept_init[nb] = untouched, pinned.numpy(), pinned[:n], pinned[n:n + nb], pinned[n + nb:]
+        untouched, host, path, alen, nxt = self._accept_init[nb]
+        host[:n] = -7  # the values that tell an untouched output
+        host[n:] = 0
         if logits_dev is not None:
-            argmax_dev = buf[n + 2 * nb:].view(nb, self.max_nodes)
+            argmax_dev = untouched.clone()
             rc = B.specasr_accept_from_logits(self.ctx, tree, nb, logits_dev, argmax_dev, path,
                                               alen, nxt, self.ws_ptr, self.ws_bytes, stream)
         else:
             rc = B.specasr_accept(self.ctx, tree, nb, argmax_dev, path, alen, nxt, self.ws_ptr,
                                   self.ws_bytes, stream)
         torch.cuda.synchronize()
-        host = buf[:n + 2 * nb].cpu().numpy()
-        return dict(status=rc, argmax=argmax_dev, path=host[:n].reshape(nb, self.max_nodes),
-                    accept_len=host[n:n + nb], next_token=host[n + nb:])
+        out = host.copy()
+        return dict(status=rc, argmax=argmax_dev, path=out[:n].reshape(nb, self.max_nodes),
+                    accept_len=out[n:n + nb], next_token=out[n + nb:])
 
     def commit(self, n_nodes, paths, stream=None):
         nb = self.batch
