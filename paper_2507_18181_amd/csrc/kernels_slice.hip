@@ -43,7 +43,7 @@ constexpr int slice_regs(int stages, int accs) {
 }
 template <int EPI, int HB, int NC>
 constexpr int slice_depth() {
-  constexpr int accs = EPI != kSliceQkv ? 1 : NC ? 3 : 2;
+  constexpr int accs = EPI == kSliceQkv ? 3 : 1;
   return slice_regs<EPI, HB, NC>(8, accs) <= 250 ? 8 : slice_regs<EPI, HB, NC>(4, accs) <= 250 ? 4 : 2;
 }
 // Accumulators per tile: what rounds is mostly the fp32 addition chain, one step per 8 products, so it is
@@ -55,7 +55,8 @@ constexpr int slice_depth() {
 template <int EPI, int HB, int NC>
 constexpr int slice_accs() {
   constexpr int D = slice_depth<EPI, HB, NC>();
-  if (NC == 0) return EPI == kSliceQkv || slice_regs<EPI, HB, NC>(D, 2) <= 250 ? 2 : 1;  // lo products have columns of their own
+  if (NC == 0)  // lo products have columns of their own; q|k|v with a ring of 8: both halves of a block and the sum
+    return EPI == kSliceQkv && D == 8 ? 3 : EPI == kSliceQkv || slice_regs<EPI, HB, NC>(D, 2) <= 250 ? 2 : 1;
   return EPI == kSliceQkv || slice_regs<EPI, HB, NC>(D, 3) <= 250 ? 3 : slice_regs<EPI, HB, NC>(D, 2) <= 250 ? 2 : 1;
 }
 // Output tiles summed through LDS at a time (1 KB per tile and wavefront, at most 128 KB).
@@ -157,15 +158,21 @@ __global__ __launch_bounds__(kSliceWaves * 64, 2) void gemm_slice_kernel(SliceAr
       for (int a = 0; a < HB; ++a)
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          f32x4 &z = acc[a][c][NA == 3 && h ? 2 : NA > 1 && D == 8 ? j >> 2 : 0];
+          f32x4 &z = acc[a][c][!BOTH && NA == 3 && h ? 2 : NA > 1 && D == 8 ? j >> 2 : 0];
           z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[j][a]), __builtin_bit_cast(bf16x8, xb[j][h][c]), z, 0, 0, 0);
         }
-    if (NA > 1 && D < 8 && j == D - 1)
+    constexpr bool sum_of_halves = BOTH && NA == 3 && D == 8;
+    if (NA > 1 && (D < 8 || sum_of_halves) && j == D - 1)
 #pragma unroll
       for (int a = 0; a < HB; ++a)
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          acc[a][c][1] += acc[a][c][0];
+          if constexpr (sum_of_halves) {
+            acc[a][c][2] += acc[a][c][0] + acc[a][c][1];
+            acc[a][c][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+          } else {
+            acc[a][c][1] += acc[a][c][0];
+          }
           acc[a][c][0] = (f32x4){0.f, 0.f, 0.f, 0.f};
         }
   };
