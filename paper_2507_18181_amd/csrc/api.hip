@@ -602,6 +602,8 @@ void gemm_stage(specasr_ctx *ctx, int stage, bool profiled_layer, const PackedMa
   }
   if (plan.mid.a > 0)
     launch_gemm_mid(W, Xp, rows, part, plan.mid, swiglu_nrm, t, t_lo, st, ev0, ev1);
+  else if (plan.pair > 0)
+    launch_gemm_wide_pair(W, Xp, rows, plan.pair, *swiglu_nrm, t, t_lo, st, ev0, ev1);
   else if (swiglu_nrm)
     launch_gemm_wide_swiglu(W, Xp, rows, *swiglu_nrm, t, t_lo, st, ev0, ev1);
   else if (plan.wide)
@@ -681,9 +683,13 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       // (An unsplit tiled gate|up finishes SwiGLU itself, but the split count stays the planner's: taken unsplit for that
       // alone, the fp32 addition chain doubles or triples and the feed-forward part is 0.8 % (1.1B, 1024 rows) to 1.9 % (13B)
       // further from the 64-bit result.  Prefill of 810: 7B 23.5 ms unsplit, 24.3 split; 700: 2.99 / 2.89 per 4 layers.)
+      if (i == 2) pls[i]->pair = plan_wide_pair(pm[i]->n_bands, pm[i]->ksteps, R, pls[i]->n_splits, ctx->n_cu);
+      // (against the tiled kernel alone: where the small tiles win, k in 4 or 8 slices keeps the feed-forward part closer to
+      // the 64-bit result than k in halves, 1.1B 768 rows 0.3 %)
       const MidPlan mp = plan_mid(pm[i]->n_bands, pm[i]->ksteps, R, wide_gemm_estimate(pm[i]->n_bands, pm[i]->ksteps, R, pls[i]->n_splits, i == 2, ctx->n_cu), i == 2, ctx->n_cu);
       if (mp.a == 0 || (size_t)mp.S * pm[i]->ldo * part_rows_pad(R) > ctx->wide_part_floats) continue;
       pls[i]->mid = mp;
+      pls[i]->pair = 0;
       pls[i]->n_splits = mp.S;
     }
   } else {
@@ -744,6 +750,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       int S = pls[i]->n_splits;
       if (sl[i]->hb) { snprintf(k, sizeof k, "slice %dx%d", sl[i]->hb, sl[i]->nc); S = sl[i]->S; }
       else if (pls[i]->mid.a) snprintf(k, sizeof k, "mid %dx%d", pls[i]->mid.a, pls[i]->mid.b);
+      else if (pls[i]->pair) snprintf(k, sizeof k, "pair %dx4", pls[i]->pair);
       else if (wide) snprintf(k, sizeof k, "wide");
       else snprintf(k, sizeof k, "skinny %d", pls[i]->lw);
       fprintf(stderr, "[specasr] plan %s rows=%d bands=%d ksteps=%d: %s, %d splits\n", nm[i], R, pm[i]->n_bands, pm[i]->ksteps, k, S);
@@ -801,7 +808,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
     if (sl_gu.hb) {
       sa.W = pk.gu.data; sa.X = hb; sa.n_half = F / 8; sa.ksteps = pk.gu.ksteps; sa.nrm = nrm_ffn; sa.t = tb; sa.t_lo = tb_lo;
       slice_stage(ctx, SPECASR_STAGE_GATE_UP, pl, kSliceSwiglu, sa, sl_gu, st);
-    } else if (pl_gu.mid.a > 0 || (wide && pl_gu.n_splits == 1)) {
+    } else if (pl_gu.mid.a > 0 || (wide && (pl_gu.n_splits == 1 || pl_gu.pair > 0))) {
       gemm_stage(ctx, SPECASR_STAGE_GATE_UP, pl, pk.gu, hb, R, part, pl_gu, st, &nrm_ffn, tb, tb_lo);
     } else {
       gemm_stage(ctx, SPECASR_STAGE_GATE_UP, pl, pk.gu, hb, R, part, pl_gu, st);

@@ -23,6 +23,7 @@ struct GemmPlan {
   int grid = 256;    // workgroups, a multiple of n_splits (one per compute unit)
   double cost_us = 0; // of the split kernel, as its planner estimates it (without launch)
   bool wide = false; // many rows: the tiled kernel (only n_splits applies) ...
+  int pair = 0;      // ... or, where > 0, the kernel with k halved inside the workgroup, this many bands each (gate|up)
   MidPlan mid;       // ... or, where mid.a > 0, the small-tile kernel (n_splits = mid.S)
 };
 
@@ -41,6 +42,10 @@ void launch_gemm_wide(const PackedMatrix &W, const uint16_t *Xp, int rows, float
                       int stage, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 void launch_gemm_wide_swiglu(const PackedMatrix &W, const uint16_t *Xp, int rows, const RowNorm &nrm, uint16_t *t,
                              uint16_t *t_lo, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// the same with k halved inside the workgroup, `bands` (8 or 10) per workgroup
+int plan_wide_pair(int n_bands, int ksteps, int rows, int splits, int n_cu);
+void launch_gemm_wide_pair(const PackedMatrix &W, const uint16_t *Xp, int rows, int bands, const RowNorm &nrm, uint16_t *t,
+                           uint16_t *t_lo, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // a few hundred rows (kernels_mid.hip)
 hipError_t gemm_mid_set_lds_limit();
 MidPlan plan_mid(int n_bands, int ksteps, int rows, double other_us, bool swiglu, int n_cu);

@@ -331,17 +331,10 @@ hipError_t gemm_skinny_set_lds_limit() {
 // wavefront (global_load_lds_dwordx4: lane l's 16 bytes land at base + 16 l -- no staging
 // registers, no LDS store instructions) and read back with conflict-free 16-byte LDS loads.
 // LDS holds a ring of 4 stages of one k-step each (8 weight tiles + 2 planes x 4 activation
-// tiles = 16 KB); the copies run 3 k-steps ahead of the MFMAs.  Per k-step: wait until this
-// wavefront's copies of the current stage have landed (vmcnt: the 8 copies of the two younger
-// stages may stay in flight) and its own LDS reads of the previous stage have returned, barrier
-// (now every wavefront's part of the current stage is there, and nobody reads the previous stage
-// any more), start the copies of k-step +3 into the previous stage's buffer, multiply.  A
-// wavefront owns 128 features x 64 rows: 4 + 2 x 2 operand tiles feed 16 MFMAs per k-step into 8
-// accumulator tiles (hi products first, then lo: 8 independent accumulators between two uses of
-// one).  The barrier is the bare s_barrier: __syncthreads would add a fence that waits for ALL
-// copies in flight.  Copies past the end of the k range are clamped to valid tiles and multiplied
-// by zero, so the number of copies in flight is the same in every iteration; before a wavefront
-// leaves the loop it waits for all of them (the LDS may be handed to another workgroup).
+// tiles = 16 KB); wide_loop below says how it turns.  A wavefront owns 128 features x 64 rows: 4 + 2 x 2 operand tiles
+// feed 16 MFMAs per k-step into 8 accumulator tiles (hi products first, then lo: 8 independent accumulators between two
+// uses of one).  With that loop, us before -> now: 7B 810 rows down 157 -> 143, o 63.5 -> 59, q|k|v 182 -> 175; 300 rows q|k|v
+// 105 -> 94; 400 rows down 86 -> 79; 1.1B 384 rows down 28.9 -> 27.4; two full rounds (7B gate|up, 640 rows) the same.
 // 64 KB LDS and < 256 registers let two workgroups share a compute unit.  Workgroups that share
 // a weight tile (the row tiles of one feature tile) get consecutive slots of one XCD.
 //   part[s][band][row][o % 32] as for the skinny kernel; nb = row groups of 32 in Xp, a multiple
@@ -354,6 +347,97 @@ constexpr int kWideStageTiles = kWideTileBands + 2 * kWideTileGroups;  // 1 KB t
 __device__ __forceinline__ void copy_tile_to_lds(const u32x4 *src_lane, u32x4 *dst_tile) {
   __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src_lane,
                                    (void __attribute__((address_space(3))) *)dst_tile, 16, 0, 0);
+}
+
+// The k loop of the two tiled kernels below: wavefront tile of a bands x b row groups, a ring of D LDS stages (s0 ..) of
+// one k-step.  src: what this wavefront copies per stage, 1 KB tiles [lane][16 bytes] at scalar bases, to tile slots dst; the
+// k-step adds a multiple of 1 KB (weights) or nb KB (activations).  The copies of the
+// D stages have been started for k-steps k0 .. k0 + D-1 before (wide_copy), this runs k-steps k0 .. k0 + n_steps - 1, of which
+// the last ones may lie past k1 (multiplied by zero, so that several wavefronts do the same number of steps).  Copies past
+// the end of k are clamped to valid tiles, so the number in flight is the same in every step.
+//
+// Between the hi and the lo products of a k-step stands the barrier that says: everybody's copies of the next stage have
+// landed (vmcnt: those of the younger stages may stay in flight), nobody reads this stage any more (lgkmcnt).  Behind it
+// this stage's buffer is filled for k-step + D, and w and xh are reloaded from the next stage one by one behind their
+// last use: LDS reads, copies and address arithmetic run under the products, without registers for prefetched operands.
+// (With wait, barrier, copies and all reads in front of the products of a step, 7B gate|up of 810 rows took 318 us, with
+// this order and 64-bit address products in vector registers 275, now 254.)  The barrier is the bare s_barrier:
+// __syncthreads would add a fence that waits for ALL copies in flight.
+struct WideCopy {
+  uint32_t ksteps, nb, lane16;
+};
+template <int C>
+__device__ __forceinline__ void wide_copy(const WideCopy &wc, const char *const (&src)[C], const bool (&weight)[C], const int (&dst)[C], u32x4 *buf, int i, uint32_t ks) {
+  const char *base = src[i] + ((uint64_t)ks * (weight[i] ? 1u : wc.nb) << 10);
+  copy_tile_to_lds(reinterpret_cast<const u32x4 *>(base + wc.lane16), buf + dst[i] * 64);
+}
+template <int a, int b, int C, int D, class S, class S3>
+__device__ __forceinline__ void wide_loop(f32x16 (&acc)[a][b], S &s0, S &s1, S &s2, S3 &s3, const WideCopy &wc, const char *const (&src)[C], const bool (&weight)[C],
+                                          const int (&dst)[C], int at_w, int at_h, int at_l, int k0, int k1, int n_full, int n_steps) {
+  static_assert(D == 3 || D == 4, "ring");
+  // s_waitcnt immediates of gfx9-class parts: vmcnt in bits 3:0 and 15:14, expcnt 6:4 (7: not waited for), lgkmcnt 11:8 (15: not)
+  constexpr int V = (D - 2) * C, V0 = (D - 1) * C;
+  constexpr int kNext = (V & 15) | ((V >> 4) << 14) | 0x0070, kFirst = (V0 & 15) | ((V0 >> 4) << 14) | 0x0F70;
+  bf16x8 w[a], xh[b], xl[b];
+  __builtin_amdgcn_s_waitcnt(kFirst);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");  // no LDS access may be scheduled above the barrier
+#pragma unroll
+  for (int i = 0; i < a; ++i) w[i] = __builtin_bit_cast(bf16x8, s0[at_w + i * 64]);
+#pragma unroll
+  for (int g = 0; g < b; ++g) xh[g] = __builtin_bit_cast(bf16x8, s0[at_h + g * 64]);
+  auto step = [&](u32x4 *cur, const u32x4 *next, int kt, auto live) {
+    const bool dead = !decltype(live)::value && kt >= k1;
+    const bf16x8 zero = __builtin_bit_cast(bf16x8, (u32x4){0u, 0u, 0u, 0u});
+    const uint32_t ks = min((uint32_t)(kt + D), wc.ksteps - 1);
+#pragma unroll
+    for (int i = 0; i < a; ++i) {
+#pragma unroll
+      for (int g = 0; g < b; ++g) acc[i][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[i], dead ? zero : xh[g], acc[i][g], 0, 0, 0);
+      if (i == 0) {
+#pragma unroll
+        for (int g = 0; g < b; ++g) xl[g] = __builtin_bit_cast(bf16x8, cur[at_l + g * 64]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(kNext);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < a; ++i) {
+#pragma unroll
+      for (int g = 0; g < b; ++g) acc[i][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[i], dead ? zero : xl[g], acc[i][g], 0, 0, 0);
+      if (i == 0)
+#pragma unroll
+        for (int g = 0; g < b; ++g) xh[g] = __builtin_bit_cast(bf16x8, next[at_h + g * 64]);
+      w[i] = __builtin_bit_cast(bf16x8, next[at_w + i * 64]);
+      if (i < C) wide_copy(wc, src, weight, dst, cur, i, ks);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = a; i < C; ++i) wide_copy(wc, src, weight, dst, cur, i, ks);
+  };
+  int t = 0;
+  for (; t + D <= n_full; t += D) {
+    step(s0, s1, k0 + t, std::true_type{});
+    step(s1, s2, k0 + t + 1, std::true_type{});
+    if constexpr (D == 3) {
+      step(s2, s0, k0 + t + 2, std::true_type{});
+    } else {
+      step(s2, s3, k0 + t + 2, std::true_type{});
+      step(s3, s0, k0 + t + 3, std::true_type{});
+    }
+  }
+  if (t < n_steps) step(s0, s1, k0 + t, std::false_type{});
+  if (t + 1 < n_steps) step(s1, s2, k0 + t + 1, std::false_type{});
+  if constexpr (D == 3) {
+    if (t + 2 < n_steps) step(s2, s0, k0 + t + 2, std::false_type{});
+  } else {
+    if (t + 2 < n_steps) step(s2, s3, k0 + t + 2, std::false_type{});
+    if (t + 3 < n_steps) step(s3, s0, k0 + t + 3, std::false_type{});
+  }
+  __builtin_amdgcn_s_waitcnt(0x0070);  // all copies and LDS reads: the LDS may be reused or handed to another workgroup
 }
 
 // SWIGLU (gate|up, unsplit): the epilogue is the finishing step instead.  gate and up rows are interleaved
@@ -381,29 +465,21 @@ __global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const u32x4 *__restri
   if (nt >= n_nt) return;
   const int k0 = (int)((int64_t)ksteps * s / S), k1 = (int)((int64_t)ksteps * (s + 1) / S);
   const int wn = wave & 1, wm = wave >> 1;
-  const int64_t x_plane = (int64_t)ksteps * nb * 64;
   // the 4 tiles this wavefront copies per stage: wavefronts 0, 1 the weight bands 4w .. 4w+3 (bands
   // past the matrix edge are clamped to the last one; their products are never stored), wavefronts
   // 2, 3 the activation tiles [plane][row group]
-  const u32x4 *src[4];
-  int64_t kstride[4];
+  const char *src[4];
+  bool weight[4];
+  int dst[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int ti = wave * 4 + i;
-    if (ti < kWideTileBands) {
-      src[i] = Wp + (int64_t)min(nt * kWideTileBands + ti, n_bands - 1) * ksteps * 64 + lane;
-      kstride[i] = 64;
-    } else {
-      const int tb = ti - kWideTileBands;
-      src[i] = Xp + (tb >> 2) * x_plane + (int64_t)(mt * kWideTileGroups + (tb & 3)) * 64 + lane;
-      kstride[i] = (int64_t)nb * 64;
-    }
+    const int ti = wave * 4 + i, tb = ti - kWideTileBands;
+    weight[i] = ti < kWideTileBands;
+    dst[i] = ti;
+    src[i] = weight[i] ? (const char *)(Wp + (int64_t)min(nt * kWideTileBands + ti, n_bands - 1) * ksteps * 64)
+                       : (const char *)(Xp + (tb >> 2) * ((int64_t)ksteps * nb * 64) + (int64_t)(mt * kWideTileGroups + (tb & 3)) * 64);
   }
-  auto issue = [&](u32x4 *buf, int kt) {
-    const int ks = min(kt, ksteps - 1);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) copy_tile_to_lds(src[i] + ks * kstride[i], buf + (wave * 4 + i) * 64);
-  };
+  const WideCopy wc{(uint32_t)ksteps, (uint32_t)nb, (uint32_t)lane * 16};
   f32x16 acc[4][2];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -411,38 +487,10 @@ __global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const u32x4 *__restri
     for (int g = 0; g < 2; ++g)
 #pragma unroll
       for (int j = 0; j < 16; ++j) acc[i][g][j] = 0.f;
-  auto compute = [&](const u32x4 *buf, bool live) {
-    const u32x4 z = (u32x4){0u, 0u, 0u, 0u};
-    bf16x8 a[4], bh[2], bl[2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = __builtin_bit_cast(bf16x8, buf[(4 * wn + i) * 64 + lane]);
+  for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      bh[g] = __builtin_bit_cast(bf16x8, live ? buf[(kWideTileBands + 2 * wm + g) * 64 + lane] : z);
-      bl[g] = __builtin_bit_cast(bf16x8, live ? buf[(kWideTileBands + kWideTileGroups + 2 * wm + g) * 64 + lane] : z);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int g = 0; g < 2; ++g) acc[i][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], bh[g], acc[i][g], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int g = 0; g < 2; ++g) acc[i][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], bl[g], acc[i][g], 0, 0, 0);
-  };
-  // s_waitcnt immediate of gfx9-class parts: vmcnt in bits 3:0 (and 15:14), expcnt 6:4, lgkmcnt 11:8
-  constexpr int kWaitCopies8Lds0 = 0x0078;  // vmcnt(8) lgkmcnt(0), expcnt untouched (7)
-  constexpr int kWaitCopies0 = 0x0F70;      // vmcnt(0)
-  auto step = [&](const u32x4 *cur, u32x4 *prev, int kt) {
-    __builtin_amdgcn_s_waitcnt(kWaitCopies8Lds0);
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");  // no LDS access of this step may be scheduled above the barrier
-    issue(prev, kt + 3);
-    compute(cur, kt < k1);
-  };
-  issue(s0, k0);
-  issue(s1, k0 + 1);
-  issue(s2, k0 + 2);
+    for (int i = 0; i < 4; ++i) wide_copy(wc, src, weight, dst, j == 0 ? s0 : j == 1 ? s1 : j == 2 ? s2 : s3, i, min(k0 + j, ksteps - 1));
   __shared__ float rms[SWIGLU ? 32 * kWideTileGroups : 1];
   if (SWIGLU) {  // 1 / rms of the tile's rows, two threads per row, while the first stages arrive
     const int rl = threadIdx.x >> 1;
@@ -452,13 +500,8 @@ __global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const u32x4 *__restri
     ss += __shfl_xor(ss, 1, 64);
     if ((threadIdx.x & 1) == 0) rms[rl] = 1.0f / sqrtf(ss / (float)sw.nrm.d + sw.nrm.eps);
   }
-  for (int kt = k0; kt < k1; kt += 4) {
-    step(s0, s3, kt);
-    step(s1, s0, kt + 1);
-    step(s2, s1, kt + 2);
-    step(s3, s2, kt + 3);
-  }
-  __builtin_amdgcn_s_waitcnt(kWaitCopies0);
+  wide_loop<4, 2, 4, 4>(acc, s0, s1, s2, s3, wc, src, weight, dst, 4 * wn * 64 + lane, (kWideTileBands + 2 * wm) * 64 + lane,
+                        (kWideTileBands + kWideTileGroups + 2 * wm) * 64 + lane, k0, k1, k1 - k0, k1 - k0);
   // C layout: register j of lane l = row l%32 of the group, output feature 8*(j/4) + 4*(l/32) + j%4
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -546,6 +589,166 @@ void launch_gemm_wide(const PackedMatrix &W, const uint16_t *Xp, int rows, float
     case 3: launch_gemm_wide_s<3>(W, Xp, rows, part, n_splits, st, ev0, ev1); break;
     default: launch_gemm_wide_s<4>(W, Xp, rows, part, n_splits, st, ev0, ev1); break;
   }
+}
+
+// --------------------------------------------------------------------------- wide gate|up, k halved inside the workgroup
+// gate|up for hundreds of rows where the tiled kernel above needs two k-splits to fill its rounds of workgroups: there the
+// fp32 partial sums of both (7B, 810 rows: 146 MB) are written, read again by a SwiGLU kernel, and cost as much as a
+// fifth of the products.  Here one workgroup of 8 wavefronts takes A bands x 4 row groups and ALL of k: wavefronts 0 .. 3
+// the first half, 4 .. 7 the second, each half with its own ring in LDS, so the addition chains are those of two
+// splits.  At the end the halves exchange half of their tiles through LDS, every wavefront finishes the tiles it
+// keeps, and SwiGLU happens in registers as in the tiled kernel.
+// What bounds it: MFMAs with random data run at a throttled 0.020 us each per SIMD (1.6 GHz; 10 bands 0.80 us per
+// step of both halves) and share power and L2 with the copies; measured 0.9.  10 bands: 5 x 2 tiles per wavefront, 160
+// accumulators, ring of 3 (of 4: 4 % slower); 8 bands: 4 x 2, ring of 4.
+// Measured, GEMM + SwiGLU kernel before -> this, us: 7B 320 rows 150 + 16 -> 125, 768 rows 258 + 29 -> 238, 810 rows 287 + 31 ->
+// 254; 13B 640 rows 325 + 36 -> 300, 810 rows 484 -> 396, 1024 rows 477 + 59 -> 457; 1.1B 810 rows 88 + 18 -> 72.  Prefill of
+// 810 positions, 7B: 23.8 -> 22.3 ms.
+constexpr int kPairGroups = 4;  // row groups per workgroup
+
+template <int A> struct PairShape {
+  static constexpr int D = A == 10 ? 3 : 4;                // ring stages of one k-step per half
+  static constexpr int tiles = A + 2 * kPairGroups;        // 1 KB tiles per stage and half
+  static constexpr int copies = (tiles + 3) / 4;           // per wavefront; surplus ones repeat the last tile
+};
+
+// grid 8 * per_xcd, block 512.  An XCD (workgroup index mod 8) owns a contiguous run of tiles, the row tiles of one
+// feature tile next to each other.
+template <int A>
+__global__ __launch_bounds__(512, 2) void gemm_wide_pair_kernel(const u32x4 *__restrict__ Wp, const u32x4 *__restrict__ Xp, int rows, int n_bands,
+                                                                int ksteps, int nb, int n_mt, int total, int per_xcd, WideSwiglu sw) {
+  constexpr int D = PairShape<A>::D, T = PairShape<A>::tiles, C = PairShape<A>::copies, B = kPairGroups, a = A / 2, b = B / 2;
+  static_assert(A % 2 == 0 && T % 2 == 0 && (D == 3 || D == 4), "wavefront grid 2 x 2, ring");
+  // separate arrays: the compiler can tell a copy into one from the reads of another
+  __shared__ u32x4 s0[2 * T * 64], s1[2 * T * 64], s2[2 * T * 64], s3[D > 3 ? 2 * T * 64 : 1];
+  __shared__ float rms[32 * B];
+  const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int half = wave8 >> 2, wave = wave8 & 3, wn = wave & 1, wm = wave >> 1;
+  const int slot = blockIdx.x >> 3, id = (blockIdx.x & 7) * per_xcd + slot;
+  if (slot >= per_xcd || id >= total) return;
+  const int mt = (uint32_t)id % (uint32_t)n_mt, nt = (uint32_t)id / (uint32_t)n_mt;
+  const int n_groups = (rows + 31) >> 5;
+  const int len = (ksteps + 1) / 2;                            // steps of the first half; the second has as many or one less
+  const int k0 = half * len, k1 = half ? ksteps : len;
+  // the tiles this wavefront copies per stage (bands and row groups past the edge repeat the last one, unused)
+  const char *src[C];
+  bool weight[C];
+  int dst[C];
+#pragma unroll
+  for (int i = 0; i < C; ++i) {
+    const int ti = min(wave * C + i, T - 1), plane = ti - A >= B, g = ti - A - plane * B;
+    weight[i] = ti < A;
+    dst[i] = half * T + ti;
+    src[i] = ti < A ? (const char *)(Wp + (int64_t)min(nt * A + ti, n_bands - 1) * ksteps * 64)
+                    : (const char *)(Xp + plane * ((int64_t)ksteps * nb * 64) + (int64_t)min(mt * B + g, n_groups - 1) * 64);
+  }
+  const WideCopy wc{(uint32_t)ksteps, (uint32_t)nb, (uint32_t)lane * 16};
+  f32x16 acc[a][b];
+#pragma unroll
+  for (int i = 0; i < a; ++i)
+#pragma unroll
+    for (int g = 0; g < b; ++g)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[i][g][j] = 0.f;
+#pragma unroll
+  for (int j = 0; j < D; ++j)
+#pragma unroll
+    for (int i = 0; i < C; ++i) wide_copy(wc, src, weight, dst, j == 0 ? s0 : j == 1 ? s1 : j == 2 ? s2 : s3, i, min(k0 + j, ksteps - 1));
+#pragma unroll
+  for (int r0 = 0; r0 < 32 * B; r0 += 64) {  // 1 / rms of the tile's rows, 8 threads per row, while the first stages arrive
+    const int rl = r0 + (threadIdx.x >> 3);
+    const float *sq = sw.nrm.ssq + (int64_t)min(mt * B * 32 + rl, rows - 1) * sw.nrm.n_slab;
+    float ss = 0.f;
+    for (int i = threadIdx.x & 7; i < sw.nrm.n_slab; i += 8) ss += sq[i];
+    ss += __shfl_xor(ss, 1, 64);
+    ss += __shfl_xor(ss, 2, 64);
+    ss += __shfl_xor(ss, 4, 64);
+    if ((threadIdx.x & 7) == 0) rms[rl] = 1.0f / sqrtf(ss / (float)sw.nrm.d + sw.nrm.eps);
+  }
+  const int at = half * T * 64 + lane;
+  wide_loop<a, b, C, D>(acc, s0, s1, s2, s3, wc, src, weight, dst, at + a * wn * 64, at + (A + b * wm) * 64, at + (A + B + b * wm) * 64, k0, k1, ksteps / 2, len);
+  __syncthreads();
+  // Tiles 0 .. H-1 of a wavefront's tile are finished by the first half, the others by the second: each gives the partner
+  // what it does not keep, HC tiles at a time (4 KB each in the ring's arrays).
+  constexpr int H = a * b / 2, TA = T / 2, FIT = TA * D / 8, HC = H < FIT ? H : FIT;
+  static_assert(HC > 0, "room for the exchange");
+  auto slot_of = [&](int w8, int i) -> float4 * {
+    const int q = w8 * HC + i, arr = q / TA, o = q - arr * TA;
+    return reinterpret_cast<float4 *>((arr == 0 ? s0 : arr == 1 ? s1 : arr == 2 ? s2 : s3) + o * 256);
+  };
+#pragma unroll
+  for (int t0 = 0; t0 < H; t0 += HC) {
+    if (t0) __syncthreads();
+#pragma unroll
+    for (int i = t0; i < H && i < t0 + HC; ++i) {
+      const f32x16 &lo = acc[i / b][i % b], &up = acc[(i + H) / b][(i + H) % b];
+      float4 *dst = slot_of(wave8, i - t0) + lane;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        dst[q * 64] = half ? make_float4(lo[4 * q], lo[4 * q + 1], lo[4 * q + 2], lo[4 * q + 3]) : make_float4(up[4 * q], up[4 * q + 1], up[4 * q + 2], up[4 * q + 3]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = t0; i < H && i < t0 + HC; ++i) {
+      const f32x16 &lo = acc[i / b][i % b], &up = acc[(i + H) / b][(i + H) % b];
+      const float4 *other = slot_of(wave8 ^ 4, i - t0) + lane;
+      float z[16];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 o = other[q * 64];
+        z[4 * q] = (half ? up[4 * q] : lo[4 * q]) + o.x;
+        z[4 * q + 1] = (half ? up[4 * q + 1] : lo[4 * q + 1]) + o.y;
+        z[4 * q + 2] = (half ? up[4 * q + 2] : lo[4 * q + 2]) + o.z;
+        z[4 * q + 3] = (half ? up[4 * q + 3] : lo[4 * q + 3]) + o.w;
+      }
+      // C layout: register j of lane l = row l%32 of the group, output feature 8*(j/4) + 4*(l/32) + j%4
+      const int ti = half ? i + H : i, band = nt * A + a * wn + ti / b, rl = (b * wm + ti % b) * 32 + (lane & 31), row = mt * B * 32 + rl;
+      if (band >= n_bands || row >= rows) continue;
+      const float rs = rms[rl];
+#pragma unroll
+      for (int q = 0; q < 4; q += 2) {
+        float y[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = swiglu_act(z[4 * q + e], z[4 * q + 4 + e], rs);
+        store_planes4(y, sw.t, sw.t_lo, packed_act_offset(row, band * 16 + 4 * q + 4 * (lane >> 5), nb));
+      }
+    }
+  }
+}
+
+// Bands per workgroup of the kernel above, or 0 where the tiled kernel (with `splits` k-splits and, if more than one, its
+// SwiGLU kernel) is estimated faster.  All in us, fitted to 7B, 13B and 1.1B at 128 ..
+// 1024 rows: 12 per launch; rounds of workgroups (one per compute unit) times half of the k-steps at 0.91 (10 bands) or 0.74
+// (8 bands); the tiled kernel 0.38 per k-step of the workgroups that follow one another on a compute unit, its SwiGLU
+// kernel 6 and 0.17 per MB of partial sums.  Measured, tiled kernel against this: 7B 256 rows 101 / 97, 512 rows 185 / 196,
+// 640 rows 240 / 220, 810 rows 297 / 254; 13B 810 rows 470 / 395; 1.1B 640 rows 57 / 55.  More than two splits stay with the
+// tiled kernel: their addition chains are shorter.
+int plan_wide_pair(int n_bands, int ksteps, int rows, int splits, int n_cu) {
+  const int64_t mt = wide_row_groups(rows) / kWideTileGroups;
+  auto rounds = [n_cu](int64_t wgs) { return (double)((wgs + n_cu - 1) / n_cu); };
+  const double out_mb = (double)n_bands * 32 * rows * 4e-6;
+  double limit = 12.0 + rounds((n_bands + kWideTileBands - 1) / kWideTileBands * mt * splits) * ksteps / splits * 0.38 + (splits > 1 ? 6.0 + 0.17 * splits * out_mb : 0.0);
+  limit *= 0.98;
+  if (splits > 2) return 0;
+  int best = 0;
+  for (const int a : {8, 10}) {
+    const double cost = 12.0 + rounds((n_bands + a - 1) / a * mt) * (ksteps / 2.0) * (a == 10 ? 0.91 : 0.74);
+    if (cost >= limit) continue;
+    limit = cost;
+    best = a;
+  }
+  return best;
+}
+
+void launch_gemm_wide_pair(const PackedMatrix &W, const uint16_t *Xp, int rows, int bands, const RowNorm &nrm, uint16_t *t, uint16_t *t_lo,
+                           hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  const int nb = wide_row_groups(rows), n_mt = nb / kPairGroups, total = n_mt * ((W.n_bands + bands - 1) / bands), per_xcd = (total + 7) / 8;
+  const WideSwiglu sw{nrm, t, t_lo};
+  const auto kernel = bands == 10 ? gemm_wide_pair_kernel<10> : gemm_wide_pair_kernel<8>;
+  if (ev0 != nullptr)
+    hipExtLaunchKernelGGL(kernel, dim3(8u * per_xcd), dim3(512), 0u, st, ev0, ev1, 0u, (const u32x4 *)W.data, (const u32x4 *)Xp, rows, W.n_bands, W.ksteps, nb, n_mt, total, per_xcd, sw);
+  else
+    kernel<<<8u * per_xcd, 512, 0, st>>>((const u32x4 *)W.data, (const u32x4 *)Xp, rows, W.n_bands, W.ksteps, nb, n_mt, total, per_xcd, sw);
 }
 
 // --------------------------------------------------------------------------- consumers of partial sums
