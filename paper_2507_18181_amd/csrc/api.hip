@@ -36,7 +36,7 @@ struct Staging {
 // offsets (in bytes) of the regions of a workspace sized for `rows_max` rows / `batch` sequences
 struct WsLayout {
   size_t meta, outs, rope, x, h, q, att, t, logits, top2_v, top2_i, total;
-  size_t hb, attb, tb, part, ssq, blk_val, blk_idx;  // bf16 activations and split-k partial sums (MFMA path)
+  size_t hb, attb, tb, part, ssq, blk;  // bf16 activations and split-k partial sums (MFMA path)
   size_t qb, attn_o, attn_ml;                   // MFMA attention: bf16 queries, per-chunk partial outputs
   size_t meta_words;
 };
@@ -254,8 +254,7 @@ WsLayout ws_layout(const specasr_ctx *ctx, int batch) {
   L.part = take(64 * ctx->part_floats * 4);  // [split][band][rows padded to 32 or 64][32]
   L.ssq = take(64 * (size_t)((c.d_model + 15) / 16) * 4);  // one per row and slab of 32, or of 16, columns
   const size_t nblk = (size_t)logits_argmax_blocks(c.vocab);
-  L.blk_val = take(R * nblk * 4);
-  L.blk_idx = take(R * nblk * 4);
+  L.blk = take(R * nblk * 8);
   L.qb = take(2 * R * dq * 2);
   const size_t mc = (size_t)tree_attention_max_chunks(c.n_kv_heads);
   L.attn_o = take(mc * R * dq * 4);
@@ -295,8 +294,7 @@ WsLayout ws_layout_wide(const specasr_ctx *ctx, int batch) {
   L.attn_ml = take(mc * R * c.n_heads * 2 * 4);
   // read-out of a wide verify / draft forward (a prefill pass has none)
   const size_t nblk = (size_t)logits_argmax_blocks(c.vocab);
-  L.blk_val = take(R * nblk * 4);
-  L.blk_idx = take(R * nblk * 4);
+  L.blk = take(R * nblk * 8);
   L.top2_v = take(R * (size_t)top2_blocks(c.vocab) * 3 * 4);
   L.top2_i = take(R * (size_t)top2_blocks(c.vocab) * 2 * 4);
   L.outs = take(R * 4);  // argmax of a prefill pass, [piece][max_nodes]
@@ -519,6 +517,8 @@ struct ReadOut {
   float *logits = nullptr;
   int32_t *top2 = nullptr;
   float *prob = nullptr;
+  // The MFMA path leaves the argmax in records for the acceptance kernel, which merges them and writes argmax.
+  bool records = false;
   // Read-out only for rows >= first_row (at most 64 of them): a prefill pass over several pieces
   // of one sequence wants the token after its last position, not a vocabulary row per position.
   int first_row = 0;
@@ -842,7 +842,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
                   (float *)(ws + L.top2_v), (int *)(ws + L.top2_i), ro.top2, ro.prob, argmax_dev, st);
     else
       launch_logits_argmax(ms, part, pls.n_splits, ctx->lm_head.ldo, nrs, V, ctx->cfg.max_nodes, logits_dev,
-                           (float *)(ws + L.blk_val), (int *)(ws + L.blk_idx), argmax_dev, st);
+                           (float2 *)(ws + L.blk), ro.records ? nullptr : argmax_dev, st);
     return SPECASR_OK;
   }
   launch_residual_gain(x, part, pending, R, pending_ld, ctx->w.final_norm, d, hb, hb_lo, nb, ssq, st);
@@ -852,7 +852,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
                 (float *)(ws + L.top2_v), (int *)(ws + L.top2_i), ro.top2, ro.prob, argmax_dev, st);
   else
     launch_logits_argmax(m, part, pl_lm.n_splits, ctx->lm_head.ldo, nrm, V, ctx->cfg.max_nodes, logits_dev,
-                         (float *)(ws + L.blk_val), (int *)(ws + L.blk_idx), argmax_dev, st);
+                         (float2 *)(ws + L.blk), ro.records ? nullptr : argmax_dev, st);
   return SPECASR_OK;
 }
 
@@ -1562,6 +1562,7 @@ specasr_status specasr_verify_tree(specasr_ctx *ctx, specasr_kv *kv, const speca
     if (s != SPECASR_OK) return s;
     ReadOut ro;
     ro.argmax = argmax_dev + grp.s0 * MN;
+    ro.records = ctx->fast && (hs.rows <= 64 || wide);  // what forward_common runs on the MFMA path
     ro.logits = out->logits ? out->logits + grp.s0 * MN * c.vocab : nullptr;
     s = forward_common(ctx, &grp.kv, &grp.tree, ro, wl, Lg, hs, sl, LayerSync(), wide);
     if (s != SPECASR_OK) return s;
@@ -1569,7 +1570,11 @@ specasr_status specasr_verify_tree(specasr_ctx *ctx, specasr_kv *kv, const speca
     KvGeom g{kv->capacity, c.n_layers, c.n_kv_heads, c.head_dim};
     int32_t *h = ctx->out_dev;  // laid out as the result block of the workspace
     const AcceptMirror host{h + grp.s0 * MN, h + BN + grp.s0 * MN, h + 2 * BN + grp.s0, h + 2 * BN + B + grp.s0};
-    launch_accept(m, c.max_nodes, argmax_dev + grp.s0 * MN, path_dev + grp.s0 * MN, len_dev + grp.s0, next_dev + grp.s0, sl, host);
+    if (ro.records)
+      launch_accept_records(m, c.max_nodes, (const float2 *)(wl + Lg.blk), logits_argmax_blocks(c.vocab), argmax_dev + grp.s0 * MN,
+                            path_dev + grp.s0 * MN, len_dev + grp.s0, next_dev + grp.s0, sl, host);
+    else
+      launch_accept(m, c.max_nodes, argmax_dev + grp.s0 * MN, path_dev + grp.s0 * MN, len_dev + grp.s0, next_dev + grp.s0, sl, host);
     launch_compact(c.dtype, g, grp.kv.batch, c.max_nodes, m.kv_len, path_dev + grp.s0 * MN, len_dev + grp.s0, grp.kv.k, grp.kv.v, sl);
     HIP_TRY(ctx, hipGetLastError());
   }

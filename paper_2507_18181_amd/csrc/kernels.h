@@ -75,6 +75,9 @@ struct AcceptMirror {
 };
 void launch_accept(const StepMeta &m, int max_nodes, const int32_t *argmax, int32_t *path,
                    int32_t *accept_len, int32_t *next_token, hipStream_t st, const AcceptMirror &host = AcceptMirror());
+// the same from records (value, lowest id) of `pieces` parts of each row's vocabulary; also writes argmax
+void launch_accept_records(const StepMeta &m, int max_nodes, const float2 *rec, int pieces, int32_t *argmax, int32_t *path,
+                           int32_t *accept_len, int32_t *next_token, hipStream_t st, const AcceptMirror &host = AcceptMirror());
 // argmax of the caller's padded logits ([batch][max_nodes][V]), then the acceptance above.  rec: rows *
 // argmax_pieces(V) pairs of floats.
 int argmax_pieces(int V);

@@ -24,8 +24,8 @@ template <> struct Vec4<bf16_t> {
 
 // --------------------------------------------------------------------------- the start of a forward
 // One launch for what depends on nothing but the call's metadata, which it reads in pinned host memory (`m` points there):
-// blocks 0 .. rows-1 fetch an embedding row each, the next ones fill the rope table, the last ones copy the metadata block
-// to the device for all later kernels.  PLANES (MFMA path): an embedding row leaves as residual_gain_kernel would
+// the first blocks fill the rope table (64-bit functions: the longest), the next ones copy the metadata block to the device
+// for all later kernels, the others fetch the embedding rows.  PLANES (MFMA path): an embedding row leaves as residual_gain_kernel would
 // leave it, x * gain in two planes and one sum of squares per 32 columns.  Bound by one read across PCIe and one of
 // the table: 7B, 32 rows copy 4.5 + embed 9.9 + rope 3.5 + residual_gain 4.9 us before.
 // Sec. II-B: a tree node is verified as if decoded after its own branch, so its rotary
@@ -33,50 +33,65 @@ template <> struct Vec4<bf16_t> {
 template <class T, bool PLANES>
 __global__ __launch_bounds__(256) void begin_kernel(StepMeta m, const T *E, const T *in_emb, int vec, int max_nodes, int d, float *x, int half, int hd,
                                                     double theta, float2 *cs, int rope_blocks, BeginPlanes pl, const int32_t *words, int32_t *dst, int n_words) {
-  const int r = blockIdx.x;
-  if (r >= m.rows + rope_blocks) {
-    const int i0 = (r - m.rows - rope_blocks) * 1024 + threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (i0 + i * 256 < n_words) dst[i0 + i * 256] = words[i0 + i * 256];
-    return;
-  }
-  if (r >= m.rows) {
-    const int idx = (r - m.rows) * 256 + threadIdx.x;
+  int blk = blockIdx.x;
+  if (blk < rope_blocks) {
+    const int idx = blk * 256 + threadIdx.x;
     if (idx >= m.rows * half) return;
     const int row = idx / half, j = idx - row * half;
     const double ang = (double)m.pos[row] * pow(theta, -2.0 * (double)j / (double)hd);
     cs[idx] = make_float2((float)cos(ang), (float)sin(ang));
     return;
   }
+  blk -= rope_blocks;
+  const int copy_blocks = (n_words + 1023) / 1024;
+  if (blk < copy_blocks) {
+    const int i0 = blk * 1024 + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i0 + i * 256 < n_words) dst[i0 + i * 256] = words[i0 + i * 256];
+    return;
+  }
+  blk -= copy_blocks;
+  const int row_blocks = (m.rows + 31) >> 5;
+  // 32 rows x 128 columns: 8 threads per row take 4 columns each, 4 times; whole lines of both planes leave a block
+  const int cols = (uint32_t)blk / (uint32_t)row_blocks, row = (blk - cols * row_blocks) * 32 + (threadIdx.x >> 3);
+  const bool live = row < m.rows;
+  const int r = live ? row : m.rows - 1;
   const T *src;
   if (in_emb != nullptr && m.use_embed[r])
     src = in_emb + ((int64_t)m.seq[r] * max_nodes + m.node[r]) * d;
   else
     src = E + (int64_t)m.token[r] * d;
-  for (int c0 = 0; c0 < d; c0 += 1024) {
-    const int c = c0 + threadIdx.x * 4;
-    const bool ok = c < d;  // d is a multiple of 8
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if (ok) {
+  float v[4][4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int c = cols * 128 + t * 32 + (threadIdx.x & 7) * 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[t][i] = 0.f;
+    if (live && c < d) {  // d is a multiple of 8
       if (vec) {
-        Vec4<T>::load(src + c, v);
+        Vec4<T>::load(src + c, v[t]);
       } else {  // a table that is not on 4 elements (a caller's slice)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = to_f32(src[c + i]);
+        for (int i = 0; i < 4; ++i) v[t][i] = to_f32(src[c + i]);
       }
-      *reinterpret_cast<float4 *>(x + (int64_t)r * d + c) = make_float4(v[0], v[1], v[2], v[3]);
     }
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int c = cols * 128 + t * 32 + (threadIdx.x & 7) * 4;
+    const bool ok = live && c < d;
+    if (ok) *reinterpret_cast<float4 *>(x + (int64_t)r * d + c) = make_float4(v[t][0], v[t][1], v[t][2], v[t][3]);
     if (PLANES) {
-      float ss = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+      float ss = v[t][0] * v[t][0] + v[t][1] * v[t][1] + v[t][2] * v[t][2] + v[t][3] * v[t][3];
       ss += __shfl_xor(ss, 1, 64);
       ss += __shfl_xor(ss, 2, 64);
       ss += __shfl_xor(ss, 4, 64);
       if (ok) {
         if ((threadIdx.x & 7) == 0) pl.ssq[(int64_t)r * pl.n_slab + (c >> 5)] = ss;
         const uint2 g = *reinterpret_cast<const uint2 *>(pl.gain + c);
-        const float y[4] = {v[0] * bf16_bits_to_f32(g.x & 0xffffu), v[1] * bf16_bits_to_f32(g.x >> 16),
-                            v[2] * bf16_bits_to_f32(g.y & 0xffffu), v[3] * bf16_bits_to_f32(g.y >> 16)};
+        const float y[4] = {v[t][0] * bf16_bits_to_f32(g.x & 0xffffu), v[t][1] * bf16_bits_to_f32(g.x >> 16),
+                            v[t][2] * bf16_bits_to_f32(g.y & 0xffffu), v[t][3] * bf16_bits_to_f32(g.y >> 16)};
         store_planes4(y, pl.hb, pl.hb_lo, packed_act_offset(r, c, pl.nb));
       }
     }
@@ -85,7 +100,8 @@ __global__ __launch_bounds__(256) void begin_kernel(StepMeta m, const T *E, cons
 
 void launch_begin(const StepMeta &hm, int dtype, const void *E, const void *in_emb, int max_nodes, int d, float *x, int hd, float theta,
                   float2 *cs, const BeginPlanes *pl, const int32_t *words, int32_t *dst, int n_words, hipStream_t st) {
-  const int half = hd / 2, rope_blocks = (hm.rows * half + 255) / 256, blocks = hm.rows + rope_blocks + (n_words + 1023) / 1024;
+  const int half = hd / 2, rope_blocks = (hm.rows * half + 255) / 256;
+  const int blocks = rope_blocks + (n_words + 1023) / 1024 + (hm.rows + 31) / 32 * ((d + 127) / 128);
   const size_t esz = dtype == 1 ? 2 : 4;
   const int vec = (((uintptr_t)E | (uintptr_t)in_emb) & (4 * esz - 1)) == 0;
   const BeginPlanes none{};
@@ -675,7 +691,7 @@ void launch_top2(const StepMeta &m, const float *src, bool from_partials, int n_
 // target's greedy token at its parent; ballot gathers the match flags into one mask; a node is
 // acceptable when its ancestor mask has no unmatched bit; the deepest acceptable node wins
 // (lowest index among equals).
-// PIECES: the argmax of a node is first merged from its piece records (argmax_pieces_kernel) and written to argmax_out;
+// PIECES: the argmax of a node is first merged from its piece records (argmax_pieces_kernel, logits_argmax_kernel) and written to argmax_out;
 // otherwise it is read from argmax.
 template <bool PIECES>
 __global__ __launch_bounds__(64) void accept_kernel(StepMeta m, int max_nodes, const int32_t *argmax,
@@ -695,7 +711,7 @@ __global__ __launch_bounds__(64) void accept_kernel(StepMeta m, int max_nodes, c
       float best = -INFINITY;
       int besti = 0x7fffffff;
       const float2 *p = rec + (int64_t)(r0 + lane) * pieces;
-#pragma unroll 8
+#pragma unroll 16
       for (int i = 0; i < pieces; ++i) {
         const float2 q = p[i];
         const int qi = __float_as_int(q.y);
@@ -739,6 +755,11 @@ void launch_accept(const StepMeta &m, int max_nodes, const int32_t *argmax, int3
   accept_kernel<false><<<m.batch, 64, 0, st>>>(m, max_nodes, argmax, nullptr, nullptr, 0, path, accept_len, next_token, host);
 }
 
+void launch_accept_records(const StepMeta &m, int max_nodes, const float2 *rec, int pieces, int32_t *argmax, int32_t *path,
+                           int32_t *accept_len, int32_t *next_token, hipStream_t st, const AcceptMirror &host) {
+  accept_kernel<true><<<m.batch, 64, 0, st>>>(m, max_nodes, nullptr, argmax, rec, pieces, path, accept_len, next_token, host);
+}
+
 void launch_argmax_accept(const StepMeta &m, const float *logits, int max_nodes, int V, float *rec, int32_t *argmax,
                           int32_t *path, int32_t *accept_len, int32_t *next_token, hipStream_t st) {
   const int pieces = argmax_pieces(V);
@@ -747,10 +768,13 @@ void launch_argmax_accept(const StepMeta &m, const float *logits, int max_nodes,
 }
 
 // --------------------------------------------------------------------------- KV compaction
-// Moves cache slot kv_len + path[k] to slot kv_len + k (k < accept_len) for one
-// (sequence, layer, KV head, K|V) per block.  Since path is strictly increasing with
-// path[k] >= k, a destination slot may be another move's source: every source row is read
-// into registers, the block synchronises, and only then is anything written.
+// Moves cache slot kv_len + path[k] to slot kv_len + k (k < accept_len) for one (sequence, layer, K|V) and up to
+// kCompactHeads KV heads per block.  Since path is strictly increasing with path[k] >= k, a destination slot may be another
+// move's source: every source row of a head is read into registers, the block synchronises, and only then is anything
+// written.  Usually the accepted path is the front of the trunk and nothing moves (path[len - 1] == len - 1 says so):
+// then the launch is bound by its number of blocks (one per head: 4 sequences on the 7B model 8192 blocks, 21 us;
+// 1024: 6 us).
+constexpr int kCompactHeads = 8;
 typedef __attribute__((ext_vector_type(4))) uint32_t mv16_t;  // one 16-byte unit of a cache row
 
 template <int UNITS>
@@ -758,52 +782,59 @@ __global__ __launch_bounds__(256) void compact_kernel(KvGeom g, int max_nodes, i
                                                       const int32_t *kv_len, const int32_t *path,
                                                       const int32_t *accept_len, char *kc, char *vc,
                                                       int elem_bytes) {
-  int idx = blockIdx.x;
+  uint32_t idx = blockIdx.x;
+  const uint32_t hg = (uint32_t)(g.n_kv_heads + kCompactHeads - 1) / kCompactHeads;
   const int which = idx & 1; idx >>= 1;
-  const int h = idx % g.n_kv_heads; idx /= g.n_kv_heads;
-  const int layer = idx % g.n_layers;
-  const int seq = idx / g.n_layers;
+  const int h_first = (int)(idx % hg) * kCompactHeads; idx /= hg;
+  const int layer = (int)(idx % (uint32_t)g.n_layers), seq = (int)(idx / (uint32_t)g.n_layers);
   const int len = accept_len[seq];
   const int32_t *p = path + (int64_t)seq * max_nodes;
-  char *base = (which ? vc : kc) + g.row(seq, layer, h, kv_len[seq]) * elem_bytes;
+  if (p[len - 1] == len - 1) return;
+  const int h_end = min(h_first + kCompactHeads, g.n_kv_heads);
   const int upr = row_bytes / 16;  // 16-byte units per row
-  const int total = len * upr;
+  const int total = len * upr;     // units of one head
+  const int64_t head_bytes = g.capacity * row_bytes;
+  char *base = (which ? vc : kc) + g.row(seq, layer, h_first, kv_len[seq]) * elem_bytes;
   if (total <= 256 * UNITS) {
-    mv16_t regs[UNITS];
+    const int heads = min(256 * UNITS / total, h_end - h_first);  // at a time
+    for (int h = h_first; h < h_end; h += heads, base += heads * head_bytes) {
+      const int n = min(heads, h_end - h) * total;
+      mv16_t regs[UNITS];
 #pragma unroll
-    for (int i = 0; i < UNITS; ++i) {
-      int u = threadIdx.x + i * 256;
-      if (u < total) {
-        int k = u / upr, w = u - k * upr;
-        int src = p[k];
-        regs[i] = (mv16_t){0u, 0u, 0u, 0u};
-        if (src != k) regs[i] = *reinterpret_cast<const mv16_t *>(base + (int64_t)src * row_bytes + w * 16);
+      for (int i = 0; i < UNITS; ++i) {
+        const int u = threadIdx.x + i * 256;
+        if (u < n) {
+          const int hh = u / total, v = u - hh * total, k = v / upr, w = v - k * upr, src = p[k];
+          regs[i] = (mv16_t){0u, 0u, 0u, 0u};
+          if (src != k) regs[i] = *reinterpret_cast<const mv16_t *>(base + hh * head_bytes + (int64_t)src * row_bytes + w * 16);
+        }
       }
-    }
-    __syncthreads();
+      __syncthreads();
 #pragma unroll
-    for (int i = 0; i < UNITS; ++i) {
-      int u = threadIdx.x + i * 256;
-      if (u < total) {
-        int k = u / upr, w = u - k * upr;
-        if (p[k] != k) *reinterpret_cast<mv16_t *>(base + (int64_t)k * row_bytes + w * 16) = regs[i];
+      for (int i = 0; i < UNITS; ++i) {
+        const int u = threadIdx.x + i * 256;
+        if (u < n) {
+          const int hh = u / total, v = u - hh * total, k = v / upr, w = v - k * upr;
+          if (p[k] != k) *reinterpret_cast<mv16_t *>(base + hh * head_bytes + (int64_t)k * row_bytes + w * 16) = regs[i];
+        }
       }
     }
   } else {
     // rows too large to stage at once: ascending order is safe because the source of move k'
     // (> k) lies beyond every destination written so far.
-    for (int k = 0; k < len; ++k) {
-      int src = p[k];
-      if (src == k) continue;
-      // one row is at most 1 KB = 64 units: every thread moves at most one
-      mv16_t v = (mv16_t){0u, 0u, 0u, 0u};
-      if ((int)threadIdx.x < upr)
-        v = *reinterpret_cast<const mv16_t *>(base + (int64_t)src * row_bytes + threadIdx.x * 16);
-      __syncthreads();
-      if ((int)threadIdx.x < upr)
-        *reinterpret_cast<mv16_t *>(base + (int64_t)k * row_bytes + threadIdx.x * 16) = v;
-      __syncthreads();
-    }
+    for (int h = h_first; h < h_end; ++h, base += head_bytes)
+      for (int k = 0; k < len; ++k) {
+        const int src = p[k];
+        if (src == k) continue;
+        // one row is at most 1 KB = 64 units: every thread moves at most one
+        mv16_t v = (mv16_t){0u, 0u, 0u, 0u};
+        if ((int)threadIdx.x < upr)
+          v = *reinterpret_cast<const mv16_t *>(base + (int64_t)src * row_bytes + threadIdx.x * 16);
+        __syncthreads();
+        if ((int)threadIdx.x < upr)
+          *reinterpret_cast<mv16_t *>(base + (int64_t)k * row_bytes + threadIdx.x * 16) = v;
+        __syncthreads();
+      }
   }
 }
 
@@ -812,7 +843,7 @@ void launch_compact(int dtype, const KvGeom &g, int batch, int max_nodes, const 
                     hipStream_t st) {
   const int eb = dtype == 1 ? 2 : 4;
   const int row_bytes = g.head_dim * eb;  // multiple of 16: head_dim % 8 == 0
-  const int blocks = batch * g.n_layers * g.n_kv_heads * 2;
+  const int blocks = batch * g.n_layers * ((g.n_kv_heads + kCompactHeads - 1) / kCompactHeads) * 2;
   compact_kernel<8><<<blocks, 256, 0, st>>>(g, max_nodes, row_bytes, kv_len, path, accept_len,
                                            (char *)kc, (char *)vc, eb);
 }

@@ -64,9 +64,10 @@ void launch_qkv_finish(const StepMeta &m, const ModelDims &md, const KvGeom &g, 
 void launch_swiglu_finish(const float *part, int n_splits, int rows, int ldp, const RowNorm &nrm,
                           int F, uint16_t *t, uint16_t *t_lo, int nb, hipStream_t st);
 void launch_to_bf16(const float *src, int rows, int K, uint16_t *dst, uint16_t *dst_lo, hipStream_t st);
+// rec: rows * logits_argmax_blocks(V) records (value, lowest id); argmax == nullptr: they are left to launch_accept_records
 int logits_argmax_blocks(int V);
 void launch_logits_argmax(const StepMeta &m, const float *part, int n_splits, int ldp,
-                          const RowNorm &nrm, int V, int max_nodes, float *logits_out, float *blk_val, int *blk_idx,
+                          const RowNorm &nrm, int V, int max_nodes, float *logits_out, float2 *rec,
                           int32_t *argmax, hipStream_t st);
 
 // tree-masked MFMA attention (kernels_attn.hip)

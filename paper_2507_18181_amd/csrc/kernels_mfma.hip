@@ -1075,12 +1075,11 @@ void launch_to_bf16(const float *src, int rows, int K, uint16_t *dst, uint16_t *
 }
 
 // logits[r][v] = sum_s part[s][r][v]; per-(row, block) best (value, lowest index); optional
-// store of the logits into the caller's padded array.  A second tiny kernel merges the blocks.
+// store of the logits into the caller's padded array.  The acceptance kernel, or a second tiny one, merges the blocks.
 __global__ __launch_bounds__(256) void logits_argmax_kernel(StepMeta m, const float *part, int n_splits,
                                                             int ldp, RowNorm nrm, int V,
                                                             int max_nodes, float *logits_out,
-                                                            float *blk_val,
-                                                            int *blk_idx) {
+                                                            float2 *rec) {
   __shared__ float bv[4];
   __shared__ int bi[4];
   const int r = blockIdx.y, rows = m.rows;
@@ -1114,20 +1113,18 @@ __global__ __launch_bounds__(256) void logits_argmax_kernel(StepMeta m, const fl
   if (threadIdx.x == 0) {
     for (int w = 1; w < 4; ++w)
       if (bv[w] > best || (bv[w] == best && bi[w] < besti)) { best = bv[w]; besti = bi[w]; }
-    blk_val[(int64_t)r * gridDim.x + blockIdx.x] = best;
-    blk_idx[(int64_t)r * gridDim.x + blockIdx.x] = besti;
+    rec[(int64_t)r * gridDim.x + blockIdx.x] = make_float2(best, __int_as_float(besti));
   }
 }
 
-__global__ __launch_bounds__(64) void argmax_merge_kernel(StepMeta m, const float *blk_val,
-                                                          const int *blk_idx, int n_blk,
-                                                          int max_nodes, int32_t *argmax) {
+__global__ __launch_bounds__(64) void argmax_merge_kernel(StepMeta m, const float2 *rec, int n_blk, int max_nodes, int32_t *argmax) {
   const int r = blockIdx.x;
   float best = -INFINITY;
   int besti = 0x7fffffff;
   for (int b = threadIdx.x; b < n_blk; b += 64) {
-    const float v = blk_val[(int64_t)r * n_blk + b];
-    const int i = blk_idx[(int64_t)r * n_blk + b];
+    const float2 q = rec[(int64_t)r * n_blk + b];
+    const float v = q.x;
+    const int i = __float_as_int(q.y);
     if (v > best || (v == best && i < besti)) { best = v; besti = i; }
   }
 #pragma unroll
@@ -1142,12 +1139,12 @@ __global__ __launch_bounds__(64) void argmax_merge_kernel(StepMeta m, const floa
 int logits_argmax_blocks(int V) { return ((V + 3) / 4 + 255) / 256; }
 
 void launch_logits_argmax(const StepMeta &m, const float *part, int n_splits, int ldp,
-                          const RowNorm &nrm, int V, int max_nodes, float *logits_out, float *blk_val, int *blk_idx,
+                          const RowNorm &nrm, int V, int max_nodes, float *logits_out, float2 *rec,
                           int32_t *argmax, hipStream_t st) {
   const int n_blk = logits_argmax_blocks(V);
   dim3 grid(n_blk, m.rows);
-  logits_argmax_kernel<<<grid, 256, 0, st>>>(m, part, n_splits, ldp, nrm, V, max_nodes, logits_out, blk_val, blk_idx);
-  argmax_merge_kernel<<<m.rows, 64, 0, st>>>(m, blk_val, blk_idx, n_blk, max_nodes, argmax);
+  logits_argmax_kernel<<<grid, 256, 0, st>>>(m, part, n_splits, ldp, nrm, V, max_nodes, logits_out, rec);
+  if (argmax != nullptr) argmax_merge_kernel<<<m.rows, 64, 0, st>>>(m, rec, n_blk, max_nodes, argmax);
 }
 
 }  // namespace specasr
