@@ -682,12 +682,21 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       if (ctx->tune.wide_splits[i] >= 1) continue;
       // (An unsplit tiled gate|up finishes SwiGLU itself, but the split count stays the planner's: taken unsplit for that
       // alone, the fp32 addition chain doubles or triples and the feed-forward part is 0.8 % (1.1B, 1024 rows) to 1.9 % (13B)
-      // further from the 64-bit result.  Prefill of 810: 7B 23.5 ms unsplit, 24.3 split; 700: 2.99 / 2.89 per 4 layers.)
-      if (i == 2) pls[i]->pair = plan_wide_pair(pm[i]->n_bands, pm[i]->ksteps, R, pls[i]->n_splits, ctx->n_cu);
+      // further from the 64-bit result.  Prefill of 810 positions, 7B: 23.5 ms unsplit, 24.3 split, 22.3 with the halves of a split in
+      // one workgroup, which keeps the split's chains.)
+      double other = wide_gemm_estimate(pm[i]->n_bands, pm[i]->ksteps, R, pls[i]->n_splits, i == 2, ctx->n_cu);
+      double pair_us = 0;
+      if (i == 2) pls[i]->pair = plan_wide_pair(pm[i]->n_bands, pm[i]->ksteps, R, pls[i]->n_splits, ctx->n_cu, &pair_us);
       // (against the tiled kernel alone: where the small tiles win, k in 4 or 8 slices keeps the feed-forward part closer to
       // the 64-bit result than k in halves, 1.1B 768 rows 0.3 %)
-      const MidPlan mp = plan_mid(pm[i]->n_bands, pm[i]->ksteps, R, wide_gemm_estimate(pm[i]->n_bands, pm[i]->ksteps, R, pls[i]->n_splits, i == 2, ctx->n_cu), i == 2, ctx->n_cu);
-      if (mp.a == 0 || (size_t)mp.S * pm[i]->ldo * part_rows_pad(R) > ctx->wide_part_floats) continue;
+      auto fits = [&](const MidPlan &m) { return m.a != 0 && (size_t)m.S * pm[i]->ldo * part_rows_pad(R) <= ctx->wide_part_floats; };
+      MidPlan mp = plan_mid(pm[i]->n_bands, pm[i]->ksteps, R, other, i == 2, ctx->n_cu);
+      if (!fits(mp)) mp = MidPlan();
+      const int slices = mp.a > 0 ? mp.S * (mp.a == 3 && mp.b == 3 ? 4 : 8) : pls[i]->pair > 0 ? 2 : pls[i]->n_splits;
+      other = mp.a > 0 ? mp.cost_us : pls[i]->pair > 0 ? pair_us : other;
+      const MidPlan tall = plan_mid_tall(pm[i]->n_bands, pm[i]->ksteps, R, mp, slices, other, i == 2, ctx->n_cu);
+      if (fits(tall)) mp = tall;
+      if (mp.a == 0) continue;
       pls[i]->mid = mp;
       pls[i]->pair = 0;
       pls[i]->n_splits = mp.S;
@@ -753,7 +762,8 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       else if (pls[i]->pair) snprintf(k, sizeof k, "pair %dx4", pls[i]->pair);
       else if (wide) snprintf(k, sizeof k, "wide");
       else snprintf(k, sizeof k, "skinny %d", pls[i]->lw);
-      fprintf(stderr, "[specasr] plan %s rows=%d bands=%d ksteps=%d: %s, %d splits\n", nm[i], R, pm[i]->n_bands, pm[i]->ksteps, k, S);
+      const bool twos = !sl[i]->hb && pls[i]->mid.tall > pls[i]->mid.a;  // two of the plan's tiles per workgroup
+      fprintf(stderr, "[specasr] plan %s rows=%d bands=%d ksteps=%d: %s, %d splits%s\n", nm[i], R, pm[i]->n_bands, pm[i]->ksteps, k, S, twos ? ", 6 bands each" : "");
     }
   }
   const BeginPlanes first{(const uint16_t *)ctx->layers[0].attn_norm, hb, hb_lo, nb, ssq, nrm.n_slab};

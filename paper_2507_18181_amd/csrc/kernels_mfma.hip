@@ -723,7 +723,7 @@ __global__ __launch_bounds__(512, 2) void gemm_wide_pair_kernel(const u32x4 *__r
 // kernel 6 and 0.17 per MB of partial sums.  Measured, tiled kernel against this: 7B 256 rows 101 / 97, 512 rows 185 / 196,
 // 640 rows 240 / 220, 810 rows 297 / 254; 13B 810 rows 470 / 395; 1.1B 640 rows 57 / 55.  More than two splits stay with the
 // tiled kernel: their addition chains are shorter.
-int plan_wide_pair(int n_bands, int ksteps, int rows, int splits, int n_cu) {
+int plan_wide_pair(int n_bands, int ksteps, int rows, int splits, int n_cu, double *cost_us) {
   const int64_t mt = wide_row_groups(rows) / kWideTileGroups;
   auto rounds = [n_cu](int64_t wgs) { return (double)((wgs + n_cu - 1) / n_cu); };
   const double out_mb = (double)n_bands * 32 * rows * 4e-6;
@@ -734,7 +734,7 @@ int plan_wide_pair(int n_bands, int ksteps, int rows, int splits, int n_cu) {
   for (const int a : {8, 10}) {
     const double cost = 12.0 + rounds((n_bands + a - 1) / a * mt) * (ksteps / 2.0) * (a == 10 ? 0.91 : 0.74);
     if (cost >= limit) continue;
-    limit = cost;
+    *cost_us = limit = cost;
     best = a;
   }
   return best;

@@ -7,7 +7,8 @@
 // features x 2 .. 3 groups of 32 rows) and k is cut INSIDE the workgroup: every wavefront takes a slice
 // of k for the whole tile and streams its operands straight into registers (a ring of D stages; both
 // operands are stored in MFMA operand order), without LDS or barriers in the loop; the slices are
-// summed through LDS at the end.  One wavefront multiplies A x B tiles from A + 2B loads.
+// summed through LDS at the end.  One wavefront multiplies A x B tiles from A + 2B loads; up to 7 x 3 tiles fit the registers
+// of a lone wavefront per SIMD (plan_mid_tall).
 // What bounds it: the bytes a compute unit can pull out of its L2, about 58 per ns.
 // Measured (us under the tracer, tiled kernel and its splits at 96 rows -> this at 87, 7B): gate|up 53.7 + its finishing
 // kernel -> 52.2 with SwiGLU, q|k|v 37.9 (5 splits) -> 28.8 (2), o 17.4 (8) -> 14.6 (5), down 31.5 (13) -> 30.1 (5); 384
@@ -85,14 +86,20 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void gemm_mid_kernel(MidArgs p) {
 #pragma unroll
       for (int b = 0; b < B; ++b) xb[j][h][b] = xp[h][b][k * xs];
   };
-  auto mul = [&](int j) {  // hi products first, then lo: A * B independent accumulators in between
+  // hi products first, then lo: A * B independent accumulators in between.  Beyond 16 tiles the accumulators outgrow the
+  // 256 accumulation registers that the compiler keeps them in, so those tiles are named as vector registers by hand (it
+  // spills otherwise: 6 x 3 tiles 940 bytes, no gain).  They come first, so that at the end of a step, the first place where
+  // anything else may touch them, 16 other MFMAs have been issued since, more than the wait states of a result.
+  auto mul = [&](int j) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll
-      for (int a = 0; a < A; ++a)
+      for (int t = 16; t < A * B; ++t)
+        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc[t / B][t % B]) : "v"(wa[j][t / B]), "v"(xb[j][h][t % B]));
 #pragma unroll
-        for (int b = 0; b < B; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wa[j][a]), __builtin_bit_cast(bf16x8, xb[j][h][b]), acc[a][b], 0, 0, 0);
+      for (int t = 0; t < 16 && t < A * B; ++t)
+        acc[t / B][t % B] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wa[j][t / B]), __builtin_bit_cast(bf16x8, xb[j][h][t % B]), acc[t / B][t % B], 0, 0, 0);
+    }
   };
   if (len > 0) {
 #pragma unroll
@@ -215,6 +222,10 @@ hipError_t gemm_mid_set_lds_limit() {
   if (e == hipSuccess) e = set_lds_mid<3, 3, 4, 4, true>();
   if (e == hipSuccess) e = set_lds_mid<3, 3, 4, 4, false, true>();
   if (e == hipSuccess) e = set_lds_mid<3, 3, 4, 4, true, true>();
+  if (e == hipSuccess) e = set_lds_mid<6, 3, 3, 4, false>();
+  if (e == hipSuccess) e = set_lds_mid<6, 3, 3, 4, true>();
+  if (e == hipSuccess) e = set_lds_mid<7, 3, 2, 4, false>();
+  if (e == hipSuccess) e = set_lds_mid<7, 3, 2, 4, true>();
   if (e == hipSuccess) e = set_lds_mid<2, 2, 4, 8, false, true>();
   if (e == hipSuccess) e = set_lds_mid<2, 2, 4, 8, true, true>();
   if (e == hipSuccess) e = set_lds_mid<3, 2, 3, 8, false, true>();
@@ -251,6 +262,37 @@ MidPlan plan_mid(int n_bands, int ksteps, int rows, double other_us, bool swiglu
       }
     }
   }
+  best.cost_us = best_cost;
+  return best;
+}
+
+// Six or seven bands per workgroup instead of the plan's kernel (`slices`: its parts of k, `other_us`: its estimate; `mid`: its
+// small-tile plan, if any), or a = 0.  A wavefront with 6 x 3 tiles loads 12 KB per 36 MFMAs where one with 3 x 3 loads 9 per
+// 18, and there is half the number of workgroups, in one round where it took two.  More than 64 rows, where the rows fill three groups.
+// Measured, us: 1.1B gate|up, 384 rows 51.8 (3 x 3, two rounds) -> 38.7, 192 rows 31.0 (one round) against 36.8 here; 7B q|k|v, 300
+// rows 94 (tiled, split) -> 64, 810 rows 163 + 8 for the second partial sum -> 147 (7 bands: 495 workgroups where 6 have 576);
+// 13B down, 192 rows 65 -> 58.  In the model, ms: 1.1B 16 x 24 nodes 3.55 -> 3.27, prefill of 330 2.89 -> 2.69, of 900 6.18 -> 5.67; 7B
+// prefill of 192 7.80 -> 6.93, of 384 11.27 -> 10.62, of 810 22.17 -> 21.48.  Costs fitted to these: 5, and per round 5 and 0.215 per k-step (7 bands 0.24); 0.12 per MB of partial sums for
+// the reader.  The other kernels' estimates are less exact, so 10 % is asked for.  k is cut into 4 slices per split, and the
+// sums' chains may not get longer than they were: no fewer slices than the other plan's.
+MidPlan plan_mid_tall(int n_bands, int ksteps, int rows, const MidPlan &mid, int slices, double other_us, bool swiglu, int n_cu) {
+  MidPlan best;
+  double limit = 0.9 * other_us;
+  const int64_t n_mt = (rows + 95) / 96;
+  const double out_mb = (double)n_bands * 32 * rows * 4e-6;
+  for (int a = 6; a <= 7; ++a)
+    for (int S = 1; S <= (swiglu ? 1 : 8) && ksteps / S >= 32; ++S) {
+      if (4 * S < slices) continue;
+      const double rounds = (double)((n_mt * ((n_bands + a - 1) / a) * S + n_cu - 1) / n_cu);
+      const double cost = 5.0 + rounds * ((double)ksteps / S * (a == 7 ? 0.24 : 0.215) + 5.0) + (swiglu ? 0.0 : S * out_mb * 0.12);
+      if (cost >= limit) continue;
+      limit = cost;
+      best.a = best.tall = a;
+      best.b = 3;
+      best.S = S;
+      best.cost_us = cost;
+    }
+  if (best.a == 6 && mid.a == 3 && mid.b == 3 && mid.S == best.S) best.a = 3;  // the same tiles and slices, two tiles per wavefront
   return best;
 }
 
@@ -273,11 +315,17 @@ void launch_gemm_mid(const PackedMatrix &W, const uint16_t *Xp, int rows, float 
   a.rows = rows; a.rows_pad = part_rows_pad(rows); a.n_bands = W.n_bands; a.ksteps = W.ksteps; a.nb = rows <= 64 ? 2 : wide_row_groups(rows); a.S = pl.S;
   if (nrm != nullptr) {  // SwiGLU epilogue
     a.nrm = *nrm; a.t = t; a.t_lo = t_lo;
-    if (rows <= 64 && pl.a == 2) launch_mid_t<2, 2, 4, 8, true, true>(a, st, ev0, ev1);
+    if (pl.tall == 7) launch_mid_t<7, 3, 2, 4, true>(a, st, ev0, ev1);
+    else if (pl.tall == 6) launch_mid_t<6, 3, 3, 4, true>(a, st, ev0, ev1);
+    else if (rows <= 64 && pl.a == 2) launch_mid_t<2, 2, 4, 8, true, true>(a, st, ev0, ev1);
     else if (rows <= 64) launch_mid_t<3, 2, 3, 8, true, true>(a, st, ev0, ev1);
     else if (pl.a == 2) launch_mid_t<2, 3, 3, 8, true>(a, st, ev0, ev1);
     else if (rows <= 96) launch_mid_t<3, 3, 4, 4, true, true>(a, st, ev0, ev1);
     else launch_mid_t<3, 3, 4, 4, true>(a, st, ev0, ev1);
+  } else if (pl.tall == 7) {
+    launch_mid_t<7, 3, 2, 4, false>(a, st, ev0, ev1);
+  } else if (pl.tall == 6) {
+    launch_mid_t<6, 3, 3, 4, false>(a, st, ev0, ev1);
   } else if (rows <= 64 && pl.a == 2) {
     launch_mid_t<2, 2, 4, 8, false, true>(a, st, ev0, ev1);
   } else if (rows <= 64) {
