@@ -458,11 +458,16 @@ __global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const u32x4 *__restri
   // four separate arrays: the compiler can tell a copy into one from the reads of another
   __shared__ u32x4 s0[kWideStageTiles * 64], s1[kWideStageTiles * 64], s2[kWideStageTiles * 64], s3[kWideStageTiles * 64];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int n_mt = nb / kWideTileGroups, n_nt = (n_bands + kWideTileBands - 1) / kWideTileBands, n_nt8 = (n_nt + 7) / 8;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int mt = slot % n_mt, rest = slot / n_mt;
-  const int nt = (rest % n_nt8) * 8 + xcd, s = rest / n_nt8;
-  if (nt >= n_nt) return;
+  // An XCD (workgroup index mod 8) takes an eighth of all (split, feature tile, row tile)s in this order.  (Feature tiles
+  // dealt to XCDs by number leave some with one more, and its splits and row tiles as a second round, where 8 does not divide
+  // them: 13B down with 20 tiles, 192 rows 108.5 us against 65, 384 rows 160 / 96, o 66 / 41.5; 1.1B q|k|v with 10, 1024 rows
+  // 42.5 / 27.7; equal where it does.  In the model, ms: 13B prefill of 384 22.7 / 19.4, 4 x 24 nodes 10.5 / 9.64, 1.1B prefill
+  // of 1024 6.55 / 6.05.)
+  const uint32_t n_mt = nb / kWideTileGroups, n_nt = (n_bands + kWideTileBands - 1) / kWideTileBands, total = n_mt * n_nt * S;
+  const uint32_t id = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (id >= total) return;
+  const uint32_t rest = id / n_mt;
+  const int mt = id % n_mt, nt = rest % n_nt, s = rest / n_nt;
   const int k0 = (int)((int64_t)ksteps * s / S), k1 = (int)((int64_t)ksteps * (s + 1) / S);
   const int wn = wave & 1, wm = wave >> 1;
   // the 4 tiles this wavefront copies per stage: wavefronts 0, 1 the weight bands 4w .. 4w+3 (bands
@@ -566,7 +571,7 @@ static void launch_gemm_wide_s(const PackedMatrix &W, const uint16_t *Xp, int ro
                                const WideSwiglu &sw = WideSwiglu{}) {
   const int nb = wide_row_groups(rows);
   const int n_nt = (W.n_bands + kWideTileBands - 1) / kWideTileBands;
-  const unsigned grid = 8u * (nb / kWideTileGroups) * ((n_nt + 7) / 8) * n_splits;
+  const unsigned grid = ((unsigned)(nb / kWideTileGroups) * n_nt * n_splits + 7u) / 8u * 8u;
   if (ev0 != nullptr)
     hipExtLaunchKernelGGL((gemm_wide_kernel<STAGE, SWIGLU>), dim3(grid), dim3(256), 0u, st, ev0, ev1, 0u, (const u32x4 *)W.data,
                           (const u32x4 *)Xp, part, rows, part_rows_pad(rows), W.n_bands, W.ksteps, nb, n_splits, sw);
