@@ -20,7 +20,7 @@
  *    only inside specasr_create (the optional repacked weight copy).  Host-side
  *    resources are created by the first call that needs them and released by
  *    specasr_destroy: a few KB of pinned staging memory with one event per
- *    staging slot (any call that uploads tree metadata), up to three internal
+ *    staging slot (any call that stages tree metadata), up to three internal
  *    streams of default priority with fork/join events (calls that fall into
  *    several sequence groups, chunked prefill) plus two events per layer
  *    (chunked prefill), and event pairs for specasr_profile_stage.

@@ -339,7 +339,7 @@ hipError_t gemm_skinny_set_lds_limit() {
 // a weight tile (the row tiles of one feature tile) get consecutive slots of one XCD.
 //   part[s][band][row][o % 32] as for the skinny kernel; nb = row groups of 32 in Xp, a multiple
 //   of 4 (the buffer is allocated to that size; rows >= `rows` hold anything and are not stored).
-// grid.x = 8 * (nb / 4) * ceil(ceil(n_bands / 8) / 8) * S, block 256.
+// grid.x = (nb / 4) * ceil(n_bands / 8) * S rounded up to 8, block 256.
 constexpr int kWideTileBands = 8;   // 256 output features per workgroup
 constexpr int kWideTileGroups = 4;  // 128 rows per workgroup
 constexpr int kWideStageTiles = kWideTileBands + 2 * kWideTileGroups;  // 1 KB tiles per stage (one k-step)
