@@ -88,17 +88,20 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void gemm_mid_kernel(MidArgs p) {
   };
   // hi products first, then lo: A * B independent accumulators in between.  Beyond 16 tiles the accumulators outgrow the
   // 256 accumulation registers that the compiler keeps them in, so those tiles are named as vector registers by hand (it
-  // spills otherwise: 6 x 3 tiles 940 bytes, no gain).  They come first, so that at the end of a step, the first place where
-  // anything else may touch them, 16 other MFMAs have been issued since, more than the wait states of a result.
+  // spills otherwise: 6 x 3 tiles 940 bytes, no gain).  It puts no wait states around what it does not know to be MFMAs, so
+  // their order is held by fences: in each plane they come first and 16 other MFMAs behind them, more than the wait states of a
+  // result, before the other plane, the end of the step or anything else may touch them.
   auto mul = [&](int j) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
       for (int t = 16; t < A * B; ++t)
         asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc[t / B][t % B]) : "v"(wa[j][t / B]), "v"(xb[j][h][t % B]));
+      if (A * B > 16) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int t = 0; t < 16 && t < A * B; ++t)
         acc[t / B][t % B] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wa[j][t / B]), __builtin_bit_cast(bf16x8, xb[j][h][t % B]), acc[t / B][t % B], 0, 0, 0);
+      if (A * B > 16) __builtin_amdgcn_sched_barrier(0);
     }
   };
   if (len > 0) {
@@ -147,6 +150,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void gemm_mid_kernel(MidArgs p) {
     for (int j = 0; j < D; ++j)
       if (base + j < len) mul(j);
   }
+  // The sums read those results behind this wait, whatever stands in front of it (20 wait states).
+  if (A * B > 16) asm volatile("s_nop 15\n\ts_nop 3");
+#pragma unroll
+  for (int t = 16; t < A * B; ++t) asm volatile("" : "+v"(acc[t / B][t % B]));
   // sum of the NW slices through LDS, CH tiles at a time.  C layout: register 4q + e of lane l = row l%32,
   // feature 8q + 4(l/32) + e, i.e. feature quad 2q + l/32
   constexpr int NT = A * B, CH = mid_chunk<A, B, NW>();
