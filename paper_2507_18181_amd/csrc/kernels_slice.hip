@@ -43,6 +43,9 @@ constexpr int slice_regs(int stages, int accs) {
 }
 template <int EPI, int HB, int NC>
 constexpr int slice_depth() {
+  // Both planes in one operand (NC = 0): the ring of 16 rows, though a deeper one would fit, so that two accumulators always
+  // do and the chains get no longer (below).
+  if (NC == 0 && EPI != kSliceQkv) return slice_depth<EPI, HB, 1>();
   constexpr int accs = EPI == kSliceQkv ? 3 : 1;
   return slice_regs<EPI, HB, NC>(8, accs) <= 250 ? 8 : slice_regs<EPI, HB, NC>(4, accs) <= 250 ? 4 : 2;
 }
@@ -55,8 +58,14 @@ constexpr int slice_depth() {
 template <int EPI, int HB, int NC>
 constexpr int slice_accs() {
   constexpr int D = slice_depth<EPI, HB, NC>();
-  if (NC == 0)  // lo products have columns of their own; q|k|v with a ring of 8: both halves of a block and the sum
-    return EPI == kSliceQkv && D == 8 ? 3 : EPI == kSliceQkv || slice_regs<EPI, HB, NC>(D, 2) <= 250 ? 2 : 1;
+  // Both planes in one operand: lo products have columns of their own; q|k|v with a ring of 8: both halves of a block and the sum.
+  // With the ring as deep as it fits, gate|up of 16384 features ran in one chain and the 13B down projection in two of half a
+  // slice: rms errors of the sums 2.04 / 2.04 units of 2^-24, with 16 rows' instances 1.30 / 1.65, now 1.24 / 1.64; times equal
+  // (10 layers, 8 rows: 13B 1442 us / 1425, 16384 features 1236 / 1222).
+  if constexpr (NC == 0) {
+    static_assert(EPI == kSliceQkv || slice_regs<EPI, HB, NC>(D, 2) <= 250, "blocks of D steps and their sum");
+    return EPI == kSliceQkv && D == 8 ? 3 : 2;
+  }
   return EPI == kSliceQkv || slice_regs<EPI, HB, NC>(D, 3) <= 250 ? 3 : slice_regs<EPI, HB, NC>(D, 2) <= 250 ? 2 : 1;
 }
 // Output tiles summed through LDS at a time (1 KB per tile and wavefront, at most 128 KB).
@@ -133,7 +142,8 @@ __global__ __launch_bounds__(kSliceWaves * 64, 2) void gemm_slice_kernel(SliceAr
   const u32x4 *xp = (const u32x4 *)p.X + (int64_t)(2 * w0 + (lane >> 5)) * nb * 64 + in_tile;
   if (BOTH && (lane & 8)) xp += plane - 8;  // operand rows 8 .. 15 are the lo plane of rows 0 .. 7
   // accumulators: 0 running products, 1 what they were after earlier blocks of D stages (D = 8: the products of the
-  // block's second half instead, no additions in the loop), 2 lo products (with NA < 3 they go with the hi ones)
+  // block's second half instead, no additions in the loop), 2 lo products (with NA < 3 they go with the hi ones).
+  // BOTH: lo products have columns of their own in all of them; 2 (q|k|v, D = 8) is the sum of both halves of earlier blocks.
   constexpr int NA = slice_accs<EPI, HB, NCP>();
   f32x4 acc[HB][NC][NA];
 #pragma unroll
