@@ -317,9 +317,12 @@ static void launch_linear_t(const LinearJob *jobs, int n, const LinearMore<T> &m
   linear_kernel<T, MODE, NORM><<<grid, 256, 0, st>>>(ls, mo, n_in, a, lda, rows, accumulate ? 1 : 0);
 }
 
+// The linear reads the gain 4 elements at a time, rmsnorm_kernel one by one: it takes a gain that is a caller's slice off that grid.
+bool linear_normalises(int d, const void *gain, int elem_bytes) { return d <= kNormWidth && ((uintptr_t)gain & (4 * elem_bytes - 1)) == 0; }
+
 template <class T, int MODE>
 static void launch_linear_norm(const LinearJob *jobs, int n, LinearMore<T> mo, const NormIn &nx, hipStream_t st) {
-  if (nx.d <= kNormWidth) {
+  if (linear_normalises(nx.d, nx.gain, sizeof(T))) {
     mo.gain = (const T *)nx.gain;
     mo.eps = nx.eps;
     launch_linear_t<T, MODE, true>(jobs, n, mo, nx.d, nx.x, nx.d, nx.rows, false, st);

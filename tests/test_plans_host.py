@@ -21,3 +21,13 @@ def test_only_shapes_that_a_planner_can_choose_are_built(built):
     want |= {(SWIGLU, hb, nc) for nc, top in ((1, 8), (2, 8), (3, 6)) for hb in range(1, top + 1)}
     want |= {(QKV, hb, nc) for hb in (1, 2, 3, 4) for nc in (1, 2)} | {(RESID, 1, 1), (RESID, 1, 2)}
     assert got == want
+
+
+def test_linears_normalise_only_with_a_gain_on_four_elements():
+    """The linear reads the gain in vectors; any other address goes to the kernel that reads it element by element."""
+    f = B.load_library()._ZN7specasr17linear_normalisesEiPKvi
+    f.restype, f.argtypes = C.c_bool, [C.c_int, C.c_void_p, C.c_int]
+    for elem in (2, 4):
+        for off in range(0, 8 * elem, elem):
+            for d, narrow in ((8, True), (1024, True), (1032, False)):
+                assert f(d, 4096 + off, elem) == (narrow and off % (4 * elem) == 0)
