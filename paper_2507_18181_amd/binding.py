@@ -148,9 +148,12 @@ class SpecasrError(RuntimeError):
 
 def _i32(a):
     """What a pointer to int32 takes for a numpy int32 array: a ctypes array over its memory, which keeps it alive (a
-    quarter of the time of a cast pointer)."""
+    quarter of the time of a cast pointer).  The library reads the elements one behind the other, so a strided or
+    transposed array is refused: a pointer to it would name other elements."""
     if a is None:
         return None
+    if not a.flags.c_contiguous:
+        raise ValueError("host arrays must be C-contiguous")
     if a.size and a.flags.writeable:
         return (C.c_int32 * a.size).from_buffer(a)
     return a.ctypes.data_as(C.POINTER(C.c_int32))

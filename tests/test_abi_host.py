@@ -57,6 +57,29 @@ def test_struct_sizes_match_header_layout():
     assert C.sizeof(B.specasr_out) == 5 * 8
 
 
+def test_host_arrays_are_passed_as_they_lie_in_memory(lib):
+    """make_out and specasr_prefill take a pointer to the caller's memory; an array that does not lie there one element
+    behind the other is refused (the others assert the same)."""
+    base = np.arange(12, dtype=np.int32).reshape(3, 4)
+    fixed = base.copy()
+    fixed.flags.writeable = False
+    for a in (base, base[1:], base[1], base[:1, :1], fixed):
+        o = B.make_out(a, a, a, a)
+        for p in (o.argmax, o.path, o.accept_len, o.next_token):
+            assert C.addressof(p.contents) == a.ctypes.data and p[:a.size] == a.ravel().tolist()
+    o = B.make_out(base, base, base, base)
+    base[0, 0] = 77
+    assert o.path[0] == 77   # no copy
+    kv = B.make_kv(FAKE, FAKE, 100, np.zeros(1, np.int32))
+    one = np.ones(1, np.int32)
+    for a in (base.T, base[:, :2], base[:, 1], base[::2], fixed.T, fixed[:, 1]):
+        with pytest.raises(ValueError):
+            B.make_out(base, a, base, base)
+        for args in ((a, None, None, one, 4, None), (base, None, None, a, 4, None), (base, None, None, one, 4, a)):
+            with pytest.raises(ValueError):
+                B.specasr_prefill(None, kv, *args, None, 0)
+
+
 def test_create_rejects_bad_configs(lib):
     cfg = wl.MODELS["tiny"]
     sw, keep = _fake_weights(cfg)
