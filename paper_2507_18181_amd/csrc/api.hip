@@ -694,7 +694,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       if (!fits(mp)) mp = MidPlan();
       const int slices = mp.a > 0 ? mp.S * (mp.a == 3 && mp.b == 3 ? 4 : 8) : pls[i]->pair > 0 ? 2 : pls[i]->n_splits;
       other = mp.a > 0 ? mp.cost_us : pls[i]->pair > 0 ? pair_us : other;
-      const MidPlan tall = plan_mid_tall(pm[i]->n_bands, pm[i]->ksteps, R, mp, slices, other, i == 2, ctx->n_cu);
+      const MidPlan tall = plan_mid_tall(pm[i]->n_bands, pm[i]->ksteps, R, slices, other, i == 2, ctx->n_cu);
       if (fits(tall)) mp = tall;
       if (mp.a == 0) continue;
       pls[i]->mid = mp;
@@ -749,7 +749,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       (sl_gu.hb && !slice_shape_built(kSliceSwiglu, sl_gu.hb, sl_gu.nc)) || (sl_dn.hb && !slice_shape_built(kSlicePartial, sl_dn.hb, sl_dn.nc)))
     return SPECASR_E_UNSUPPORTED;
   const RowNorm nrm16{ssq, d / 16, d, md.rms_eps};  // statistics as the o projection's epilogue leaves them
-  if (ctx->tune.debug) {  // the kernel of every projection, with its tile (half-bands x 16 rows, bands x 32 rows)
+  if (ctx->tune.debug) {  // the kernel of every projection, with its tile (half-bands x 16 rows, 0: 8; bands x 32 rows)
     const GemmPlan *pls[5] = {&pl_qkv, &pl_o, &pl_gu, &pl_dn, &pl_lm};
     const SlicePlan none, *sl[5] = {&sl_qkv, &sl_o, &sl_gu, &sl_dn, &none};
     const char *nm[5] = {"qkv", "o", "gate_up", "down", "lm_head"};
@@ -757,13 +757,12 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
     for (int i = 0; i < 5; ++i) {
       char k[32];
       int S = pls[i]->n_splits;
-      if (sl[i]->hb) { snprintf(k, sizeof k, "slice %dx%d", sl[i]->hb, sl[i]->nc); S = sl[i]->S; }
+      if (sl[i]->hb) { snprintf(k, sizeof k, "slice %dx%d", sl[i]->hb, slice_groups_launched(sl[i]->nc, R)); S = sl[i]->S; }
       else if (pls[i]->mid.a) snprintf(k, sizeof k, "mid %dx%d", pls[i]->mid.a, pls[i]->mid.b);
-      else if (pls[i]->pair) snprintf(k, sizeof k, "pair %dx4", pls[i]->pair);
+      else if (pls[i]->pair) { snprintf(k, sizeof k, "pair %dx4", pls[i]->pair); S = 1; }
       else if (wide) snprintf(k, sizeof k, "wide");
       else snprintf(k, sizeof k, "skinny %d", pls[i]->lw);
-      const bool twos = !sl[i]->hb && pls[i]->mid.tall > pls[i]->mid.a;  // two of the plan's tiles per workgroup
-      fprintf(stderr, "[specasr] plan %s rows=%d bands=%d ksteps=%d: %s, %d splits%s\n", nm[i], R, pm[i]->n_bands, pm[i]->ksteps, k, S, twos ? ", 6 bands each" : "");
+      fprintf(stderr, "[specasr] plan %s rows=%d bands=%d ksteps=%d: %s, %d splits\n", nm[i], R, pm[i]->n_bands, pm[i]->ksteps, k, S);
     }
   }
   const BeginPlanes first{(const uint16_t *)ctx->layers[0].attn_norm, hb, hb_lo, nb, ssq, nrm.n_slab};

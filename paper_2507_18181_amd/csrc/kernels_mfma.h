@@ -15,7 +15,6 @@ struct PackedMatrix {
 
 struct MidPlan {
   int a = 0, b = 0, S = 1;  // bands x row groups per workgroup, k-splits; a = 0: not this kernel
-  int tall = 0;             // where > 0, so many bands per workgroup: a, or two of the plan's tiles
   double cost_us = 0;       // as its planner estimates it, or of the other kernel where a = 0
 };
 
@@ -51,7 +50,7 @@ void launch_gemm_wide_pair(const PackedMatrix &W, const uint16_t *Xp, int rows, 
 // a few hundred rows (kernels_mid.hip)
 hipError_t gemm_mid_set_lds_limit();
 MidPlan plan_mid(int n_bands, int ksteps, int rows, double other_us, bool swiglu, int n_cu);
-MidPlan plan_mid_tall(int n_bands, int ksteps, int rows, const MidPlan &mid, int slices, double other_us, bool swiglu, int n_cu);
+MidPlan plan_mid_tall(int n_bands, int ksteps, int rows, int slices, double other_us, bool swiglu, int n_cu);
 double wide_gemm_estimate(int n_bands, int ksteps, int rows, int splits, bool swiglu, int n_cu);
 // nrm == nullptr: partial sums; otherwise (gate|up) the planes of silu(gate) * up
 void launch_gemm_mid(const PackedMatrix &W, const uint16_t *Xp, int rows, float *part, const MidPlan &pl, const RowNorm *nrm,

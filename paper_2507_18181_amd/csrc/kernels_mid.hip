@@ -273,16 +273,17 @@ MidPlan plan_mid(int n_bands, int ksteps, int rows, double other_us, bool swiglu
   return best;
 }
 
-// Six or seven bands per workgroup instead of the plan's kernel (`slices`: its parts of k, `other_us`: its estimate; `mid`: its
-// small-tile plan, if any), or a = 0.  A wavefront with 6 x 3 tiles loads 12 KB per 36 MFMAs where one with 3 x 3 loads 9 per
-// 18, and there is half the number of workgroups, in one round where it took two.  More than 64 rows, where the rows fill three groups.
+// Six or seven bands per workgroup instead of the plan's kernel (`slices`: its parts of k, `other_us`: its estimate), or a = 0.
+// A wavefront with 6 x 3 tiles loads 12 KB per 36 MFMAs where one with 3 x 3 loads 9 per 18, and there is half the number of
+// workgroups, in one round where it took two.  More than 64 rows, where the rows fill three groups.
 // Measured, us: 1.1B gate|up, 384 rows 51.8 (3 x 3, two rounds) -> 38.7, 192 rows 31.0 (one round) against 36.8 here; 7B q|k|v, 300
 // rows 94 (tiled, split) -> 64, 810 rows 163 + 8 for the second partial sum -> 147 (7 bands: 495 workgroups where 6 have 576);
-// 13B down, 192 rows 65 -> 58.  In the model, ms: 1.1B 16 x 24 nodes 3.55 -> 3.27, prefill of 330 2.89 -> 2.69, of 900 6.18 -> 5.67; 7B
-// prefill of 192 7.80 -> 6.93, of 384 11.27 -> 10.62, of 810 22.17 -> 21.48.  Costs fitted to these: 5, and per round 5 and 0.215 per k-step (7 bands 0.24); 0.12 per MB of partial sums for
-// the reader.  The other kernels' estimates are less exact, so 10 % is asked for.  k is cut into 4 slices per split, and the
-// sums' chains may not get longer than they were: no fewer slices than the other plan's.
-MidPlan plan_mid_tall(int n_bands, int ksteps, int rows, const MidPlan &mid, int slices, double other_us, bool swiglu, int n_cu) {
+// 13B down, 192 rows 65 -> 58.  In the model, ms: 1.1B 16 x 24 nodes 3.55 -> 3.27, prefill of 330 2.89 -> 2.69, of 900 6.18 ->
+// 5.67; 7B prefill of 192 7.80 -> 6.93, of 384 11.27 -> 10.62, of 810 22.17 -> 21.48.  Costs fitted to these: 5, and per round 5
+// and 0.215 per k-step (7 bands 0.24); 0.12 per MB of partial sums for the reader.  The other kernels' estimates are less exact,
+// so 10 % is asked for.  k is cut into 4 slices per split, and the sums' chains may not get longer than they were: no fewer
+// slices than the other plan's.
+MidPlan plan_mid_tall(int n_bands, int ksteps, int rows, int slices, double other_us, bool swiglu, int n_cu) {
   MidPlan best;
   double limit = 0.9 * other_us;
   const int64_t n_mt = (rows + 95) / 96;
@@ -294,12 +295,11 @@ MidPlan plan_mid_tall(int n_bands, int ksteps, int rows, const MidPlan &mid, int
       const double cost = 5.0 + rounds * ((double)ksteps / S * (a == 7 ? 0.24 : 0.215) + 5.0) + (swiglu ? 0.0 : S * out_mb * 0.12);
       if (cost >= limit) continue;
       limit = cost;
-      best.a = best.tall = a;
+      best.a = a;
       best.b = 3;
       best.S = S;
       best.cost_us = cost;
     }
-  if (best.a == 6 && mid.a == 3 && mid.b == 3 && mid.S == best.S) best.a = 3;  // the same tiles and slices, two tiles per wavefront
   return best;
 }
 
@@ -322,16 +322,16 @@ void launch_gemm_mid(const PackedMatrix &W, const uint16_t *Xp, int rows, float 
   a.rows = rows; a.rows_pad = part_rows_pad(rows); a.n_bands = W.n_bands; a.ksteps = W.ksteps; a.nb = rows <= 64 ? 2 : wide_row_groups(rows); a.S = pl.S;
   if (nrm != nullptr) {  // SwiGLU epilogue
     a.nrm = *nrm; a.t = t; a.t_lo = t_lo;
-    if (pl.tall == 7) launch_mid_t<7, 3, 2, 4, true>(a, st, ev0, ev1);
-    else if (pl.tall == 6) launch_mid_t<6, 3, 3, 4, true>(a, st, ev0, ev1);
+    if (pl.a == 7) launch_mid_t<7, 3, 2, 4, true>(a, st, ev0, ev1);
+    else if (pl.a == 6) launch_mid_t<6, 3, 3, 4, true>(a, st, ev0, ev1);
     else if (rows <= 64 && pl.a == 2) launch_mid_t<2, 2, 4, 8, true, true>(a, st, ev0, ev1);
     else if (rows <= 64) launch_mid_t<3, 2, 3, 8, true, true>(a, st, ev0, ev1);
     else if (pl.a == 2) launch_mid_t<2, 3, 3, 8, true>(a, st, ev0, ev1);
     else if (rows <= 96) launch_mid_t<3, 3, 4, 4, true, true>(a, st, ev0, ev1);
     else launch_mid_t<3, 3, 4, 4, true>(a, st, ev0, ev1);
-  } else if (pl.tall == 7) {
+  } else if (pl.a == 7) {
     launch_mid_t<7, 3, 2, 4, false>(a, st, ev0, ev1);
-  } else if (pl.tall == 6) {
+  } else if (pl.a == 6) {
     launch_mid_t<6, 3, 3, 4, false>(a, st, ev0, ev1);
   } else if (rows <= 64 && pl.a == 2) {
     launch_mid_t<2, 2, 4, 8, false, true>(a, st, ev0, ev1);

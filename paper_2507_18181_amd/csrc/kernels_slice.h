@@ -40,6 +40,8 @@ struct SlicePlan {
   int S = 1;
 };
 
+// Row groups of the instance that is launched for a plan's nc: 0 stands for 8 rows with both planes in one operand.
+inline int slice_groups_launched(int nc, int rows) { return nc == 1 && rows <= 8 ? 0 : nc; }
 bool slice_shape_built(int epi, int hb, int nc);
 hipError_t gemm_slice_set_lds_limit();
 // false (nothing launched) if the plan's shape is not built

@@ -395,7 +395,7 @@ bool launch_epi(const SliceArgs &a, const SlicePlan &pl, hipStream_t st, hipEven
     if constexpr (NC == 1) {
       // up to 8 rows one operand holds both planes: half the activation loads and products (1.1B, 1 row: gate|up 12.5 ->
       // 11.8 us, q|k|v 7.0 -> 6.2, down 7.1 -> 6.6, o 6.3 -> 5.6)
-      if (a.rows <= 8) return launch_one<EPI, HB, 0>(a, st, ev0, ev1);
+      if (slice_groups_launched(NC, a.rows) == 0) return launch_one<EPI, HB, 0>(a, st, ev0, ev1);
     }
     launch_one<EPI, HB, NC>(a, st, ev0, ev1);
   });

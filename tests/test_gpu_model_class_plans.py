@@ -14,23 +14,31 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-# rows: kernel and splits of q|k|v, o, gate|up, down (slice: half-bands x 16 rows, mid: bands x 32 rows, skinny: ring)
+# rows: kernel and splits of q|k|v, o, gate|up, down (slice: half-bands x 16 rows, 0: 8 rows with both
+# activation planes in one operand; mid: bands x 32 rows, pair: bands x 32 rows, skinny: ring)
 PLANS = {
-    ("1b", 1): "slice 1x1 1, slice 1x1 1, slice 3x1 1, slice 2x1 4",
+    ("1b", 1): "slice 1x0 1, slice 1x0 1, slice 3x0 1, slice 2x0 4",
+    ("1b", 8): "slice 1x0 1, slice 1x0 1, slice 3x0 1, slice 2x0 4",
     ("1b", 16): "slice 1x1 1, slice 1x1 1, slice 3x1 1, slice 2x1 4",
     ("1b", 24): "slice 1x2 1, slice 1x2 1, slice 3x2 1, skinny 4 16",
     ("1b", 37): "skinny 8 2, skinny 4 4, slice 3x3 1, slice 4x3 8",
     ("1b", 64): "skinny 8 2, skinny 4 4, skinny 8 2, slice 4x4 8",
     ("1b", 72): "mid 2x2 3, mid 2x2 4, mid 2x3 1, mid 2x3 8",
     ("1b", 160): "mid 3x3 4, mid 2x3 4, mid 3x3 1, mid 3x3 5",
-    ("1b", 384): "mid 3x3 2, mid 2x3 2, mid 3x3 1, wide 8",
+    ("1b", 384): "mid 3x3 2, mid 2x3 2, mid 6x3 1, wide 8",
     ("1b", 1024): "wide 3, mid 3x3 1, wide 2, wide 4",
-    ("7b", 1): "slice 3x1 1, slice 1x1 1, slice 6x1 1, slice 2x1 2",
+    ("7b", 1): "slice 3x0 1, slice 1x0 1, slice 6x0 1, slice 2x0 2",
+    ("7b", 5): "slice 3x0 1, slice 1x0 1, slice 6x0 1, slice 2x0 2",
+    ("7b", 8): "slice 3x0 1, slice 1x0 1, slice 6x0 1, slice 2x0 2",
     ("7b", 32): "slice 3x2 1, slice 1x2 1, slice 6x2 1, skinny 12 8",
     ("7b", 40): "skinny 8 4, skinny 8 4, slice 6x3 1, slice 4x3 4",
     ("7b", 64): "skinny 8 4, skinny 8 4, mid 3x2 1, mid 3x2 5",
     ("7b", 87): "mid 3x3 2, mid 3x3 5, mid 3x3 1, mid 3x3 5",
     ("7b", 128): "wide 5, mid 2x2 2, wide 2, wide 13",
+    ("7b", 384): "mid 6x3 1, wide 5, pair 10x4 1, wide 5",
+    ("7b", 810): "mid 7x3 1, wide 2, pair 10x4 1, wide 2",
+    ("13b", 2): "slice 4x0 1, skinny 8 8, slice 7x0 1, slice 4x0 3",
+    ("13b", 8): "slice 4x0 1, skinny 8 8, slice 7x0 1, slice 4x0 3",
     ("13b", 9): "slice 4x1 1, skinny 8 8, slice 7x1 1, slice 4x1 3",
     ("13b", 32): "slice 4x2 1, skinny 8 8, slice 7x2 1, skinny 8 16",
     ("13b", 48): "skinny 8 8, mid 3x2 4, skinny 8 8, skinny 8 16",
@@ -39,9 +47,9 @@ PLANS = {
 
 
 @pytest.mark.parametrize("model,sizes", [
-    ("1b", (1,)), ("1b", (16,)), ("1b", (24,)), ("1b", (37,)), ("1b", (64,)), ("1b", (40, 32)), ("1b", (64, 64, 32)), ("1b", (64,) * 6), ("1b", (64,) * 16),
-    ("7b", (1,)), ("7b", (32,)), ("7b", (40,)), ("7b", (64,)), ("7b", (24, 21, 23, 19)), ("7b", (64, 64)),
-    ("13b", (9,)), ("13b", (32,)), ("13b", (48,)), ("13b", (40, 40)),
+    ("1b", (1,)), ("1b", (8,)), ("1b", (16,)), ("1b", (24,)), ("1b", (37,)), ("1b", (64,)), ("1b", (40, 32)), ("1b", (64, 64, 32)), ("1b", (64,) * 6), ("1b", (64,) * 16),
+    ("7b", (1,)), ("7b", (5,)), ("7b", (8,)), ("7b", (32,)), ("7b", (40,)), ("7b", (64,)), ("7b", (24, 21, 23, 19)), ("7b", (64, 64)), ("7b", (64,) * 6), ("7b", (64,) * 12 + (42,)),
+    ("13b", (2,)), ("13b", (8,)), ("13b", (9,)), ("13b", (32,)), ("13b", (48,)), ("13b", (40, 40)),
 ])
 def test_one_layer_against_the_oracle(model, sizes, monkeypatch, capfd):
     from paper_2507_18181_amd.runtime import Verifier
