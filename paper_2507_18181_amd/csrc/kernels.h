@@ -26,7 +26,7 @@ struct BeginPlanes {
 void launch_begin(const StepMeta &hm, int dtype, const void *tok_embed, const void *input_embeds, int max_nodes, int d, float *x, int hd,
                   float theta, float2 *cs, const BeginPlanes *pl, const int32_t *words, int32_t *dst, int n_words, hipStream_t st);
 // Input of the linears below: residual rows x [rows][d] that are normalised first, x * rsqrt(mean(x^2)+eps) * gain, either
-// by the linear itself or (wide rows, a gain that is not on 4 elements) into the scratch rows h
+// by the linear itself or (wide rows, many rows, a gain that is not on 4 elements) into the scratch rows h
 struct NormIn {
   const float *x;
   const void *gain;
@@ -34,7 +34,7 @@ struct NormIn {
   float eps;
   float *h;
 };
-bool linear_normalises(int d, const void *gain, int elem_bytes);
+bool linear_normalises(int d, const void *gain, int elem_bytes, int rows);
 // y[row][o] += sum_k W[o][k] * a[row][k]
 void launch_linear_add(int dtype, const void *W, int n_out, int n_in, const float *a, float *y, int rows, hipStream_t st);
 struct LinearJob {

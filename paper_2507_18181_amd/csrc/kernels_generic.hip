@@ -317,12 +317,17 @@ static void launch_linear_t(const LinearJob *jobs, int n, const LinearMore<T> &m
   linear_kernel<T, MODE, NORM><<<grid, 256, 0, st>>>(ls, mo, n_in, a, lda, rows, accumulate ? 1 : 0);
 }
 
+// With many rows the launch that is saved is small against the norm that every workgroup repeats.  Norm in the linear / as a
+// kernel, us per verify, fp32 (bf16 alike): d_model 256, 2 layers, 256 rows 282 / 285, 384 376 / 371, 1024 838 / 778; 512, 4
+// layers, 256 rows 870 / 866, 384 1220 / 1178, 1024 2934 / 2685; 1024, 4 layers, 512 rows 3296 / 3330, 768 4841 / 4800.
 // The linear reads the gain 4 elements at a time, rmsnorm_kernel one by one: it takes a gain that is a caller's slice off that grid.
-bool linear_normalises(int d, const void *gain, int elem_bytes) { return d <= kNormWidth && ((uintptr_t)gain & (4 * elem_bytes - 1)) == 0; }
+bool linear_normalises(int d, const void *gain, int elem_bytes, int rows) {
+  return d <= kNormWidth && rows <= (d / 2 > 256 ? d / 2 : 256) && ((uintptr_t)gain & (4 * elem_bytes - 1)) == 0;
+}
 
 template <class T, int MODE>
 static void launch_linear_norm(const LinearJob *jobs, int n, LinearMore<T> mo, const NormIn &nx, hipStream_t st) {
-  if (linear_normalises(nx.d, nx.gain, sizeof(T))) {
+  if (linear_normalises(nx.d, nx.gain, sizeof(T), nx.rows)) {
     mo.gain = (const T *)nx.gain;
     mo.eps = nx.eps;
     launch_linear_t<T, MODE, true>(jobs, n, mo, nx.d, nx.x, nx.d, nx.rows, false, st);

@@ -39,3 +39,27 @@ def test_linears_that_normalise_their_input(d_model):
         k1, v1 = ver.get_cache()
         check_tree_kv(k1[0], v1[0], L, ref, 1e-5)
     ver.close()
+
+
+@pytest.mark.parametrize("d_model,sizes", [(16, (64,) * 4), (16, (64,) * 4 + (1,)), (520, (64,) * 4 + (4,)), (520, (64,) * 4 + (5,))])
+def test_many_rows_on_both_sides_of_the_line(d_model, sizes):
+    """fp32 against the fp64 oracle at the number of rows from which the norm is a kernel of its own."""
+    from paper_2507_18181_amd.runtime import Verifier
+    cfg = dict(wl.MODELS["tiny"], n_layers=2, d_model=d_model, d_ffn=24, n_heads=3, n_kv_heads=1, head_dim=8, vocab=9)
+    w = wl.make_weights(cfg, 725, "f32")
+    rng = np.random.default_rng(726)
+    L, cap, nb = 11, 80, len(sizes)
+    om = oracle.OracleModel(cfg, w)
+    ver = Verifier(cfg, w, "f32", max_nodes=64, capacity=cap, max_batch=nb)
+    K, V = wl.seeded_cache(cfg, 727, np.full(nb, L, np.int32), cap, "f32", batch=nb)
+    ver.set_cache(K, V, [L] * nb)
+    trees = [wl.random_tree(rng, n, max_children=3) for n in sizes]
+    toks = [rng.integers(0, cfg["vocab"], n).astype(np.int32) for n in sizes]
+    fw = ver.tree_forward(toks, trees)
+    assert fw["status"] == 0
+    k1, v1 = ver.get_cache()
+    for b, n in enumerate(sizes):
+        ref = om.tree_forward(np.ascontiguousarray(K[b]), np.ascontiguousarray(V[b]), L, toks[b], trees[b])
+        assert row_rel_err(fw["logits"][b].cpu().numpy()[:n], ref["logits"]).max() <= 1e-5
+        check_tree_kv(k1[b], v1[b], L, ref, 1e-5)
+    ver.close()

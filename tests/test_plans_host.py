@@ -23,11 +23,13 @@ def test_only_shapes_that_a_planner_can_choose_are_built(built):
     assert got == want
 
 
-def test_linears_normalise_only_with_a_gain_on_four_elements():
-    """The linear reads the gain in vectors; any other address goes to the kernel that reads it element by element."""
-    f = B.load_library()._ZN7specasr17linear_normalisesEiPKvi
-    f.restype, f.argtypes = C.c_bool, [C.c_int, C.c_void_p, C.c_int]
+def test_where_linears_normalise_their_input():
+    """Up to 1024 features, up to 256 rows or half the features, and with a gain on four elements: the linear reads it in vectors,
+    any other address goes to the kernel that reads it element by element."""
+    f = B.load_library()._ZN7specasr17linear_normalisesEiPKvii
+    f.restype, f.argtypes = C.c_bool, [C.c_int, C.c_void_p, C.c_int, C.c_int]
     for elem in (2, 4):
         for off in range(0, 8 * elem, elem):
-            for d, narrow in ((8, True), (1024, True), (1032, False)):
-                assert f(d, 4096 + off, elem) == (narrow and off % (4 * elem) == 0)
+            for d, most in ((8, 256), (256, 256), (512, 256), (520, 260), (1024, 512), (1032, 0)):
+                for rows in (1, 256, 257, 260, 261, 512, 513, 1024):
+                    assert f(d, 4096 + off, elem, rows) == (rows <= most and off % (4 * elem) == 0)
