@@ -132,8 +132,10 @@ __global__ void rmsnorm_kernel(const float *x, const T *g, int d, float eps, flo
 // 96).  n_in % 4 == 0.  On a tiny model a launch costs more than its work, so what stands between two products is
 // done by them: gate and up of one feature belong to one wavefront, which applies SwiGLU; q, k and v are one launch
 // whose wavefronts own the two halves of a rotary pair, rotate it and write k and v to the cache; the logits go to the
-// caller's array; and up to kNormWidth input features a workgroup normalises its 8 rows itself, in LDS.  Bound by the
-// chain of launches, about 7 us each: tiny fp32 step of 8 nodes 178 -> 148 us (15 launches for 24).
+// caller's array; and up to kNormWidth input features and a few hundred rows a workgroup normalises its 8 rows itself, in
+// LDS.  Bound by the chain of launches, about 7 us each: tiny fp32 verify of 8 nodes 170 us with a kernel for each of these
+// (24 launches), now 138 (15, the first and last kernels of a call merged as well).
+
 // Sums 16 values over the 64 lanes; every lane returns the sum of value 8*b5 + 4*b4 + 2*b3 + b2 (bits of its
 // index).
 __device__ __forceinline__ float wave_sum16(float (&v)[16], int lane) {
@@ -802,8 +804,9 @@ void launch_argmax_accept(const StepMeta &m, const float *logits, int max_nodes,
 // kCompactHeads KV heads per block.  Since path is strictly increasing with path[k] >= k, a destination slot may be another
 // move's source: every source row of a head is read into registers, the block synchronises, and only then is anything
 // written.  Usually the accepted path is the front of the trunk and nothing moves (path[len - 1] == len - 1 says so):
-// then the launch is bound by its number of blocks (one per head: 4 sequences on the 7B model 8192 blocks, 21 us;
-// 1024: 6 us).
+// then the launch is bound by its number of blocks.  7B class, one block per head -> this: 4 sequences, nothing moves 22.2
+// -> 2.3 us, 19 of 64 rows move 45 -> 16; one sequence 7.5 -> 1.9, 12.4 -> 8.3.  (Where few heads are left to few blocks, moving
+// takes a little longer: 1.1B class, one sequence 4.6 -> 4.9, 62 rows 5.0 -> 6.4.)
 constexpr int kCompactHeads = 8;
 typedef __attribute__((ext_vector_type(4))) uint32_t mv16_t;  // one 16-byte unit of a cache row
 
