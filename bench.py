@@ -4,7 +4,7 @@
 A "step" is one whole verification round through the C ABI (specasr_verify_tree): tree
 preprocessing, embedding gather, every decoder layer over the tree tokens against the resident
 KV cache, LM head + per-node argmax, greedy acceptance, in-place KV compaction, and the
-device-to-host copy of the results.  Weights, KV cache and tree live in HBM before the timed
+results' way to host memory.  Weights, KV cache and tree live in HBM before the timed
 region starts; kv_len is reset on the host between steps.
 
 With `--workload draft_1b_recycle` the step is the draft-side tree forward instead
