@@ -153,7 +153,8 @@ void specasr_destroy(specasr_ctx *ctx);
 /* Bytes of device workspace a call with `batch` sequences needs (256-byte aligned
  * base required).  Depends on the model, max_nodes and batch only.  On the bf16 MFMA path it
  * covers one set of buffers per internal stream plus one set for passes over up to
- * max(16, batch) x max_nodes rows (prefill, large batches). */
+ * max(16, batch) x max_nodes rows (prefill, large batches) and, for models up to d_model 2048, the
+ * hand-over buffers of forwards whose layers run in one launch (up to 16 nodes of one sequence). */
 size_t specasr_workspace_bytes(const specasr_ctx *ctx, int32_t batch);
 
 /* One whole verification round (Sec. II-B, Sec. IV-C): tree forward, per-node
@@ -270,7 +271,8 @@ specasr_status specasr_commit(specasr_ctx *ctx, specasr_kv *kv, const int32_t *n
 int32_t specasr_uses_mfma(const specasr_ctx *ctx, int32_t rows);
 
 const char *specasr_strerror(specasr_status s);
-/* hipError_t value of the last failing HIP call seen by this context (0 if none). */
+/* hipError_t value of the last failing HIP call seen by this context (0 if none); hipErrorLaunchTimeOut
+ * with SPECASR_E_HIP: a wait inside an earlier forward ran out (two seconds), its results are void. */
 int32_t specasr_last_hip_error(const specasr_ctx *ctx);
 /* Library/ABI version, bumped when a signature or struct changes. */
 int32_t specasr_abi_version(void);

@@ -16,6 +16,7 @@
 #include "../../include/specasr_profile.h"
 #include "kernels.h"
 #include "kernels_mfma.h"
+#include "kernels_one.h"
 #include "kernels_slice.h"
 
 using namespace specasr;
@@ -58,12 +59,14 @@ struct Tuning {
   int gemm_splits[5] = {0, 0, 0, 0, 0};      // SPECASR_GEMM_SPLITS "qkv,o,gate_up,down,lm_head": k-splits of the skinny GEMMs (0: planner)
   int wide_splits[5] = {0, 0, 0, 0, 0};      // SPECASR_WIDE_SPLITS: the same for the tiled GEMM of wide passes
   int attn_chunk = 0;                        // SPECASR_ATTN_CHUNK: lower bound of the attention key chunk
+  int one_polls = kOnePolls;                 // SPECASR_ONE_POLLS: bound of the waits of a forward in one launch, 0: always the chain of kernels
   bool debug = false;                        // SPECASR_DEBUG: print kernel plans and host timings to stderr
   void read_env() {
     if (const char *e = getenv("SPECASR_LANES")) { const int v = atoi(e); lanes = v < 1 ? 1 : v > kMaxLanes ? kMaxLanes : v; }
     if (const char *e = getenv("SPECASR_GEMM_SPLITS")) sscanf(e, "%d,%d,%d,%d,%d", &gemm_splits[0], &gemm_splits[1], &gemm_splits[2], &gemm_splits[3], &gemm_splits[4]);
     if (const char *e = getenv("SPECASR_WIDE_SPLITS")) sscanf(e, "%d,%d,%d,%d,%d", &wide_splits[0], &wide_splits[1], &wide_splits[2], &wide_splits[3], &wide_splits[4]);
     if (const char *e = getenv("SPECASR_ATTN_CHUNK")) attn_chunk = atoi(e);
+    if (const char *e = getenv("SPECASR_ONE_POLLS")) one_polls = atoi(e);
     debug = getenv("SPECASR_DEBUG") != nullptr;
   }
 };
@@ -75,6 +78,7 @@ struct specasr_ctx {
   std::vector<void *> owned;  // device allocations made by create
   int col_k = 0, col_v = 0;  // column offsets inside the concatenated q|k|v output
   bool paired = false;       // query and key heads packed in rotary pairs (launch_repack_rope)
+  OneLayer *one_layers = nullptr;  // device table for forwards in one launch (nullptr: the model has none)
   size_t part_floats = 0;
   size_t wide_part_floats = 0;  // partial-sum buffer of a wide prefill pass, in floats (0: no wide path)
   // stage profiling (benchmark aid)
@@ -95,6 +99,7 @@ struct specasr_ctx {
   int32_t *out_host = nullptr;  // pinned, results of verify_tree
   int32_t *out_dev = nullptr;   // the same, as the device sees it
   size_t out_host_words = 0;
+  uint32_t *gave_up = nullptr, *gave_up_dev = nullptr;  // pinned word that a forward in one launch sets when a wait ran out
   int32_t last_hip = 0;
   int device = 0;
   int n_cu = 256;  // compute units = workgroups of the persistent-style GEMM grid
@@ -424,6 +429,11 @@ specasr_status ensure_staging(specasr_ctx *ctx) {
   ctx->out_host_words = (size_t)c.max_batch * c.max_nodes * 2 + (size_t)c.max_batch * 2;
   if (!ctx->out_host) HIP_TRY(ctx, hipHostMalloc((void **)&ctx->out_host, ctx->out_host_words * 4, kPinned));
   if (!ctx->out_dev) HIP_TRY(ctx, hipHostGetDevicePointer((void **)&ctx->out_dev, ctx->out_host, 0));
+  if (!ctx->gave_up) {
+    HIP_TRY(ctx, hipHostMalloc((void **)&ctx->gave_up, 4, kPinned));
+    *ctx->gave_up = 0;
+  }
+  if (!ctx->gave_up_dev) HIP_TRY(ctx, hipHostGetDevicePointer((void **)&ctx->gave_up_dev, ctx->gave_up, 0));
   ctx->staging_ready = true;
   return SPECASR_OK;
 }
@@ -439,10 +449,19 @@ specasr_status next_slot(specasr_ctx *ctx, Staging **out) {
   return SPECASR_OK;
 }
 
+// A wait inside an earlier forward ran out (its results are void): reported once, by the call that sees it.
+specasr_status check_gave_up(specasr_ctx *ctx) {
+  if (ctx->gave_up == nullptr || *(volatile uint32_t *)ctx->gave_up == 0) return SPECASR_OK;
+  *(volatile uint32_t *)ctx->gave_up = 0;
+  ctx->last_hip = (int32_t)hipErrorLaunchTimeOut;
+  return SPECASR_E_HIP;
+}
+
 // Lay the metadata block out in a pinned staging slot, where the first kernel of the call reads it.  staged() has to
 // follow that kernel: the slot is not written again before it has ended.
 specasr_status stage_meta(specasr_ctx *ctx, HostStep &hs) {
-  specasr_status rc = next_slot(ctx, &hs.staged);
+  specasr_status rc = check_gave_up(ctx);
+  if (rc == SPECASR_OK) rc = next_slot(ctx, &hs.staged);
   if (rc != SPECASR_OK) return rc;
   memcpy(hs.staged->host, hs.words.data(), hs.words.size() * 4);
   return SPECASR_OK;
@@ -465,10 +484,14 @@ int ws_lanes(const specasr_ctx *ctx, int batch) {
   return n < 2 ? 2 : n;  // two lanes at least: consecutive prefill chunks of one sequence overlap
 }
 
+// Scratch of a forward in one launch follows the lanes' and the wide buffers.
+size_t one_offset(const specasr_ctx *ctx, int batch) { return ws_layout(ctx, batch).total * ws_lanes(ctx, batch) + ws_layout_wide(ctx, batch).total; }
+size_t ws_bytes(const specasr_ctx *ctx, int batch) { return one_offset(ctx, batch) + (ctx->one_layers ? one_launch_bytes(ctx->md) : 0); }
+
 specasr_status check_ws(const specasr_ctx *ctx, const void *ws, size_t bytes, int batch) {
   if (!ws) return SPECASR_E_WORKSPACE;
   if (((uintptr_t)ws & 255u) != 0) return SPECASR_E_WORKSPACE;
-  if (bytes < ws_layout(ctx, batch).total * ws_lanes(ctx, batch) + ws_layout_wide(ctx, batch).total) return SPECASR_E_WORKSPACE;
+  if (bytes < ws_bytes(ctx, batch)) return SPECASR_E_WORKSPACE;
   return SPECASR_OK;
 }
 
@@ -522,6 +545,7 @@ struct ReadOut {
   // Read-out only for rows >= first_row (at most 64 of them): a prefill pass over several pieces
   // of one sequence wants the token after its last position, not a vocabulary row per position.
   int first_row = 0;
+  char *one = nullptr;  // scratch of a forward in one launch, where the call is a single sequence's forward
   // nothing requested: the forward only fills the cache (all but the last pass of a prefill)
   bool none() const { return !argmax && !logits && !top2; }
 };
@@ -749,12 +773,18 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       (sl_gu.hb && !slice_shape_built(kSliceSwiglu, sl_gu.hb, sl_gu.nc)) || (sl_dn.hb && !slice_shape_built(kSlicePartial, sl_dn.hb, sl_dn.nc)))
     return SPECASR_E_UNSUPPORTED;
   const RowNorm nrm16{ssq, d / 16, d, md.rms_eps};  // statistics as the o projection's epilogue leaves them
+  // Few rows of one sequence: all layers in one launch.  Forced plans and stage timings are about the kernels of the chain.
+  OnePlan one;
+  if (ro.one != nullptr && ctx->tune.one_polls > 0 && m.batch == 1 && ro.first_row == 0 && !sync.record && !sync.wait && ctx->prof_stage < 0 && ctx->tune.attn_chunk == 0 &&
+      std::all_of(ctx->tune.gemm_splits, ctx->tune.gemm_splits + 4, [](int v) { return v == 0; }))
+    one = plan_one_launch(md, R, m.kv_len0);
   if (ctx->tune.debug) {  // the kernel of every projection, with its tile (half-bands x 16 rows, 0: 8; bands x 32 rows)
     const GemmPlan *pls[5] = {&pl_qkv, &pl_o, &pl_gu, &pl_dn, &pl_lm};
     const SlicePlan none, *sl[5] = {&sl_qkv, &sl_o, &sl_gu, &sl_dn, &none};
     const char *nm[5] = {"qkv", "o", "gate_up", "down", "lm_head"};
     const PackedMatrix *pm[5] = {&p0.qkv, &p0.o, &p0.gu, &p0.down, &ctx->lm_head};
-    for (int i = 0; i < 5; ++i) {
+    if (one.rows > 0) fprintf(stderr, "[specasr] plan layers rows=%d: one launch, planes of %d rows, %d key chunks\n", R, one.rp, one.n_chunks);
+    for (int i = one.rows > 0 ? 4 : 0; i < 5; ++i) {
       char k[32];
       int S = pls[i]->n_splits;
       if (sl[i]->hb) { snprintf(k, sizeof k, "slice %dx%d", sl[i]->hb, slice_groups_launched(sl[i]->nc, R)); S = sl[i]->S; }
@@ -765,14 +795,36 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
       fprintf(stderr, "[specasr] plan %s rows=%d bands=%d ksteps=%d: %s, %d splits\n", nm[i], R, pm[i]->n_bands, pm[i]->ksteps, k, S);
     }
   }
-  const BeginPlanes first{(const uint16_t *)ctx->layers[0].attn_norm, hb, hb_lo, nb, ssq, nrm.n_slab};
+  BeginPlanes first{(const uint16_t *)ctx->layers[0].attn_norm, hb, hb_lo, nb, ssq, nrm.n_slab};
+  if (one.rows > 0) {
+    char *ll = ro.one + kOneCtl;
+    first.rp = one.rp;
+    first.hb = (uint16_t *)(ll + one.lay.hb0);
+    first.hb_lo = first.hb + (size_t)d * one.rp;
+    first.ssq = (float *)(ll + one.lay.s0);
+    first.fill = (uint4 *)(ll + one.lay.q);  // all regions behind what begin_kernel itself writes
+    first.fill_units = (uint32_t)(((size_t)md.n_layers * one.lay.bytes - one.lay.q) / 16);
+    first.fill_blocks = (int)std::min<size_t>(512, (first.fill_units + 2047) / 2048);
+    first.ctl = (uint32_t *)ro.one;
+    x = (float *)(ll + one.lay.x0);
+  }
   const specasr_status begun = begin_forward(ctx, hs, tree, ws, L, 1, x, cs, &first, st);
   if (begun != SPECASR_OK) return begun;
+  if (one.rows > 0) {
+    OneArgs a{};
+    a.layers = ctx->one_layers; a.n_layers = md.n_layers; a.d = d; a.dq = dq; a.F = F; a.H = md.n_heads; a.Hkv = md.n_kv_heads;
+    a.col_k = ctx->col_k; a.col_v = ctx->col_v; a.rows = R; a.rp = one.rp; a.L = m.kv_len0; a.n_rg = one.n_rg;
+    a.n_chunks = one.n_chunks; a.chunk_tiles = one.chunk_tiles; a.n_half_qkv = 2 * p0.qkv.n_bands; a.n_half_gu = F / 8;
+    a.eps = md.rms_eps; a.qscale = tree_attention_qscale(md.head_dim); a.anc = m.anc; a.cs = cs;
+    a.kc = (uint16_t *)kv->k; a.vc = (uint16_t *)kv->v; a.g = g; a.ll = ro.one + kOneCtl; a.lay = one.lay; a.ctl = (uint32_t *)ro.one;
+    a.gave_up = ctx->gave_up_dev; a.polls = ctx->tune.one_polls; a.hb = hb; a.hb_lo = hb_lo; a.ssq = ssq;
+    launch_one(a, ctx->n_cu, st);
+  }
   int pending = 0, pending_ld = 0;  // partial sums of the previous down projection, not yet added to x
   // kv_len, row_start, n_nodes of the sequences as build_step laid them out
   const int32_t *seq_words = hs.words.data() + 10 * (size_t)hs.batch * ctx->cfg.max_nodes;
   const int prof_layer = (int)(ctx->prof_calls++ % md.n_layers);
-  for (int l = 0; l < md.n_layers; ++l) {
+  for (int l = 0; l < md.n_layers && one.rows == 0; ++l) {
     const bool pl = l == prof_layer;
     const specasr_layer_weights &lw = ctx->layers[l];
     const PackedLayer &pk = ctx->packed[l];
@@ -854,13 +906,14 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
                            (float2 *)(ws + L.blk), ro.records ? nullptr : argmax_dev, st);
     return SPECASR_OK;
   }
-  launch_residual_gain(x, part, pending, R, pending_ld, ctx->w.final_norm, d, hb, hb_lo, nb, ssq, st);
+  if (one.rows == 0) launch_residual_gain(x, part, pending, R, pending_ld, ctx->w.final_norm, d, hb, hb_lo, nb, ssq, st);
+  const RowNorm &nrm_out = one.rows > 0 ? nrm16 : nrm;
   gemm_stage(ctx, SPECASR_STAGE_LM_HEAD, true, ctx->lm_head, hb, R, part, pl_lm, st);
   if (ro.top2)
-    launch_top2(m, part, true, pl_lm.n_splits, ctx->lm_head.ldo, nrm, V, ctx->cfg.max_nodes, logits_dev,
+    launch_top2(m, part, true, pl_lm.n_splits, ctx->lm_head.ldo, nrm_out, V, ctx->cfg.max_nodes, logits_dev,
                 (float *)(ws + L.top2_v), (int *)(ws + L.top2_i), ro.top2, ro.prob, argmax_dev, st);
   else
-    launch_logits_argmax(m, part, pl_lm.n_splits, ctx->lm_head.ldo, nrm, V, ctx->cfg.max_nodes, logits_dev,
+    launch_logits_argmax(m, part, pl_lm.n_splits, ctx->lm_head.ldo, nrm_out, V, ctx->cfg.max_nodes, logits_dev,
                          (float2 *)(ws + L.blk), ro.records ? nullptr : argmax_dev, st);
   return SPECASR_OK;
 }
@@ -933,6 +986,7 @@ specasr_status build_packed(specasr_ctx *ctx) {
   HIP_TRY(ctx, gemm_skinny_set_lds_limit());
   HIP_TRY(ctx, gemm_slice_set_lds_limit());
   HIP_TRY(ctx, gemm_mid_set_lds_limit());
+  HIP_TRY(ctx, one_launch_set_lds_limit());
   {
     int dev = 0, cus = 0;
     HIP_TRY(ctx, hipGetDevice(&dev));
@@ -1003,6 +1057,17 @@ specasr_status build_packed(specasr_ctx *ctx) {
     // a pass of few short pieces (<= 64 rows in all) runs on the skinny kernels in the same buffers
     if (wb < 64 * bound) wb = 64 * bound;
     ctx->wide_part_floats = wb;
+  }
+  if (one_launch_model(ctx->md, ctx->n_cu)) {
+    std::vector<OneLayer> table(c.n_layers);
+    for (int l = 0; l < c.n_layers; ++l) {
+      const PackedLayer &pk = ctx->packed[l];
+      const void *next = l + 1 < c.n_layers ? ctx->layers[l + 1].attn_norm : ctx->w.final_norm;
+      table[l] = OneLayer{pk.qkv.data, pk.o.data, pk.gu.data, pk.down.data, (const uint16_t *)ctx->layers[l].ffn_norm, (const uint16_t *)next};
+    }
+    HIP_TRY(ctx, hipMalloc((void **)&ctx->one_layers, table.size() * sizeof(OneLayer)));
+    ctx->owned.push_back(ctx->one_layers);
+    HIP_TRY(ctx, hipMemcpy(ctx->one_layers, table.data(), table.size() * sizeof(OneLayer), hipMemcpyHostToDevice));
   }
   ctx->fast = true;
   return SPECASR_OK;
@@ -1183,6 +1248,7 @@ void specasr_destroy(specasr_ctx *ctx) {
     if (ctx->stage[i].done) (void)hipEventDestroy(ctx->stage[i].done);
   }
   if (ctx->out_host) (void)hipHostFree(ctx->out_host);
+  if (ctx->gave_up) (void)hipHostFree(ctx->gave_up);
   for (void *p : ctx->owned) (void)hipFree(p);
   if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
   for (auto &set : ctx->layer_ev)
@@ -1197,7 +1263,7 @@ void specasr_destroy(specasr_ctx *ctx) {
 
 size_t specasr_workspace_bytes(const specasr_ctx *ctx, int32_t batch) {
   if (!ctx || batch < 1 || batch > ctx->cfg.max_batch) return 0;
-  return ws_layout(ctx, batch).total * ws_lanes(ctx, batch) + ws_layout_wide(ctx, batch).total;
+  return ws_bytes(ctx, batch);
 }
 
 specasr_status specasr_tree_forward(specasr_ctx *ctx, specasr_kv *kv, const specasr_tree *tree,
@@ -1231,6 +1297,7 @@ specasr_status specasr_tree_forward(specasr_ctx *ctx, specasr_kv *kv, const spec
     ReadOut ro;
     ro.argmax = argmax_dev + grp.s0 * MN;
     ro.logits = logits_dev ? logits_dev + grp.s0 * MN * ctx->cfg.vocab : nullptr;
+    if (kv->batch == 1 && ctx->one_layers) ro.one = ws + one_offset(ctx, 1);
     s = forward_common(ctx, &grp.kv, &grp.tree, ro, wl, Lg, hs, lanes.stream(gi), LayerSync(), wide);
     if (s != SPECASR_OK) return s;
   }
@@ -1269,6 +1336,7 @@ specasr_status specasr_tree_forward_top2(specasr_ctx *ctx, specasr_kv *kv, const
     ro.top2 = top2_dev + grp.s0 * MN * 2;
     ro.prob = top1_prob_dev + grp.s0 * MN;
     ro.logits = logits_dev ? logits_dev + grp.s0 * MN * ctx->cfg.vocab : nullptr;
+    if (kv->batch == 1 && ctx->one_layers) ro.one = ws + one_offset(ctx, 1);
     s = forward_common(ctx, &grp.kv, &grp.tree, ro, wl, Lg, hs, lanes.stream(gi), LayerSync(), wide);
     if (s != SPECASR_OK) return s;
   }
@@ -1573,6 +1641,7 @@ specasr_status specasr_verify_tree(specasr_ctx *ctx, specasr_kv *kv, const speca
     ro.argmax = argmax_dev + grp.s0 * MN;
     ro.records = ctx->fast && (hs.rows <= 64 || wide);  // what forward_common runs on the MFMA path
     ro.logits = out->logits ? out->logits + grp.s0 * MN * c.vocab : nullptr;
+    if (B == 1 && ctx->one_layers) ro.one = ws + one_offset(ctx, 1);
     s = forward_common(ctx, &grp.kv, &grp.tree, ro, wl, Lg, hs, sl, LayerSync(), wide);
     if (s != SPECASR_OK) return s;
     StepMeta m = device_meta(ctx, wl, Lg, hs);
@@ -1591,6 +1660,8 @@ specasr_status specasr_verify_tree(specasr_ctx *ctx, specasr_kv *kv, const speca
   if (s != SPECASR_OK) return s;
   const auto t_enqueued = std::chrono::steady_clock::now();
   HIP_TRY(ctx, hipStreamSynchronize(st));
+  s = check_gave_up(ctx);
+  if (s != SPECASR_OK) return s;
   if (debug_timing) {  // host time spent enqueueing the step vs waiting for the GPU to finish it
     const auto t_done = std::chrono::steady_clock::now();
     fprintf(stderr, "[specasr] verify_tree: enqueue %.1f us, wait %.1f us\n",

@@ -22,6 +22,12 @@ struct BeginPlanes {
   int nb;
   float *ssq;
   int n_slab;
+  // for a forward in one launch (kernels_one.hip): rows of its planes (0: packed as above), and what is filled with ones
+  int rp = 0;
+  uint4 *fill = nullptr;
+  uint32_t fill_units = 0;
+  int fill_blocks = 0;
+  uint32_t *ctl = nullptr;
 };
 void launch_begin(const StepMeta &hm, int dtype, const void *tok_embed, const void *input_embeds, int max_nodes, int d, float *x, int hd,
                   float theta, float2 *cs, const BeginPlanes *pl, const int32_t *words, int32_t *dst, int n_words, hipStream_t st);

@@ -27,80 +27,12 @@
 // What bounds it: per 32 x 32 tile 32 MFMAs (head_dim 128; 1024 cycles) and about 170 vector
 // instructions; two wavefronts per SIMD overlap the two.
 #include "kernels.h"
+#include "attn_tile.h"
 #include "kernels_mfma.h"
 
 namespace specasr {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
-
-// The K operands of a tile (16-byte LDS reads) with their wait, and transposing LDS reads with theirs.  As assembly, because for ordinary LDS reads the compiler waits for every direct-to-LDS load in
-// flight, those of the other buffer among them.  Transposing read: 16 lanes give the addresses of 4 rows x 16 columns (8 bytes
-// each) and get 4 rows of one column each.
-template <int N>
-__device__ __forceinline__ void read_k(u32x4 (&k)[N], const uint32_t (&a)[N]) {
-  if constexpr (N == 8)
-    asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
-                 "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&v"(k[0]), "=&v"(k[1]), "=&v"(k[2]), "=&v"(k[3]), "=&v"(k[4]), "=&v"(k[5]), "=&v"(k[6]), "=&v"(k[7])
-                 : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]) : "memory");
-  else
-    asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&v"(k[0]), "=&v"(k[1]), "=&v"(k[2]), "=&v"(k[3]) : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]) : "memory");
-}
-// V^T quads of (cb, part) = 0 .. N-1 for the keys OFF / row size .. +15 of the tile
-template <int N, int OFF>
-__device__ __forceinline__ void read_v(u32x2 (&v)[N], const uint32_t (&a)[N]) {
-  if constexpr (N == 8)
-    asm volatile("ds_read_b64_tr_b16 %0, %8 offset:%16\n\tds_read_b64_tr_b16 %1, %9 offset:%16\n\tds_read_b64_tr_b16 %2, %10 offset:%16\n\tds_read_b64_tr_b16 %3, %11 offset:%16\n\t"
-                 "ds_read_b64_tr_b16 %4, %12 offset:%16\n\tds_read_b64_tr_b16 %5, %13 offset:%16\n\tds_read_b64_tr_b16 %6, %14 offset:%16\n\tds_read_b64_tr_b16 %7, %15 offset:%16\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
-                 : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "i"(OFF) : "memory");
-  else
-    asm volatile("ds_read_b64_tr_b16 %0, %4 offset:%8\n\tds_read_b64_tr_b16 %1, %5 offset:%8\n\tds_read_b64_tr_b16 %2, %6 offset:%8\n\tds_read_b64_tr_b16 %3, %7 offset:%8\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "i"(OFF) : "memory");
-}
-
-// a / b with inv = 1 / b: the residual of the product corrects it, 3 instructions for the 10 of a division (one tile
-// per wavefront, 1.1B: 6.5 -> 6.4 us)
-__device__ __forceinline__ float div_by(float a, float b, float inv) {
-  const float q = a * inv;
-  return fmaf(fmaf(-b, q, a), inv, q);
-}
-__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
-// maximum / sum of a value over lanes l and l ^ 32
-__device__ __forceinline__ float max_halves(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_halves(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-// 16 bytes per lane to 64 consecutive places.  Direct copies are only defined for aligned addresses; a cache that is not
-// on 16 bytes (a caller's slice of a larger tensor) goes through registers.
-template <bool DIRECT>
-__device__ __forceinline__ void load_16_to_lds(const char *src_lane, u32x4 *dst_64, int lane) {
-  if constexpr (!DIRECT) {
-    u32x4 v;
-    __builtin_memcpy(&v, src_lane, 16);
-    dst_64[lane] = v;
-    return;
-  }
-  __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src_lane, (void __attribute__((address_space(3))) *)dst_64, 16, 0, 0);
-}
-
 constexpr int kAttnWaves = 4;  // 8 were measured: 5 .. 30 % slower everywhere (more outputs to merge per workgroup)
-
-// Chunk (16 bytes) c of row r of a tile sits at chunk c ^ swizzle(r) of that row.
-template <int HD>
-__device__ __forceinline__ int swizzle(int r) {
-  return HD == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
-}
 
 // grid (8 * n_rg * ceil(n_chunks * Hkv / 8), 1, batch), block 256.  Workgroups go to the 8 XCDs
 // round-robin by their linear index, so the n_rg workgroups that stream the SAME keys for
@@ -187,26 +119,8 @@ __global__ __launch_bounds__(64 * kAttnWaves, HD == 64 ? 3 : 2) void tree_attent
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) qlo[kk] = *reinterpret_cast<const u32x4 *>(qb_lo + qoff + 16 * kk);
   }
-  float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's keys only, the halves are added at the end
-  f32x16 o[CB];
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-    for (int j = 0; j < 16; ++j) o[cb][j] = 0.f;
-
-  // LDS addresses of the operands.  K: row ql, chunk 2 kk + h.  V^T of (mm, part, cb): lane i of a group of
-  // 16 addresses row 16 mm + 8 part + 4 h + i/4, columns 32 cb + 16 (group & 1) + 4 (i%4).
-  uint32_t ka[KK];
-#pragma unroll
-  for (int kk = 0; kk < KK; ++kk) ka[kk] = (uint32_t)(uintptr_t)(lds_u32x4 *)(kb + ql * CR + (h ^ swizzle<HD>(ql) ^ (2 * kk)));
-  const int vi = lane & 15, vrow = 4 * h + (vi >> 2);
-  const int vx = (2 * ((lane >> 4) & 1) + ((vi & 3) >> 1)) ^ swizzle<HD>(vrow);
-  uint32_t va[2 * CB];  // LDS byte address of (cb, part); mm adds 16 rows
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-    for (int part = 0; part < 2; ++part)
-      va[2 * cb + part] = (uint32_t)(uintptr_t)(lds_u32x4 *)(vb + (vrow + 8 * part) * CR + (vx ^ (4 * cb) ^ (2 * part))) + (vi & 1) * 8;
+  TileState<HD> ts;
+  ts.init(kb, vb, lane);
 
   // s_waitcnt immediates: vmcnt in bits 3:0 and 15:14; lgkmcnt and expcnt not waited for
   constexpr int kVm = 0x0F70 | NI, kVm0 = 0x0F70;
@@ -215,87 +129,19 @@ __global__ __launch_bounds__(64 * kAttnWaves, HD == 64 ? 3 : 2) void tree_attent
     // K of this tile has landed; the NI loads of its V may still be in flight
     __builtin_amdgcn_s_waitcnt(kVm);
     asm volatile("" ::: "memory");
-    f32x16 sT;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) sT[j] = 0.f;
-    {  // (the reads have returned where their assembly ends: the buffer is free then)
-      u32x4 kreg[KK];
-      read_k(kreg, ka);
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        sT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kreg[kk]), __builtin_bit_cast(bf16x8, qlo[kk]), sT, 0, 0, 0);
-        sT = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kreg[kk]), __builtin_bit_cast(bf16x8, qh[kk]), sT, 0, 0, 0);
-      }
-    }
+    ts.scores(qh, qlo);
     if (more) issue(kbase, kb, t0 + 32 * NW);
-    // lane holds, for query ql, the keys t0 + 8*(j/4) + 4*h + j%4
     if (t0 + 32 > L) {  // a tile with tree slots: bit i of w = key t0 + i is visible
       const int d = t0 - L;
       uint32_t w = d >= 0 ? (uint32_t)(anc >> d) : ((uint32_t)(anc << -d) | ((1u << -d) - 1u));
-      w >>= 4 * h;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) sT[j] = (w >> (8 * (j >> 2) + (j & 3))) & 1u ? sT[j] : -INFINITY;
+      ts.mask(w, h);
     }
-    float mx = sT[0];
-#pragma unroll
-    for (int j = 1; j < 16; ++j) mx = fmaxf(mx, sT[j]);
-    mx = max_halves(mx);
-    // The running maximum itself is subtracted: the largest probability is 1, exact in two bf16 planes.  (A
-    // reference that may lag by 2^8 saves rescaling but rounds that probability as well: attention output 2 .. 5 %
-    // further from the 64-bit result over 1 .. 1024 rows of the 1.1B, 7B and 13B shapes, at the same times: 7B 64
-    // nodes 4.74 / 4.75 ms, prefill of 810 23.84 / 23.89 ms.)
-    const bool grow = mx > m_run;  // also at the first visible key (m_run = -inf)
-    if (__ballot(grow) != 0ull) {
-      const float m_new = grow ? mx : m_run;
-      const float alpha = grow ? exp2_fast(m_run - m_new) : 1.f;
-      m_run = m_new;
-      l_run *= alpha;
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) o[cb][j] *= alpha;
-    }
-    // a query that has seen no key yet subtracts 0: its scores stay -inf and give probability 0
-    const float m_sub = m_run == -INFINITY ? 0.f : m_run;
-    float p[16], ps[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      p[j] = exp2_fast(sT[j] - m_sub);
-      ps[j & 3] += p[j];
-    }
-    l_run += (ps[0] + ps[1]) + (ps[2] + ps[3]);
-    // P^T as B operand: MFMA mm covers keys 16*mm .. 16*mm+15 of the tile; this lane's k-slots
-    // i = 0..7 are keys 16*mm + 8*(i/4) + 4*h + i%4, i.e. its own p[8*mm + i]
-    u32x4 pb[2], pl[2];
-#pragma unroll
-    for (int mm = 0; mm < 2; ++mm)
-#pragma unroll
-      for (int i2 = 0; i2 < 4; ++i2) {
-        uint32_t hi2, lo2;
-        split_bf16_pair(p[8 * mm + 2 * i2], p[8 * mm + 2 * i2 + 1], hi2, lo2);
-        pb[mm][i2] = hi2;
-        pl[mm][i2] = lo2;
-      }
+    ts.softmax();
     // V of this tile has landed; the NI loads of the next K may still be in flight
     if (more) __builtin_amdgcn_s_waitcnt(kVm);
     else __builtin_amdgcn_s_waitcnt(kVm0);
     asm volatile("" ::: "memory");
-    auto pv = [&](const u32x2 (&v)[2 * CB], int mm) {
-#pragma unroll
-      for (int pass = 0; pass < 2; ++pass)  // lo products, then hi: CB independent accumulators in between
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-          const u32x4 vv = (u32x4){v[2 * cb][0], v[2 * cb][1], v[2 * cb + 1][0], v[2 * cb + 1][1]};
-          o[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv), __builtin_bit_cast(bf16x8, pass ? pb[mm] : pl[mm]), o[cb], 0, 0, 0);
-        }
-    };
-    {
-      u32x2 v0[2 * CB], v1[2 * CB];
-      read_v<2 * CB, 0>(v0, va);
-      pv(v0, 0);
-      read_v<2 * CB, 16 * HD * 2>(v1, va);
-      pv(v1, 1);
-    }
+    ts.values();
     if (more) issue(vbase, vb, t0 + 32 * NW);
   }
 
@@ -303,15 +149,15 @@ __global__ __launch_bounds__(64 * kAttnWaves, HD == 64 ? 3 : 2) void tree_attent
   // the head in kbuf, of the upper half in vbuf), C layout [cb][q][lane] x 4 columns, then all threads
   // reduce: item = (cb, q, lane) = query lane%32, columns 32 cb + 8 q + 4 (lane/32) .. +3
   constexpr int HB = CB / 2;
-  l_run = sum_halves(l_run);
+  ts.l_run = sum_halves(ts.l_run);
   float4 *ko = reinterpret_cast<float4 *>(kbuf), *vo = reinterpret_cast<float4 *>(vbuf);
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
     float4 *dst = (cb < HB ? ko : vo) + wave * TU + (cb % HB) * 256 + lane;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) dst[q * 64] = make_float4(o[cb][4 * q], o[cb][4 * q + 1], o[cb][4 * q + 2], o[cb][4 * q + 3]);
+    for (int q = 0; q < 4; ++q) dst[q * 64] = make_float4(ts.o[cb][4 * q], ts.o[cb][4 * q + 1], ts.o[cb][4 * q + 2], ts.o[cb][4 * q + 3]);
   }
-  if (h == 0) ml[wave * 32 + ql] = make_float2(m_run, l_run);
+  if (h == 0) ml[wave * 32 + ql] = make_float2(ts.m_run, ts.l_run);
   __syncthreads();
   if (!valid) return;
   float wgt[NW], M = -INFINITY, Lsum = 0.f;

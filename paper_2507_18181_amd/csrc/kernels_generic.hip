@@ -52,6 +52,12 @@ __global__ __launch_bounds__(256) void begin_kernel(StepMeta m, const T *E, cons
     return;
   }
   blk -= copy_blocks;
+  if (PLANES && blk < pl.fill_blocks) {  // regions whose data carry their own readiness start as all ones
+    if (blk == 0 && threadIdx.x < 2) pl.ctl[threadIdx.x] = 0;
+    for (uint32_t i = blk * 256 + threadIdx.x; i < pl.fill_units; i += pl.fill_blocks * 256) pl.fill[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    return;
+  }
+  if (PLANES) blk -= pl.fill_blocks;
   const int row_blocks = (m.rows + 31) >> 5;
   // 32 rows x 128 columns: 8 threads per row take 4 columns each, 4 times; whole lines of both planes leave a block
   const int cols = (uint32_t)blk / (uint32_t)row_blocks, row = (blk - cols * row_blocks) * 32 + (threadIdx.x >> 3);
@@ -92,7 +98,18 @@ __global__ __launch_bounds__(256) void begin_kernel(StepMeta m, const T *E, cons
         const uint2 g = *reinterpret_cast<const uint2 *>(pl.gain + c);
         const float y[4] = {v[t][0] * bf16_bits_to_f32(g.x & 0xffffu), v[t][1] * bf16_bits_to_f32(g.x >> 16),
                             v[t][2] * bf16_bits_to_f32(g.y & 0xffffu), v[t][3] * bf16_bits_to_f32(g.y >> 16)};
-        store_planes4(y, pl.hb, pl.hb_lo, packed_act_offset(r, c, pl.nb));
+        if (pl.rp) {
+          uint2 hi, lo;
+          split_bf16_pair(y[0], y[1], hi.x, lo.x);
+          split_bf16_pair(y[2], y[3], hi.y, lo.y);
+          if ((hi.x & hi.y) == ~0u) hi.x = ~1u;  // NaN, but not what stands for missing
+          if ((lo.x & lo.y) == ~0u) lo.x = ~1u;
+          const int64_t o = ((int64_t)(c >> 3) * pl.rp + r) * 8 + (c & 4);
+          *reinterpret_cast<uint2 *>(pl.hb + o) = hi;
+          *reinterpret_cast<uint2 *>(pl.hb_lo + o) = lo;
+        } else {
+          store_planes4(y, pl.hb, pl.hb_lo, packed_act_offset(r, c, pl.nb));
+        }
       }
     }
   }
@@ -101,7 +118,7 @@ __global__ __launch_bounds__(256) void begin_kernel(StepMeta m, const T *E, cons
 void launch_begin(const StepMeta &hm, int dtype, const void *E, const void *in_emb, int max_nodes, int d, float *x, int hd, float theta,
                   float2 *cs, const BeginPlanes *pl, const int32_t *words, int32_t *dst, int n_words, hipStream_t st) {
   const int half = hd / 2, rope_blocks = (hm.rows * half + 255) / 256;
-  const int blocks = rope_blocks + (n_words + 1023) / 1024 + (hm.rows + 31) / 32 * ((d + 127) / 128);
+  const int blocks = rope_blocks + (n_words + 1023) / 1024 + (hm.rows + 31) / 32 * ((d + 127) / 128) + (pl ? pl->fill_blocks : 0);
   const size_t esz = dtype == 1 ? 2 : 4;
   const int vec = (((uintptr_t)E | (uintptr_t)in_emb) & (4 * esz - 1)) == 0;
   const BeginPlanes none{};

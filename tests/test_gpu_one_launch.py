@@ -1,0 +1,156 @@
+"""Forwards of up to 16 rows of one sequence, whose layers are one launch: against the oracle and against the chain of kernels, at the
+edges of its row, key and shape ranges; replayed as a graph; and what happens when a wait inside it runs out."""
+import numpy as np
+import pytest
+
+import oracle
+import workload as wl
+from parity_util import TOL_BF16, check_forward, check_tree_kv
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = {
+    "tiny": dict(n_layers=2, d_model=256, n_heads=4, n_kv_heads=4, d_ffn=672),      # 8 stages of k over 8 wavefronts, ragged half-bands
+    "odd": dict(n_layers=3, d_model=608, n_heads=6, n_kv_heads=2, d_ffn=1184),      # wavefronts with 1 and 2 .. 5 stages
+    "small": dict(n_layers=2, d_model=128, n_heads=2, n_kv_heads=1, d_ffn=160),     # wavefronts without any
+    "wide": dict(n_layers=2, d_model=2048, n_heads=32, n_kv_heads=4, d_ffn=5632),   # the largest
+}
+
+
+def _cfg(shape):
+    return dict(wl.MODELS["tiny"], head_dim=64, vocab=96, **SHAPES[shape])
+
+
+def _verifier(cfg, w, cap, batch=1):
+    from paper_2507_18181_amd.runtime import Verifier
+    return Verifier(cfg, w, "bf16", max_nodes=32, capacity=cap, max_batch=batch)
+
+
+def _one(err):
+    return "one launch" in err
+
+
+@pytest.mark.parametrize("shape,n,L", [
+    ("tiny", 1, 0), ("tiny", 2, 1), ("tiny", 8, 31), ("tiny", 9, 32), ("tiny", 16, 33), ("tiny", 16, 260), ("tiny", 5, 2048), ("tiny", 16, 2050),
+    ("tiny", 1, 1190), ("tiny", 3, 4096), ("odd", 1, 40), ("odd", 4, 300), ("odd", 7, 0), ("odd", 12, 97), ("odd", 16, 1), ("small", 6, 20),
+    ("small", 11, 64), ("wide", 1, 30), ("wide", 8, 70), ("wide", 16, 15),
+])
+def test_against_the_oracle_and_the_chain(shape, n, L, monkeypatch, capfd):
+    cfg = _cfg(shape)
+    w = wl.make_weights(cfg, 911, "bf16")
+    rng = np.random.default_rng([912, n, L])
+    cap = L + n + 3
+    K, V = wl.seeded_cache(cfg, 913, np.asarray([L], np.int32), cap, "bf16", batch=1)
+    tree = wl.random_tree(rng, n, max_children=3)
+    tok = rng.integers(0, cfg["vocab"], n).astype(np.int32)
+    ref = oracle.OracleModel(cfg, w).tree_forward(np.ascontiguousarray(K[0]), np.ascontiguousarray(V[0]), L, tok, tree)
+    monkeypatch.setenv("SPECASR_DEBUG", "1")
+    got = []
+    for polls in (None, "0"):
+        if polls:
+            monkeypatch.setenv("SPECASR_ONE_POLLS", polls)
+        ver = _verifier(cfg, w, cap)
+        ver.set_cache(K, V, [L])
+        capfd.readouterr()
+        fw = ver.tree_forward([tok], [tree])
+        assert fw["status"] == 0
+        assert _one(capfd.readouterr().err) == (polls is None)
+        k1, v1 = ver.get_cache()
+        lg = fw["logits"][0].cpu().numpy()
+        check_forward(ref, lg, fw["argmax"][0].cpu().numpy(), TOL_BF16)
+        check_tree_kv(k1[0], v1[0], L, ref, TOL_BF16)
+        if polls is None:  # the same bits again: every sum has one order
+            fw = ver.tree_forward([tok], [tree])
+            k2, v2 = ver.get_cache()
+            assert np.array_equal(lg, fw["logits"][0].cpu().numpy()) and np.array_equal(k1, k2) and np.array_equal(v1, v2)
+        got.append(lg[:n].astype(np.float64))
+        ver.close()
+    # two orders of fp32 sums and, behind them, single K and V elements that round the other way (a step of 2^-8 of an element)
+    assert np.linalg.norm(got[0] - got[1]) <= 2.5e-3 * np.linalg.norm(got[1])
+
+
+@pytest.mark.parametrize("n,batch,L,layers", [(17, 1, 20, 2), (4, 2, 20, 2), (4, 1, 4097, 2), (4, 1, 20, 1)])
+def test_what_stays_on_the_chain(n, batch, L, layers, monkeypatch, capfd):
+    cfg = dict(_cfg("tiny"), n_layers=layers)
+    w = wl.make_weights(cfg, 921, "bf16")
+    monkeypatch.setenv("SPECASR_DEBUG", "1")
+    ver = _verifier(cfg, w, L + n, batch)
+    ver.kv_len[:] = L
+    capfd.readouterr()
+    fw = ver.tree_forward([np.arange(n, dtype=np.int32)] * batch, [np.arange(-1, n - 1, dtype=np.int32)] * batch)
+    err = capfd.readouterr().err
+    assert fw["status"] == 0 and "plan qkv" in err and not _one(err)
+    ver.close()
+
+
+def test_whole_rounds_and_input_rows():
+    """verify_tree and the draft-side read-out on this path, with embedding rows among the inputs, against the chain."""
+    import os
+    cfg = _cfg("odd")
+    w = wl.make_weights(cfg, 931, "bf16")
+    rng = np.random.default_rng(932)
+    n, L, cap = 13, 50, 96
+    K, V = wl.seeded_cache(cfg, 933, np.asarray([L], np.int32), cap, "bf16", batch=1)
+    tree = wl.random_tree(rng, n, max_children=2)
+    tok = rng.integers(0, cfg["vocab"], n).astype(np.int32)
+    emb = torch.from_numpy(rng.standard_normal((1, 32, cfg["d_model"])).astype(np.float32)).to("cuda:0").to(torch.bfloat16)
+    outs = []
+    for polls in (None, "0"):
+        if polls:
+            os.environ["SPECASR_ONE_POLLS"] = polls
+        try:
+            ver = _verifier(cfg, w, cap)
+        finally:
+            os.environ.pop("SPECASR_ONE_POLLS", None)
+        ver.set_cache(K, V, [L])
+        top = ver.tree_forward_top2([tok], [tree], want_logits=True, embeds=emb, use_embed=[[i % 3 == 0 for i in range(n)]])
+        vt = ver.verify_tree([tok], [tree], want_logits=True)
+        assert top["status"] == 0 and vt["status"] == 0
+        outs.append((top["logits"][0, :n].double().cpu().numpy(), vt["logits"][0, :n].double().cpu().numpy(), vt["accept_len"][0], int(ver.kv_len[0])))
+        ver.close()
+    for a, b in ((outs[0][0], outs[1][0]), (outs[0][1], outs[1][1])):
+        assert np.linalg.norm(a - b) <= 2.5e-3 * np.linalg.norm(b)
+    assert outs[0][2:] == outs[1][2:]
+
+
+def test_replayed_as_a_graph():
+    """The launch counts its items in scratch that the first kernel of the call clears: replays give the eager bits."""
+    from paper_2507_18181_amd import binding as B
+    cfg = _cfg("tiny")
+    w = wl.make_weights(cfg, 941, "bf16")
+    rng = np.random.default_rng(942)
+    n, L = 10, 40
+    K, V = wl.seeded_cache(cfg, 943, np.asarray([L], np.int32), 64, "bf16", batch=1)
+    tree = wl.random_tree(rng, n, max_children=3)
+    tok = rng.integers(0, cfg["vocab"], n).astype(np.int32)
+    ver = _verifier(cfg, w, 64)
+    ver.set_cache(K, V, [L])
+    eager = ver.tree_forward([tok], [tree])["logits"].clone()
+    argmax = torch.full((1, 32), -1, dtype=torch.int32, device="cuda:0")
+    logits = torch.zeros((1, 32, cfg["vocab"]), device="cuda:0")
+    t, keep = ver._tree([tok], [tree])
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        assert B.specasr_tree_forward(ver.ctx, ver._kv, t, argmax, logits, ver.ws_ptr, ver.ws_bytes, s.cuda_stream) == 0
+    for _ in range(4):
+        logits.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(logits, eager)
+    ver.close()
+
+
+def test_a_wait_that_runs_out_is_reported(monkeypatch):
+    """With a bound of a single look every wait is given up at once: the launch ends all the same, and the call says so."""
+    from paper_2507_18181_amd import binding as B
+    cfg = _cfg("tiny")
+    w = wl.make_weights(cfg, 951, "bf16")
+    monkeypatch.setenv("SPECASR_ONE_POLLS", "1")
+    ver = _verifier(cfg, w, 64)
+    ver.kv_len[:] = 20
+    out = ver.verify_tree([np.arange(9, dtype=np.int32)], [np.arange(-1, 8, dtype=np.int32)])
+    assert out["status"] == B.SPECASR_E_HIP and ver.kv_len[0] == 20
+    ver.close()
