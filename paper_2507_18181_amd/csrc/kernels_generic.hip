@@ -145,30 +145,12 @@ __global__ void rmsnorm_kernel(const float *x, const T *g, int d, float eps, flo
 
 // --------------------------------------------------------------------------- linear
 // One wavefront owns OW output features and RB activation rows; lanes stride over k in 4-element vectors; the
-// OW * RB dot products are finished together by a halving exchange (17 shuffles for 16 sums instead of
-// 96).  n_in % 4 == 0.  On a tiny model a launch costs more than its work, so what stands between two products is
+// OW * RB dot products are finished together by a halving exchange (17 steps for 16 sums instead of 96).  n_in % 4 == 0.  On a tiny model a launch costs more than its work, so what stands between two products is
 // done by them: gate and up of one feature belong to one wavefront, which applies SwiGLU; q, k and v are one launch
 // whose wavefronts own the two halves of a rotary pair, rotate it and write k and v to the cache; the logits go to the
 // caller's array; and up to kNormWidth input features and a few hundred rows a workgroup normalises its 8 rows itself, in
-// LDS.  Bound by the chain of launches, about 7 us each: tiny fp32 verify of 8 nodes 170 us with a kernel for each of these
-// (24 launches), now 138 (15, the first and last kernels of a call merged as well).
-
-// Sums 16 values over the 64 lanes; every lane returns the sum of value 8*b5 + 4*b4 + 2*b3 + b2 (bits of its
-// index).
-__device__ __forceinline__ float wave_sum16(float (&v)[16], int lane) {
-#pragma unroll
-  for (int n = 8, bit = 32; n >= 1; n >>= 1, bit >>= 1) {
-    const bool up = lane & bit;
-#pragma unroll
-    for (int i = 0; i < n; ++i) {
-      const float keep = up ? v[i + n] : v[i], send = up ? v[i] : v[i + n];
-      v[i] = keep + __shfl_xor(send, bit, 64);
-    }
-  }
-  v[0] += __shfl_xor(v[0], 2, 64);
-  v[0] += __shfl_xor(v[0], 1, 64);
-  return v[0];
-}
+// LDS.  Bound by the chain of launches, about 5 us each: tiny fp32 verify of 8 nodes 170 us with a kernel for each of these
+// (24 launches), 138 with 15 (the first and last kernels of a call merged as well), 113 since the exchange is one of registers.
 
 // The matrices of one launch: blocks [first[i], first[i+1]) work on matrix i.
 template <class T>
