@@ -18,8 +18,8 @@
 //
 // What bounds it: per layer 5 hand-overs of 3 .. 5 us each (store to memory 0.7, the look that finds it 1, products, sums through LDS and
 // epilogue 1.5, the latest workgroup), and at the last of them the weights that 48 workgroups could not ask for earlier.
-// Measured (us per call, 1.1B, 330 keys, chain of kernels -> this): 1 row 965 -> 671, 8 rows 1005 -> 730, 16 rows 1026 -> 746; 3200 keys,
-// 1 row 1002 -> 778, 16 rows 1103 -> 1010; 12 layers of d 1024, 1 row 460 -> 331; 2 layers of d 256, 8 rows 115 -> 103.
+// Measured (us per call, 1.1B, 330 keys, chain of kernels -> this): 1 row 965 -> 642, 8 rows 1005 -> 667, 16 rows 1026 -> 724; 3200 keys,
+// 1 row 1002 -> 745, 16 rows 1103 -> 922; 12 layers of d 1024, 1 row 460 -> 331; 2 layers of d 256, 8 rows 115 -> 103 (the last two before one wavefront looked for all).
 #include "kernels.h"
 #include "kernels_mfma.h"
 #include "kernels_one.h"
@@ -82,6 +82,14 @@ __device__ __forceinline__ bool give_up(const OneArgs &p, int it) {
   return (it & 255) == 255 && __hip_atomic_load(p.ctl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
 }
 
+__device__ __forceinline__ void barrier_only() {  // loads in flight stay in flight
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 enum OneEpi { kOneQkv, kOneSwiglu, kOneResid };
 
 struct OneShared {
@@ -119,9 +127,12 @@ __device__ __forceinline__ void one_gemm(const OneArgs &p, OneShared &sh, int pa
   const int in_tile = 32 * ((lane >> 4) & 1) + (lane & 15);
   // The o projection is taken two phases early, while the 180 KB that the last workgroups of down need are on their way: its weights
   // wait until the first queries are there (16 rows 865 -> 780 us, 1 row 718 -> 698; the same for other phases only costs).
+  // Up to 8 rows one wavefront looks for all (1 row 652 -> 642; 16 rows 724 -> 731).
   if (EPI == kOneResid && LW == 8) {
-    for (int it = 0; __ballot(!missing16(ll_load16(rs, p.lay.q + (uint32_t)(lane * 16) % (uint32_t)(p.dq * 2)))) == 0ull && !give_up(p, it); ++it)
-      __builtin_amdgcn_s_sleep(8);
+    if (NP == 2 || wave == 0)
+      for (int it = 0; __ballot(!missing16(ll_load16(rs, p.lay.q + (uint32_t)(lane * 16) % (uint32_t)(p.dq * 2)))) == 0ull && !give_up(p, it); ++it)
+        __builtin_amdgcn_s_sleep(NP == 2 ? 8 : 16);
+    if (NP == 1) barrier_only();
   }
   u32x4 wa[LW][HB];
 #pragma unroll
@@ -190,9 +201,12 @@ __device__ __forceinline__ void one_gemm(const OneArgs &p, OneShared &sh, int pa
   constexpr int RW = NP;  // rows of a wavefront in the norm: wave, wave + 8
   float ssum[RW];
   Next next;
-  // A workgroup that is a phase ahead looks at one stage now and then, until that is there (all its stages all the time: 965 us
-  // against 804 with one row, the looks get in the way of the data).
-  for (int it = 0; __ballot(missing16(ll_load16(rs, x0))) != 0ull && !give_up(p, it); ++it) __builtin_amdgcn_s_sleep(8);
+  // A workgroup that is a phase ahead looks at one stage now and then, until that is there, and one wavefront looks for all of it:
+  // the looks of 256 workgroups past the caches get in the way of the data (us per call, 1 / 8 / 16 rows: each wavefront looks at a
+  // stage of its own 672 / 729 / 742, one of them 652 / 670 / 724; one at the first and the last stage 659 / 681 / 763).
+  if (wave == 0)
+    for (int it = 0; __ballot(missing16(ll_load16(rs, x0))) != 0ull && !give_up(p, it); ++it) __builtin_amdgcn_s_sleep(24);
+  barrier_only();
 #pragma unroll
   for (int c0 = 0; c0 < LW; c0 += DX) {
     u32x4 xb[DX][NP];
