@@ -19,7 +19,7 @@
 // What bounds it: per layer 5 hand-overs of 3 .. 5 us each (store to memory 0.7, the look that finds it 1, products, sums through LDS and
 // epilogue 1.5, the latest workgroup), and at the last of them the weights that 48 workgroups could not ask for earlier.
 // Measured (us per call, 1.1B, 330 keys, chain of kernels -> this): 1 row 965 -> 642, 8 rows 1005 -> 667, 16 rows 1026 -> 724; 3200 keys,
-// 1 row 1002 -> 745, 16 rows 1103 -> 922; 12 layers of d 1024, 1 row 460 -> 331; 2 layers of d 256, 8 rows 115 -> 103 (the last two before one wavefront looked for all).
+// 1 row 1002 -> 745, 16 rows 1103 -> 902; 12 layers of d 1024, 1 row 460 -> 331; 2 layers of d 256, 8 rows 115 -> 103 (the last two before one wavefront looked for all).
 #include "kernels.h"
 #include "kernels_mfma.h"
 #include "kernels_one.h"
@@ -391,6 +391,9 @@ __device__ __forceinline__ void one_attention(const OneArgs &p, OneShared &sh, i
   u32x4 qh[KK], qlo[KK];
   {
     const uint32_t qoff = p.lay.q + ((uint32_t)(node * p.H + head) * HD + 8 * h) * 2, plane = (uint32_t)p.dq * 2 * p.rp;
+    if (wave == 0)  // (as in one_gemm: 16 rows, 3200 keys 920 -> 902 us)
+      for (int it = 0; __ballot(missing16(ll_load16(rs, qoff))) != 0ull && !give_up(p, it); ++it) __builtin_amdgcn_s_sleep(8);
+    barrier_only();
     for (int it = 0;; ++it) {
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) {
