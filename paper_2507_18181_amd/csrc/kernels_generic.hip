@@ -150,7 +150,8 @@ __global__ void rmsnorm_kernel(const float *x, const T *g, int d, float eps, flo
 // whose wavefronts own the two halves of a rotary pair, rotate it and write k and v to the cache; the logits go to the
 // caller's array; and up to kNormWidth input features and a few hundred rows a workgroup normalises its 8 rows itself, in
 // LDS.  Bound by the chain of launches, about 5 us each: tiny fp32 verify of 8 nodes 170 us with a kernel for each of these
-// (24 launches), 138 with 15 (the first and last kernels of a call merged as well), 113 since the exchange is one of registers.
+// (24 launches), 138 with 15 (the first and last kernels of a call merged as well), 116 since the exchange is one of registers, 111 with
+// everything that a product needs requested at once.
 
 // The matrices of one launch: blocks [first[i], first[i+1]) work on matrix i.
 template <class T>
@@ -187,7 +188,8 @@ enum LinearMode {
 };
 
 // NORM: a holds residual rows; the product takes a * gain / rms(a), as rmsnorm_kernel leaves it.
-template <class T, int MODE, bool NORM>
+// KB: blocks of 256 inputs that a wavefront asks for at once (not NORM, which asks for all of them).
+template <class T, int MODE, bool NORM, int KB>
 __global__ __launch_bounds__(256) void linear_kernel(LinearSet<T> ls, LinearMore<T> mo, int n_in, const float *a, int lda, int rows, int accumulate) {
   constexpr int RB = kLinRows, OW = kLinOut, NIT = kNormWidth / 256;
   __shared__ float4 as[NORM ? RB * (kNormWidth / 4) : 1];
@@ -214,6 +216,10 @@ __global__ __launch_bounds__(256) void linear_kernel(LinearSet<T> ls, LinearMore
   if (!NORM && !live) return;
   const T *w0 = W + (int64_t)min(o0, n_out - 1) * n_in;
   const T *w1 = MODE == kLinSwiglu ? ls.W[1] + (int64_t)min(o0, n_out - 1) * n_in : W + (int64_t)min(o1, n_out - 1) * n_in;
+  // what the sums are added to, requested before them
+  const int e_o = lane < 32 ? o0 : o1, e_r = r0 + ((lane >> 2) & 7);
+  float before = 0.f;
+  if (MODE == kLinPlain && accumulate && (lane & 3) == 0 && e_r < rows && e_o < n_out) before = y[(int64_t)e_r * ldy + e_o];
   float acc[OW * RB];
 #pragma unroll
   for (int i = 0; i < OW * RB; ++i) acc[i] = 0.f;
@@ -259,22 +265,31 @@ __global__ __launch_bounds__(256) void linear_kernel(LinearSet<T> ls, LinearMore
             acc[i * RB + j] += w[t][i][0] * av.x + w[t][i][1] * av.y + w[t][i][2] * av.z + w[t][i][3] * av.w;
         }
   } else {
-#pragma unroll 2
-    for (int k = lane * 4; k < n_in; k += 256) {
-      float w[OW][4];
-      Vec4<T>::load(w0 + k, w[0]);
-      Vec4<T>::load(w1 + k, w[1]);
+    for (int k0 = lane * 4; k0 < n_in; k0 += 256 * KB) {
+      float w[KB][OW][4];
+      float4 av[KB][RB];
 #pragma unroll
-      for (int j = 0; j < RB; ++j) {
-        const float4 av = *reinterpret_cast<const float4 *>(a + (int64_t)min(r0 + j, rows - 1) * lda + k);
+      for (int t = 0; t < KB; ++t) {
+        const int k = k0 + t * 256;
+        if (k < n_in) {
+          Vec4<T>::load(w0 + k, w[t][0]);
+          Vec4<T>::load(w1 + k, w[t][1]);
 #pragma unroll
-        for (int i = 0; i < OW; ++i)
-          acc[i * RB + j] += w[i][0] * av.x + w[i][1] * av.y + w[i][2] * av.z + w[i][3] * av.w;
+          for (int j = 0; j < RB; ++j) av[t][j] = *reinterpret_cast<const float4 *>(a + (int64_t)min(r0 + j, rows - 1) * lda + k);
+        }
       }
+#pragma unroll
+      for (int t = 0; t < KB; ++t)
+        if (k0 + t * 256 < n_in)
+#pragma unroll
+          for (int j = 0; j < RB; ++j)
+#pragma unroll
+            for (int i = 0; i < OW; ++i)
+              acc[i * RB + j] += w[t][i][0] * av[t][j].x + w[t][i][1] * av[t][j].y + w[t][i][2] * av[t][j].z + w[t][i][3] * av[t][j].w;
     }
   }
   const float s = wave_sum16(acc, lane);  // of output (lane < 32 ? o0 : o1), row r0 + (lane/4)%8
-  const int j = (lane >> 2) & 7, o = lane < 32 ? o0 : o1, r = r0 + j;
+  const int o = e_o, r = e_r;
   const bool mine = (lane & 3) == 0 && r < rows;
   if (MODE == kLinSwiglu) {
     const float up = __shfl_xor(s, 32, 64);
@@ -296,7 +311,7 @@ __global__ __launch_bounds__(256) void linear_kernel(LinearSet<T> ls, LinearMore
   } else if (mine && o < n_out) {
     const int64_t yr = MODE == kLinLogits ? (int64_t)mo.seq[r] * mo.max_nodes + mo.node[r] : r;
     float *dst = y + yr * ldy + o;
-    *dst = MODE == kLinPlain && accumulate ? (*dst + s) : s;
+    *dst = MODE == kLinPlain && accumulate ? before + s : s;
   }
 }
 
@@ -315,7 +330,11 @@ static void launch_linear_t(const LinearJob *jobs, int n, const LinearMore<T> &m
     else if (i < n) blocks += (j.n_out + 4 * kLinOut - 1) / (4 * kLinOut);
   }
   dim3 grid(blocks, (rows + kLinRows - 1) / kLinRows);
-  linear_kernel<T, MODE, NORM><<<grid, 256, 0, st>>>(ls, mo, n_in, a, lda, rows, accumulate ? 1 : 0);
+  // All 4 blocks of 1024 inputs at once take 200 registers, 2 wavefronts per SIMD: where no more than that are there, they wait once instead of
+  // twice or three times; with more, 2 blocks and twice the wavefronts (us per verify, fp32, 2 / 4: d_model 256, 8 rows 116 / 111, 64 rows
+  // 127 / 123; 512, 8 rows 344 / 290; 1024, 16 rows 392 / 347, 64 rows (1024 workgroups) 637 / 642).
+  if (NORM || (int64_t)grid.x * grid.y > 512) linear_kernel<T, MODE, NORM, 2><<<grid, 256, 0, st>>>(ls, mo, n_in, a, lda, rows, accumulate ? 1 : 0);
+  else linear_kernel<T, MODE, NORM, NORM ? 2 : 4><<<grid, 256, 0, st>>>(ls, mo, n_in, a, lda, rows, accumulate ? 1 : 0);
 }
 
 // With many rows the launch that is saved is small against the norm that every workgroup repeats.  Norm in the linear / as a
@@ -411,7 +430,7 @@ __global__ __launch_bounds__(256) void attention_generic_kernel(StepMeta m, KvGe
     if (valid) {
       const T *kr = kbase + (int64_t)t * hd;
       float acc = 0.f;
-#pragma unroll 4
+#pragma unroll 16
       for (int e = 0; e < hd; e += 4) {  // hd is a multiple of 8
         float k4[4];
         Vec4<T>::load(kr + e, k4);
