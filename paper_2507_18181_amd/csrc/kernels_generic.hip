@@ -499,9 +499,16 @@ __global__ __launch_bounds__(256) void argmax_kernel(StepMeta m, const float *lo
   const float *row = logits + (int64_t)(padded ? orow : r) * V;
   float best = -INFINITY;
   int besti = 0x7fffffff;
-  for (int t = threadIdx.x; t < V; t += 256) {
-    float v = row[t];
-    if (v > best || (v == best && t < besti)) { best = v; besti = t; }
+  for (int t0 = threadIdx.x; t0 < V; t0 += 256 * 8) {  // 8 loads in flight
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (t0 + i * 256 < V) v[i] = row[t0 + i * 256];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int t = t0 + i * 256;
+      if (t < V && (v[i] > best || (v[i] == best && t < besti))) { best = v[i]; besti = t; }
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
