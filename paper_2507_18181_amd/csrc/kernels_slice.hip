@@ -12,7 +12,8 @@
 //     nothing is stored twice.  Weights and activations stream together through a ring of D
 //     register stages: no LDS, no barrier before the epilogue, 128 .. 320 KB in flight per compute unit.
 //   * What bounds it: the weight stream while HB >= NC, the bytes one compute unit can pull out of
-//     its L2 (about 60 bytes/ns) where activations outweigh weights (few features per workgroup).
+//     its L2 beside that stream (about 60 bytes/ns together; activations alone come at 110 .. 134) where activations outweigh
+//     weights (few features per workgroup).
 //   * The 8 slices are summed through LDS; the summing thread applies the finishing step.
 // Measured (us per launch under the tracer, split kernel + its finishing kernel against this one): 7B, 32 rows
 // gate|up 33.6 + 5.4 -> 33.4, q|k|v 18.9 + 4.7 -> 23.2; 13B gate|up 51.6 + 6.2 -> 48.5, q|k|v 32.8 + 5.7 -> 33.2; 1.1B,
