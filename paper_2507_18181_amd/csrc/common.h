@@ -87,20 +87,6 @@ __host__ __device__ __forceinline__ int64_t part_offset(int s, int row, int col,
 }
 __host__ __device__ __forceinline__ int part_rows_pad(int rows) { return rows <= 32 ? 32 : (rows + 63) / 64 * 64; }
 
-// v += partial sums of 4 columns, `stride` floats apart, in the order of the splits.  Up to 8 are requested at once, whatever their number: a
-// loop over them unrolled by 4 waits for each of the n_splits % 4 last ones by itself.
-__device__ __forceinline__ void add_splits4(float4 &v, const float *p, int64_t stride, int n_splits) {
-  for (int s0 = 0; s0 < n_splits; s0 += 8) {
-    float4 t[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (s0 + i < n_splits) t[i] = *reinterpret_cast<const float4 *>(p + (s0 + i) * stride);
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (s0 + i < n_splits) { v.x += t[i].x; v.y += t[i].y; v.z += t[i].z; v.w += t[i].w; }
-  }
-}
-
 // ---- per-call tree metadata as the kernels see it ------------------------
 // Rows are the tree nodes of all sequences of the call, flattened without
 // padding: row = row_start[seq] + node.

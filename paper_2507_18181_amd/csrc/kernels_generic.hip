@@ -627,27 +627,27 @@ __global__ __launch_bounds__(256) void top2_blocks_kernel(StepMeta m, const floa
   __shared__ Top2 wt[4];
   __shared__ float ws[4];
   const int r = blockIdx.y, rows = m.rows;
-  const bool normed = SRC == 1 && nrm.ssq != nullptr;
-  const float lane_ssq = normed ? row_ssq_lane(nrm, r) : 0.f;  // in flight together with the partial sums
-  const int orow = logits_out ? m.seq[r] * max_nodes + m.node[r] : 0;
+  const float rs = (SRC == 1 && nrm.ssq != nullptr) ? row_rms_scale(nrm, r) : 1.0f;
   const int v0 = (blockIdx.x * 256 + threadIdx.x) * 4;
   float vals[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (SRC == 1 && v0 < V) add_splits4(a, src + part_offset(0, r, v0, ldp >> 5, part_rows_pad(rows)), (int64_t)ldp * part_rows_pad(rows), n_splits);
-  const float rs = normed ? row_rms_finish(nrm, lane_ssq) : 1.0f;
   if (v0 < V) {
     if (SRC == 0) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (v0 + i < V) vals[i] = src[(int64_t)r * V + v0 + i];
     } else {
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int s = 0; s < n_splits; ++s) {
+        const float4 p = *reinterpret_cast<const float4 *>(src + part_offset(s, r, v0, ldp >> 5, part_rows_pad(rows)));
+        a.x += p.x; a.y += p.y; a.z += p.z; a.w += p.w;
+      }
       const float t[4] = {a.x * rs, a.y * rs, a.z * rs, a.w * rs};
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (v0 + i < V) vals[i] = t[i];
     }
     if (logits_out) {
-      float *dst = logits_out + (int64_t)orow * V + v0;
+      float *dst = logits_out + ((int64_t)m.seq[r] * max_nodes + m.node[r]) * V + v0;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (v0 + i < V) dst[i] = vals[i];

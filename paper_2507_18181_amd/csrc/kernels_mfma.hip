@@ -773,14 +773,26 @@ __global__ __launch_bounds__(512) void residual_gain_kernel(float *x, const floa
   const int r = blockIdx.y * 64 + (threadIdx.x >> 3), c = blockIdx.x * kSlabCols + (threadIdx.x & 7) * 4;
   const bool ok = r < rows && c < d;
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-  uint2 g = make_uint2(0u, 0u);
   if (ok) {
-    g = *reinterpret_cast<const uint2 *>(gain + c);
     float *xr = x + (int64_t)r * d + c;
     v = *reinterpret_cast<const float4 *>(xr);
     const float *pp = part + part_offset(0, r, c, ldp >> 5, rows_pad);
     const int64_t sstride = (int64_t)ldp * rows_pad;
-    add_splits4(v, pp, sstride, n_splits);
+    int s = 0;
+    for (; s + 4 <= n_splits; s += 4) {  // four independent loads in flight, summed in split order
+      const float4 p0 = *reinterpret_cast<const float4 *>(pp + (s + 0) * sstride);
+      const float4 p1 = *reinterpret_cast<const float4 *>(pp + (s + 1) * sstride);
+      const float4 p2 = *reinterpret_cast<const float4 *>(pp + (s + 2) * sstride);
+      const float4 p3 = *reinterpret_cast<const float4 *>(pp + (s + 3) * sstride);
+      v.x += p0.x; v.y += p0.y; v.z += p0.z; v.w += p0.w;
+      v.x += p1.x; v.y += p1.y; v.z += p1.z; v.w += p1.w;
+      v.x += p2.x; v.y += p2.y; v.z += p2.z; v.w += p2.w;
+      v.x += p3.x; v.y += p3.y; v.z += p3.z; v.w += p3.w;
+    }
+    for (; s < n_splits; ++s) {
+      const float4 p = *reinterpret_cast<const float4 *>(pp + s * sstride);
+      v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+    }
     if (n_splits > 0) *reinterpret_cast<float4 *>(xr) = v;
   }
   float ss = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
@@ -789,6 +801,7 @@ __global__ __launch_bounds__(512) void residual_gain_kernel(float *x, const floa
   ss += __shfl_xor(ss, 4, 64);
   if (ok) {
     if ((threadIdx.x & 7) == 0) ssq[(int64_t)r * n_slab + blockIdx.x] = ss;
+    const uint2 g = *reinterpret_cast<const uint2 *>(gain + c);
     const float y[4] = {v.x * bf16_bits_to_f32(g.x & 0xffffu), v.y * bf16_bits_to_f32(g.x >> 16),
                         v.z * bf16_bits_to_f32(g.y & 0xffffu), v.w * bf16_bits_to_f32(g.y >> 16)};
     store_planes4(y, hb, hb_lo, packed_act_offset(r, c, nb));
@@ -833,23 +846,16 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(StepMeta m, KvGeom g, i
   const float *pr = part + part_offset(0, r, 0, ldp >> 5, rows_pad);  // column c at (c/32)*rows_pad*32 + c%32
   const int64_t sstride = (int64_t)ldp * rows_pad;
   auto at = [rows_pad](int col) { return (col >> 5) * (rows_pad << 5) + (col & 31); };
-  // sums of the split-k partials of up to four columns, loads of up to 8 splits issued together
+  // sums of the split-k partials of up to four columns, loads of one split issued together
   auto val4 = [&](int c0, int c1, int c2, int c3, float (&out)[4]) {
     out[0] = out[1] = out[2] = out[3] = 0.f;
-    for (int s0 = 0; s0 < n_splits; s0 += 8) {
-      float w[8][4];
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (s0 + i < n_splits) {
-          const float *q = pr + (s0 + i) * sstride;
-          w[i][0] = q[at(c0)]; w[i][1] = q[at(c1)]; w[i][2] = q[at(c2)]; w[i][3] = q[at(c3)];
-        }
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (s0 + i < n_splits) { out[0] += w[i][0]; out[1] += w[i][1]; out[2] += w[i][2]; out[3] += w[i][3]; }
+#pragma unroll 4
+    for (int s = 0; s < n_splits; ++s) {
+      const float *q = pr + s * sstride;
+      const float v0 = q[at(c0)], v1 = q[at(c1)], v2 = q[at(c2)], v3 = q[at(c3)];
+      out[0] += v0; out[1] += v1; out[2] += v2; out[3] += v3;
     }
   };
-  const int64_t base = a < H ? 0 : g.row(m.seq[r], layer, a - H, m.slot[r]);
   float t[4];
   const int jc = rope_col(j, paired), j2 = jc + rope_step(half, paired);
   if (a < H)
@@ -871,7 +877,9 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(StepMeta m, KvGeom g, i
       q[o + half] = y1;
     }
   } else {
+    const int b = a - H;
     const float x0 = t[0], x1 = t[1];
+    const int64_t base = g.row(m.seq[r], layer, b, m.slot[r]);
     kc[base + j] = f32_to_bf16_bits(x0 * c.x - x1 * c.y);
     kc[base + j + half] = f32_to_bf16_bits(x1 * c.x + x0 * c.y);
     vc[base + j] = f32_to_bf16_bits(t[2]);
@@ -909,10 +917,13 @@ __global__ __launch_bounds__(256) void qkv_finish_wide_kernel(StepMeta m, KvGeom
   const float rs = 1.0f / sqrtf(ss / (float)nrm.d + nrm.eps);
   if (r >= rows) return;
   const int rows_pad = part_rows_pad(rows), n_bands = ldp >> 5;
-  const int64_t base = a < H ? 0 : g.row(m.seq[r], layer, a - H, m.slot[r]);
   auto sum4 = [&](int col) {  // sum over the splits of 4 consecutive columns of row r, times 1/rms
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    add_splits4(v, part + part_offset(0, r, col, n_bands, rows_pad), (int64_t)ldp * rows_pad, n_splits);
+#pragma unroll 4
+    for (int s = 0; s < n_splits; ++s) {
+      const float4 p = *reinterpret_cast<const float4 *>(part + part_offset(s, r, col, n_bands, rows_pad));
+      v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+    }
     v.x *= rs; v.y *= rs; v.z *= rs; v.w *= rs;
     return v;
   };
@@ -940,6 +951,7 @@ __global__ __launch_bounds__(256) void qkv_finish_wide_kernel(StepMeta m, KvGeom
       store_planes4(y1, qb, qb_lo, o + half);
     } else {
       const float4 v0 = sum4(col_v + b * hd + j), v1 = sum4(col_v + b * hd + j + half);
+      const int64_t base = g.row(m.seq[r], layer, b, m.slot[r]);
       store_bf16x4(y0, kc + base + j);
       store_bf16x4(y1, kc + base + j + half);
       const float w0[4] = {v0.x, v0.y, v0.z, v0.w}, w1[4] = {v1.x, v1.y, v1.z, v1.w};
@@ -996,9 +1008,13 @@ __global__ __launch_bounds__(256) void swiglu_finish_kernel(const float *part, i
   if (!ok) return;
   float4 gt = make_float4(0.f, 0.f, 0.f, 0.f), up = gt;
   const int rows_pad = part_rows_pad(rows), n_bands = ldp >> 5;
-  const float *pg = part + part_offset(0, r, gate_col(f), n_bands, rows_pad);
-  add_splits4(gt, pg, (int64_t)ldp * rows_pad, n_splits);
-  add_splits4(up, pg + 8, (int64_t)ldp * rows_pad, n_splits);
+#pragma unroll 4
+  for (int s = 0; s < n_splits; ++s) {
+    const float4 a = *reinterpret_cast<const float4 *>(part + part_offset(s, r, gate_col(f), n_bands, rows_pad));
+    const float4 b = *reinterpret_cast<const float4 *>(part + part_offset(s, r, gate_col(f) + 8, n_bands, rows_pad));
+    gt.x += a.x; gt.y += a.y; gt.z += a.z; gt.w += a.w;
+    up.x += b.x; up.y += b.y; up.z += b.z; up.w += b.w;
+  }
   const float y[4] = {swiglu_act(gt.x, up.x, rs), swiglu_act(gt.y, up.y, rs), swiglu_act(gt.z, up.z, rs), swiglu_act(gt.w, up.w, rs)};
   store_planes4(y, t, t_lo, packed_act_offset(r, f, nb));
 }
@@ -1016,9 +1032,13 @@ __global__ __launch_bounds__(256) void swiglu_finish_rows_kernel(const float *pa
   float4 gt = make_float4(0.f, 0.f, 0.f, 0.f), up = gt;
   const int rows_pad = part_rows_pad(rows), n_bands = ldp >> 5;
   if (f < F) {
-    const float *pg = part + part_offset(0, r, gate_col(f), n_bands, rows_pad);
-    add_splits4(gt, pg, (int64_t)ldp * rows_pad, n_splits);
-    add_splits4(up, pg + 8, (int64_t)ldp * rows_pad, n_splits);
+#pragma unroll 4
+    for (int s = 0; s < n_splits; ++s) {
+      const float4 a = *reinterpret_cast<const float4 *>(part + part_offset(s, r, gate_col(f), n_bands, rows_pad));
+      const float4 b = *reinterpret_cast<const float4 *>(part + part_offset(s, r, gate_col(f) + 8, n_bands, rows_pad));
+      gt.x += a.x; gt.y += a.y; gt.z += a.z; gt.w += a.w;
+      up.x += b.x; up.y += b.y; up.z += b.z; up.w += b.w;
+    }
   }
   const float rs = row_rms_finish(nrm, lane_ssq);
   if (f >= F) return;
@@ -1069,13 +1089,15 @@ __global__ __launch_bounds__(256) void logits_argmax_kernel(StepMeta m, const fl
   __shared__ int bi[4];
   const int r = blockIdx.y, rows = m.rows;
   const int v0 = (blockIdx.x * 256 + threadIdx.x) * 4;
-  const float lane_ssq = row_ssq_lane(nrm, r);  // in flight together with the partial sums
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (v0 < V) add_splits4(a, part + part_offset(0, r, v0, ldp >> 5, part_rows_pad(rows)), (int64_t)ldp * part_rows_pad(rows), n_splits);
-  const float rs = row_rms_finish(nrm, lane_ssq);
+  const float rs = row_rms_scale(nrm, r);
   float best = -INFINITY;
   int besti = 0x7fffffff;
   if (v0 < V) {
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s = 0; s < n_splits; ++s) {
+      const float4 p = *reinterpret_cast<const float4 *>(part + part_offset(s, r, v0, ldp >> 5, part_rows_pad(rows)));
+      a.x += p.x; a.y += p.y; a.z += p.z; a.w += p.w;
+    }
     const float vals[4] = {a.x * rs, a.y * rs, a.z * rs, a.w * rs};
     if (logits_out) {
       float *dst = logits_out + ((int64_t)m.seq[r] * max_nodes + m.node[r]) * V + v0;
