@@ -54,6 +54,12 @@ __device__ __forceinline__ void store_bf16x4(const float (&y)[4], uint16_t *p) {
                                             __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){y[2], y[3]}, bf16x2_t)));
 }
 
+// Sum of four squares and the rotation of a pair, with what is fused written out: left to the compiler it is another product after every
+// change around it, and the results move by an ulp, which turns single K and V elements.
+__device__ __forceinline__ float sum_squares4(float x, float y, float z, float w) { return fmaf(w, w, fmaf(z, z, fmaf(x, x, y * y))); }
+__device__ __forceinline__ float rotated_first(float x0, float x1, float c, float s) { return fmaf(x0, c, -(x1 * s)); }
+__device__ __forceinline__ float rotated_second(float x0, float x1, float c, float s) { return fmaf(x1, c, x0 * s); }
+
 // SwiGLU of one feature with the row's 1/rms: silu(g * rs) * (u * rs), the quotient g / (1 + exp(-g)) from the hardware's
 // reciprocal and one residual step.  The hardware flushes reciprocals below 2^-126, and 1 + exp(-g) reaches 2^128: it is
 // taken of a 16th.  exp(-g) = inf (g < -88.7) leaves no residual; there the quotient is -0 already.  7B prefill of 810,

@@ -795,7 +795,7 @@ __global__ __launch_bounds__(512) void residual_gain_kernel(float *x, const floa
     }
     if (n_splits > 0) *reinterpret_cast<float4 *>(xr) = v;
   }
-  float ss = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+  float ss = sum_squares4(v.x, v.y, v.z, v.w);
   ss += __shfl_xor(ss, 1, 64);
   ss += __shfl_xor(ss, 2, 64);
   ss += __shfl_xor(ss, 4, 64);
@@ -867,7 +867,7 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(StepMeta m, KvGeom g, i
   t[0] *= rs; t[1] *= rs; t[2] *= rs; t[3] *= rs;
   if (a < H) {
     const float x0 = t[0], x1 = t[1];
-    const float y0 = x0 * c.x - x1 * c.y, y1 = x1 * c.x + x0 * c.y;
+    const float y0 = rotated_first(x0, x1, c.x, c.y), y1 = rotated_second(x0, x1, c.x, c.y);
     const int64_t o = ((int64_t)r * H + a) * hd + j;
     if (qb) {
       split_bf16(y0 * qscale, qb[o], qb_lo[o]);
@@ -880,8 +880,8 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(StepMeta m, KvGeom g, i
     const int b = a - H;
     const float x0 = t[0], x1 = t[1];
     const int64_t base = g.row(m.seq[r], layer, b, m.slot[r]);
-    kc[base + j] = f32_to_bf16_bits(x0 * c.x - x1 * c.y);
-    kc[base + j + half] = f32_to_bf16_bits(x1 * c.x + x0 * c.y);
+    kc[base + j] = f32_to_bf16_bits(rotated_first(x0, x1, c.x, c.y));
+    kc[base + j + half] = f32_to_bf16_bits(rotated_second(x0, x1, c.x, c.y));
     vc[base + j] = f32_to_bf16_bits(t[2]);
     vc[base + j + half] = f32_to_bf16_bits(t[3]);
   }
@@ -940,8 +940,8 @@ __global__ __launch_bounds__(256) void qkv_finish_wide_kernel(StepMeta m, KvGeom
     float y0[4], y1[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      y0[i] = a0[i] * co[i] - a1[i] * si[i];
-      y1[i] = a1[i] * co[i] + a0[i] * si[i];
+      y0[i] = rotated_first(a0[i], a1[i], co[i], si[i]);
+      y1[i] = rotated_second(a0[i], a1[i], co[i], si[i]);
     }
     if (is_q) {
       const int64_t o = ((int64_t)r * H + a) * hd + j;

@@ -307,8 +307,8 @@ __device__ __forceinline__ void one_gemm(const OneArgs &p, OneShared &sh, int pa
       float y0[4], y1[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        y0[i] = v0[i] * co[i] - v1[i] * si[i];
-        y1[i] = v1[i] * co[i] + v0[i] * si[i];
+        y0[i] = rotated_first(v0[i], v1[i], co[i], si[i]);
+        y1[i] = rotated_second(v0[i], v1[i], co[i], si[i]);
       }
       if (q_kind == 0) {
 #pragma unroll
@@ -336,7 +336,7 @@ __device__ __forceinline__ void one_gemm(const OneArgs &p, OneShared &sh, int pa
     const float y[4] = {__uint_as_float(e_x[0]) + v.x, __uint_as_float(e_x[1]) + v.y, __uint_as_float(e_x[2]) + v.z, __uint_as_float(e_x[3]) + v.w};
     const float z[4] = {y[0] * bf16_bits_to_f32(e_g.x & 0xffffu), y[1] * bf16_bits_to_f32(e_g.x >> 16),
                         y[2] * bf16_bits_to_f32(e_g.y & 0xffffu), y[3] * bf16_bits_to_f32(e_g.y >> 16)};
-    float sq = e_ok ? y[0] * y[0] + y[1] * y[1] + y[2] * y[2] + y[3] * y[3] : 0.f;
+    float sq = e_ok ? sum_squares4(y[0], y[1], y[2], y[3]) : 0.f;
     if (e_ok) {
       if (last) {
         store_planes4(z, p.hb, p.hb_lo, packed_act_offset(e_row, e_col, 1));

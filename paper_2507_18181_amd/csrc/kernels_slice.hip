@@ -284,8 +284,8 @@ __global__ __launch_bounds__(kSliceWaves * 64, 2) void gemm_slice_kernel(SliceAr
         float y0[4], y1[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          y0[i] = x0[i] * co[i] - x1[i] * si[i];
-          y1[i] = x1[i] * co[i] + x0[i] * si[i];
+          y0[i] = rotated_first(x0[i], x1[i], co[i], si[i]);
+          y1[i] = rotated_second(x0[i], x1[i], co[i], si[i]);
         }
         if (q_kind == 0) {
           const int64_t o = ((int64_t)q_row * p.H + q_head) * p.hd + q_j;
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kSliceWaves * 64, 2) void gemm_slice_kernel(SliceAr
           const float z[4] = {y[0] * bf16_bits_to_f32(r_g.x & 0xffffu), y[1] * bf16_bits_to_f32(r_g.x >> 16),
                               y[2] * bf16_bits_to_f32(r_g.y & 0xffffu), y[3] * bf16_bits_to_f32(r_g.y >> 16)};
           store_planes4(z, p.t, p.t_lo, packed_act_offset(r_row, r_col, nb));
-          sq = y[0] * y[0] + y[1] * y[1] + y[2] * y[2] + y[3] * y[3];
+          sq = sum_squares4(y[0], y[1], y[2], y[3]);
         }
         sq += __shfl_xor(sq, 16, 64);
         sq += __shfl_xor(sq, 32, 64);

@@ -15,11 +15,11 @@ torch = pytest.importorskip("torch")
 CLASS = dict(n_layers=2, d_model=2048, n_heads=32, n_kv_heads=4, head_dim=64, d_ffn=5632, vocab=1000, rms_eps=1e-5, rope_theta=10000.0)
 # (kernels, tree sizes, cached keys): digest.  one: all layers in one launch, chain: a kernel per stage, generic: the dtype-generic kernels
 DIGESTS = {
-    ("one", (1,), 330): "ad988f5a67c7e56d",
-    ("one", (8,), 330): "5a8292986de586cc",
-    ("one", (13,), 330): "42b807a24fd9ccae",
-    ("one", (2,), 1500): "fe4786aac86db332",
-    ("one", (16,), 2100): "03d19add25a3d4c9",
+    ("one", (1,), 330): "6a1f6aee04cbc2c7",
+    ("one", (8,), 330): "90dfd5069ac32c00",
+    ("one", (13,), 330): "d7c68775a2310169",
+    ("one", (2,), 1500): "e9e20c018c50c79e",
+    ("one", (16,), 2100): "9c46cd2a0a4273b6",
     ("chain", (1,), 330): "f679de54be5d451a",
     ("chain", (16,), 330): "8877651cfc79f8be",
     ("chain", (24,), 500): "0be7ddba71154ed3",
