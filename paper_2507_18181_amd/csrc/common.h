@@ -54,6 +54,10 @@ __device__ __forceinline__ void store_bf16x4(const float (&y)[4], uint16_t *p) {
                                             __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){y[2], y[3]}, bf16x2_t)));
 }
 
+// A word as it goes into the hand-over regions of a forward in one launch, where all ones means "not there yet": a NaN of just those bits
+// loses the last one and stays a NaN, as a float and as two bf16.
+__device__ __forceinline__ uint32_t ready_word(uint32_t u) { return u < ~1u ? u : ~1u; }
+
 // Sum of four squares and the rotation of a pair, with what is fused written out: left to the compiler it is another product after every
 // change around it, and the results move by an ulp, which turns single K and V elements.
 __device__ __forceinline__ float sum_squares4(float x, float y, float z, float w) { return fmaf(w, w, fmaf(z, z, fmaf(x, x, y * y))); }

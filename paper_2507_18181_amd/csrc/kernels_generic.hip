@@ -87,14 +87,14 @@ __global__ __launch_bounds__(256) void begin_kernel(StepMeta m, const T *E, cons
   for (int t = 0; t < 4; ++t) {
     const int c = cols * 128 + t * 32 + (threadIdx.x & 7) * 4;
     const bool ok = live && c < d;
-    if (ok) *reinterpret_cast<float4 *>(x + (int64_t)r * d + c) = make_float4(v[t][0], v[t][1], v[t][2], v[t][3]);
+    if (ok) *reinterpret_cast<float4 *>(x + (int64_t)r * d + c) = make_float4(v[t][0], v[t][1], v[t][2], v[t][3]);  // (widened bf16 is never all ones)
     if (PLANES) {
       float ss = v[t][0] * v[t][0] + v[t][1] * v[t][1] + v[t][2] * v[t][2] + v[t][3] * v[t][3];
       ss += __shfl_xor(ss, 1, 64);
       ss += __shfl_xor(ss, 2, 64);
       ss += __shfl_xor(ss, 4, 64);
       if (ok) {
-        if ((threadIdx.x & 7) == 0) pl.ssq[(int64_t)r * pl.n_slab + (c >> 5)] = ss;
+        if ((threadIdx.x & 7) == 0) pl.ssq[(int64_t)r * pl.n_slab + (c >> 5)] = pl.rp ? __uint_as_float(ready_word(__float_as_uint(ss))) : ss;
         const uint2 g = *reinterpret_cast<const uint2 *>(pl.gain + c);
         const float y[4] = {v[t][0] * bf16_bits_to_f32(g.x & 0xffffu), v[t][1] * bf16_bits_to_f32(g.x >> 16),
                             v[t][2] * bf16_bits_to_f32(g.y & 0xffffu), v[t][3] * bf16_bits_to_f32(g.y >> 16)};
@@ -102,11 +102,9 @@ __global__ __launch_bounds__(256) void begin_kernel(StepMeta m, const T *E, cons
           uint2 hi, lo;
           split_bf16_pair(y[0], y[1], hi.x, lo.x);
           split_bf16_pair(y[2], y[3], hi.y, lo.y);
-          if ((hi.x & hi.y) == ~0u) hi.x = ~1u;  // NaN, but not what stands for missing
-          if ((lo.x & lo.y) == ~0u) lo.x = ~1u;
           const int64_t o = ((int64_t)(c >> 3) * pl.rp + r) * 8 + (c & 4);
-          *reinterpret_cast<uint2 *>(pl.hb + o) = hi;
-          *reinterpret_cast<uint2 *>(pl.hb_lo + o) = lo;
+          *reinterpret_cast<uint2 *>(pl.hb + o) = make_uint2(ready_word(hi.x), ready_word(hi.y));
+          *reinterpret_cast<uint2 *>(pl.hb_lo + o) = make_uint2(ready_word(lo.x), ready_word(lo.y));
         } else {
           store_planes4(y, pl.hb, pl.hb_lo, packed_act_offset(r, c, pl.nb));
         }

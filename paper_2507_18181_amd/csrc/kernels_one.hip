@@ -7,9 +7,10 @@
 //
 // Hand-over.  Between the workgroups of one launch nothing orders plain stores and loads, and fences cost more than a launch
 // (15 us when every workgroup invalidates its caches).  So every datum carries its own readiness: the regions below are
-// filled with ones before the launch, are written once, by 4- or 8-byte stores that go through to memory, and a reader loads
-// them past its caches until none of its words is all ones.  There is no flag, no counter, no order between two stores to rely
-// on: what has been read is checked itself.  Values that would be all ones (NaN) are stored with their last bit cleared.
+// filled with ones before the launch, are written once, by stores of whole words that go through to memory, and a reader loads
+// them past its caches until none of its words is all ones.  There is no flag, no counter, no order between two stores or between the
+// words of one to rely on: every 4 bytes that have been read are checked themselves.  A word that would be all ones (NaN) is stored with
+// its last bit cleared (ready_word).
 //
 // Progress.  Items are numbered in the order of their dependencies and handed out by one counter, so a workgroup only ever waits
 // for items that running workgroups have taken before: any number of resident workgroups, also one, finishes the forward,
@@ -46,15 +47,13 @@ constexpr int kThrough = 17;  // cache policy sc0 sc1: past the caches (sc1 alon
 
 __device__ __forceinline__ u32x4 ll_load16(rsrc_t r, uint32_t off) { return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kThrough)); }
 __device__ __forceinline__ uint32_t ll_load4(rsrc_t r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kThrough); }
-__device__ __forceinline__ bool missing16(const u32x4 &v) { return (v[0] & v[1]) == ~0u || (v[2] & v[3]) == ~0u; }
+__device__ __forceinline__ bool missing16(const u32x4 &v) { return max(max(v[0], v[1]), max(v[2], v[3])) == ~0u; }  // any word
 __device__ __forceinline__ void ll_store8(rsrc_t r, uint32_t off, uint32_t a, uint32_t b) {
-  if ((a & b) == ~0u) a = ~1u;
   typedef __attribute__((ext_vector_type(2))) uint32_t u2;
-  __builtin_amdgcn_raw_buffer_store_b64((u2){a, b}, r, off, 0, kThrough);
+  __builtin_amdgcn_raw_buffer_store_b64((u2){ready_word(a), ready_word(b)}, r, off, 0, kThrough);
 }
 __device__ __forceinline__ void ll_store4(rsrc_t r, uint32_t off, float v) {
-  const uint32_t u = __float_as_uint(v);
-  __builtin_amdgcn_raw_buffer_store_b32(u == ~0u ? ~1u : u, r, off, 0, kThrough);
+  __builtin_amdgcn_raw_buffer_store_b32(ready_word(__float_as_uint(v)), r, off, 0, kThrough);
 }
 __device__ __forceinline__ void ll_store_f4(rsrc_t r, uint32_t off, const float (&y)[4]) {
   ll_store8(r, off, __float_as_uint(y[0]), __float_as_uint(y[1]));

@@ -154,3 +154,51 @@ def test_a_wait_that_runs_out_is_reported(monkeypatch):
     out = ver.verify_tree([np.arange(9, dtype=np.int32)], [np.arange(-1, 8, dtype=np.int32)])
     assert out["status"] == B.SPECASR_E_HIP and ver.kv_len[0] == 20
     ver.close()
+
+
+@pytest.mark.parametrize("what", ["embedding", "input row", "key", "value", "infinite key", "gain", "weight row"])
+@pytest.mark.parametrize("shape,n,L", [("odd", 7, 40), ("tiny", 12, 2090)])
+def test_nan_and_infinity_as_in_the_chain(shape, n, L, what, monkeypatch):
+    """All ones, a NaN in float and in bf16, stands for missing data between the workgroups of the launch and may be data all the same.  A value that a
+    reader would wait for in vain gives up after 20000 looks (the status says so) instead of 2 million."""
+    cfg = _cfg(shape)
+    w = wl.make_weights(cfg, 961, "bf16")
+    rng = np.random.default_rng([962, n])
+    cap = L + n
+    K, V = wl.seeded_cache(cfg, 963, np.asarray([L], np.int32), cap, "bf16", batch=1)
+    tok = np.arange(n, dtype=np.int32)
+    tree = wl.random_tree(rng, n, max_children=3)
+    emb, use = None, None
+    if what == "embedding":
+        w["tok_embed"][tok[n - 1]] = 0xffff
+    elif what == "input row":
+        emb = torch.full((1, 32, cfg["d_model"]), -1, dtype=torch.int16, device="cuda:0").view(torch.bfloat16)
+        use = [[i == n // 2 for i in range(n)]]
+    elif what == "key":
+        K[0, 1, 0, L // 2] = 0xffff
+    elif what == "value":
+        V[0, 0, -1, L - 1] = 0xffff
+    elif what == "infinite key":
+        K[0, 1, 0, 3, 5] = 0x7f80
+    elif what == "gain":
+        w["layers"][1]["ffn_norm"][-3:] = 0xffff
+    else:
+        w["layers"][0]["wv"][1] = 0xffff
+        w["layers"][1]["w_up"][-1] = 0xffff
+    got = []
+    for polls in ("20000", "0"):
+        monkeypatch.setenv("SPECASR_ONE_POLLS", polls)
+        ver = _verifier(cfg, w, cap)
+        ver.set_cache(K, V, [L])
+        fw = ver.tree_forward([tok], [tree], embeds=emb, use_embed=use)
+        again = ver.verify_tree([tok], [tree]) if emb is None else fw  # synchronises: reports a wait that ran out
+        assert fw["status"] == 0 and again["status"] == 0
+        k1, v1 = ver.get_cache()
+        got.append([fw["logits"][0, :n].double().cpu().numpy()] + [wl.bf16_to_f32(c[..., L:L + n, :]).astype(np.float64) for c in (k1, v1)])
+        ver.close()
+    assert any(np.isnan(a).any() for a in got[1])
+    for a, b in zip(*got):
+        assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isinf(a), np.isinf(b))
+        ok = np.isfinite(b)
+        # the bound of two orders of fp32 sums, as above, over what is finite
+        assert np.linalg.norm(a[ok] - b[ok]) <= 2.5e-3 * max(np.linalg.norm(b[ok]), 1e-30)
