@@ -170,7 +170,8 @@ specasr_status specasr_verify_tree(specasr_ctx *ctx, specasr_kv *kv, const speca
  * verification of Sec. II-B).  Writes K/V of node i to slot kv_len+i, the greedy
  * token per node to argmax_dev (DEVICE int32 [batch][max_nodes]) and, if
  * logits_dev != NULL, fp32 logits [batch][max_nodes][vocab].  Asynchronous;
- * kv_len is not changed. */
+ * kv_len is not changed.  After synchronising, specasr_last_hip_error tells
+ * whether a wait inside the forward ran out. */
 specasr_status specasr_tree_forward(specasr_ctx *ctx, specasr_kv *kv, const specasr_tree *tree,
                                     int32_t *argmax_dev, float *logits_dev, void *workspace,
                                     size_t workspace_bytes, void *stream);
@@ -271,8 +272,15 @@ specasr_status specasr_commit(specasr_ctx *ctx, specasr_kv *kv, const int32_t *n
 int32_t specasr_uses_mfma(const specasr_ctx *ctx, int32_t rows);
 
 const char *specasr_strerror(specasr_status s);
-/* hipError_t value of the last failing HIP call seen by this context (0 if none); hipErrorLaunchTimeOut
- * with SPECASR_E_HIP: a wait inside an earlier forward ran out (two seconds), its results are void. */
+/* hipError_t value of the last failing HIP call seen by this context (0 if none).
+ *
+ * hipErrorLaunchTimeOut also stands for a forward of this context (up to 16 nodes of one sequence, models whose
+ * layers run in one launch) in which a wait between workgroups ran out, after about two million looks or some
+ * seconds: its results are void, NaN where a row depends on what was missing, and so are the K/V rows it wrote behind kv_len.
+ * The caller of an asynchronous forward, or of a replayed graph that holds one, learns it here once the stream has been
+ * synchronised; specasr_verify_tree returns SPECASR_E_HIP itself.  The state stays: every later call of the context that
+ * would run, accept or commit a forward returns SPECASR_E_HIP with nothing enqueued and kv_len unchanged, whatever its
+ * stream and cache, until the context is destroyed. */
 int32_t specasr_last_hip_error(const specasr_ctx *ctx);
 /* Library/ABI version, bumped when a signature or struct changes. */
 int32_t specasr_abi_version(void);

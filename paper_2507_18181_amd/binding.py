@@ -28,6 +28,7 @@ SPECASR_FLAG_GENERIC_KERNELS = 1
 SPECASR_FLAG_NO_REPACK = 2
 SPECASR_FLAG_NO_WIDE = 4
 SPECASR_MAX_NODES = 64
+HIP_ERROR_LAUNCH_TIMEOUT = 702  # hipErrorLaunchTimeOut, what specasr_last_hip_error says of a wait that ran out
 SPECASR_STATIC_MAX_BATCH = 16
 
 EXPORTS = ("specasr_create", "specasr_destroy", "specasr_workspace_bytes", "specasr_verify_tree",

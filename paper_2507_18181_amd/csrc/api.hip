@@ -99,7 +99,7 @@ struct specasr_ctx {
   int32_t *out_host = nullptr;  // pinned, results of verify_tree
   int32_t *out_dev = nullptr;   // the same, as the device sees it
   size_t out_host_words = 0;
-  uint32_t *gave_up = nullptr, *gave_up_dev = nullptr;  // pinned word that a forward in one launch sets when a wait ran out
+  uint32_t *gave_up = nullptr, *gave_up_dev = nullptr;  // pinned word that a forward in one launch sets when a wait ran out, for good
   int32_t last_hip = 0;
   int device = 0;
   int n_cu = 256;  // compute units = workgroups of the persistent-style GEMM grid
@@ -449,10 +449,12 @@ specasr_status next_slot(specasr_ctx *ctx, Staging **out) {
   return SPECASR_OK;
 }
 
-// A wait inside an earlier forward ran out (its results are void): reported once, by the call that sees it.
+// A wait inside a forward in one launch ran out, whose results are void.  The word is never cleared: which call, stream or cache the
+// forward belonged to is known to its caller alone, so from then on every call that would run, read or commit a forward says so, before
+// it enqueues anything.
+bool gave_up(const specasr_ctx *ctx) { return ctx->gave_up != nullptr && *(const volatile uint32_t *)ctx->gave_up != 0; }
 specasr_status check_gave_up(specasr_ctx *ctx) {
-  if (ctx->gave_up == nullptr || *(volatile uint32_t *)ctx->gave_up == 0) return SPECASR_OK;
-  *(volatile uint32_t *)ctx->gave_up = 0;
+  if (!gave_up(ctx)) return SPECASR_OK;
   ctx->last_hip = (int32_t)hipErrorLaunchTimeOut;
   return SPECASR_E_HIP;
 }
@@ -460,8 +462,7 @@ specasr_status check_gave_up(specasr_ctx *ctx) {
 // Lay the metadata block out in a pinned staging slot, where the first kernel of the call reads it.  staged() has to
 // follow that kernel: the slot is not written again before it has ended.
 specasr_status stage_meta(specasr_ctx *ctx, HostStep &hs) {
-  specasr_status rc = check_gave_up(ctx);
-  if (rc == SPECASR_OK) rc = next_slot(ctx, &hs.staged);
+  const specasr_status rc = next_slot(ctx, &hs.staged);
   if (rc != SPECASR_OK) return rc;
   memcpy(hs.staged->host, hs.words.data(), hs.words.size() * 4);
   return SPECASR_OK;
@@ -1110,7 +1111,10 @@ const char *specasr_strerror(specasr_status s) {
   return "unknown status";
 }
 
-int32_t specasr_last_hip_error(const specasr_ctx *ctx) { return ctx ? ctx->last_hip : 0; }
+int32_t specasr_last_hip_error(const specasr_ctx *ctx) {
+  if (!ctx) return 0;
+  return gave_up(ctx) ? (int32_t)hipErrorLaunchTimeOut : ctx->last_hip;
+}
 
 int32_t specasr_uses_mfma(const specasr_ctx *ctx, int32_t rows) {
   return (ctx && ctx->fast && rows >= 1) ? 1 : 0;
@@ -1276,6 +1280,8 @@ specasr_status specasr_tree_forward(specasr_ctx *ctx, specasr_kv *kv, const spec
   if (s != SPECASR_OK) return s;
   s = check_ws(ctx, workspace, workspace_bytes, kv->batch);
   if (s != SPECASR_OK) return s;
+  s = check_gave_up(ctx);
+  if (s != SPECASR_OK) return s;
   hipStream_t st = (hipStream_t)stream;
   char *ws = (char *)workspace;
   const WsLayout L = ws_layout(ctx, kv->batch);
@@ -1313,6 +1319,8 @@ specasr_status specasr_tree_forward_top2(specasr_ctx *ctx, specasr_kv *kv, const
   s = validate_tree(ctx, tree, kv->batch, kv->kv_len, kv->capacity, true);
   if (s != SPECASR_OK) return s;
   s = check_ws(ctx, workspace, workspace_bytes, kv->batch);
+  if (s != SPECASR_OK) return s;
+  s = check_gave_up(ctx);
   if (s != SPECASR_OK) return s;
   hipStream_t st = (hipStream_t)stream;
   char *ws = (char *)workspace;
@@ -1364,6 +1372,8 @@ specasr_status specasr_prefill(specasr_ctx *ctx, specasr_kv *kv, const int32_t *
     }
   }
   s = check_ws(ctx, workspace, workspace_bytes, B);
+  if (s != SPECASR_OK) return s;
+  s = check_gave_up(ctx);
   if (s != SPECASR_OK) return s;
   hipStream_t st = (hipStream_t)stream;
   char *ws = (char *)workspace;
@@ -1515,6 +1525,8 @@ specasr_status specasr_accept(specasr_ctx *ctx, const specasr_tree *tree, int32_
   if (s != SPECASR_OK) return s;
   s = check_ws(ctx, workspace, workspace_bytes, batch);
   if (s != SPECASR_OK) return s;
+  s = check_gave_up(ctx);
+  if (s != SPECASR_OK) return s;
   hipStream_t st = (hipStream_t)stream;
   char *ws = (char *)workspace;
   const WsLayout L = ws_layout(ctx, batch);
@@ -1538,6 +1550,8 @@ specasr_status specasr_accept_from_logits(specasr_ctx *ctx, const specasr_tree *
   specasr_status s = validate_tree(ctx, tree, batch, nullptr, 0, false);
   if (s != SPECASR_OK) return s;
   s = check_ws(ctx, workspace, workspace_bytes, batch);
+  if (s != SPECASR_OK) return s;
+  s = check_gave_up(ctx);
   if (s != SPECASR_OK) return s;
   hipStream_t st = (hipStream_t)stream;
   char *ws = (char *)workspace;
@@ -1574,6 +1588,8 @@ specasr_status specasr_commit(specasr_ctx *ctx, specasr_kv *kv, const int32_t *n
       if (p[k] <= p[k - 1] || p[k] >= n) return SPECASR_E_PATH;
   }
   s = check_ws(ctx, workspace, workspace_bytes, B);
+  if (s != SPECASR_OK) return s;
+  s = check_gave_up(ctx);
   if (s != SPECASR_OK) return s;
   hipStream_t st = (hipStream_t)stream;
   char *ws = (char *)workspace;
@@ -1612,6 +1628,8 @@ specasr_status specasr_verify_tree(specasr_ctx *ctx, specasr_kv *kv, const speca
   s = validate_tree(ctx, tree, kv->batch, kv->kv_len, kv->capacity, true);
   if (s != SPECASR_OK) return s;
   s = check_ws(ctx, workspace, workspace_bytes, kv->batch);
+  if (s != SPECASR_OK) return s;
+  s = check_gave_up(ctx);
   if (s != SPECASR_OK) return s;
   const specasr_config &c = ctx->cfg;
   const int B = kv->batch;
@@ -1768,6 +1786,8 @@ specasr_status specasr_accept_from_logits_static(specasr_ctx *ctx, const specasr
   specasr_status s = validate_tree(ctx, tree, batch, nullptr, 0, false);
   if (s != SPECASR_OK) return s;
   if (batch > kStaticMaxBatch) return SPECASR_E_UNSUPPORTED;  // beyond what the device array holds
+  s = check_gave_up(ctx);
+  if (s != SPECASR_OK) return s;
   char *sp = nullptr;
   s = static_scratch(ctx, &sp);
   if (s != SPECASR_OK) return s;

@@ -81,6 +81,12 @@ class Verifier:
         torch.cuda.synchronize()
         return (_to_host(self.k[:, :, :, lo:hi].contiguous()), _to_host(self.v[:, :, :, lo:hi].contiguous()))
 
+    def _after_sync(self, rc):
+        """The status of an asynchronous forward once the GPU has finished it: a wait inside it may have run out."""
+        if rc == B.SPECASR_OK and B.specasr_last_hip_error(self.ctx) == B.HIP_ERROR_LAUNCH_TIMEOUT:
+            return B.SPECASR_E_HIP
+        return rc
+
     # -- marshalling helpers ----------------------------------------------------
     def _tree(self, tokens, parents, embeds=None, use_embed=None):
         """tokens/parents: list (one per sequence) of int sequences."""
@@ -132,7 +138,7 @@ class Verifier:
         rc = B.specasr_tree_forward(self.ctx, self._kv, tree, argmax, logits, self.ws_ptr,
                                     self.ws_bytes, stream)
         torch.cuda.synchronize()
-        return dict(status=rc, argmax=argmax, logits=logits)
+        return dict(status=self._after_sync(rc), argmax=argmax, logits=logits)
 
     def tree_forward_top2(self, tokens, parents, want_logits=False, embeds=None, use_embed=None,
                           stream=None):
@@ -149,7 +155,7 @@ class Verifier:
         rc = B.specasr_tree_forward_top2(self.ctx, self._kv, tree, top2, prob, logits, self.ws_ptr,
                                          self.ws_bytes, stream)
         torch.cuda.synchronize()
-        return dict(status=rc, top2=top2, prob=prob, logits=logits)
+        return dict(status=self._after_sync(rc), top2=top2, prob=prob, logits=logits)
 
     def prefill(self, tokens, embeds=None, use_embed=None, want_next=True, stream=None):
         """Append positions to every sequence: tokens = list (one per sequence) of int sequences,

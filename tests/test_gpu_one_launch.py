@@ -202,3 +202,63 @@ def test_nan_and_infinity_as_in_the_chain(shape, n, L, what, monkeypatch):
         ok = np.isfinite(b)
         # the bound of two orders of fp32 sums, as above, over what is finite
         assert np.linalg.norm(a[ok] - b[ok]) <= 2.5e-3 * max(np.linalg.norm(b[ok]), 1e-30)
+
+
+def _gives_up(monkeypatch, looks="1"):
+    cfg = _cfg("tiny")
+    monkeypatch.setenv("SPECASR_ONE_POLLS", looks)
+    ver = _verifier(cfg, wl.make_weights(cfg, 951, "bf16"), 64)
+    K, V = wl.seeded_cache(cfg, 952, np.asarray([20], np.int32), 64, "bf16", batch=1)
+    ver.set_cache(K, V, [20])
+    return ver, np.arange(9, dtype=np.int32), np.arange(-1, 8, dtype=np.int32)
+
+
+@pytest.mark.parametrize("call", ["tree_forward", "tree_forward_top2"])
+def test_a_forward_that_gave_up_is_not_handed_on(call, monkeypatch):
+    """The wrappers wait for the forward, so its own status says that it is void."""
+    from paper_2507_18181_amd import binding as B
+    ver, tok, par = _gives_up(monkeypatch)
+    assert getattr(ver, call)([tok], [par])["status"] == B.SPECASR_E_HIP
+    ver.close()
+
+
+@pytest.mark.parametrize("replay", [False, True])
+def test_a_forward_that_gave_up_is_not_committed(replay, monkeypatch):
+    """An asynchronous forward, eager or replayed: told after the synchronisation, and nothing that follows accepts or commits it, on this stream
+    or another, however often it is asked."""
+    from paper_2507_18181_amd import binding as B
+    ver, tok, par = _gives_up(monkeypatch)
+    argmax = torch.full((1, 32), -1, dtype=torch.int32, device="cuda:0")
+    logits = torch.zeros((1, 32, ver.cfg["vocab"]), device="cuda:0")
+    t, keep = ver._tree([tok], [par])
+    s = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+
+    def forward():
+        return B.specasr_tree_forward(ver.ctx, ver._kv, t, argmax, logits, ver.ws_ptr, ver.ws_bytes, s.cuda_stream)
+
+    assert ver.accept([tok], [par], argmax_dev=argmax)["status"] == B.SPECASR_OK  # pinned memory is there: nothing is allocated under capture
+    if replay:
+        with torch.cuda.graph(g, stream=s):
+            assert forward() == B.SPECASR_OK
+        assert B.specasr_last_hip_error(ver.ctx) == 0
+        g.replay()
+    else:
+        assert forward() == B.SPECASR_OK
+    torch.cuda.synchronize()
+    assert B.specasr_last_hip_error(ver.ctx) == B.HIP_ERROR_LAUNCH_TIMEOUT
+    assert torch.isnan(logits[0, :9]).any()  # computed from what was missing
+    before = ver.get_cache()
+    for _ in range(2):
+        assert ver.commit([9], [[0, 2, 4]]) == B.SPECASR_E_HIP
+        assert ver.verify_tree([tok], [par])["status"] == B.SPECASR_E_HIP
+        assert ver.accept([tok], [par], argmax_dev=argmax)["status"] == B.SPECASR_E_HIP
+        assert ver.accept([tok], [par], logits_dev=logits)["status"] == B.SPECASR_E_HIP
+        assert ver.prefill([tok])["status"] == B.SPECASR_E_HIP
+        out = [torch.zeros(32, dtype=torch.int32, device="cuda:0") for _ in range(4)]
+        assert B.specasr_accept_from_logits_static(ver.ctx, t, 1, logits, *out, None) == B.SPECASR_E_HIP
+        assert B.specasr_last_hip_error(ver.ctx) == B.HIP_ERROR_LAUNCH_TIMEOUT
+    assert ver.kv_len[0] == 20
+    assert all(np.array_equal(a, b) for a, b in zip(before, ver.get_cache()))
+    ver.close()
