@@ -485,9 +485,15 @@ int ws_lanes(const specasr_ctx *ctx, int batch) {
   return n < 2 ? 2 : n;  // two lanes at least: consecutive prefill chunks of one sequence overlap
 }
 
-// Scratch of a forward in one launch follows the lanes' and the wide buffers.
-size_t one_offset(const specasr_ctx *ctx, int batch) { return ws_layout(ctx, batch).total * ws_lanes(ctx, batch) + ws_layout_wide(ctx, batch).total; }
-size_t ws_bytes(const specasr_ctx *ctx, int batch) { return one_offset(ctx, batch) + (ctx->one_layers ? one_launch_bytes(ctx->md) : 0); }
+// Scratch of a forward in one launch: a call of one sequence has it where a wide pass has its buffers, behind the lanes'.  It works in
+// those of the first lane alone, and on the caller's stream, as every wide pass does, so neither sees the other's data.
+size_t one_offset(const specasr_ctx *ctx) { return ws_layout(ctx, 1).total * ws_lanes(ctx, 1); }
+bool one_launch_on(const specasr_ctx *ctx) { return ctx->one_layers != nullptr && ctx->tune.one_polls > 0; }
+// A workspace for several sequences also serves calls of one.
+size_t ws_bytes(const specasr_ctx *ctx, int batch) {
+  const size_t all = ws_layout(ctx, batch).total * ws_lanes(ctx, batch) + ws_layout_wide(ctx, batch).total;
+  return one_launch_on(ctx) ? std::max(all, one_offset(ctx) + one_launch_bytes(ctx->md)) : all;
+}
 
 specasr_status check_ws(const specasr_ctx *ctx, const void *ws, size_t bytes, int batch) {
   if (!ws) return SPECASR_E_WORKSPACE;
@@ -776,7 +782,7 @@ specasr_status forward_fast(specasr_ctx *ctx, const StepMeta &m, const KvGeom &g
   const RowNorm nrm16{ssq, d / 16, d, md.rms_eps};  // statistics as the o projection's epilogue leaves them
   // Few rows of one sequence: all layers in one launch.  Forced plans and stage timings are about the kernels of the chain.
   OnePlan one;
-  if (ro.one != nullptr && ctx->tune.one_polls > 0 && m.batch == 1 && ro.first_row == 0 && !sync.record && !sync.wait && ctx->prof_stage < 0 && ctx->tune.attn_chunk == 0 &&
+  if (ro.one != nullptr && m.batch == 1 && ro.first_row == 0 && !sync.record && !sync.wait && ctx->prof_stage < 0 && ctx->tune.attn_chunk == 0 &&
       std::all_of(ctx->tune.gemm_splits, ctx->tune.gemm_splits + 4, [](int v) { return v == 0; }))
     one = plan_one_launch(md, R, m.kv_len0);
   if (ctx->tune.debug) {  // the kernel of every projection, with its tile (half-bands x 16 rows, 0: 8; bands x 32 rows)
@@ -1303,7 +1309,7 @@ specasr_status specasr_tree_forward(specasr_ctx *ctx, specasr_kv *kv, const spec
     ReadOut ro;
     ro.argmax = argmax_dev + grp.s0 * MN;
     ro.logits = logits_dev ? logits_dev + grp.s0 * MN * ctx->cfg.vocab : nullptr;
-    if (kv->batch == 1 && ctx->one_layers) ro.one = ws + one_offset(ctx, 1);
+    if (kv->batch == 1 && one_launch_on(ctx)) ro.one = ws + one_offset(ctx);
     s = forward_common(ctx, &grp.kv, &grp.tree, ro, wl, Lg, hs, lanes.stream(gi), LayerSync(), wide);
     if (s != SPECASR_OK) return s;
   }
@@ -1344,7 +1350,7 @@ specasr_status specasr_tree_forward_top2(specasr_ctx *ctx, specasr_kv *kv, const
     ro.top2 = top2_dev + grp.s0 * MN * 2;
     ro.prob = top1_prob_dev + grp.s0 * MN;
     ro.logits = logits_dev ? logits_dev + grp.s0 * MN * ctx->cfg.vocab : nullptr;
-    if (kv->batch == 1 && ctx->one_layers) ro.one = ws + one_offset(ctx, 1);
+    if (kv->batch == 1 && one_launch_on(ctx)) ro.one = ws + one_offset(ctx);
     s = forward_common(ctx, &grp.kv, &grp.tree, ro, wl, Lg, hs, lanes.stream(gi), LayerSync(), wide);
     if (s != SPECASR_OK) return s;
   }
@@ -1659,7 +1665,7 @@ specasr_status specasr_verify_tree(specasr_ctx *ctx, specasr_kv *kv, const speca
     ro.argmax = argmax_dev + grp.s0 * MN;
     ro.records = ctx->fast && (hs.rows <= 64 || wide);  // what forward_common runs on the MFMA path
     ro.logits = out->logits ? out->logits + grp.s0 * MN * c.vocab : nullptr;
-    if (B == 1 && ctx->one_layers) ro.one = ws + one_offset(ctx, 1);
+    if (B == 1 && one_launch_on(ctx)) ro.one = ws + one_offset(ctx);
     s = forward_common(ctx, &grp.kv, &grp.tree, ro, wl, Lg, hs, sl, LayerSync(), wide);
     if (s != SPECASR_OK) return s;
     StepMeta m = device_meta(ctx, wl, Lg, hs);

@@ -262,3 +262,57 @@ def test_a_forward_that_gave_up_is_not_committed(replay, monkeypatch):
     assert ver.kv_len[0] == 20
     assert all(np.array_equal(a, b) for a, b in zip(before, ver.get_cache()))
     ver.close()
+
+
+def test_workspace(monkeypatch):
+    """The launch has its scratch where wide passes have theirs: as long as it fits, no call needs a larger workspace for it; without wide
+    passes a workspace for one sequence grows by it, and one for several sequences also serves calls of one."""
+    from paper_2507_18181_amd import binding as B
+    from paper_2507_18181_amd.runtime import Verifier
+    cfg = _cfg("wide")
+    w = wl.make_weights(cfg, 971, "bf16")
+    sizes = {}
+    for polls in (None, "0"):
+        if polls:
+            monkeypatch.setenv("SPECASR_ONE_POLLS", polls)
+        for flags in (0, B.SPECASR_FLAG_NO_WIDE):
+            ver = Verifier(cfg, w, "bf16", max_nodes=32, capacity=64, max_batch=16, flags=flags)
+            sizes[polls, flags] = [B.specasr_workspace_bytes(ver.ctx, b) for b in (1, 2, 16)]
+            ver.close()
+    assert sizes[None, 0] == sizes["0", 0]
+    one, chain = sizes[None, B.SPECASR_FLAG_NO_WIDE], sizes["0", B.SPECASR_FLAG_NO_WIDE]
+    assert one[0] > chain[0] and one == sorted(one) and one[2] == chain[2]
+
+
+@pytest.mark.parametrize("wide", [True, False])
+def test_between_passes_over_many_rows(wide, monkeypatch):
+    """Prefill, a forward in one launch and prefill again, enqueued one behind the other in one workspace, against contexts of their own."""
+    from paper_2507_18181_amd import binding as B
+    from paper_2507_18181_amd.runtime import Verifier
+    cfg = _cfg("odd")
+    w = wl.make_weights(cfg, 981, "bf16")
+    rng = np.random.default_rng(982)
+    first, second, tok = (rng.integers(0, cfg["vocab"], n).astype(np.int32) for n in (90, 70, 11))
+    par = wl.random_tree(rng, 11, max_children=3)
+    flags = 0 if wide else B.SPECASR_FLAG_NO_WIDE
+
+    def run(calls):
+        ver = Verifier(cfg, w, "bf16", max_nodes=32, capacity=256, flags=flags)
+        argmax = torch.full((1, 32), -1, dtype=torch.int32, device="cuda:0")
+        logits = torch.zeros((1, 32, cfg["vocab"]), device="cuda:0")
+        for what in calls:
+            if isinstance(what, str):
+                t, keep = ver._tree([tok], [par])
+                assert B.specasr_tree_forward(ver.ctx, ver._kv, t, argmax, logits, ver.ws_ptr, ver.ws_bytes, None) == 0
+            else:
+                n = np.asarray([len(what)], np.int32)
+                assert B.specasr_prefill(ver.ctx, ver._kv, what[None], None, None, n, len(what), None, ver.ws_ptr, ver.ws_bytes, None) == 0
+        torch.cuda.synchronize()
+        out = logits.cpu().numpy(), [c[..., :ver.kv_len[0], :] for c in ver.get_cache()]
+        ver.close()
+        return out
+
+    mixed = run([first, "tree", second, "tree", first])
+    prefills = run([first, second, first])
+    assert all(np.array_equal(a, b) for a, b in zip(mixed[1], prefills[1]))
+    assert np.array_equal(mixed[0], run([first, second, "tree"])[0])
