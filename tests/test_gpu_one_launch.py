@@ -15,6 +15,7 @@ SHAPES = {
     "tiny": dict(n_layers=2, d_model=256, n_heads=4, n_kv_heads=4, d_ffn=672),      # 8 stages of k over 8 wavefronts, ragged half-bands
     "odd": dict(n_layers=3, d_model=608, n_heads=6, n_kv_heads=2, d_ffn=1184),      # wavefronts with 1 and 2 .. 5 stages
     "small": dict(n_layers=2, d_model=128, n_heads=2, n_kv_heads=1, d_ffn=160),     # wavefronts without any
+    "grouped": dict(n_layers=2, d_model=512, n_heads=16, n_kv_heads=2, d_ffn=992),  # 8 query heads per KV head
     "wide": dict(n_layers=2, d_model=2048, n_heads=32, n_kv_heads=4, d_ffn=5632),   # the largest
 }
 
@@ -316,3 +317,46 @@ def test_between_passes_over_many_rows(wide, monkeypatch):
     prefills = run([first, second, first])
     assert all(np.array_equal(a, b) for a, b in zip(mixed[1], prefills[1]))
     assert np.array_equal(mixed[0], run([first, second, "tree"])[0])
+
+
+@pytest.mark.parametrize("n,L,groups,chunks", [(1, 1200, 1, 3), (2, 4096, 1, 8), (5, 2100, 2, 5), (8, 4096, 2, 8), (9, 2100, 3, 5), (16, 2100, 4, 5), (16, 4096, 4, 8)])
+def test_groups_of_query_rows_and_chunks_of_keys(n, L, groups, chunks, monkeypatch, capfd):
+    """Several of both: which partial output is whose.  The number of chunks is the plan's own, so that another rule cannot leave this without any."""
+    assert groups == (8 * n + 31) // 32
+    test_against_the_oracle_and_the_chain("grouped", n, L, monkeypatch, capfd)
+    monkeypatch.delenv("SPECASR_ONE_POLLS")
+    cfg = _cfg("grouped")
+    ver = _verifier(cfg, wl.make_weights(cfg, 911, "bf16"), L + n)
+    ver.kv_len[:] = L
+    capfd.readouterr()
+    assert ver.tree_forward([np.arange(n, dtype=np.int32)], [np.arange(-1, n - 1, dtype=np.int32)])["status"] == 0
+    assert "%d key chunks" % chunks in capfd.readouterr().err
+    ver.close()
+
+
+@pytest.mark.parametrize("shift", [1, 4])
+@pytest.mark.parametrize("n,L", [(8, 300), (8, 2100), (13, 300), (16, 2100)])
+def test_cache_that_is_not_on_16_bytes(n, L, shift):
+    """K and V 2 or 8 bytes into a larger tensor, read through registers: the bits of an aligned cache, up to 8 rows and beyond."""
+    from paper_2507_18181_amd import binding as B
+    cfg = _cfg("grouped")
+    w = wl.make_weights(cfg, 991, "bf16")
+    rng = np.random.default_rng([992, n, L])
+    cap = L + n + 5
+    K, V = wl.seeded_cache(cfg, 993, np.asarray([L], np.int32), cap, "bf16", batch=1)
+    tree = wl.random_tree(rng, n, max_children=3)
+    tok = rng.integers(0, cfg["vocab"], n).astype(np.int32)
+    res = []
+    for s in (0, shift):
+        ver = _verifier(cfg, w, cap)
+        ver.k, ver.v = (torch.zeros(t.numel() + s, dtype=t.dtype, device=t.device)[s:].view(t.shape) for t in (ver.k, ver.v))
+        assert ver.k.data_ptr() % 16 == ver.v.data_ptr() % 16 == 2 * s
+        ver._kv = B.make_kv(ver.k, ver.v, cap, ver.kv_len)
+        ver.set_cache(K, V, [L])
+        fw = ver.tree_forward([tok], [tree])
+        vt = ver.verify_tree([tok], [tree], want_logits=True)
+        assert fw["status"] == 0 and vt["status"] == 0
+        res.append([fw["logits"].cpu().numpy(), vt["logits"].cpu().numpy(), vt["path"]] + list(ver.get_cache()))
+        ver.close()
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
