@@ -41,6 +41,9 @@ constexpr int one_hb_o(int np) { return np == 1 ? 2 : 1; }  // us per call: 1 ro
 constexpr int kOneSums = 4 * kOneWaves * 64;  // float4 of the sums of up to 4 half-bands
 constexpr int kOneHd = 64;
 constexpr int kTU = 32 * kOneHd / 8;          // 16-byte units of a key tile
+constexpr int kOneKeys = 4096, kChunkTiles = 16;  // cached keys of a call at most; tiles of a chunk at least, where there are several
+constexpr int kMaxChunks = 8;                     // so many chunks are in flight in one_merge, and have room in the scratch
+static_assert((kOneKeys / 32 + kChunkTiles - 1) / kChunkTiles <= kMaxChunks, "every prefix that is taken fits");
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr int kThrough = 17;  // cache policy sc0 sc1: past the caches (sc1 alone is as fast)
@@ -508,7 +511,7 @@ __device__ __forceinline__ void one_attention(const OneArgs &p, OneShared &sh, i
 __device__ __forceinline__ void one_merge(const OneArgs &p, OneShared &sh, int par, int item, rsrc_t rs) {
   Next next;
   next.ask(p);
-  constexpr int TPR = kOneHd / 4, MC = 8;
+  constexpr int TPR = kOneHd / 4, MC = kMaxChunks;
   const uint32_t rh = (item * kOneThreads + threadIdx.x) / TPR;
   const int c = (threadIdx.x % TPR) * 4;
   const bool ok = rh < (uint32_t)(p.rows * p.H);
@@ -590,7 +593,6 @@ __global__ __launch_bounds__(kOneThreads, 2) void one_launch_kernel(OneArgs args
 
 // --------------------------------------------------------------------------- plan and launch
 namespace {
-constexpr int kMaxChunks = 8;
 constexpr unsigned kOneLds = 2 * kOneWaves * kTU * 16;
 
 OneLayout one_layout(const ModelDims &md, int rp, int n_chunks) {
@@ -617,15 +619,14 @@ bool one_launch_model(const ModelDims &md, int n_cu) {
 
 OnePlan plan_one_launch(const ModelDims &md, int rows, int kv_len) {
   OnePlan pl;
-  if (rows > 16 || kv_len > 4096) return pl;
+  if (rows > 16 || kv_len > kOneKeys) return pl;
   pl.rows = rows;
   for (pl.rp = 1; pl.rp < rows;) pl.rp *= 2;
   pl.n_rg = (md.n_heads / md.n_kv_heads * rows + 31) / 32;
   const int tiles = (kv_len + 31) / 32;
   // One chunk per KV head: 0.9 us for every 8 tiles against about 7 for the partial outputs and another hand-over (1.1B, us per call,
   // one chunk / chunks of 16 tiles: 1 row, 800 keys 730 / 750, 1600 789 / 751; 8 rows, 1600 849 / 945, 3200 about 1010 / 890).
-  pl.n_chunks = tiles <= (rows <= 2 ? 36 : 64) ? 1 : (tiles + 15) / 16;
-  if (pl.n_chunks > kMaxChunks) pl.n_chunks = kMaxChunks;
+  pl.n_chunks = tiles <= (rows <= 2 ? 36 : 64) ? 1 : (tiles + kChunkTiles - 1) / kChunkTiles;
   pl.chunk_tiles = (tiles + pl.n_chunks - 1) / pl.n_chunks;
   if (pl.chunk_tiles > 0) pl.n_chunks = (tiles + pl.chunk_tiles - 1) / pl.chunk_tiles;
   pl.lay = one_layout(md, pl.rp, pl.n_chunks);
