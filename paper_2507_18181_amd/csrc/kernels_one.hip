@@ -624,9 +624,10 @@ OnePlan plan_one_launch(const ModelDims &md, int rows, int kv_len) {
   for (pl.rp = 1; pl.rp < rows;) pl.rp *= 2;
   pl.n_rg = (md.n_heads / md.n_kv_heads * rows + 31) / 32;
   const int tiles = (kv_len + 31) / 32;
-  // One chunk per KV head: 0.9 us for every 8 tiles against about 7 for the partial outputs and another hand-over (1.1B, us per call,
-  // one chunk / chunks of 16 tiles: 1 row, 800 keys 730 / 750, 1600 789 / 751; 8 rows, 1600 849 / 945, 3200 about 1010 / 890).
-  pl.n_chunks = tiles <= (rows <= 2 ? 36 : 64) ? 1 : (tiles + kChunkTiles - 1) / kChunkTiles;
+  // One chunk per KV head: 0.9 us per layer for every 8 tiles, against another hand-over and the partial outputs, 1.5 us where these are few (2 layers
+  // of 1 head: 8 rows, 2000 keys 69 us per call in one chunk, 59 in chunks) and 6 with 8 rows of 32 heads (1.1B, us per call, one chunk / chunks of 16
+  // tiles: 1 row, 800 keys 648 / 690, 1600 714 / 685, 3200 872 / 700; 8 rows, 1600 750 / 800, 3200 908 / 743; 16 rows, 3200 992 / 876).
+  pl.n_chunks = tiles <= (rows * md.n_heads <= 64 ? 36 : 64) ? 1 : (tiles + kChunkTiles - 1) / kChunkTiles;
   pl.chunk_tiles = (tiles + pl.n_chunks - 1) / pl.n_chunks;
   if (pl.chunk_tiles > 0) pl.n_chunks = (tiles + pl.chunk_tiles - 1) / pl.chunk_tiles;
   pl.lay = one_layout(md, pl.rp, pl.n_chunks);

@@ -319,7 +319,7 @@ def test_between_passes_over_many_rows(wide, monkeypatch):
     assert np.array_equal(mixed[0], run([first, second, "tree"])[0])
 
 
-@pytest.mark.parametrize("n,L,groups,chunks", [(1, 1200, 1, 3), (2, 4096, 1, 8), (5, 2100, 2, 5), (8, 4096, 2, 8), (9, 2100, 3, 5), (16, 2100, 4, 5), (16, 4096, 4, 8)])
+@pytest.mark.parametrize("n,L,groups,chunks", [(1, 1200, 1, 3), (2, 4096, 1, 8), (4, 1152, 1, 1), (4, 1153, 1, 3), (5, 1153, 2, 1), (5, 2048, 2, 1), (5, 2100, 2, 5), (8, 4096, 2, 8), (9, 2100, 3, 5), (16, 2100, 4, 5), (16, 4096, 4, 8)])
 def test_groups_of_query_rows_and_chunks_of_keys(n, L, groups, chunks, monkeypatch, capfd):
     """Several of both: which partial output is whose.  The number of chunks is the plan's own, so that another rule cannot leave this without any."""
     assert groups == (8 * n + 31) // 32
@@ -360,3 +360,17 @@ def test_cache_that_is_not_on_16_bytes(n, L, shift):
         ver.close()
     for a, b in zip(*res):
         assert np.array_equal(a, b)
+
+
+def test_few_heads_are_cut_early(monkeypatch, capfd):
+    """Up to 64 rows of heads the partial outputs are few: chunks from 37 tiles of 32 keys on, also with 16 rows (2000 keys of one KV head in one chunk took longer
+    than the chain of kernels)."""
+    test_against_the_oracle_and_the_chain("small", 16, 2000, monkeypatch, capfd)
+    monkeypatch.delenv("SPECASR_ONE_POLLS")
+    cfg = _cfg("small")
+    ver = _verifier(cfg, wl.make_weights(cfg, 911, "bf16"), 2016)
+    ver.kv_len[:] = 2000
+    capfd.readouterr()
+    assert ver.tree_forward([np.arange(16, dtype=np.int32)], [np.arange(-1, 15, dtype=np.int32)])["status"] == 0
+    assert "4 key chunks" in capfd.readouterr().err
+    ver.close()
