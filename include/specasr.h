@@ -26,7 +26,7 @@
  *    (chunked prefill), and event pairs for specasr_profile_stage.
  *  - The library reads no environment variable after specasr_create.  That
  *    call reads the development aids SPECASR_LANES, SPECASR_GEMM_SPLITS,
- *    SPECASR_WIDE_SPLITS, SPECASR_ATTN_CHUNK and SPECASR_DEBUG once (forced kernel
+ *    SPECASR_WIDE_SPLITS, SPECASR_ATTN_CHUNK, SPECASR_ONE_POLLS and SPECASR_DEBUG once (forced kernel
  *    plans for sweeps, diagnostics on stderr); results do not depend on them
  *    beyond summation order, and a deployment sets none.
  *  - `stream` is a raw hipStream_t (NULL = the default stream).

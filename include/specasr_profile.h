@@ -3,7 +3,8 @@
  *
  * Not part of the verification path (include/specasr.h): these calls let a benchmark time one
  * projection GEMM per forward with HIP events attached to that dispatch on the caller's stream.
- * They have no effect on results.
+ * They have no effect on results beyond the order of sums: while a stage is profiled, forwards of up to 16 nodes that have all
+ * their layers in one launch otherwise take the kernel per stage that is asked about.
  */
 #ifndef SPECASR_PROFILE_H
 #define SPECASR_PROFILE_H

@@ -53,7 +53,7 @@ struct OneArgs {
 
 // Words in front of the regions: the counters that the first kernel of the call clears.
 constexpr size_t kOneCtl = 256;
-constexpr int kOnePolls = 1 << 21;  // about two seconds
+constexpr int kOnePolls = 1 << 21;  // looks of a wait at most: two to four seconds
 
 bool one_launch_model(const ModelDims &md, int n_cu);
 OnePlan plan_one_launch(const ModelDims &md, int rows, int kv_len);

@@ -3,7 +3,8 @@
 // As a chain of kernels such a forward is 6 dependent launches per layer, each 1.3 us of boundary plus the way of its first
 // bytes: weights that could have been on their way are only asked for when the kernel before has drained.  Here workgroups
 // stay: a workgroup takes an item (q|k|v, attention, o, gate|up or down of a layer, for a few output features or query
-// rows), asks for ALL its weights, 32 .. 180 KB in registers, and only then looks for its input.
+// rows), asks for ALL its weights and only then looks for its input.  They wait in registers: 1.1B, gate|up 256 KB, down 180, q|k|v 128, o 128
+// up to 8 rows and 64 beyond, which is half of a workgroup's registers at most.
 //
 // Hand-over.  Between the workgroups of one launch nothing orders plain stores and loads, and fences cost more than a launch
 // (15 us when every workgroup invalidates its caches).  So every datum carries its own readiness: the regions below are
@@ -14,13 +15,16 @@
 //
 // Progress.  Items are numbered in the order of their dependencies and handed out by one counter, so a workgroup only ever waits
 // for items that running workgroups have taken before: any number of resident workgroups, also one, finishes the forward,
-// whatever else runs on the chip.  Each wait is bounded all the same, at
-// about two seconds; a wait that is given up ends all others, and the library reports it.
+// whatever else runs on the chip.  Each wait is bounded all the same, at 2^21 looks, two to four seconds; a wait that is given up ends all
+// others, what was computed without its data is NaN, and the library reports it.
 //
-// What bounds it: per layer 5 hand-overs of 3 .. 5 us each (store to memory 0.7, the look that finds it 1, products, sums through LDS and
-// epilogue 1.5, the latest workgroup), and at the last of them the weights that 48 workgroups could not ask for earlier.
-// Measured (us per call, 1.1B, 330 keys, chain of kernels -> this): 1 row 965 -> 642, 8 rows 1005 -> 667, 16 rows 1026 -> 724; 3200 keys,
-// 1 row 1002 -> 745, 16 rows 1103 -> 902; 12 layers of d 1024, 1 row 460 -> 331; 2 layers of d 256, 8 rows 115 -> 103 (the last two before one wavefront looked for all).
+// What bounds it: a layer is 5 phases that wait for each other, 24 us together with one row and 29 with 16 where its weights need 14 (each the store to
+// memory, 0.7, the look that finds it, 1, products, sums through LDS and epilogue, 1.5, and the latest workgroup), and at the last of them the
+// weights that 48 workgroups could not ask for earlier.
+// Measured (us per draft forward, chain of kernels -> this): 1.1B, 330 keys, 1 row 940 -> 609, 8 rows 946 -> 640, 16 rows 1014 -> 718; 3200 keys,
+// 1 row 1017 -> 700, 8 rows 1072 -> 744, 16 rows 1115 -> 876; 12 layers of d 1024, 1 row 466 -> 310; 2 layers of d 256, 8 rows, 1160 keys 80 -> 62.  No
+// combination of 1 .. 32 KV heads, d 64 .. 2048, 1 .. 16 rows and 0 .. 4000 keys is slower than the chain.  The variants named below are of the same
+// state and unit.
 #include "kernels.h"
 #include "kernels_mfma.h"
 #include "kernels_one.h"
@@ -35,9 +39,9 @@ typedef __attribute__((address_space(1))) u32x4 global_u32x4;  // (a pointer out
 constexpr int kOneWaves = 8, kOneThreads = kOneWaves * 64;
 // Half-bands of an item.  Two phases that follow each other should fit the 256 workgroups, so that the weights of the second are on
 // their way before its input exists: 1.1B 80 + 4 items, 64 (9 .. 16 rows 128), 176 and 128.  With half as many features per item
-// (160, 128, 235, 128) late workgroups ask for 180 KB when everything else waits for them, 780 us against 726 with one row.
+// (160, 128, 235, 128) late workgroups ask for 180 KB when everything else waits for them: 330 keys, 1 row 609 -> 671, 16 rows 718 -> 768.
 constexpr int kHbQkv = 2, kHbGu = 4, kHbDn = 1;
-constexpr int one_hb_o(int np) { return np == 1 ? 2 : 1; }  // us per call: 1 row 684 (2), 707 (1); 16 rows 779, 760
+constexpr int one_hb_o(int np) { return np == 1 ? 2 : 1; }  // 1 row 609 (2), 638 (1); 16 rows 330 keys 699, 718, 3200 keys 915, 876
 constexpr int kOneSums = 4 * kOneWaves * 64;  // float4 of the sums of up to 4 half-bands
 constexpr int kOneHd = 64;
 constexpr int kTU = 32 * kOneHd / 8;          // 16-byte units of a key tile
@@ -128,8 +132,8 @@ __device__ __forceinline__ void one_gemm(const OneArgs &p, OneShared &sh, int pa
   const int end = max(len, 1) - 1;  // stages past the slice repeat its last one, unused
   const int in_tile = 32 * ((lane >> 4) & 1) + (lane & 15);
   // The o projection is taken two phases early, while the 180 KB that the last workgroups of down need are on their way: its weights
-  // wait until the first queries are there (16 rows 865 -> 780 us, 1 row 718 -> 698; the same for other phases only costs).
-  // Up to 8 rows one wavefront looks for all (1 row 652 -> 642; 16 rows 724 -> 731).
+  // wait until the first queries are there (1 row 634 -> 609, 8 rows 669 -> 640, 16 rows 749 -> 718; the same for other phases only costs).
+  // Up to 8 rows one wavefront looks for all (1 row 616 -> 609, 8 rows 647 -> 640; 16 rows the same either way).
   if (EPI == kOneResid && LW == 8) {
     if (NP == 2 || wave == 0)
       for (int it = 0; __ballot(!missing16(ll_load16(rs, p.lay.q + (uint32_t)(lane * 16) % (uint32_t)(p.dq * 2)))) == 0ull && !give_up(p, it); ++it)
@@ -204,8 +208,8 @@ __device__ __forceinline__ void one_gemm(const OneArgs &p, OneShared &sh, int pa
   float ssum[RW];
   Next next;
   // A workgroup that is a phase ahead looks at one stage now and then, until that is there, and one wavefront looks for all of it:
-  // the looks of 256 workgroups past the caches get in the way of the data (us per call, 1 / 8 / 16 rows: each wavefront looks at a
-  // stage of its own 672 / 729 / 742, one of them 652 / 670 / 724; one at the first and the last stage 659 / 681 / 763).
+  // the looks of 256 workgroups past the caches get in the way of the data (1 / 8 / 16 rows: each wavefront looks at a stage of its
+  // own 634 / 659 / 763, one of them 609 / 640 / 718).
   if (wave == 0)
     for (int it = 0; __ballot(missing16(ll_load16(rs, x0))) != 0ull && !give_up(p, it); ++it) __builtin_amdgcn_s_sleep(24);
   barrier_only();
@@ -228,7 +232,7 @@ __device__ __forceinline__ void one_gemm(const OneArgs &p, OneShared &sh, int pa
     for (int k = 0; k < DX; ++k)
       if (c0 + k < LW) load_x(k);
     if (norm) load_s();
-    for (int it = 0;; ++it) {  // (all of them again: asking only for what is missing is 3 % slower)
+    for (int it = 0;; ++it) {  // (all of them again: asking only for what is missing was slower)
       bool bad = false;
 #pragma unroll
       for (int k = 0; k < DX; ++k)
@@ -393,7 +397,7 @@ __device__ __forceinline__ void one_attention(const OneArgs &p, OneShared &sh, i
   u32x4 qh[KK], qlo[KK];
   {
     const uint32_t qoff = p.lay.q + ((uint32_t)(node * p.H + head) * HD + 8 * h) * 2, plane = (uint32_t)p.dq * 2 * p.rp;
-    if (wave == 0)  // (as in one_gemm: 16 rows, 3200 keys 920 -> 902 us)
+    if (wave == 0)  // (as in one_gemm: 3200 keys, 8 rows 769 -> 743, 16 rows 895 -> 876; 330 keys 635 -> 640, 708 -> 718)
       for (int it = 0; __ballot(missing16(ll_load16(rs, qoff))) != 0ull && !give_up(p, it); ++it) __builtin_amdgcn_s_sleep(8);
     barrier_only();
     for (int it = 0;; ++it) {
@@ -555,7 +559,8 @@ __device__ __forceinline__ void one_merge(const OneArgs &p, OneShared &sh, int p
   __syncthreads();
 }
 
-// grid: one workgroup per compute unit (or fewer items), block 512.  DIRECT: the cache is on 16 bytes
+// grid: one workgroup per compute unit (or fewer items), block 512.  DIRECT: the cache is on 16 bytes.  All 256 registers; NP = 2 spills 6
+// constants of a thread (20 bytes of scratch), one of which q|k|v reads back while its weights are on their way, and so waits for those.
 template <int NP, bool DIRECT>
 __global__ __launch_bounds__(kOneThreads, 2) void one_launch_kernel(OneArgs args) {
   extern __shared__ u32x4 kv_lds[];
