@@ -97,6 +97,27 @@ __host__ __device__ __forceinline__ int64_t part_offset(int s, int row, int col,
 }
 __host__ __device__ __forceinline__ int part_rows_pad(int rows) { return rows <= 32 ? 32 : (rows + 63) / 64 * 64; }
 
+// v += partial sums of 4 columns, `stride` floats apart, in the order of the splits: rounds of 4 that are requested together, and so are the last
+// n_splits % 4 (the compiler's own unrolling by 4 waits for each of those by itself).
+__device__ __forceinline__ void add_splits4(float4 &v, const float *p, int64_t stride, int n_splits) {
+  auto add = [&](const float4 &t) { v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w; };
+  int s = 0;
+  for (; s + 4 <= n_splits; s += 4, p += 4 * stride) {
+    float4 t[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = *reinterpret_cast<const float4 *>(p + i * stride);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) add(t[i]);
+  }
+  float4 t[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    if (s + i < n_splits) t[i] = *reinterpret_cast<const float4 *>(p + i * stride);
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    if (s + i < n_splits) add(t[i]);
+}
+
 // ---- per-call tree metadata as the kernels see it ------------------------
 // Rows are the tree nodes of all sequences of the call, flattened without
 // padding: row = row_start[seq] + node.

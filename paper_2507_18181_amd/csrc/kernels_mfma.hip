@@ -765,6 +765,8 @@ void launch_gemm_wide_pair(const PackedMatrix &W, const uint16_t *Xp, int rows, 
 //   hb[r][:]   = hi/lo bf16 planes of x[r][:] * gain[:]
 //   ssq[r][slab] = sum over the slab of x[r][c]^2
 // Block = 8 threads per row (4 columns each, <= 64 rows), grid = (slabs of 32 columns, row blocks).
+// Bound by one trip to memory and the launch: gain, x and all splits up to 3 are requested together (us per launch, with the last splits one
+// by one and the gain behind the store of x -> now: 1.1B, 37 rows 3.6 -> 3.5, 13B, 160 rows 7.6 -> 7.2; 7B the same).
 constexpr int kSlabCols = 32;
 __global__ __launch_bounds__(512) void residual_gain_kernel(float *x, const float *part, int n_splits,
                                                             int rows, int ldp, const uint16_t *gain,
@@ -773,35 +775,22 @@ __global__ __launch_bounds__(512) void residual_gain_kernel(float *x, const floa
   const int r = blockIdx.y * 64 + (threadIdx.x >> 3), c = blockIdx.x * kSlabCols + (threadIdx.x & 7) * 4;
   const bool ok = r < rows && c < d;
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  uint2 g = make_uint2(0u, 0u);
+  float *xr = x + (int64_t)r * d + c;
   if (ok) {
-    float *xr = x + (int64_t)r * d + c;
+    g = *reinterpret_cast<const uint2 *>(gain + c);
     v = *reinterpret_cast<const float4 *>(xr);
     const float *pp = part + part_offset(0, r, c, ldp >> 5, rows_pad);
     const int64_t sstride = (int64_t)ldp * rows_pad;
-    int s = 0;
-    for (; s + 4 <= n_splits; s += 4) {  // four independent loads in flight, summed in split order
-      const float4 p0 = *reinterpret_cast<const float4 *>(pp + (s + 0) * sstride);
-      const float4 p1 = *reinterpret_cast<const float4 *>(pp + (s + 1) * sstride);
-      const float4 p2 = *reinterpret_cast<const float4 *>(pp + (s + 2) * sstride);
-      const float4 p3 = *reinterpret_cast<const float4 *>(pp + (s + 3) * sstride);
-      v.x += p0.x; v.y += p0.y; v.z += p0.z; v.w += p0.w;
-      v.x += p1.x; v.y += p1.y; v.z += p1.z; v.w += p1.w;
-      v.x += p2.x; v.y += p2.y; v.z += p2.z; v.w += p2.w;
-      v.x += p3.x; v.y += p3.y; v.z += p3.z; v.w += p3.w;
-    }
-    for (; s < n_splits; ++s) {
-      const float4 p = *reinterpret_cast<const float4 *>(pp + s * sstride);
-      v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-    }
-    if (n_splits > 0) *reinterpret_cast<float4 *>(xr) = v;
+    add_splits4(v, pp, sstride, n_splits);
   }
   float ss = sum_squares4(v.x, v.y, v.z, v.w);
   ss += __shfl_xor(ss, 1, 64);
   ss += __shfl_xor(ss, 2, 64);
   ss += __shfl_xor(ss, 4, 64);
-  if (ok) {
+  if (ok) {  // all stores behind the sums: in front of them a wait for loads would be one for the store of x as well
+    if (n_splits > 0) *reinterpret_cast<float4 *>(xr) = v;
     if ((threadIdx.x & 7) == 0) ssq[(int64_t)r * n_slab + blockIdx.x] = ss;
-    const uint2 g = *reinterpret_cast<const uint2 *>(gain + c);
     const float y[4] = {v.x * bf16_bits_to_f32(g.x & 0xffffu), v.y * bf16_bits_to_f32(g.x >> 16),
                         v.z * bf16_bits_to_f32(g.y & 0xffffu), v.w * bf16_bits_to_f32(g.y >> 16)};
     store_planes4(y, hb, hb_lo, packed_act_offset(r, c, nb));
@@ -891,6 +880,9 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(StepMeta m, KvGeom g, i
 // (head, group of 32 rows); thread t takes row t/8 and the rotary pairs j = 4*(t%8)..+3 (+32 per
 // further band of the half head), so that every load is 16 bytes per thread out of a contiguous
 // 4 KB band block and every store 8 bytes of 4 consecutive bf16.
+// Bound by its trips to memory, one after the other: statistics, then the splits of each half.  Cache slots travel with the first splits, and up to 3
+// splits together (us per launch, slots behind the sums and the last n % 4 splits one by one -> now: 7B, 4 x 24 rows 8.9 -> 7.3, 2 x 64 11.8 -> 11.1;
+// 1.1B, 330 rows 6.3 -> 5.7, 384 6.5 -> 5.9, 1024 16.9 -> 15.7; 13B, 4 x 40 11.3 -> 10.0, 2 x 40, 4 splits, 9.35 -> 9.5).
 __global__ __launch_bounds__(256) void qkv_finish_wide_kernel(StepMeta m, KvGeom g, int layer, int H, int Hkv,
                                                               int hd, const float *part, int n_splits,
                                                               int ldp, RowNorm nrm, int col_k, int col_v,
@@ -917,13 +909,10 @@ __global__ __launch_bounds__(256) void qkv_finish_wide_kernel(StepMeta m, KvGeom
   const float rs = 1.0f / sqrtf(ss / (float)nrm.d + nrm.eps);
   if (r >= rows) return;
   const int rows_pad = part_rows_pad(rows), n_bands = ldp >> 5;
+  int seq = m.seq[r], slot = m.slot[r];  // in flight together with the partial sums
   auto sum4 = [&](int col) {  // sum over the splits of 4 consecutive columns of row r, times 1/rms
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 4
-    for (int s = 0; s < n_splits; ++s) {
-      const float4 p = *reinterpret_cast<const float4 *>(part + part_offset(s, r, col, n_bands, rows_pad));
-      v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-    }
+    add_splits4(v, part + part_offset(0, r, col, n_bands, rows_pad), (int64_t)ldp * rows_pad, n_splits);
     v.x *= rs; v.y *= rs; v.z *= rs; v.w *= rs;
     return v;
   };
@@ -951,7 +940,8 @@ __global__ __launch_bounds__(256) void qkv_finish_wide_kernel(StepMeta m, KvGeom
       store_planes4(y1, qb, qb_lo, o + half);
     } else {
       const float4 v0 = sum4(col_v + b * hd + j), v1 = sum4(col_v + b * hd + j + half);
-      const int64_t base = g.row(m.seq[r], layer, b, m.slot[r]);
+      asm volatile("" : "+v"(seq), "+v"(slot));  // waited for here, not in front of the sums
+      const int64_t base = g.row(seq, layer, b, slot);
       store_bf16x4(y0, kc + base + j);
       store_bf16x4(y1, kc + base + j + half);
       const float w0[4] = {v0.x, v0.y, v0.z, v0.w}, w1[4] = {v1.x, v1.y, v1.z, v1.w};
