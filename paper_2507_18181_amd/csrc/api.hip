@@ -99,7 +99,7 @@ struct specasr_ctx {
   int32_t *out_host = nullptr;  // pinned, results of verify_tree
   int32_t *out_dev = nullptr;   // the same, as the device sees it
   size_t out_host_words = 0;
-  uint32_t *gave_up = nullptr, *gave_up_dev = nullptr;  // pinned word that a forward in one launch sets when a wait ran out, for good
+  uint32_t *gave_up = nullptr, *gave_up_dev = nullptr;  // word behind the results that a forward in one launch sets when a wait ran out, for good
   int32_t last_hip = 0;
   int device = 0;
   int n_cu = 256;  // compute units = workgroups of the persistent-style GEMM grid
@@ -427,13 +427,14 @@ specasr_status ensure_staging(specasr_ctx *ctx) {
     if (!ctx->stage[i].done) HIP_TRY(ctx, hipEventCreateWithFlags(&ctx->stage[i].done, hipEventDisableTiming));
   }
   ctx->out_host_words = (size_t)c.max_batch * c.max_nodes * 2 + (size_t)c.max_batch * 2;
-  if (!ctx->out_host) HIP_TRY(ctx, hipHostMalloc((void **)&ctx->out_host, ctx->out_host_words * 4, kPinned));
-  if (!ctx->out_dev) HIP_TRY(ctx, hipHostGetDevicePointer((void **)&ctx->out_dev, ctx->out_host, 0));
-  if (!ctx->gave_up) {
-    HIP_TRY(ctx, hipHostMalloc((void **)&ctx->gave_up, 4, kPinned));
-    *ctx->gave_up = 0;
+  const size_t gave_up_at = (ctx->out_host_words + 15) / 16 * 16;  // a line of its own behind the results
+  if (!ctx->out_host) {
+    HIP_TRY(ctx, hipHostMalloc((void **)&ctx->out_host, (gave_up_at + 16) * 4, kPinned));
+    ctx->out_host[gave_up_at] = 0;
+    ctx->gave_up = reinterpret_cast<uint32_t *>(ctx->out_host) + gave_up_at;
   }
-  if (!ctx->gave_up_dev) HIP_TRY(ctx, hipHostGetDevicePointer((void **)&ctx->gave_up_dev, ctx->gave_up, 0));
+  if (!ctx->out_dev) HIP_TRY(ctx, hipHostGetDevicePointer((void **)&ctx->out_dev, ctx->out_host, 0));
+  ctx->gave_up_dev = reinterpret_cast<uint32_t *>(ctx->out_dev) + gave_up_at;
   ctx->staging_ready = true;
   return SPECASR_OK;
 }
@@ -1258,7 +1259,6 @@ void specasr_destroy(specasr_ctx *ctx) {
     if (ctx->stage[i].done) (void)hipEventDestroy(ctx->stage[i].done);
   }
   if (ctx->out_host) (void)hipHostFree(ctx->out_host);
-  if (ctx->gave_up) (void)hipHostFree(ctx->gave_up);
   for (void *p : ctx->owned) (void)hipFree(p);
   if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
   for (auto &set : ctx->layer_ev)
