@@ -540,8 +540,15 @@ def main():
         out = step()
     torch.cuda.synchronize()
     log("timing %d steps" % args.steps)
-    assert B.specasr_profile_stage(ver.ctx, stage_id, True) == 0
+    # A profiled forward has a kernel per stage, which forwards of up to 16 nodes on the smaller models otherwise do
+    # not have (all layers in one launch): there the stage is timed in steps of its own.
+    apart = n <= 16 and cfg["d_model"] <= 2048
+    if not apart:
+        assert B.specasr_profile_stage(ver.ctx, stage_id, True) == 0
     dt, step_ms, outs = time_steps(step, args.steps, stream)
+    if apart:
+        assert B.specasr_profile_stage(ver.ctx, stage_id, True) == 0
+        time_steps(step, args.steps, stream)
     accepted = sum(int(o["accept_len"][0]) for o in outs)
     rc, stage_ms, stage_launches, stage_bytes = B.specasr_stage_time(ver.ctx)
     assert rc == 0 and stage_launches > 0
@@ -600,7 +607,7 @@ def main():
         "step_hbm_gbs": round(step_gbs, 1), "step_hbm_frac": round(step_gbs / HBM_PEAK_GBS, 4),
         "read_ceiling_gbs": ceiling,
         "step_frac_of_read_ceiling": None if not ceiling else round(step_gbs / ceiling, 4),
-        "roofline": {"bound": "hbm", "kernel": "weight-streaming GEMM (%s projection)" % args.stage,
+        "roofline": {"bound": "hbm", "kernel": "weight-streaming GEMM (%s projection%s)" % (args.stage, ", as a kernel of its own" if apart else ""),
                      "achieved": round(kern_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(kern_gbs / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_source": traffic_src, "launches_timed": stage_launches, "avg_launch_us": round(kern_ms * 1e3, 2),
