@@ -225,8 +225,8 @@ struct RowNorm {
   float eps;  // added to the mean square inside the root
 };
 // 1 / rms of residual row r from the slab sums of squares (eps inside the root, Sec. II-A's decoder
-// block), in two steps so that a kernel can have its own loads in flight together with these:
-// row_ssq_lane issues the loads of this lane's share (up to 4 at once) and adds them up;
+// block), in two steps: row_ssq_lane issues the loads of this lane's share (up to 4 at once) and adds
+// them up, which waits for them, so that loads that follow it in a kernel are a trip of their own;
 // row_rms_finish sums over the wavefront.  Every lane of the calling wavefront must be active in
 // row_rms_finish; all lanes get the same value.
 __device__ __forceinline__ float row_ssq_lane(const RowNorm &nrm, int r) {

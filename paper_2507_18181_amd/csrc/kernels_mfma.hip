@@ -828,7 +828,7 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(StepMeta m, KvGeom g, i
   const int idx0 = blockIdx.x * 256 + threadIdx.x, n_items = (H + Hkv) * half;
   const bool live = idx0 < n_items;
   const int idx = live ? idx0 : n_items - 1;  // surplus threads of the last block repeat its last item, without stores
-  const float lane_ssq = row_ssq_lane(nrm, r);  // in flight together with the partial sums below
+  const float lane_ssq = row_ssq_lane(nrm, r);
   const int a = idx / half, j = idx - a * half;
   const float2 c = cs[(int64_t)r * half + j];
   const int rows_pad = part_rows_pad(rows);
@@ -1018,7 +1018,7 @@ __global__ __launch_bounds__(256) void swiglu_finish_rows_kernel(const float *pa
                                                             uint16_t *t, uint16_t *t_lo, int nb) {
   const int r = blockIdx.y;
   const int f = (blockIdx.x * 256 + threadIdx.x) * 4;
-  const float lane_ssq = row_ssq_lane(nrm, r);  // in flight together with the partial sums below
+  const float lane_ssq = row_ssq_lane(nrm, r);
   float4 gt = make_float4(0.f, 0.f, 0.f, 0.f), up = gt;
   const int rows_pad = part_rows_pad(rows), n_bands = ldp >> 5;
   if (f < F) {
