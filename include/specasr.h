@@ -154,7 +154,8 @@ void specasr_destroy(specasr_ctx *ctx);
  * base required).  Depends on the model, max_nodes and batch only.  On the bf16 MFMA path it
  * covers one set of buffers per internal stream plus one set for passes over up to
  * max(16, batch) x max_nodes rows (prefill, large batches), which at least holds, for models up to d_model
- * 2048, the hand-over buffers of forwards whose layers run in one launch (up to 16 nodes of one sequence). */
+ * 2048, the hand-over buffers of forwards whose layers run in one launch (up to 16 nodes of one sequence).
+ * Without room for those a workspace is accepted all the same, and such forwards run as a chain of kernels. */
 size_t specasr_workspace_bytes(const specasr_ctx *ctx, int32_t batch);
 
 /* One whole verification round (Sec. II-B, Sec. IV-C): tree forward, per-node

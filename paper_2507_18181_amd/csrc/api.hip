@@ -490,16 +490,22 @@ int ws_lanes(const specasr_ctx *ctx, int batch) {
 // those of the first lane alone, and on the caller's stream, as every wide pass does, so neither sees the other's data.
 size_t one_offset(const specasr_ctx *ctx) { return ws_layout(ctx, 1).total * ws_lanes(ctx, 1); }
 bool one_launch_on(const specasr_ctx *ctx) { return ctx->one_layers != nullptr && ctx->tune.one_polls > 0; }
-// A workspace for several sequences also serves calls of one.
+size_t ws_bytes_chain(const specasr_ctx *ctx, int batch) { return ws_layout(ctx, batch).total * ws_lanes(ctx, batch) + ws_layout_wide(ctx, batch).total; }
+size_t ws_bytes_one(const specasr_ctx *ctx) { return one_offset(ctx) + one_launch_bytes(ctx->md); }
+// What a caller is told to bring.  A workspace for several sequences also serves calls of one.
 size_t ws_bytes(const specasr_ctx *ctx, int batch) {
-  const size_t all = ws_layout(ctx, batch).total * ws_lanes(ctx, batch) + ws_layout_wide(ctx, batch).total;
-  return one_launch_on(ctx) ? std::max(all, one_offset(ctx) + one_launch_bytes(ctx->md)) : all;
+  const size_t all = ws_bytes_chain(ctx, batch);
+  return one_launch_on(ctx) ? std::max(all, ws_bytes_one(ctx)) : all;
+}
+// Scratch of a forward in one launch for this call, or nullptr: it is not one sequence, or the workspace only holds the chain of kernels.
+char *one_scratch(const specasr_ctx *ctx, char *ws, size_t bytes, int batch) {
+  return batch == 1 && one_launch_on(ctx) && bytes >= ws_bytes_one(ctx) ? ws + one_offset(ctx) : nullptr;
 }
 
 specasr_status check_ws(const specasr_ctx *ctx, const void *ws, size_t bytes, int batch) {
   if (!ws) return SPECASR_E_WORKSPACE;
   if (((uintptr_t)ws & 255u) != 0) return SPECASR_E_WORKSPACE;
-  if (bytes < ws_bytes(ctx, batch)) return SPECASR_E_WORKSPACE;
+  if (bytes < ws_bytes_chain(ctx, batch)) return SPECASR_E_WORKSPACE;
   return SPECASR_OK;
 }
 
@@ -1309,7 +1315,7 @@ specasr_status specasr_tree_forward(specasr_ctx *ctx, specasr_kv *kv, const spec
     ReadOut ro;
     ro.argmax = argmax_dev + grp.s0 * MN;
     ro.logits = logits_dev ? logits_dev + grp.s0 * MN * ctx->cfg.vocab : nullptr;
-    if (kv->batch == 1 && one_launch_on(ctx)) ro.one = ws + one_offset(ctx);
+    ro.one = one_scratch(ctx, ws, workspace_bytes, kv->batch);
     s = forward_common(ctx, &grp.kv, &grp.tree, ro, wl, Lg, hs, lanes.stream(gi), LayerSync(), wide);
     if (s != SPECASR_OK) return s;
   }
@@ -1350,7 +1356,7 @@ specasr_status specasr_tree_forward_top2(specasr_ctx *ctx, specasr_kv *kv, const
     ro.top2 = top2_dev + grp.s0 * MN * 2;
     ro.prob = top1_prob_dev + grp.s0 * MN;
     ro.logits = logits_dev ? logits_dev + grp.s0 * MN * ctx->cfg.vocab : nullptr;
-    if (kv->batch == 1 && one_launch_on(ctx)) ro.one = ws + one_offset(ctx);
+    ro.one = one_scratch(ctx, ws, workspace_bytes, kv->batch);
     s = forward_common(ctx, &grp.kv, &grp.tree, ro, wl, Lg, hs, lanes.stream(gi), LayerSync(), wide);
     if (s != SPECASR_OK) return s;
   }
@@ -1665,7 +1671,7 @@ specasr_status specasr_verify_tree(specasr_ctx *ctx, specasr_kv *kv, const speca
     ro.argmax = argmax_dev + grp.s0 * MN;
     ro.records = ctx->fast && (hs.rows <= 64 || wide);  // what forward_common runs on the MFMA path
     ro.logits = out->logits ? out->logits + grp.s0 * MN * c.vocab : nullptr;
-    if (B == 1 && one_launch_on(ctx)) ro.one = ws + one_offset(ctx);
+    ro.one = one_scratch(ctx, ws, workspace_bytes, B);
     s = forward_common(ctx, &grp.kv, &grp.tree, ro, wl, Lg, hs, sl, LayerSync(), wide);
     if (s != SPECASR_OK) return s;
     StepMeta m = device_meta(ctx, wl, Lg, hs);

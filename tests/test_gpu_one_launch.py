@@ -285,6 +285,36 @@ def test_workspace(monkeypatch):
     assert one[0] > chain[0] and one == sorted(one) and one[2] == chain[2]
 
 
+@pytest.mark.parametrize("call", ["tree_forward", "tree_forward_top2", "verify_tree"])
+def test_workspace_that_only_holds_the_chain(call, monkeypatch):
+    """What a call needs without the launch is still enough for it: it runs as the chain, whose bits it gives; one byte less is refused."""
+    from paper_2507_18181_amd import binding as B
+    from paper_2507_18181_amd.runtime import Verifier
+    cfg = _cfg("wide")
+    w = wl.make_weights(cfg, 971, "bf16")
+    K, V = wl.seeded_cache(cfg, 972, np.asarray([20], np.int32), 64, "bf16", batch=1)
+    tok, par = np.arange(9, dtype=np.int32), np.arange(-1, 8, dtype=np.int32)
+    monkeypatch.setenv("SPECASR_ONE_POLLS", "0")
+    res, size = [], None
+    for chain in (True, False):
+        if not chain:
+            monkeypatch.delenv("SPECASR_ONE_POLLS")
+        ver = Verifier(cfg, w, "bf16", max_nodes=32, capacity=64, flags=B.SPECASR_FLAG_NO_WIDE)
+        ver.set_cache(K, V, [20])
+        if chain:
+            size = ver.ws_bytes
+        assert size <= ver.ws_bytes and chain == (size == ver.ws_bytes)
+        ver.ws_bytes = size
+        out = getattr(ver, call)([tok], [par], want_logits=True)
+        assert out["status"] == 0
+        res.append([out["logits"].cpu().numpy()] + list(ver.get_cache()))
+        ver.ws_bytes = size - 1
+        ver.kv_len[0] = 20
+        assert getattr(ver, call)([tok], [par])["status"] == B.SPECASR_E_WORKSPACE
+        ver.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*res))
+
+
 @pytest.mark.parametrize("wide", [True, False])
 def test_between_passes_over_many_rows(wide, monkeypatch):
     """Prefill, a forward in one launch and prefill again, enqueued one behind the other in one workspace, against contexts of their own."""
